@@ -211,15 +211,14 @@ int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, void* stream
 
 /* Stencil cost of n candidates (host array) sharing one stencil (host); results to
  * d_out (device, tm_stencil_cost[n]).  Candidates may differ in launch rank (each
- * at most st->lrank; TM_EINVAL otherwise).  Counted exactly as a weighted sum over
- * coordinate classes: along each launch dim, consecutive coordinates with the same
- * contribution to the final index and the same offsets to their star neighbours
- * form a class, and every cell of a tuple of classes has the same distinct foreign
- * owners (Sec. 4.2's volume, evaluated once per class tuple and multiplied by the
- * cells it stands for).  TM_ENOTSUP if a halo exceeds 4, a candidate's owner table
- * (its final-space volume) exceeds the per-workgroup LDS budget of 32768 words, or
- * it has more than 2^30 rows (points / last extent); the coordinate tables and
- * classes have no size limit (large ones are read from global memory). */
+ * at most st->lrank; TM_EINVAL otherwise).  Counted exactly over coordinate groups:
+ * along each launch dim the coordinates with the same contribution to the final index
+ * form a group, the cells of a tuple of groups share their owner, and the distinct
+ * foreign owners of their neighbours (Sec. 4.2's volume) are summed owner by owner from
+ * how many members of each group see an offset that it owns.  TM_ENOTSUP if a halo
+ * exceeds 4, a candidate's owner table (its final-space volume) exceeds the
+ * per-workgroup LDS budget of 32768 words, or it has more than 2^30 rows (points / last
+ * extent); extents and group counts have no further limit. */
 int tm_eval_stencil_batch(const tm_candidate* c, int64_t n, const tm_stencil* st,
                           tm_stencil_cost* d_out, void* stream);
 
@@ -227,9 +226,9 @@ int tm_eval_stencil_batch(const tm_candidate* c, int64_t n, const tm_stencil* st
  * tight serving loops, harnesses that forbid allocation): tm_eval_stencil_batch
  * with the same arguments, results and validation, allocating no device memory and
  * no pinned host memory.
- * The batch header, descriptors, tables and work counter live in a device array of
- * TM_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until the
- * process ends; TM_ECAPACITY (nothing launched) when the batch needs more.  Every
+ * The descriptors live in a device array of TM_NOALLOC_SCRATCH_BYTES that the library
+ * holds on every GPU it runs on until the process ends; TM_ECAPACITY (nothing launched)
+ * when the batch needs more, counting each candidate's tables with its descriptor.  Every
  * call on a GPU shares that GPU's array: calls that overlap on one GPU (on other
  * streams or threads) race, and the caller must serialise them.  The descriptors are
  * copied from host memory before the call returns (it waits for `stream` to finish
@@ -302,26 +301,24 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
                             int32_t nodes, int32_t gpus_per_node, const int32_t* halo, tm_candidate* out);
 
 /* ---------------------------------------------------------------- batch plans
- * A plan owns device memory for up to max_cands candidates and max_words table
- * words.  tm_plan_load validates a batch on the host and uploads its descriptors
- * (asynchronously, on `stream`); tm_plan_run replays one hipGraph: reset -> table
- * build (owner tables, coordinate tables, coordinate classes) -> one persistent
- * counting launch over a work queue of (candidate, range of class tuples) items,
- * whatever the candidates' launch ranks -> bytes + selection.  d_out:
- * tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  Work items hold about
- * cells_per_item class tuples of the candidate's bound (0 = a default from the
- * batch: about 16 items per CU, 2^10 to 2^16 tuples; at most 2^26, else
- * TM_EINVAL). */
+ * A plan owns device memory for up to max_cands candidates and, for the map of one of
+ * them, max_words table words (both grow).  tm_plan_load validates a batch on the host
+ * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run replays one
+ * hipGraph: one evaluation launch whatever the candidates' launch ranks (two when their
+ * LDS needs differ much), which also selects for batches of at most 2048 candidates.
+ * d_out: tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  A work item is a workgroup:
+ * a candidate, or a part of one holding about cells_per_item of its group tuples (0 = a
+ * default: whole candidates, but parts where they are too few to fill the GPU; at most
+ * 2^26, else TM_EINVAL). */
 typedef struct tm_plan tm_plan;
 
 int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** out);
 int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const tm_stencil* st,
                  int64_t cells_per_item, void* stream);
 int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, void* stream);
-/* stage 0: table build (which also zeroes d_out and the work counters); 1: counting
- * (for batches of at most 2048 candidates its last workgroup also writes the bytes
- * and selects); 2: bytes + selection (same work as tm_plan_run, one stage at a time,
- * in this order, each replayed from its own graph). */
+/* stage 0: zeroes d_out; 1: the evaluation (which also selects, for batches of at most
+ * 2048 candidates in one launch); 2: bytes + selection (together the work of tm_plan_run,
+ * one stage at a time, in this order, each replayed from its own graph). */
 int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t* d_best,
                       void* stream);
 /* Processor map of candidate *d_index (device int64; index into the loaded batch),
@@ -336,18 +333,19 @@ int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t host_index, 
  * batch is TM_EINVAL, a short map TM_ECAPACITY. */
 int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, int32_t* d_map, int64_t cap,
                     void* stream);
-/* Class tuples of the loaded batch (the counting kernel's work): the sum over its
- * candidates of the product of their per-dim class counts, as built by the last
- * run -> *tuples (host).  Synchronous: waits for `stream`.  TM_EINVAL before the
+/* Class tuples of the loaded batch, a measure of its size: the sum over its candidates
+ * of the product of their per-dim class counts, a class being a run of consecutive
+ * coordinates with the same contribution and the same offsets to their star neighbours
+ * -> *tuples (host).  Synchronous: waits for `stream`.  TM_EINVAL before the
  * first run. */
 int tm_plan_class_tuples(tm_plan* p, int64_t* tuples, void* stream);
-/* Times cells_per_item and grid variants of the loaded batch, keeps the fastest;
+/* Times cells_per_item and grid variants of the loaded batch's evaluation, keeps the fastest;
  * writes the chosen cells_per_item and workgroups per CU (host pointers, nullable). */
 int tm_plan_autotune(tm_plan* p, tm_stencil_cost* d_out, int64_t* cells_per_item,
                      int32_t* wg_per_cu, void* stream);
 /* Sets the launch configuration of the loaded batch without timing anything: work
- * items of cells_per_item cells (0 = default) and at most wg_per_cu counting
- * workgroups per CU (0 = as many as occupancy allows) -- e.g. a configuration found
+ * items of cells_per_item tuples (0 = default) and at most wg_per_cu workgroups per CU,
+ * which then take several items each (0 = one item each) -- e.g. a configuration found
  * by tm_plan_autotune earlier.  TM_EINVAL on negative values or cells_per_item above
  * 2^26. */
 int tm_plan_set_launch(tm_plan* p, int64_t cells_per_item, int32_t wg_per_cu, void* stream);

@@ -6,6 +6,8 @@
 #include <cstring>
 #include <vector>
 
+#include "tm_compile.h"
+#include "tm_eval.h"
 #include "tm_internal.h"
 #include "tm_plan.h"
 #include "tm_ranker.h"
@@ -172,6 +174,49 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
     return TM_OK;
 }
 
+// The evaluation's launches.  One launch takes all candidates when the largest need
+// (eval_need) is small, else those above kEvalSmall* go in a launch of their own, so that
+// they do not cost the others their occupancy; a candidate gets as many more records than
+// it needs as fit its launch's words.
+void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
+    EvalPlan& e = cp.eval;
+    e = EvalPlan{};
+    e.n = (int64_t)cp.cands.size();
+    e.elem_bytes = cp.hdr.elem_bytes;
+    for (int k = 0; k < TM_MAX_LRANK; ++k) e.halo[k] = cp.hdr.halo[k];
+    e.H = cp.H;
+    e.node_level = node_level ? 1 : 0;
+    e.per_item = tuples_per_item;
+    e.fill = std::max<int64_t>(1, kEvalFill / std::max<int64_t>(e.n, 1));
+    const bool wave = e.n >= kEvalWaveBatch;
+    const int32_t small = wave ? kEvalSmallWave : kEvalSmallBlock, most = wave ? kEvalMostWave : kEvalMostBlock;
+    const EvalShape shape{e.H, e.node_level, e.per_item, e.fill};
+    int32_t words[2] = {0, 0}, whole[2] = {0, 0}, largest = 0;  // of the needs up to small, above it
+    for (auto& c : cp.cands) {
+        DevDim dim[TM_MAX_LRANK];
+        bool cyclic = false;
+        for (int k = 0; k < c.lrank; ++k) {
+            count_groups(c, k, &dim[k]);
+            cyclic = cyclic || dim[k].ncyc > 0;
+        }
+        const EvalNeed n = eval_need(dim, c.lrank, c.vol, cyclic, is_bijective(c), shape);
+        e.items += n.parts;
+        e.parts = std::max(e.parts, n.parts);
+        largest = std::max(largest, n.words);
+        const int b = n.words > small ? 1 : 0;
+        words[b] = std::max(words[b], n.words);
+        whole[b] = std::max(whole[b], n.whole);
+    }
+    if (largest <= most) {
+        e.split = largest;
+        e.words[0] = std::max(largest, std::min(std::max(whole[0], whole[1]), small));
+    } else {
+        e.split = small;
+        e.words[0] = std::max(words[0], std::min(whole[0], small));
+        e.words[1] = words[1];
+    }
+}
+
 // ------------------------------------------------------------------ staging
 
 // Per-thread pinned staging for descriptor uploads; reused once the previous copy
@@ -316,21 +361,24 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
     Compiled cp;
     int rc = compile_batch(c, n, st, 0, true, cp);
     if (rc != TM_OK) return rc;
-    cp.hdr.node_level = node_level ? 1 : 0;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
-    DeviceBatch db;
-    rc = upload_batch(cp, db, s);
+    layout_eval(cp, 0, node_level);
+    const EvalShape shape{cp.eval.H, cp.eval.node_level, cp.eval.per_item, cp.eval.fill};
+    DevEval* d_evals = nullptr;
+    const size_t bytes = (size_t)n * sizeof(DevEval);
+    TM_HIP(hipMallocAsync((void**)&d_evals, bytes, s));
+    void* stg = nullptr;
+    rc = staging_acquire(bytes, &stg);
     if (rc == TM_OK) {
-        const int grid = count_grid(cp.cnt_words, cp.items, 0);
-        const bool fin = n <= kFinInCount;
-        hipError_t e = launch_build_tables(db.hdr, db.cands, n, db.arena, 1, s, d_out, db.counter);
-        if (e == hipSuccess)
-            e = launch_count(db.hdr, db.cands, db.arena, db.counter, d_out, grid, cp.cnt_words, s, fin, nullptr);
-        if (e == hipSuccess && !fin) e = launch_finalize_select(db.hdr, d_out, nullptr, n, s);
-        if (e != hipSuccess) rc = set_error(TM_EDEVICE, "stencil launch: %s", hipGetErrorString(e));
+        for (int64_t i = 0; i < n; ++i) fill_eval(cp.cands[(size_t)i], shape, static_cast<DevEval*>(stg) + i);
+        hipError_t e = hipMemcpyAsync(d_evals, stg, bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) rc = staging_release(s);
+        if (rc == TM_OK && e == hipSuccess)
+            e = launch_eval_batch(cp.eval, d_evals, d_out, nullptr, nullptr, num_cus(), s);
+        if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "stencil launch: %s", hipGetErrorString(e));
     }
-    free_batch(db, s);
+    (void)hipFreeAsync(d_evals, s);
     return rc;
 }
 
@@ -534,6 +582,7 @@ static void plan_free(tm_plan* p) {
     plan_drop_graphs(p);
     search_free(p->sb);
     if (p->d_cands) (void)hipFree(p->d_cands);
+    if (p->d_evals) (void)hipFree(p->d_evals);
     if (p->d_arena) (void)hipFree(p->d_arena);
     if (p->d_hdr) (void)hipFree(p->d_hdr);
     if (p->d_counter) (void)hipFree(p->d_counter);
@@ -541,6 +590,7 @@ static void plan_free(tm_plan* p) {
     if (p->h_hdr) (void)hipHostFree(p->h_hdr);
     if (p->h_seg) (void)hipHostFree(p->h_seg);
     p->d_cands = nullptr;
+    p->d_evals = nullptr;
     p->d_arena = nullptr;
     p->d_hdr = nullptr;
     p->d_counter = nullptr;
@@ -550,6 +600,7 @@ static void plan_free(tm_plan* p) {
     p->cap_hseg = 0;
     p->cap_cands = 0;
     p->cap_words = 0;
+    p->cap_arena = 0;
 }
 
 // Descriptor buffers for up to `cands` candidates (the table arena is allocated
@@ -558,8 +609,9 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
     plan_free(p);
     cands = std::max<int64_t>(cands, 1);
     if (hipMalloc((void**)&p->d_cands, (size_t)cands * sizeof(DevCand)) != hipSuccess ||
+        hipMalloc((void**)&p->d_evals, (size_t)cands * sizeof(DevEval)) != hipSuccess ||
         hipMalloc((void**)&p->d_hdr, sizeof(DevHeader)) != hipSuccess ||
-        hipMalloc((void**)&p->d_counter, 256) != hipSuccess ||
+        hipMalloc((void**)&p->d_counter, 256) != hipSuccess || hipMemset(p->d_counter, 0, 256) != hipSuccess ||
         hipHostMalloc((void**)&p->h_cands, (size_t)cands * sizeof(DevCand), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&p->h_hdr, sizeof(DevHeader), hipHostMallocDefault) != hipSuccess) {
         plan_free(p);
@@ -569,18 +621,21 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
     return TM_OK;
 }
 
-// Table arena of the whole loaded batch; grows (after draining `s`) when needed.
+// Table words of the loaded batch's largest candidate, for the map of one candidate.
+static int64_t plan_map_words(const tm_plan* p) { return std::max<int64_t>(p->cp.max_all_words, 1); }
+
+// Device memory for one candidate's tables; grows (after draining `s`) when needed.
 static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
-    const int64_t words = std::max<int64_t>(p->cp.arena_words, 1);
-    if (p->d_arena && p->cap_words >= words) return TM_OK;
+    const int64_t words = plan_map_words(p);
+    if (p->d_arena && p->cap_arena >= words) return TM_OK;
     TM_HIP(hipStreamSynchronize(s));
     if (p->d_arena) (void)hipFree(p->d_arena);
     p->d_arena = nullptr;
-    p->cap_words = 0;
+    p->cap_arena = 0;
     plan_drop_graphs(p);
     if (hipMalloc((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
         return set_error(TM_ENOMEM, "table arena of %lld words", (long long)words);
-    p->cap_words = words;
+    p->cap_arena = words;
     return TM_OK;
 }
 
@@ -596,42 +651,17 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
     if (nc) TM_HIP(hipMemcpyAsync(p->d_cands, p->h_cands, nc, hipMemcpyHostToDevice, s));
     TM_HIP(hipEventRecord(p->up_ev, s));
     p->up_pending = true;
+    TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, s));
     return TM_OK;
 }
 
-// Enqueues one stage of a run on stream s (direct launches; also used for capture).
-static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, int grid, hipStream_t s) {
+// Enqueues a run, or one stage of it, on stream s (direct launches; also used for
+// capture).  Stage 2 on its own repeats the selection (idempotent).
+static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, hipStream_t s) {
     const Compiled& cp = p->cp;
-    const bool fin = cp.hdr.n <= kFinInCount;  // bytes and selection inside the counting launch
-    hipError_t e = hipSuccess;
-    if (stage == 0 || stage < 0) {
-        e = launch_build_tables(p->d_hdr, p->d_cands, cp.hdr.n, p->d_arena, 1, s, out, p->d_counter);
-        if (e != hipSuccess) return e;
-    }
-    if (stage == 1 || stage < 0) {
-        e = launch_count(p->d_hdr, p->d_cands, p->d_arena, p->d_counter, out, grid, cp.cnt_words, s, fin, best);
-        if (e != hipSuccess) return e;
-    }
-    // stage 2 on its own repeats the selection (idempotent); the whole run needs it
-    // only when the counting launch did not do it
-    if (stage == 2 || (stage < 0 && !fin)) e = launch_finalize_select(p->d_hdr, out, best, cp.hdr.n, s);
-    return e;
-}
-
-static int capture(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, int grid, hipGraphExec_t* exec) {
-    hipGraph_t g = nullptr;
-    TM_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-    const hipError_t e = plan_enqueue(p, stage, out, best, grid, p->cap_stream);
-    const hipError_t e2 = hipStreamEndCapture(p->cap_stream, &g);
-    if (e != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return set_error(TM_EDEVICE, "capture: %s", hipGetErrorString(e));
-    }
-    TM_HIP(e2);
-    const hipError_t e3 = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    TM_HIP(e3);
-    return TM_OK;
+    if (stage == 0) return launch_zero_costs(out, cp.hdr.n, s);
+    if (stage == 2) return launch_bytes_select(out, cp.hdr.n, cp.hdr.elem_bytes, best, s);
+    return launch_eval_batch(cp.eval, p->d_evals, out, best, p->d_counter, num_cus(), s);
 }
 
 // Map grid for a device-side index: the largest over the loaded candidates.
@@ -641,15 +671,21 @@ static int plan_map_grid(const tm_plan* p) {
     return grid;
 }
 
-// The whole run followed by the map of candidate *best, as one graph.
-static int capture_run_map(tm_plan* p, tm_stencil_cost* out, int64_t* best, int32_t* map, int grid,
-                           hipGraphExec_t* exec) {
+// Tables, then the map, of candidate *d_index (or index).
+static hipError_t plan_enqueue_map(tm_plan* p, const int64_t* d_index, int64_t index, int32_t* map, int grid,
+                                   hipStream_t s) {
+    const int64_t n = p->cp.hdr.n;
+    hipError_t e = launch_build_one(p->d_hdr, p->d_cands, n, d_index, index, p->d_arena, s);
+    if (e == hipSuccess) e = launch_map(p->d_cands, n, p->d_arena, d_index, index, map, grid, p->cp.max_words, s);
+    return e;
+}
+
+// Captures a run (stage -1), a stage (0..2) or, with map, a run and the map of *best.
+static int capture(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, int32_t* map, hipGraphExec_t* exec) {
     hipGraph_t g = nullptr;
     TM_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = plan_enqueue(p, -1, out, best, grid, p->cap_stream);
-    if (e == hipSuccess)
-        e = launch_map(p->d_cands, p->cp.hdr.n, p->d_arena, best, 0, map, plan_map_grid(p), p->cp.max_words,
-                       p->cap_stream);
+    hipError_t e = plan_enqueue(p, stage, out, best, p->cap_stream);
+    if (e == hipSuccess && map) e = plan_enqueue_map(p, best, 0, map, plan_map_grid(p), p->cap_stream);
     const hipError_t e2 = hipStreamEndCapture(p->cap_stream, &g);
     if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -662,21 +698,13 @@ static int capture_run_map(tm_plan* p, tm_stencil_cost* out, int64_t* best, int3
     return TM_OK;
 }
 
-static int plan_graphs(tm_plan* p, tm_stencil_cost* out, int64_t* best) {
-    const int grid = count_grid(p->cp.cnt_words, p->cp.items, p->wg_per_cu);
-    if (p->g_valid && p->g_grid == grid && p->g_out == out && p->g_best == best) return TM_OK;
+// The graphs of the last (out, best): dropped when either changes, captured on first use.
+static void plan_graphs(tm_plan* p, tm_stencil_cost* out, int64_t* best) {
+    if (p->g_valid && p->g_out == out && p->g_best == best) return;
     plan_drop_graphs(p);
-    int rc = capture(p, -1, out, best, grid, &p->g_full);
-    for (int st = 0; st < 3 && rc == TM_OK; ++st) rc = capture(p, st, out, best, grid, &p->g_stage[st]);
-    if (rc != TM_OK) {
-        plan_drop_graphs(p);
-        return rc;
-    }
     p->g_valid = true;
-    p->g_grid = grid;
     p->g_out = out;
     p->g_best = best;
-    return TM_OK;
 }
 
 }  // namespace tmk
@@ -690,7 +718,7 @@ extern "C" int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** ou
     int rc = plan_alloc(p, max_cands);
     if (rc == TM_OK && max_words > 0) {
         if (hipMalloc((void**)&p->d_arena, (size_t)max_words * 4) != hipSuccess) rc = set_error(TM_ENOMEM, "arena");
-        else p->cap_words = max_words;
+        else p->cap_words = p->cap_arena = max_words;
     }
     if (rc == TM_OK && hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming) != hipSuccess)
         rc = set_error(TM_EDEVICE, "event");
@@ -733,6 +761,8 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
         p->up_pending = false;
     }
     if (cells_per_item > 0) p->cells_per_item = cells_per_item;
+    layout_eval(cp, p->cells_per_item, false);
+    cp.eval.wg_per_cu = p->wg_per_cu;
     p->cp = std::move(cp);
     p->loaded = true;
     plan_drop_graphs(p);
@@ -743,9 +773,10 @@ extern "C" int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, 
     if (!p || !p->loaded) return set_error(TM_EINVAL, "plan not loaded");
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
-    int rc = plan_ensure_arena(p, (hipStream_t)stream);
-    if (rc == TM_OK) rc = plan_graphs(p, d_out, d_best);
+    plan_graphs(p, d_out, d_best);
+    const int rc = p->g_full ? TM_OK : capture(p, -1, d_out, d_best, nullptr, &p->g_full);
     if (rc != TM_OK) return rc;
+    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
     TM_HIP(hipGraphLaunch(p->g_full, (hipStream_t)stream));
     return TM_OK;
 }
@@ -757,14 +788,16 @@ extern "C" int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_be
     if (!d_out || !d_best || !d_map) return set_error(TM_EINVAL, "null output");
     if (cap < p->cp.max_points) return set_error(TM_ECAPACITY, "map needs %lld entries", (long long)p->cp.max_points);
     int rc = plan_ensure_arena(p, (hipStream_t)stream);
-    if (rc == TM_OK) rc = plan_graphs(p, d_out, d_best);
-    if (rc == TM_OK && (!p->g_map || p->g_map_ptr != d_map)) {
+    if (rc != TM_OK) return rc;
+    plan_graphs(p, d_out, d_best);
+    if (!p->g_map || p->g_map_ptr != d_map) {
         if (p->g_map) (void)hipGraphExecDestroy(p->g_map);
         p->g_map = nullptr;
-        rc = capture_run_map(p, d_out, d_best, d_map, p->g_grid, &p->g_map);
+        rc = capture(p, -1, d_out, d_best, d_map, &p->g_map);
         p->g_map_ptr = rc == TM_OK ? d_map : nullptr;
     }
     if (rc != TM_OK) return rc;
+    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
     TM_HIP(hipGraphLaunch(p->g_map, (hipStream_t)stream));
     return TM_OK;
 }
@@ -775,9 +808,10 @@ extern "C" int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_o
     if (stage < 0 || stage > 2) return set_error(TM_EINVAL, "stage %d", stage);
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
-    int rc = plan_ensure_arena(p, (hipStream_t)stream);
-    if (rc == TM_OK) rc = plan_graphs(p, d_out, d_best);
+    plan_graphs(p, d_out, d_best);
+    const int rc = p->g_stage[stage] ? TM_OK : capture(p, stage, d_out, d_best, nullptr, &p->g_stage[stage]);
     if (rc != TM_OK) return rc;
+    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
     TM_HIP(hipGraphLaunch(p->g_stage[stage], (hipStream_t)stream));
     return TM_OK;
 }
@@ -798,10 +832,11 @@ extern "C" int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t h
         grid = plan_map_grid(p);
     }
     if (cap < need) return set_error(TM_ECAPACITY, "map needs %lld entries", (long long)need);
-    if (!p->d_arena || p->cap_words < cp.arena_words)
-        return set_error(TM_EINVAL, "no tables yet: run the plan before materialising a map");
-    const hipError_t e = launch_map(p->d_cands, cp.hdr.n, p->d_arena, d_index, host_index, d_map, grid, cp.max_words,
-                                    (hipStream_t)stream);
+    if (p->cap_words < cp.arena_words)
+        return set_error(TM_EINVAL, "not run yet: run the plan before materialising a map");
+    const int rc = plan_ensure_arena(p, (hipStream_t)stream);
+    if (rc != TM_OK) return rc;
+    const hipError_t e = plan_enqueue_map(p, d_index, host_index, d_map, grid, (hipStream_t)stream);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
     return TM_OK;
 }
@@ -809,7 +844,7 @@ extern "C" int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t h
 extern "C" int tm_plan_info(const tm_plan* p, int64_t* n, int64_t* items, int64_t* points) {
     if (!p) return set_error(TM_EINVAL, "null plan");
     if (n) *n = p->loaded ? p->cp.hdr.n : 0;
-    if (items) *items = p->loaded ? p->cp.items : 0;
+    if (items) *items = p->loaded ? p->cp.eval.items : 0;
     if (points) *points = p->loaded ? p->cp.points : 0;
     return TM_OK;
 }
@@ -819,13 +854,13 @@ extern "C" int tm_plan_class_tuples(tm_plan* p, int64_t* tuples, void* stream) {
     if (!tuples) return set_error(TM_EINVAL, "null output");
     *tuples = 0;
     if (p->cp.hdr.n == 0) return TM_OK;
-    if (!p->d_arena || p->cap_words < p->cp.arena_words) return set_error(TM_EINVAL, "no tables yet: run the plan first");
+    if (p->cap_words < p->cp.arena_words) return set_error(TM_EINVAL, "not run yet: run the plan first");
     hipStream_t s = (hipStream_t)stream;
     unsigned long long* d_tot = nullptr;
     TM_HIP(hipMallocAsync((void**)&d_tot, 8, s));
     unsigned long long h = 0;
     hipError_t e = hipMemsetAsync(d_tot, 0, 8, s);
-    if (e == hipSuccess) e = launch_class_tuples(p->d_cands, p->cp.hdr.n, p->d_arena, d_tot, s);
+    if (e == hipSuccess) e = launch_class_tuples(p->d_cands, p->cp.hdr.n, p->cp.hdr.halo, d_tot, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&h, d_tot, 8, hipMemcpyDeviceToHost, s);
     (void)hipFreeAsync(d_tot, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -834,40 +869,42 @@ extern "C" int tm_plan_class_tuples(tm_plan* p, int64_t* tuples, void* stream) {
     return TM_OK;
 }
 
+// A launch configuration for the loaded batch (cells_per_item 0: the default).
+static int plan_relayout(tm_plan* p, int64_t cells_per_item, int wg_per_cu, hipStream_t s) {
+    p->cells_per_item = cells_per_item;
+    p->wg_per_cu = wg_per_cu;
+    if (p->cp.hdr.n == 0) return TM_OK;
+    layout_items(p->cp, cells_per_item > 0 ? cells_per_item : default_tuples_per_item(p->cp.tuples));
+    layout_eval(p->cp, cells_per_item, false);
+    p->cp.eval.wg_per_cu = wg_per_cu;
+    plan_drop_graphs(p);
+    return plan_upload(p, s);
+}
+
 extern "C" int tm_plan_autotune(tm_plan* p, tm_stencil_cost* d_out, int64_t* cells_per_item, int32_t* wg_per_cu,
                                 void* stream) {
     if (!p || !p->loaded) return set_error(TM_EINVAL, "plan not loaded");
     if (p->cp.hdr.n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
     hipStream_t s = (hipStream_t)stream;
-    int arc = plan_ensure_arena(p, s);
-    if (arc != TM_OK) return arc;
     hipEvent_t e0, e1;
     TM_HIP(hipEventCreate(&e0));
     TM_HIP(hipEventCreate(&e1));
     const int64_t cells_opts[] = {1 << 10, 1 << 12, 1 << 14};
     const int wg_opts[] = {0, 2, 1};
     float best_ms = 1e30f;
-    int64_t best_c = default_tuples_per_item(p->cp.tuples);
+    int64_t best_c = cells_opts[0];
     int best_w = 0;
     int rc = TM_OK;
     for (int64_t cpi : cells_opts) {
-        layout_items(p->cp, cpi);
-        rc = plan_ensure_arena(p, s);
-        if (rc == TM_OK) rc = plan_upload(p, s);
-        if (rc != TM_OK) break;
-        // tables once per layout (they do not depend on it)
-        if (plan_enqueue(p, 0, d_out, nullptr, 1, s) != hipSuccess) {
-            rc = set_error(TM_EDEVICE, "autotune build");
-            break;
-        }
+        layout_eval(p->cp, cpi, false);
+        rc = plan_upload(p, s);
         for (int w : wg_opts) {
-            const int grid = count_grid(p->cp.cnt_words, p->cp.items, w);
+            p->cp.eval.wg_per_cu = w;
             float tot = 0.f;
             for (int rep = 0; rep < 3 && rc == TM_OK; ++rep) {
-                hipError_t e = launch_reset(p->d_hdr, p->d_counter, d_out, p->cp.hdr.n, s);
-                if (e == hipSuccess) e = hipEventRecord(e0, s);
-                if (e == hipSuccess) e = plan_enqueue(p, 1, d_out, nullptr, grid, s);
+                hipError_t e = hipEventRecord(e0, s);
+                if (e == hipSuccess) e = plan_enqueue(p, 1, d_out, nullptr, s);
                 if (e == hipSuccess) e = hipEventRecord(e1, s);
                 if (e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.f;
@@ -887,12 +924,7 @@ extern "C" int tm_plan_autotune(tm_plan* p, tm_stencil_cost* d_out, int64_t* cel
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != TM_OK) return rc;
-    p->cells_per_item = best_c;
-    p->wg_per_cu = best_w;
-    layout_items(p->cp, best_c);
-    plan_drop_graphs(p);
-    rc = plan_ensure_arena(p, s);
-    if (rc == TM_OK) rc = plan_upload(p, s);
+    rc = plan_relayout(p, best_c, best_w, s);
     if (cells_per_item) *cells_per_item = best_c;
     if (wg_per_cu) *wg_per_cu = best_w;
     return rc;
@@ -903,12 +935,7 @@ extern "C" int tm_plan_set_launch(tm_plan* p, int64_t cells_per_item, int32_t wg
     if (cells_per_item < 0 || cells_per_item > kMaxCellsPerItem || wg_per_cu < 0)
         return set_error(TM_EINVAL, "cells_per_item %lld (at most 2^26), wg_per_cu %d", (long long)cells_per_item,
                          wg_per_cu);
-    p->cells_per_item = cells_per_item;
-    p->wg_per_cu = wg_per_cu;
-    if (p->cp.hdr.n == 0) return TM_OK;
-    layout_items(p->cp, cells_per_item > 0 ? cells_per_item : default_tuples_per_item(p->cp.tuples));
-    plan_drop_graphs(p);
-    return plan_upload(p, (hipStream_t)stream);
+    return plan_relayout(p, cells_per_item, wg_per_cu, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------ search support
@@ -1112,10 +1139,8 @@ int plan_exhaustive_search(tm_plan* p, const int64_t* seg, int64_t nseg, int64_t
     if (!d_best) return set_error(TM_EINVAL, "null output");
     SearchBufs* sb = nullptr;
     int rc = plan_search_prepare(p, seg, nseg, 0, 0, false, &sb, s);
-    if (rc == TM_OK) rc = plan_ensure_arena(p, s);
     if (rc != TM_OK) return rc;
-    const int grid = count_grid(p->cp.cnt_words, p->cp.items, p->wg_per_cu);
-    hipError_t e = plan_enqueue(p, -1, sb->all_out, nullptr, grid, s);
+    hipError_t e = plan_enqueue(p, -1, sb->all_out, nullptr, s);
     if (e == hipSuccess) e = launch_select_segments(sb->all_out, sb->seg, nseg, d_best, s);
     if (e == hipSuccess) e = launch_pick_costs(d_best, sb->seg, sb->all_out, nseg, d_best_cost, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "exhaustive search: %s", hipGetErrorString(e));

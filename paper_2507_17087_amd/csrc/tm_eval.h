@@ -1,0 +1,64 @@
+// tm_eval.h -- launch interface of the stencil evaluation (tm_eval.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "tm_internal.h"
+
+namespace tmk {
+
+// One launch: candidates that need words in (min_words, max_words], with lds_words of LDS,
+// in up to `parts` workgroups each.  parts == 1: whole cost rows are stored; else the cells are added to
+// rows the caller zeroed (bytes follow in another launch).  best (parts == 1, one launch
+// for all candidates): the last workgroup also selects; counter starts at 0 and is left
+// so.
+struct EvalArgs {
+    const DevEval* evals;
+    int64_t n;
+    tm_stencil_cost* out;
+    int64_t* best;
+    unsigned long long* counter;
+    int64_t elem_bytes;
+    int32_t halo[TM_MAX_LRANK];
+    int32_t node_level, parts, min_words, max_words, lds_words;
+};
+
+// A batch's launches.
+struct EvalPlan {
+    int64_t n = 0, items = 0, elem_bytes = 0;
+    int64_t per_item = 0, fill = 1;  // the caller's tuples per work item, or the parts to fill the GPU with
+    int32_t halo[TM_MAX_LRANK] = {0, 0, 0, 0};
+    int32_t H = 0, parts = 1, node_level = 0;
+    int32_t split = 0;          // candidates needing at most this many LDS words: the first launch
+    int32_t words[2] = {0, 0};  // LDS words of the two launches (0: no such candidate)
+    int32_t wg_per_cu = 0;      // at most this many workgroups per CU (0: one per item)
+};
+
+// Evaluates the batch into out (n rows) and, with best, selects into *best.  counter: a
+// device word that holds 0 between launches.
+hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
+                             unsigned long long* counter, int cus, hipStream_t s);
+// The evaluation's view of n compiled candidates.
+hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, hipStream_t s);
+// The rows zeroed; and the bytes of rows that hold cells, with the selection.
+hipError_t launch_zero_costs(tm_stencil_cost* out, int64_t n, hipStream_t s);
+hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s);
+// Sum over the candidates of the product of their class counts (tm_plan_class_tuples).
+hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* halo, unsigned long long* total,
+                               hipStream_t s);
+
+// Batches of at least this many candidates run one-wave workgroups.
+constexpr int64_t kEvalWaveBatch = 2048;
+
+// LDS words of a launch: records share the LDS up to kEvalSmall* words (5 KB per one-wave
+// workgroup keeps 26 of them on a CU, 20 KB per four-wave one 8); all candidates go in one
+// launch up to kEvalMost*.  Measured on 4,096 random candidates, largest need 1,350 words:
+// one launch 32 us, two (1,280 words and the rest) 50 us.
+constexpr int32_t kEvalSmallWave = 1280, kEvalMostWave = 2048;
+constexpr int32_t kEvalSmallBlock = 5120, kEvalMostBlock = 8192;
+// Without a caller's item size, batches smaller than this many workgroups split their
+// candidates into parts of at least kEvalPartTuples tuples.
+constexpr int64_t kEvalFill = 512, kEvalPartTuples = 1024;
+
+}  // namespace tmk

@@ -10,6 +10,69 @@
 
 namespace tmk {
 
+// One transformation as the kernels undo it, on linear indices (C order) of the
+// processor space: the dims it touches form a contiguous range of its input shape
+// (swap and merge: from the lower to the higher position; the others: one dim), inside
+// which it maps the range's digits; the dims before and after pass through.  lo: the
+// product of the dims after the range; wi / wo: volume of the range in the input /
+// output shape; then per kind (u, and in f the reciprocals of its divisors):
+//   split, balance_split  u = {b, c}: output digits (a of extent b, a1 of extent c)
+//   merge                 u = {mid, s_p, s_q}; f = {1/mid, 1/s_p}
+//   swap                  u = {mid * s_lo, s_lo, s_hi, mid}; f = {1/(mid * s_lo), 1/s_lo}
+//   decompose             u = the factors (1 past their number); f = 1/u
+// A balance_split whose factor divides is recorded as the split it equals.  One 64-byte
+// record: four 16-byte LDS reads.
+struct DevOp {
+    int32_t kind;                 // tm_op_kind | kOpNoLo / kOpNoHi: lo == 1 / nothing before the range
+    uint32_t lo, wi, wo;
+    float rlo, rwo;               // 1/lo, 1/wo
+    uint32_t u[5];
+    float f[5];
+};
+constexpr int32_t kOpKind = 0xff, kOpNoLo = 0x100, kOpNoHi = 0x200;
+
+// A final dim of size above 1 as a launch dim's coordinates see it.
+struct DevProj {
+    int32_t s, stride;            // its size and its stride in the final space
+    double rs;                    // 1/s
+};
+
+// Coordinate groups of one launch dim.  Coordinates with the same contribution to the
+// final index form a group.  The block projections' change points (cells where one of
+// their block indices steps) cut [0, l) into segments in which they are constant; within
+// a segment the contribution depends only on x modulo M, the least common multiple of
+// the cyclic sizes.  Group g = a M + r holds segment a's coordinates x0 + r, x0 + r + M,
+// ... .  When that would give no fewer groups than coordinates, every coordinate is a
+// segment of its own (ident: nseg = l, M = 1).  Coinciding change points of several
+// block projections give empty segments.  48 bytes: three 16-byte LDS reads.
+struct DevDim {
+    int32_t l, M;                 // extent, residues
+    int32_t nseg, G;              // segments; groups: nseg * M
+    int32_t first, nblk, ncyc;    // its entries of DevEval::pj: the block ones, then the cyclic ones
+    int32_t ident;
+    double rl;                    // 1/l
+    double rM;                    // 1/M
+};
+
+// What the stencil evaluation reads of a candidate: 896 bytes, staged in LDS with one
+// 16-byte load per lane.
+struct alignas(16) DevEval {
+    int32_t vol, lrank, nops, gbits;
+    int32_t gpus;
+    float rgpus;                  // 1/gpus
+    int32_t bij;                  // every op is a bijection: distinct coordinates, distinct owners
+    int32_t flags;                // kEval*
+    int32_t words, parts, dim_d;  // LDS words the evaluation needs, its workgroups; the dim with the most groups
+    int32_t pad[5];
+    DevDim dim[TM_MAX_LRANK];
+    DevProj pj[TM_MAX_MRANK];
+    DevOp inv[TM_MAX_OPS];
+};
+// kEvalCyclic: some launch dim has a cyclic projection; kEvalExtra: some has several
+// block or several cyclic ones
+constexpr int32_t kEvalCyclic = 1, kEvalExtra = 2;
+static_assert(sizeof(DevEval) == 896, "staged by the first 56 lanes of a wave");
+
 // Compiled candidate as the kernels read it.  The host fills in the shapes of the
 // processor space before every transformation (validation computes them anyway);
 // the table-build kernel derives everything per coordinate from these.
@@ -123,6 +186,14 @@ __host__ __device__ inline int32_t count_items(const DevCand& c, int64_t per_ite
     return (int32_t)(it < 1 ? 1 : (it > (int64_t(1) << 30) ? (int64_t(1) << 30) : it));
 }
 
+// Stride (int32 words) of the stencil evaluation's group records (tm_groups.h) for halos
+// up to h, with cyclic projections, with masks.
+__host__ __device__ inline int32_t group_stride(bool cyclic, int32_t h, bool masks) {
+    return 2 + (cyclic ? 4 : 2) * h + (masks ? (h + 2) & ~1 : 0);
+}
+// The records are laid out for halos up to 1, 2 or 4.
+__host__ __device__ inline int32_t halo_class(int32_t h) { return h <= 1 ? 1 : (h <= 2 ? 2 : 4); }
+
 int set_error(int code, const char* fmt, ...);
 int validate_shapes(const tm_candidate* c, Shapes* sh);
 int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
@@ -133,8 +204,10 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
 hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena,
                                int32_t mode_halo, hipStream_t s, tm_stencil_cost* out = nullptr,
                                unsigned long long* counter = nullptr);
-hipError_t launch_reset(DevHeader* hdr, unsigned long long* counter, tm_stencil_cost* out, int64_t n,
-                        hipStream_t s);
+// Tables (owners and coordinates, no classes) of one candidate, *d_index or index, to
+// the start of `arena`.
+hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t n, const int64_t* d_index,
+                            int64_t index, int32_t* arena, hipStream_t s);
 // Counting; with fin the last workgroup to finish also writes the bytes and, when
 // best is given, selects (the work of k_finalize_select; for small batches).
 hipError_t launch_count(const DevHeader* hdr, const DevCand* cands, const int32_t* arena,
@@ -142,8 +215,6 @@ hipError_t launch_count(const DevHeader* hdr, const DevCand* cands, const int32_
                         hipStream_t s, bool fin = false, int64_t* best = nullptr);
 // Batches up to this many candidates finalise inside the counting launch.
 constexpr int64_t kFinInCount = 2048;
-hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* arena, unsigned long long* total,
-                               hipStream_t s);
 // n_max: an upper bound on the header's candidate count; without best, batches above
 // kFinBytesGrid candidates take their bytes in a grid-wide launch.
 constexpr int64_t kFinBytesGrid = 65536;
@@ -151,6 +222,7 @@ hipError_t launch_finalize_select(const DevHeader* hdr, tm_stencil_cost* out, in
                                   hipStream_t s);
 hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg,
                                   int64_t* best, hipStream_t s, const int64_t* key = nullptr);
+// arena: the mapped candidate's tables.
 hipError_t launch_map(const DevCand* cands, int64_t n, const int32_t* arena, const int64_t* d_index,
                       int64_t index, int32_t* out, int grid, int lds_words, hipStream_t s);
 hipError_t launch_chain_table(const DevCand* cand, const int32_t* arena, int32_t* out, hipStream_t s);

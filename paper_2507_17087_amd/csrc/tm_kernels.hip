@@ -206,18 +206,23 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
                                                       const DevCand* __restrict__ cands,
                                                       int32_t* __restrict__ arena, int use_halo,
                                                       tm_stencil_cost* __restrict__ out,
-                                                      unsigned long long* __restrict__ counter, int split) {
+                                                      unsigned long long* __restrict__ counter, int split,
+                                                      int64_t one, const int64_t* __restrict__ d_one) {
     __shared__ DevCand sc;
     __shared__ int32_t s_wt[4];
     __shared__ int32_t s_ct[kBuildStage];
     __shared__ float s_rt[kRecipSlots];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
     const int upc = split ? TM_MAX_LRANK : 1;  // units per candidate
-    const int64_t units = hdr->n * upc;
+    // a single candidate (one or *d_one; its tables start the arena), or the whole batch
+    const bool single = one >= 0 || d_one;
+    if (d_one) one = uniform64(*d_one);
+    if (single && (one < 0 || one >= hdr->n)) return;  // no candidate selected
+    const int64_t units = (single ? 1 : hdr->n) * upc;
     if (counter && blockIdx.x == 0 && tid < 2) counter[tid] = 0ull;
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const int64_t ci = u / upc;
-        const int dlo = (int)(u - ci * upc);
+        const int64_t ui = u / upc, ci = single ? one : ui;
+        const int dlo = (int)(u - ui * upc);
         const int K = (int)__builtin_amdgcn_readfirstlane((uint32_t)cands[ci].lrank);
         if (dlo >= K) continue;  // uniform
         const int dhi = split ? dlo + 1 : K;
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
         lds_sync(nw);
         op_reciprocals(sc, s_rt, tid, blockDim.x);
         lds_sync(nw);
-        int32_t* base = arena + sc.arena_off;
+        int32_t* base = arena + (single ? 0 : sc.arena_off);
         if (dlo == 0) {
             if (out && tid < 4) reinterpret_cast<int64_t*>(&out[ci])[tid] = 0;
             if (use_halo)  // this candidate's entries of the item table (work item -> candidate)
@@ -323,27 +328,16 @@ hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64
     const int64_t grid = units < 131072 ? (units > 0 ? units : 1) : 131072;
     const int bs = n >= kSmallBlockBatch ? 64 : 256;
     hipLaunchKernelGGL(k_build_tables, dim3((unsigned)grid), dim3(bs), 0, s, hdr, cands, arena, use_halo, out,
-                       counter, split);
+                       counter, split, (int64_t)-1, (const int64_t*)nullptr);
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ reset
-
-__global__ void k_reset(DevHeader* hdr, unsigned long long* counter, tm_stencil_cost* out, int64_t cap) {
-    const int64_t n = hdr->n < cap ? hdr->n : cap;
-    int64_t* o = reinterpret_cast<int64_t*>(out);
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 4 * n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        o[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x < 2) counter[threadIdx.x] = 0ull;  // work and completion counters
-}
-
-hipError_t launch_reset(DevHeader* hdr, unsigned long long* counter, tm_stencil_cost* out, int64_t n,
-                        hipStream_t s) {
-    int64_t grid = (4 * n + 255) / 256;
-    if (grid < 1) grid = 1;
-    if (grid > 4096) grid = 4096;
-    hipLaunchKernelGGL(k_reset, dim3((unsigned)grid), dim3(256), 0, s, hdr, counter, out, n);
+hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t n, const int64_t* d_index,
+                            int64_t index, int32_t* arena, hipStream_t s) {
+    (void)n;
+    hipLaunchKernelGGL(k_build_tables, dim3(TM_MAX_LRANK), dim3(256), 0, s, hdr, cands, arena, 0,
+                       (tm_stencil_cost*)nullptr, (unsigned long long*)nullptr, 1, d_index ? (int64_t)-1 : index,
+                       d_index);
     return hipGetLastError();
 }
 
@@ -507,30 +501,6 @@ hipError_t launch_count(const DevHeader* hdr, const DevCand* cands, const int32_
     return hipGetLastError();
 }
 
-// Sum over candidates of the product of their class counts (the counting work).
-__global__ __launch_bounds__(256) void k_class_tuples(const DevCand* __restrict__ cands, int64_t n,
-                                                      const int32_t* __restrict__ arena,
-                                                      unsigned long long* __restrict__ total) {
-    unsigned long long acc = 0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const DevCand& c = cands[i];
-        const int32_t* rec = arena + c.arena_off + c.cls_base;
-        unsigned long long t = 1;
-        for (int d = 0; d < c.lrank; ++d) t *= (unsigned long long)(rec[d] > 0 ? rec[d] : 0);
-        acc += t;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((threadIdx.x & 63) == 0 && acc) atomicAdd(total, acc);
-}
-
-hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* arena, unsigned long long* total,
-                               hipStream_t s) {
-    const int64_t grid = std::min<int64_t>(std::max<int64_t>((n + 255) / 256, 1), 1024);
-    hipLaunchKernelGGL(k_class_tuples, dim3((unsigned)grid), dim3(256), 0, s, cands, n, arena, total);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ bytes + selection
 
 // One workgroup: bytes from cell counts, then the minimum of (bytes, inter_bytes,
@@ -678,7 +648,7 @@ __global__ __launch_bounds__(NT) void k_map(const DevCand* __restrict__ cands, i
     if (ci < 0 || ci >= n) return;  // no candidate selected (empty batch)
     const DevCand* __restrict__ c = &cands[ci];
     const int32_t words = uniform32(c->lds_words);
-    const int32_t* G = arena + uniform64(c->arena_off);  // outer tables (and a last-dim table that did not fit)
+    const int32_t* G = arena;  // this candidate's tables
     {
         const i32x4* s4 = reinterpret_cast<const i32x4*>(G);
         i32x4* d4 = reinterpret_cast<i32x4*>(lds);

@@ -8,7 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <vector>
 
+#include "tm_compile.h"
 #include "tm_internal.h"
 #include "tm_plan.h"
 
@@ -39,6 +41,10 @@ static int scratch_ptr(void** out) {
     return TM_OK;
 }
 
+// A candidate counts for its compiled descriptor and its table words against
+// TM_NOALLOC_SCRATCH_BYTES; the evaluation's descriptor, all that is stored, takes less.
+static_assert(sizeof(DevEval) <= sizeof(DevCand), "the evaluation's descriptors fit");
+
 static int64_t up256(int64_t x) { return (x + 255) & ~int64_t(255); }
 
 }  // namespace tmk
@@ -65,24 +71,16 @@ extern "C" int tm_eval_stencil_batch_noalloc(const tm_candidate* c, int64_t n, c
     char* base = nullptr;
     rc = scratch_ptr((void**)&base);
     if (rc != TM_OK) return rc;
-    DevHeader* hdr = reinterpret_cast<DevHeader*>(base);
-    DevCand* cands = reinterpret_cast<DevCand*>(base + o_cands);
-    int32_t* arena = reinterpret_cast<int32_t*>(base + o_arena);
-    unsigned long long* counter = reinterpret_cast<unsigned long long*>(base + o_count);
-    // the descriptors go up from this call's host memory; waiting for the copies keeps
-    // it alive until they are done (nothing here allocates pinned staging)
-    hipError_t e = hipMemcpyAsync(hdr, &cp.hdr, sizeof(DevHeader), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(cands, cp.cands.data(), (size_t)n * sizeof(DevCand), hipMemcpyHostToDevice, s);
+    layout_eval(cp, 0, false);
+    const EvalShape shape{cp.eval.H, cp.eval.node_level, cp.eval.per_item, cp.eval.fill};
+    std::vector<DevEval> evals((size_t)n);
+    for (int64_t i = 0; i < n; ++i) fill_eval(cp.cands[(size_t)i], shape, &evals[(size_t)i]);
+    DevEval* d_evals = reinterpret_cast<DevEval*>(base + o_cands);
+    // the descriptors go up from this call's host memory; waiting for the copy keeps it
+    // alive until it is done (nothing here allocates pinned staging)
+    hipError_t e = hipMemcpyAsync(d_evals, evals.data(), (size_t)n * sizeof(DevEval), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    // the table build writes the whole arena (tables and item table) and zeroes the
-    // outputs and both counters before the counting starts
-    const bool fin = n <= kFinInCount;
-    if (e == hipSuccess) e = launch_build_tables(hdr, cands, n, arena, 1, s, d_out, counter);
-    if (e == hipSuccess)
-        e = launch_count(hdr, cands, arena, counter, d_out, count_grid(cp.cnt_words, cp.items, 0), cp.cnt_words, s,
-                         fin, nullptr);
-    if (e == hipSuccess && !fin) e = launch_finalize_select(hdr, d_out, nullptr, n, s);
+    if (e == hipSuccess) e = launch_eval_batch(cp.eval, d_evals, d_out, nullptr, nullptr, 0, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "stencil launch (no allocation): %s", hipGetErrorString(e));
     return TM_OK;
 }

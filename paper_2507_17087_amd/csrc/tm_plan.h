@@ -6,6 +6,7 @@
 
 #include <vector>
 
+#include "tm_eval.h"
 #include "tm_internal.h"
 
 namespace tmk {
@@ -22,6 +23,7 @@ struct Compiled {
     int64_t tuples = 0;         // class-tuple bound of the batch (sum of the candidates')
     int64_t tables_words = 0;   // arena words of the tables (the item table follows)
     int32_t max_citems = 0;     // most counting work items of one candidate
+    EvalPlan eval;              // the evaluation's launches
     int K = 0, H = 1;
 };
 
@@ -51,9 +53,12 @@ struct SearchBufs {
 
 struct tm_plan {
     int device = 0;
-    int64_t cap_cands = 0, cap_words = 0;
+    int64_t cap_cands = 0;
+    int64_t cap_words = 0;            // table words of the largest batch run so far (or reserved at creation)
+    int64_t cap_arena = 0;            // words of d_arena
     tmk::DevCand* d_cands = nullptr;
-    int32_t* d_arena = nullptr;
+    tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
+    int32_t* d_arena = nullptr;       // tables of the candidate being mapped
     tmk::DevHeader* d_hdr = nullptr;
     unsigned long long* d_counter = nullptr;
     tmk::DevCand* h_cands = nullptr;  // pinned staging
@@ -69,7 +74,6 @@ struct tm_plan {
     int wg_per_cu = 0;
     // graph cache: one entry
     bool g_valid = false;
-    int g_grid = 0;
     void* g_out = nullptr;
     void* g_best = nullptr;
     hipGraphExec_t g_full = nullptr, g_stage[3] = {nullptr, nullptr, nullptr};
@@ -84,6 +88,9 @@ namespace tmk {
 // classes; need_lds: every owner table must fit the kernels' LDS budget).
 int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_t tuples_per_item, bool need_lds,
                   Compiled& cp);
+// Lays out the evaluation of a compiled stencil batch (per-candidate LDS words, dim and
+// parts; the launches).  node_level: the node-level volume.
+void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 // Grid of the persistent counting launch for `items` work items.
 int count_grid(int lds_words, int64_t items, int wg_per_cu);
 
