@@ -301,14 +301,6 @@ static int num_cus() {
     return n;
 }
 
-int count_grid(int lds_words, int64_t items, int wg_per_cu) {
-    int per_cu = 0;
-    if (count_kernel_occupancy(lds_words, &per_cu) != 0 || per_cu < 1) per_cu = 1;
-    if (wg_per_cu > 0) per_cu = std::min(per_cu, wg_per_cu);
-    const int64_t g = (int64_t)per_cu * num_cus();
-    return (int)std::max<int64_t>(1, std::min<int64_t>(g, items));
-}
-
 }  // namespace tmk
 
 using namespace tmk;
@@ -547,7 +539,7 @@ extern "C" int tm_select_best(const tm_stencil_cost* d_costs, const int64_t* seg
         std::memcpy(stg, seg, (size_t)(nseg + 1) * 8);
         hipError_t e = hipMemcpyAsync(d_seg, stg, (size_t)(nseg + 1) * 8, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) rc = staging_release(s);
-        if (rc == TM_OK && e == hipSuccess) e = launch_select_segments(d_costs, d_seg, nseg, d_best, s);
+        if (rc == TM_OK && e == hipSuccess) e = launch_select_segments(d_costs, d_seg, nseg, nullptr, 0, d_best, nullptr, s);
         if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "select launch: %s", hipGetErrorString(e));
     }
     (void)hipFreeAsync(d_seg, s);
@@ -571,8 +563,7 @@ static void plan_drop_graphs(tm_plan* p) {
 }
 
 static void search_free(SearchBufs& b) {
-    void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.cross, b.seg, b.sel, b.sub, b.map, b.sub_seg, b.sub_hdr,
-                    b.sub_arena, b.sub_counter, b.sub_out, b.sub_best, b.all_out};
+    void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.cross, b.seg, b.sel, b.sub_out, b.all_out};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     b = SearchBufs{};
@@ -946,10 +937,6 @@ int64_t plan_size(const tm_plan* p) { return p->cp.hdr.n; }
 const DevCand* plan_cands(const tm_plan* p) { return p->d_cands; }
 int32_t plan_max_vol(const tm_plan* p) { return p->cp.max_vol; }
 const int32_t* plan_halo(const tm_plan* p) { return p->d_hdr->halo; }
-const DevHeader* plan_hdr(const tm_plan* p) { return p->d_hdr; }
-int64_t plan_cells_per_item(const tm_plan* p) {
-    return p->cells_per_item > 0 ? p->cells_per_item : default_tuples_per_item(p->cp.tuples);
-}
 
 // Ranker buffers: features and outputs of n rows; scores and chain statistics of
 // max(n, m) entries (m: the second stage's survivors of a ranked search).
@@ -1024,8 +1011,6 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
     SearchBufs& b = p->sb;
     const int64_t nsel = ranked ? nseg * (int64_t)topk : 0;
     const int64_t npre = ranked ? nseg * (int64_t)prefilter : 0;
-    // survivors' tables, then their item table
-    const int64_t words = nsel * (std::max<int64_t>(p->cp.max_all_words, 1) + p->cp.max_citems) + 4;
     auto grow = [&](bool need) -> int {
         if (!need) return TM_OK;
         TM_HIP(hipStreamSynchronize(s));
@@ -1043,31 +1028,18 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
                 return set_error(TM_ENOMEM, "prefilter buffer");
             b.cap_pre = npre;
         }
-        if (b.cap_sel < nsel || b.cap_words < words) {
+        if (b.cap_sel < nsel) {
             int rc = grow(true);
             if (rc != TM_OK) return rc;
-            void* ptrs[] = {b.sel, b.sub, b.map, b.sub_arena, b.sub_out};
-            for (void* q : ptrs)
-                if (q) (void)hipFree(q);
+            if (b.sel) (void)hipFree(b.sel);
+            if (b.sub_out) (void)hipFree(b.sub_out);
             b.sel = nullptr;
-            b.sub = nullptr;
-            b.map = nullptr;
-            b.sub_arena = nullptr;
             b.sub_out = nullptr;
-            b.cap_sel = b.cap_words = 0;
+            b.cap_sel = 0;
             if (hipMalloc((void**)&b.sel, (size_t)nsel * 8) != hipSuccess ||
-                hipMalloc((void**)&b.sub, (size_t)nsel * sizeof(DevCand)) != hipSuccess ||
-                hipMalloc((void**)&b.map, (size_t)nsel * 8) != hipSuccess ||
-                hipMalloc((void**)&b.sub_arena, (size_t)std::max<int64_t>(words, 1) * 4) != hipSuccess ||
                 hipMalloc((void**)&b.sub_out, (size_t)nsel * sizeof(tm_stencil_cost)) != hipSuccess)
                 return set_error(TM_ENOMEM, "survivor buffers");
             b.cap_sel = nsel;
-            b.cap_words = words;
-        }
-        if (!b.sub_hdr) {
-            if (hipMalloc((void**)&b.sub_hdr, sizeof(DevHeader)) != hipSuccess ||
-                hipMalloc((void**)&b.sub_counter, 256) != hipSuccess)
-                return set_error(TM_ENOMEM, "survivor header");
         }
     } else if (b.cap_all < n) {
         int rc = grow(b.all_out != nullptr);
@@ -1083,13 +1055,9 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
         int rc = grow(true);
         if (rc != TM_OK) return rc;
         if (b.seg) (void)hipFree(b.seg);
-        if (b.sub_seg) (void)hipFree(b.sub_seg);
-        if (b.sub_best) (void)hipFree(b.sub_best);
-        b.seg = b.sub_seg = b.sub_best = nullptr;
+        b.seg = nullptr;
         b.cap_seg = 0;
-        if (hipMalloc((void**)&b.seg, (size_t)(nseg + 1) * 8) != hipSuccess ||
-            hipMalloc((void**)&b.sub_seg, (size_t)(nseg + 1) * 8) != hipSuccess ||
-            hipMalloc((void**)&b.sub_best, (size_t)(nseg + 1) * 8) != hipSuccess)
+        if (hipMalloc((void**)&b.seg, (size_t)(nseg + 1) * 8) != hipSuccess)
             return set_error(TM_ENOMEM, "segment buffers");
         b.cap_seg = nseg + 1;
     }
@@ -1117,21 +1085,13 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
     return TM_OK;
 }
 
-// Exact costs of the survivors gathered in sb (descriptors and header on device).
-hipError_t plan_eval_sub(tm_plan* p, SearchBufs* sb, hipStream_t s) {
+// The best of the candidates chosen in sb (sb->sel), by their exact costs.
+hipError_t plan_eval_chosen(tm_plan* p, SearchBufs* sb, int64_t* d_best, tm_stencil_cost* d_best_cost, hipStream_t s) {
     const int64_t nsel = sb->nseg * sb->k;
-    const Compiled& cp = p->cp;
-    hipError_t e = launch_build_tables(sb->sub_hdr, sb->sub, nsel, sb->sub_arena, 1, s, sb->sub_out, sb->sub_counter);
-    if (e == hipSuccess) {
-        // survivors' work items are bounded by the batch's largest candidate (its item
-        // count under the plan's current layout)
-        const int64_t max_items = cp.max_citems;
-        const int grid = count_grid(cp.cnt_words, std::max<int64_t>(1, max_items * nsel), p->wg_per_cu);
-        e = launch_count(sb->sub_hdr, sb->sub, sb->sub_arena, sb->sub_counter, sb->sub_out, grid, cp.cnt_words, s,
-                         nsel <= kFinInCount, nullptr);
-    }
-    if (e == hipSuccess && nsel > kFinInCount) e = launch_finalize_select(sb->sub_hdr, sb->sub_out, nullptr, nsel, s);
-    return e;
+    const hipError_t e = launch_eval_batch(p->cp.eval, p->d_evals, sb->sub_out, nullptr, p->d_counter, num_cus(), s,
+                                           sb->sel, nsel);
+    if (e != hipSuccess) return e;
+    return launch_select_segments(sb->sub_out, sb->seg, sb->nseg, sb->sel, sb->k, d_best, d_best_cost, s);
 }
 
 int plan_exhaustive_search(tm_plan* p, const int64_t* seg, int64_t nseg, int64_t* d_best,
@@ -1141,8 +1101,7 @@ int plan_exhaustive_search(tm_plan* p, const int64_t* seg, int64_t nseg, int64_t
     int rc = plan_search_prepare(p, seg, nseg, 0, 0, false, &sb, s);
     if (rc != TM_OK) return rc;
     hipError_t e = plan_enqueue(p, -1, sb->all_out, nullptr, s);
-    if (e == hipSuccess) e = launch_select_segments(sb->all_out, sb->seg, nseg, d_best, s);
-    if (e == hipSuccess) e = launch_pick_costs(d_best, sb->seg, sb->all_out, nseg, d_best_cost, s);
+    if (e == hipSuccess) e = launch_select_segments(sb->all_out, sb->seg, nseg, nullptr, 0, d_best, d_best_cost, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "exhaustive search: %s", hipGetErrorString(e));
     return TM_OK;
 }

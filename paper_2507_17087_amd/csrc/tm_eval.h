@@ -15,6 +15,7 @@ namespace tmk {
 // so.
 struct EvalArgs {
     const DevEval* evals;
+    const int64_t* idx;  // row i evaluates candidate idx[i] (negative: no row); null: i
     int64_t n;
     tm_stencil_cost* out;
     int64_t* best;
@@ -36,9 +37,11 @@ struct EvalPlan {
 };
 
 // Evaluates the batch into out (n rows) and, with best, selects into *best.  counter: a
-// device word that holds 0 between launches.
+// device word that holds 0 between launches.  With idx, the nidx candidates idx[i] instead
+// (whole ones; rows of negative entries are left alone).
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
-                             unsigned long long* counter, int cus, hipStream_t s);
+                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
+                             int64_t nidx = 0);
 // The evaluation's view of n compiled candidates.
 hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, hipStream_t s);
 // The rows zeroed; and the bytes of rows that hold cells, with the selection.

@@ -366,8 +366,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : 
     // the record of a dim of one coordinate: {0, 1}, no offsets
     if (tid < kOneRecord) lds[A.lds_words + tid] = tid == 1 ? 1 : 0;
     for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const int64_t ci = A.parts == 1 ? item : item / A.parts;
-        const int part = (int)(item - ci * A.parts);
+        const int64_t row = A.parts == 1 ? item : item / A.parts;
+        const int part = (int)(item - row * A.parts);
+        const int64_t ci = A.idx ? wave_uniform64(A.idx[row]) : row;
+        if (ci < 0) continue;
         if (item != (int64_t)blockIdx.x) lds_sync(NW);  // the previous item's LDS is no longer read
         stage_eval(&ev, A.evals + ci, tid);
         lds_sync(NW);
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : 
                     inter += s_sum[w][1];
                 }
             }
-            tm_stencil_cost* o = &A.out[ci];
+            tm_stencil_cost* o = &A.out[row];
             const int64_t gc = (int64_t)tot, ic = (int64_t)inter;
             if (A.parts == 1) {
                 *o = tm_stencil_cost{gc, ic, gc * A.elem_bytes, ic * A.elem_bytes};
@@ -492,22 +494,25 @@ hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_byt
 }
 
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
-                             unsigned long long* counter, int cus, hipStream_t s) {
-    if (p.n <= 0) return hipSuccess;
+                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx, int64_t nidx) {
+    const int64_t n = idx ? nidx : p.n;
+    if (n <= 0) return hipSuccess;
+    const int32_t parts = idx ? 1 : p.parts;
     EvalArgs A{};
     A.evals = evals;
-    A.n = p.n;
+    A.idx = idx;
+    A.n = n;
     A.out = out;
     A.counter = counter;
     A.elem_bytes = p.elem_bytes;
     A.node_level = p.node_level;
-    A.parts = p.parts;
+    A.parts = parts;
     for (int d = 0; d < TM_MAX_LRANK; ++d) A.halo[d] = p.halo[d];
     // the last workgroup of a single launch over few rows selects; else a launch of its own
-    const bool fin = best && p.parts == 1 && p.n <= kFinInCount && (p.words[0] == 0 || p.words[1] == 0);
+    const bool fin = best && parts == 1 && n <= kFinInCount && (p.words[0] == 0 || p.words[1] == 0);
     if (fin) A.best = best;
-    hipError_t e = p.parts > 1 ? launch_zero_costs(out, p.n, s) : hipSuccess;
-    int64_t grid = p.n * p.parts;
+    hipError_t e = parts > 1 ? launch_zero_costs(out, n, s) : hipSuccess;
+    int64_t grid = n * parts;
     if (p.wg_per_cu > 0) grid = std::min<int64_t>(grid, (int64_t)p.wg_per_cu * cus);
     for (int b = 0; b < 2 && e == hipSuccess; ++b) {
         if (p.words[b] == 0) continue;
@@ -516,8 +521,8 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
         A.lds_words = p.words[b];
         e = launch_eval(A, p.H, grid, s);
     }
-    if (e == hipSuccess && p.parts > 1) return launch_bytes_select(out, p.n, p.elem_bytes, best, s);
-    if (e == hipSuccess && best && !fin) e = launch_select_rows(out, p.n, best, s);
+    if (e == hipSuccess && parts > 1) return launch_bytes_select(out, n, p.elem_bytes, best, s);
+    if (e == hipSuccess && best && !fin) e = launch_select_rows(out, n, best, s);
     return e;
 }
 

@@ -208,20 +208,12 @@ hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64
 // the start of `arena`.
 hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t n, const int64_t* d_index,
                             int64_t index, int32_t* arena, hipStream_t s);
-// Counting; with fin the last workgroup to finish also writes the bytes and, when
-// best is given, selects (the work of k_finalize_select; for small batches).
-hipError_t launch_count(const DevHeader* hdr, const DevCand* cands, const int32_t* arena,
-                        unsigned long long* counter, tm_stencil_cost* out, int grid, int lds_words,
-                        hipStream_t s, bool fin = false, int64_t* best = nullptr);
-// Batches up to this many candidates finalise inside the counting launch.
+// Batches up to this many candidates select inside the evaluation launch.
 constexpr int64_t kFinInCount = 2048;
-// n_max: an upper bound on the header's candidate count; without best, batches above
-// kFinBytesGrid candidates take their bytes in a grid-wide launch.
-constexpr int64_t kFinBytesGrid = 65536;
-hipError_t launch_finalize_select(const DevHeader* hdr, tm_stencil_cost* out, int64_t* best, int64_t n_max,
-                                  hipStream_t s);
-hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg,
-                                  int64_t* best, hipStream_t s, const int64_t* key = nullptr);
+// Per segment the best cost row: of rows [seg[s], seg[s+1]), or with idx (row -> candidate,
+// negative: no row) of the k rows from s k; best_cost may be null.
+hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg, const int64_t* idx,
+                                  int64_t k, int64_t* best, tm_stencil_cost* best_cost, hipStream_t s);
 // arena: the mapped candidate's tables.
 hipError_t launch_map(const DevCand* cands, int64_t n, const int32_t* arena, const int64_t* d_index,
                       int64_t index, int32_t* out, int grid, int lds_words, hipStream_t s);
@@ -256,6 +248,5 @@ hipError_t launch_matmul(const DevCand* cands, int64_t n, const int32_t* arena, 
 hipError_t launch_matmul_finalize(const DevCand* cands, int64_t n, const int64_t* proc_off,
                                   const unsigned long long* per_proc, int64_t tile_bytes,
                                   tm_matmul_cost* out, int64_t* out_per_proc, hipStream_t s);
-int count_kernel_occupancy(int lds_words, int* blocks_per_cu);
 
 }  // namespace tmk

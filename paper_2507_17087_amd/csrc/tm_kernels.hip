@@ -58,104 +58,6 @@ __device__ __forceinline__ void stage_words(int32_t* __restrict__ dst, const int
     for (; i < n4; i += 256) d4[i] = s4[i];
 }
 
-// Sum over the wave of non-negative per-lane counts, in 64 bits (a wave's counts for
-// one work item can exceed 2^31 on very long rows).
-__device__ __forceinline__ unsigned long long wave_sum64(int v) {
-    unsigned long long s = (unsigned long long)(unsigned)v;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    return s;
-}
-
-// ------------------------------------------------------------------ class-tuple counting
-
-constexpr int kFoundCache = 4;  // distinct foreign owners held in registers per tuple
-
-
-// Counts the class tuples t0, t0 + step, ... below tb of one candidate (tuples in C
-// order over its per-dim classes, last dim fastest): per tuple the distinct foreign
-// owners (and those on another node) of its cells, times its weight.
-__device__ __forceinline__ void count_tuples(const int32_t* __restrict__ T, const int32_t* const (&CE)[TM_MAX_LRANK],
-                                             const int32_t* const (&CS)[TM_MAX_LRANK],
-                                             const int32_t* const (&CO)[TM_MAX_LRANK],
-                                             const int32_t (&R)[TM_MAX_LRANK], int K, int gbits, int hs, int64_t tb,
-                                             int64_t t0, int32_t step, unsigned long long& cnt,
-                                             unsigned long long& icnt) {
-    const int32_t RL = R[K - 1];
-    // tuple t -> (row, k): row over the outer dims, k the last dim's class
-    int64_t t = t0;
-    int32_t row = (int32_t)(t / RL), k = (int32_t)(t - (int64_t)row * RL);
-    const int32_t qs = step / RL, rs = step % RL;
-    int32_t mrow = -1, vo = 0;
-    int64_t wo = 1;
-    // per outer dim of the current row: offset count and the offset list's position
-    int32_t ndo[TM_MAX_LRANK], odo[TM_MAX_LRANK];
-#pragma unroll
-    for (int d = 0; d < TM_MAX_LRANK; ++d) ndo[d] = odo[d] = 0;
-    for (; t < tb; t += step) {
-        if (row != mrow) {  // outer classes of this row: contribution, weight, offset lists
-            uint32_t rr = (uint32_t)row;
-            vo = 0;
-            wo = 1;
-#pragma unroll
-            for (int d = TM_MAX_LRANK - 2; d >= 0; --d) {  // unrolled: the arrays stay in registers
-                if (d > K - 2) continue;
-                const uint32_t kd = rr % (uint32_t)R[d];
-                rr /= (uint32_t)R[d];
-                const int32_t e = CE[d][kd];
-                vo += e & kValMask;
-                ndo[d] = (e >> kCntShift) & 0xf;
-                odo[d] = (int32_t)kd * hs;
-                wo *= CS[d][kd + 1] - CS[d][kd];
-            }
-            mrow = row;
-        }
-        const int32_t el = CE[K - 1][k];
-        const int32_t v = vo + (el & kValMask);
-        const int64_t w = wo * (int64_t)(CS[K - 1][k + 1] - CS[K - 1][k]);
-        const int32_t o = T[v];
-        const int32_t onode = o >> gbits;
-        int32_t f[kFoundCache];
-        int nf = 0, c = 0, ic = 0;
-#pragma unroll
-        for (int d = 0; d < TM_MAX_LRANK; ++d) {
-            if (d >= K) continue;
-            const int32_t nd = d == K - 1 ? (el >> kCntShift) & 0xf : ndo[d];
-            const int32_t* od = CO[d] + (d == K - 1 ? k * hs : odo[d]);
-            for (int i = 0; i < nd; ++i) {
-                const int32_t ot = T[v + od[i]];
-                if (ot == o) continue;
-                bool seen = false;
-#pragma unroll
-                for (int u = 0; u < kFoundCache; ++u) seen = seen || (u < nf && f[u] == ot);
-                if (!seen && nf > kFoundCache) {
-                    // more distinct owners than the cache holds: look at every earlier offset
-                    for (int d2 = 0; d2 <= d && !seen; ++d2) {
-                        const int32_t n2 = d2 == K - 1 ? (el >> kCntShift) & 0xf : ndo[d2];
-                        const int32_t* o2 = CO[d2] + (d2 == K - 1 ? k * hs : odo[d2]);
-                        const int e2 = d2 < d ? n2 : i;
-                        for (int i2 = 0; i2 < e2 && !seen; ++i2) seen = T[v + o2[i2]] == ot;
-                    }
-                }
-                if (seen) continue;
-#pragma unroll
-                for (int u = 0; u < kFoundCache; ++u) f[u] = u == nf ? ot : f[u];
-                ++nf;
-                ++c;
-                ic += (ot >> gbits) != onode ? 1 : 0;
-            }
-        }
-        cnt += (unsigned long long)w * (unsigned long long)c;
-        icnt += (unsigned long long)w * (unsigned long long)ic;
-        k += rs;
-        row += qs;
-        if (k >= RL) {
-            k -= RL;
-            ++row;
-        }
-    }
-}
-
 // ------------------------------------------------------------------ table build
 
 // Sorted distinct non-zero offsets C[x +- s] - C[x] (1 <= s <= h, in-domain
@@ -341,285 +243,57 @@ hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t 
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ stencil counting
-//
-// The distinct foreign owners of a cell depend only on the class of its coordinate
-// along every launch dim (tm_internal.h): the cell's linear final index is the sum
-// of the classes' contributions, and its star neighbours sit at that index plus
-// the classes' offsets.  So a candidate's count is a sum over the tuples of its
-// per-dim classes (the Cartesian product), each tuple evaluated once and weighted
-// by the number of cells it stands for, the product of its classes' run lengths.
-//
-// A work item is a contiguous range of one candidate's class tuples in C order
-// (last dim fastest); a candidate's items split its tuples evenly.  Workgroups take
-// items from a global atomic counter (the next one is requested while the current
-// one runs) and stage the candidate's owner table and class blocks in LDS when the
-// candidate changes and they fit (else they are read from global memory).  Each
-// thread evaluates every 256th tuple of the item: owner o = T[v], then the owners
-// T[v + delta] over the classes' offsets; the distinct ones other than o are
-// counted (and those on another node) times the tuple's weight, in 64 bits.  Waves
-// reduce, and one 64-bit atomic per wave and item adds to the candidate's totals.
+// ------------------------------------------------------------------ selection
 
-
-__device__ void finalize_select_block(const DevHeader* __restrict__ hdr, tm_stencil_cost* __restrict__ out,
-                                      int64_t* __restrict__ best, int64_t* sb, int64_t* si, int64_t* sx);
-
-__global__ __launch_bounds__(256) void k_count(const DevHeader* __restrict__ hdr, const DevCand* __restrict__ cands,
-                                               const int32_t* __restrict__ arena,
-                                               unsigned long long* __restrict__ counter,
-                                               tm_stencil_cost* __restrict__ out, int fin,
-                                               int64_t* __restrict__ best) {
-    extern __shared__ __attribute__((aligned(16))) int32_t lds[];
-    __shared__ long long s_item;
-    __shared__ int32_t s_cand;
-    __shared__ int s_last;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int64_t total = uniform64(hdr->total_items);
-    const int32_t budget = uniform32(hdr->cnt_words);  // LDS words of this launch
-
-    int64_t cur = -1;
-    int K = 1, gbits = 0, hs = 0, nit = 1;
-    int64_t ifirst = 0;
-    bool poisoned = false;
-    int32_t R[TM_MAX_LRANK];
-    const int32_t* T = arena;
-    const int32_t* CE[TM_MAX_LRANK];
-    const int32_t* CS[TM_MAX_LRANK];
-    const int32_t* CO[TM_MAX_LRANK];
-#pragma unroll
-    for (int d = 0; d < TM_MAX_LRANK; ++d) {
-        R[d] = 1;
-        CE[d] = CS[d] = CO[d] = arena;
-    }
-
-    // workgroup b takes item b first; the later items come from the work counter
-    // (items gridDim.x, gridDim.x + 1, ...), the next one and its candidate (from the
-    // item table) fetched while the current item runs
-    const int32_t* __restrict__ itab = arena + hdr->item_tab;
-    unsigned long long next = blockIdx.x;
-    int32_t next_c = 0;
-    if (tid == 0) next_c = (int64_t)next < total ? itab[next] : 0;
-    for (;;) {
-        if (tid == 0) {
-            s_item = (long long)next;
-            s_cand = next_c;
-        }
-        __syncthreads();
-        const int64_t item = uniform64(s_item);
-        const int64_t lo = uniform32(s_cand);
-        __syncthreads();
-        if (item >= total) break;
-        if (tid == 0) {
-            next = gridDim.x + atomicAdd(counter, 1ull);
-            next_c = (int64_t)next < total ? itab[next] : 0;
-        }
-        if (lo != cur) {
-            const DevCand* c = &cands[lo];
-            const int32_t* src = arena + c->arena_off;
-            const int32_t vol = uniform32(c->vol), cb = uniform32(c->cls_base), cw = uniform32(c->cls_words);
-            const int32_t tw = (vol + 3) & ~3;
-            const bool staged = tw + cw <= budget;
-            __syncthreads();  // the previous candidate's staged tables are no longer read
-            if (staged) {  // both regions 16-byte aligned, whole multiples of 4 words
-                stage_words(lds, src, tw);
-                stage_words(lds + tw, src + cb, cw);
-            }
-            T = staged ? lds : src;
-            K = uniform32(c->lrank);
-            gbits = uniform32(c->gbits);
-            hs = uniform32(c->hstride);
-            nit = uniform32(c->citems);
-            ifirst = uniform64(c->item_first);
-            poisoned = false;
-#pragma unroll
-            for (int d = 0; d < TM_MAX_LRANK; ++d) {
-                R[d] = 1;
-                if (d < K) {
-                    R[d] = uniform32(src[cb + d]);
-                    poisoned = poisoned || R[d] < 0;
-                    const int64_t cap = uniform32(c->cls_cap[d]);
-                    const int32_t rel = uniform32(c->cls_off[d]);  // dim d's block, from the arena or LDS
-                    CE[d] = staged ? lds + tw + (rel - cb) : src + rel;
-                    CS[d] = CE[d] + ((cap + 3) & ~int64_t(3));
-                    CO[d] = CS[d] + ((cap + 4) & ~int64_t(3));
-                }
-            }
-            cur = lo;
-            __syncthreads();
-        }
-        if (poisoned) {  // a class block overflowed its capacity: make the result unmistakable
-            if (tid == 0) atomicAdd(reinterpret_cast<unsigned long long*>(&out[cur].ghost_cells), 1ull << 62);
-            continue;
-        }
-        // this item's tuples [ta, tb) of the candidate's N = prod R_d, split evenly
-        const int64_t j = item - ifirst;
-        int64_t N = 1;
-        for (int d = 0; d < K; ++d) N *= R[d];
-        const int64_t q = N / nit, r = N % nit;
-        const int64_t ta = j * q + (j < r ? j : r);
-        const int64_t tb = ta + q + (j < r ? 1 : 0);
-        unsigned long long cnt = 0, icnt = 0;
-        count_tuples(T, CE, CS, CO, R, K, gbits, hs, tb, ta + tid, 256, cnt, icnt);
-#pragma unroll
-        for (int o2 = 32; o2 > 0; o2 >>= 1) {
-            cnt += __shfl_xor(cnt, o2, 64);
-            icnt += __shfl_xor(icnt, o2, 64);
-        }
-        if (lane == 0 && (cnt | icnt)) {
-            atomicAdd(reinterpret_cast<unsigned long long*>(&out[cur].ghost_cells), cnt);
-            atomicAdd(reinterpret_cast<unsigned long long*>(&out[cur].inter_cells), icnt);
-        }
-    }
-    if (!fin) return;
-    // the last workgroup to finish writes the bytes and selects
-    __shared__ int64_t sb[256], si[256], sx[256];
-    __syncthreads();
-    if (tid == 0) {
-        __threadfence();  // this workgroup's counts are visible before it reports done
-        s_last = atomicAdd(counter + 1, 1ull) == (unsigned long long)gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    finalize_select_block(hdr, out, best, sb, si, sx);
-}
-
-int count_kernel_occupancy(int lds_words, int* blocks_per_cu) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_count), 256,
-                                                     (size_t)lds_words * 4) != hipSuccess)
-        return -1;
-    *blocks_per_cu = nb;
-    return 0;
-}
-
-hipError_t launch_count(const DevHeader* hdr, const DevCand* cands, const int32_t* arena,
-                        unsigned long long* counter, tm_stencil_cost* out, int grid, int lds_words,
-                        hipStream_t s, bool fin, int64_t* best) {
-    hipLaunchKernelGGL(k_count, dim3(grid), dim3(256), (size_t)lds_words * 4, s, hdr, cands, arena, counter, out,
-                       fin ? 1 : 0, best);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ bytes + selection
-
-// One workgroup: bytes from cell counts, then the minimum of (bytes, inter_bytes,
-// index) -> *best (when given).  The counts are read at device scope (the counting
-// kernel's atomics).
-__device__ void finalize_select_block(const DevHeader* __restrict__ hdr, tm_stencil_cost* __restrict__ out,
-                                      int64_t* __restrict__ best, int64_t* sb, int64_t* si, int64_t* sx) {
-    const int nt = blockDim.x, t = threadIdx.x;
-    const int64_t n = hdr->n;
-    const int64_t eb = hdr->elem_bytes;
-    int64_t kb = INT64_MAX, ki = INT64_MAX, kx = INT64_MAX;
-    for (int64_t i = t; i < n; i += nt) {
-        int64_t* o = reinterpret_cast<int64_t*>(&out[i]);
-        const int64_t gc = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t ic = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t b = gc * eb, ib = ic * eb;
-        o[2] = b;
-        o[3] = ib;
-        if (b < kb || (b == kb && (ib < ki || (ib == ki && i < kx)))) {
-            kb = b;
-            ki = ib;
-            kx = i;
-        }
-    }
-    sb[t] = kb;
-    si[t] = ki;
-    sx[t] = kx;
-    __syncthreads();
-    for (int w = nt / 2; w > 0; w >>= 1) {
-        if (t < w) {
-            const int o = t + w;
-            if (sb[o] < sb[t] || (sb[o] == sb[t] && (si[o] < si[t] || (si[o] == si[t] && sx[o] < sx[t])))) {
-                sb[t] = sb[o];
-                si[t] = si[o];
-                sx[t] = sx[o];
-            }
-        }
-        __syncthreads();
-    }
-    if (t == 0 && best) *best = n > 0 ? sx[0] : -1;
-}
-
-__global__ __launch_bounds__(1024) void k_finalize_select(const DevHeader* __restrict__ hdr,
-                                                          tm_stencil_cost* __restrict__ out,
-                                                          int64_t* __restrict__ best) {
-    __shared__ int64_t sb[1024], si[1024], sx[1024];
-    finalize_select_block(hdr, out, best, sb, si, sx);
-}
-
-// Bytes from cell counts only (no selection), grid-stride over the candidates.
-__global__ __launch_bounds__(256) void k_finalize_bytes(const DevHeader* __restrict__ hdr,
-                                                        tm_stencil_cost* __restrict__ out) {
-    const int64_t n = hdr->n, eb = hdr->elem_bytes;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t* o = reinterpret_cast<int64_t*>(&out[i]);
-        const int64_t gc = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t ic = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        o[2] = gc * eb;
-        o[3] = ic * eb;
-    }
-}
-
-hipError_t launch_finalize_select(const DevHeader* hdr, tm_stencil_cost* out, int64_t* best, int64_t n_max,
-                                  hipStream_t s) {
-    if (!best && n_max > kFinBytesGrid) {
-        const int64_t g = std::min<int64_t>((n_max + 255) / 256, 2048);
-        hipLaunchKernelGGL(k_finalize_bytes, dim3((unsigned)g), dim3(256), 0, s, hdr, out);
-    } else {
-        hipLaunchKernelGGL(k_finalize_select, dim3(1), dim3(1024), 0, s, hdr, out, best);
-    }
-    return hipGetLastError();
-}
-
-// One workgroup per segment.
-// Ties on (bytes, inter_bytes) go to the smallest tie key: key[i] when given (the
-// original candidate index of a gathered sub-batch), else i.  Writes the position.
+// One workgroup per segment: the entry minimising (bytes, inter_bytes, index) of segment
+// s's cost rows -- rows [seg[s], seg[s + 1]), or with idx the k rows from s k whose
+// candidate idx[i] is not negative -- as an index relative to seg[s], and its row.  Empty
+// segments give -1.  Bound: the latency of a strided read and one cross-wave step.
 __global__ __launch_bounds__(256) void k_select_segments(const tm_stencil_cost* __restrict__ costs,
                                                          const int64_t* __restrict__ seg,
-                                                         const int64_t* __restrict__ key,
-                                                         int64_t* __restrict__ best) {
-    __shared__ int64_t sb[256], si[256], sx[256], sp[256];
-    const int64_t a = seg[blockIdx.x], e = seg[blockIdx.x + 1];
-    int64_t kb = INT64_MAX, ki = INT64_MAX, kx = INT64_MAX, kp = INT64_MAX;
-    for (int64_t i = a + threadIdx.x; i < e; i += blockDim.x) {
-        const int64_t b = costs[i].bytes, ib = costs[i].inter_bytes;
-        const int64_t x = key ? key[i] : i;
-        if (b < kb || (b == kb && (ib < ki || (ib == ki && x < kx)))) {
+                                                         const int64_t* __restrict__ idx, int64_t k,
+                                                         int64_t* __restrict__ best,
+                                                         tm_stencil_cost* __restrict__ best_cost) {
+    __shared__ int64_t sb[4], si[4], sx[4], sp[4];
+    const int t = threadIdx.x;
+    const int64_t first = seg[blockIdx.x];
+    const int64_t a = idx ? blockIdx.x * k : first, e = idx ? a + k : seg[blockIdx.x + 1];
+    int64_t kb = INT64_MAX, ki = INT64_MAX, kx = INT64_MAX, kp = -1;
+    auto take = [&](int64_t b, int64_t ib, int64_t x, int64_t p) {
+        if (p >= 0 && (b < kb || (b == kb && (ib < ki || (ib == ki && x < kx))))) {
             kb = b;
             ki = ib;
             kx = x;
-            kp = i;
+            kp = p;
         }
+    };
+    for (int64_t i = a + t; i < e; i += 256) {
+        const int64_t x = idx ? idx[i] : i;
+        if (x >= 0) take(costs[i].bytes, costs[i].inter_bytes, x, i);
     }
-    sp[threadIdx.x] = kp;
-    sb[threadIdx.x] = kb;
-    si[threadIdx.x] = ki;
-    sx[threadIdx.x] = kx;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const int64_t b = __shfl_xor(kb, o, 64), ib = __shfl_xor(ki, o, 64), x = __shfl_xor(kx, o, 64),
+                      p = __shfl_xor(kp, o, 64);
+        take(b, ib, x, p);
+    }
+    if ((t & 63) == 0) {
+        sb[t >> 6] = kb;
+        si[t >> 6] = ki;
+        sx[t >> 6] = kx;
+        sp[t >> 6] = kp;
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            const int o = threadIdx.x + w;
-            if (sb[o] < sb[threadIdx.x] ||
-                (sb[o] == sb[threadIdx.x] &&
-                 (si[o] < si[threadIdx.x] || (si[o] == si[threadIdx.x] && sx[o] < sx[threadIdx.x])))) {
-                sb[threadIdx.x] = sb[o];
-                si[threadIdx.x] = si[o];
-                sx[threadIdx.x] = sx[o];
-                sp[threadIdx.x] = sp[o];
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) best[blockIdx.x] = e > a ? sp[0] - a : -1;
+    if (t != 0) return;
+    for (int w = 1; w < 4; ++w) take(sb[w], si[w], sx[w], sp[w]);
+    best[blockIdx.x] = kp >= 0 ? kx - first : -1;
+    if (best_cost) best_cost[blockIdx.x] = kp >= 0 ? costs[kp] : tm_stencil_cost{-1, -1, -1, -1};
 }
 
-hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg,
-                                  int64_t* best, hipStream_t s, const int64_t* key) {
+hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg, const int64_t* idx,
+                                  int64_t k, int64_t* best, tm_stencil_cost* best_cost, hipStream_t s) {
     if (nseg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_select_segments, dim3((unsigned)nseg), dim3(256), 0, s, costs, seg, key, best);
+    hipLaunchKernelGGL(k_select_segments, dim3((unsigned)nseg), dim3(256), 0, s, costs, seg, idx, k, best, best_cost);
     return hipGetLastError();
 }
 

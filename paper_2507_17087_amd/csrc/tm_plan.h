@@ -29,7 +29,7 @@ struct Compiled {
 
 // Device buffers of a search over a loaded plan (grown on demand).
 struct SearchBufs {
-    int64_t cap_n = 0, cap_sc = 0, cap_pre = 0, cap_sel = 0, cap_seg = 0, cap_words = 0, cap_all = 0;
+    int64_t cap_n = 0, cap_sc = 0, cap_pre = 0, cap_sel = 0, cap_seg = 0, cap_all = 0;
     uint16_t* X = nullptr;          // [n][kFeat] bf16 features
     float* Y = nullptr;             // [n][kOut] network outputs
     float* score = nullptr;         // [cap_sc] ranking scores (both stages)
@@ -37,14 +37,7 @@ struct SearchBufs {
     int64_t* pre = nullptr;         // [nseg*prefilter] candidates kept by the network's scores
     int64_t* seg = nullptr;         // [nseg+1] instance segments
     int64_t* sel = nullptr;         // [nseg*k] chosen candidate indices
-    DevCand* sub = nullptr;         // [nseg*k] survivors
-    int64_t* map = nullptr;         // [nseg*k] survivor -> candidate index
-    int64_t* sub_seg = nullptr;     // [nseg+1] survivor segments
-    DevHeader* sub_hdr = nullptr;
-    int32_t* sub_arena = nullptr;
-    unsigned long long* sub_counter = nullptr;
-    tm_stencil_cost* sub_out = nullptr;
-    int64_t* sub_best = nullptr;    // [nseg]
+    tm_stencil_cost* sub_out = nullptr;  // [nseg*k] their exact costs
     tm_stencil_cost* all_out = nullptr;  // [n] exhaustive costs
     int64_t nseg = 0, k = 0;
 };
@@ -91,20 +84,16 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
 // Lays out the evaluation of a compiled stencil batch (per-candidate LDS words, dim and
 // parts; the launches).  node_level: the node-level volume.
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
-// Grid of the persistent counting launch for `items` work items.
-int count_grid(int lds_words, int64_t items, int wg_per_cu);
 
 int64_t plan_size(const tm_plan* p);
 const DevCand* plan_cands(const tm_plan* p);
 int32_t plan_max_vol(const tm_plan* p);
 const int32_t* plan_halo(const tm_plan* p);
-const DevHeader* plan_hdr(const tm_plan* p);
-int64_t plan_cells_per_item(const tm_plan* p);
 int plan_features(const tm_plan* p, float* d_feat, hipStream_t s);
 int plan_block_estimates(const tm_plan* p, double* d_est, hipStream_t s);
 int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t prefilter, int32_t topk, bool ranked,
                         SearchBufs** out, hipStream_t s);
-hipError_t plan_eval_sub(tm_plan* p, SearchBufs* sb, hipStream_t s);
+hipError_t plan_eval_chosen(tm_plan* p, SearchBufs* sb, int64_t* d_best, tm_stencil_cost* d_best_cost, hipStream_t s);
 int plan_exhaustive_search(tm_plan* p, const int64_t* seg, int64_t nseg, int64_t* d_best,
                            tm_stencil_cost* d_best_cost, hipStream_t s);
 

@@ -1,8 +1,7 @@
 // tm_ranker.hip -- learned ranker kernels (gfx950): descriptor features, a 3-layer
 // BF16 MLP (MFMA v_mfma_f32_16x16x32_bf16, FP32 accumulation) inference / forward /
 // backward, Adam, the chain statistics and block-model estimates of a ranked
-// search's second stage, per-segment k-smallest selection, and the on-device gather
-// of the survivors for exact re-evaluation.
+// search's second stage, and per-segment k-smallest selection.
 //
 // MFMA fragment layout used throughout (16x16x32, one wave): lane l holds row
 // (l % 16) of A and column (l % 16) of B, eight consecutive k values starting at
@@ -1165,164 +1164,6 @@ __global__ void k_combine(const float* __restrict__ Y, const double* __restrict_
     s[i] = __builtin_isfinite(v) ? v : INFINITY;
 }
 
-// ------------------------------------------------------------------ survivors
-
-// Builds the sub-batch of selected candidates on the device, in three launches.
-// k_gather_sizes reads each selected candidate's table words and counting items;
-// k_gather (one workgroup, 4 consecutive entries per thread) lays out their tables
-// and work items by prefix sums over the selection (per-thread sums, wave scans,
-// then the waves' totals), writes the sub-batch entry j of
-// every selected candidate -- map[j] = its original index and the three fields that
-// change (arena_off, item_first, citems) -- the sub-batch segments and header;
-// k_gather_copy then copies the rest of the descriptors, word by word across the
-// grid.  sel[s] < 0 entries are skipped; seg_out gives the sub-batch segments.
-constexpr int kDescWords = (int)(sizeof(DevCand) / 4);
-constexpr int kArenaWord = (int)(offsetof(DevCand, arena_off) / 4);
-constexpr int kItemWord = (int)(offsetof(DevCand, item_first) / 4);
-constexpr int kCitemsWord = (int)(offsetof(DevCand, citems) / 4);
-static_assert(sizeof(DevCand) % 4 == 0, "descriptor copied as words");
-
-__device__ __forceinline__ int64_t wave_incl_scan(int64_t v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t u = __shfl_up(v, o, 64);
-        v += lane >= o ? u : 0;
-    }
-    return v;
-}
-
-// Sizes of the selected candidates, one thread per entry: sizes[2s] = the table
-// words of candidate sel[s] (-1 when sel[s] < 0), sizes[2s+1] = its counting items.
-__global__ void k_gather_sizes(const DevCand* __restrict__ cands, const int64_t* __restrict__ sel, int64_t nsel,
-                               int64_t cells_per_item, int64_t* __restrict__ sizes) {
-    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= nsel) return;
-    const int64_t ci = sel[s];
-    int64_t w = -1, it = 0;
-    if (ci >= 0) {
-        const DevCand& c = cands[ci];
-        w = c.words;
-        it = count_items(c, cells_per_item);
-    }
-    sizes[2 * s] = w;
-    sizes[2 * s + 1] = it;
-}
-
-constexpr int kGatherPer = 4;  // consecutive entries per thread of k_gather
-
-__global__ __launch_bounds__(1024) void k_gather(const int64_t* __restrict__ sel, const int64_t* __restrict__ sizes,
-                                                 int64_t nsel, int k, DevCand* __restrict__ sub,
-                                                 int64_t* __restrict__ map, int64_t* __restrict__ seg_out,
-                                                 DevHeader* __restrict__ hdr, const DevHeader* __restrict__ proto) {
-    __shared__ int64_t s_tot[16][3];  // per wave: words, items, present
-    __shared__ int64_t carry[3];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
-    if (tid < 3) carry[tid] = 0;
-    __syncthreads();
-    const int64_t span = (int64_t)blockDim.x * kGatherPer;
-    for (int64_t base = 0; base < nsel; base += span) {
-        // this thread's entries s0 .. s0 + kGatherPer - 1: their totals, then a
-        // block-wide scan of the totals, then the entries in order
-        const int64_t s0 = base + (int64_t)tid * kGatherPer;
-        int64_t words = 0, items = 0, present = 0;
-        for (int q = 0; q < kGatherPer && s0 + q < nsel; ++q) {
-            const int64_t w = sizes[2 * (s0 + q)];
-            if (w >= 0) {
-                words += w;
-                items += sizes[2 * (s0 + q) + 1];
-                ++present;
-            }
-        }
-        const int64_t iw = wave_incl_scan(words, lane), ii = wave_incl_scan(items, lane),
-                      ic = wave_incl_scan(present, lane);
-        if (lane == 63) {
-            s_tot[wid][0] = iw;
-            s_tot[wid][1] = ii;
-            s_tot[wid][2] = ic;
-        }
-        __syncthreads();
-        int64_t pw = carry[0] + iw - words, pi = carry[1] + ii - items, pc = carry[2] + ic - present;
-        for (int w = 0; w < wid; ++w) {
-            pw += s_tot[w][0];
-            pi += s_tot[w][1];
-            pc += s_tot[w][2];
-        }
-        for (int q = 0; q < kGatherPer && s0 + q < nsel; ++q) {
-            const int64_t s = s0 + q;
-            // segment starts: first slot of each segment of k
-            if (s % k == 0) seg_out[s / k] = pc;
-            const int64_t w = sizes[2 * s];
-            if (w >= 0) {
-                const int64_t it = sizes[2 * s + 1];
-                map[pc] = sel[s];
-                sub[pc].arena_off = pw;
-                sub[pc].item_first = pi;
-                sub[pc].citems = (int32_t)it;
-                pw += w;
-                pi += it;
-                ++pc;
-            }
-        }
-        __syncthreads();  // every thread has read carry and s_tot
-        if (tid < 3) {
-            int64_t t = 0;
-            for (int w = 0; w < nw; ++w) t += s_tot[w][tid];
-            carry[tid] += t;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        seg_out[(nsel + k - 1) / k] = carry[2];
-        DevHeader h = *proto;
-        h.n = carry[2];
-        h.total_items = carry[1];
-        h.item_tab = carry[0];  // the survivors' item table follows their tables
-        *hdr = h;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_gather_copy(const DevCand* __restrict__ cands,
-                                                     const int64_t* __restrict__ map,
-                                                     const DevHeader* __restrict__ hdr, DevCand* __restrict__ sub) {
-    const int64_t total = hdr->n * kDescWords;
-    const int32_t* src = reinterpret_cast<const int32_t*>(cands);
-    int32_t* dst = reinterpret_cast<int32_t*>(sub);
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t j = t / kDescWords;
-        const int w = (int)(t - j * kDescWords);
-        if (w == kArenaWord || w == kArenaWord + 1 || w == kItemWord || w == kItemWord + 1 || w == kCitemsWord)
-            continue;  // written by k_gather
-        dst[t] = src[map[j] * kDescWords + w];
-    }
-}
-
-// best[s] = map[sub_best[s] + seg[s]] (original candidate index) and its cost.
-__global__ void k_map_best(const int64_t* __restrict__ sub_best, const int64_t* __restrict__ seg,
-                           const int64_t* __restrict__ map, const tm_stencil_cost* __restrict__ sub_cost,
-                           int64_t nseg, const int64_t* __restrict__ orig_seg, int64_t* __restrict__ best,
-                           tm_stencil_cost* __restrict__ best_cost) {
-    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= nseg) return;
-    const int64_t b = sub_best[s];
-    if (b < 0) {
-        best[s] = -1;
-        if (best_cost) best_cost[s] = tm_stencil_cost{-1, -1, -1, -1};
-        return;
-    }
-    const int64_t j = seg[s] + b;
-    best[s] = map[j] - orig_seg[s];
-    if (best_cost) best_cost[s] = sub_cost[j];
-}
-
-// Exhaustive path: best index is already relative; copy costs out.
-__global__ void k_pick_costs(const int64_t* __restrict__ best, const int64_t* __restrict__ seg,
-                             const tm_stencil_cost* __restrict__ cost, int64_t nseg,
-                             tm_stencil_cost* __restrict__ best_cost) {
-    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= nseg || !best_cost) return;
-    best_cost[s] = best[s] < 0 ? tm_stencil_cost{-1, -1, -1, -1} : cost[seg[s] + best[s]];
-}
-
 // ------------------------------------------------------------------ launchers
 
 hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_halo, double* est, uint16_t* X,
@@ -1436,38 +1277,6 @@ hipError_t launch_combine(const float* Y, const double* est, int64_t n, const fl
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Y, est, n, mu[0], sigma[0],
                        mu[1], sigma[1], lambda, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather(const DevCand* cands, const int64_t* sel, int64_t nsel, int k, int64_t cells_per_item,
-                         DevCand* sub, int64_t* map, int64_t* seg_out, DevHeader* hdr, const DevHeader* proto,
-                         int64_t* sizes, hipStream_t s) {
-    if (nsel > 0)
-        hipLaunchKernelGGL(k_gather_sizes, dim3((unsigned)((nsel + 255) / 256)), dim3(256), 0, s, cands, sel, nsel,
-                           cells_per_item, sizes);
-    hipLaunchKernelGGL(k_gather, dim3(1), dim3(1024), 0, s, sel, sizes, nsel, k, sub, map, seg_out, hdr, proto);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nsel <= 0) return e;
-    const int64_t blocks = (nsel * kDescWords + 255) / 256;
-    hipLaunchKernelGGL(k_gather_copy, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, cands, map,
-                       hdr, sub);
-    return hipGetLastError();
-}
-
-hipError_t launch_map_best(const int64_t* sub_best, const int64_t* seg, const int64_t* map,
-                           const tm_stencil_cost* sub_cost, int64_t nseg, const int64_t* orig_seg, int64_t* best,
-                           tm_stencil_cost* best_cost, hipStream_t s) {
-    if (nseg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_map_best, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, s, sub_best, seg, map, sub_cost,
-                       nseg, orig_seg, best, best_cost);
-    return hipGetLastError();
-}
-
-hipError_t launch_pick_costs(const int64_t* best, const int64_t* seg, const tm_stencil_cost* cost, int64_t nseg,
-                             tm_stencil_cost* best_cost, hipStream_t s) {
-    if (nseg <= 0 || !best_cost) return hipSuccess;
-    hipLaunchKernelGGL(k_pick_costs, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, s, best, seg, cost, nseg,
-                       best_cost);
     return hipGetLastError();
 }
 

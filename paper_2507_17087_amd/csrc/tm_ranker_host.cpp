@@ -472,7 +472,6 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
     int rc = plan_search_prepare(p, seg, nseg, prefilter, topk, true, &sb, s);
     if (rc != TM_OK) return rc;
     const int64_t n = plan_size(p);
-    const int64_t nsel = nseg * topk;
     // the network's score of every candidate: descriptor features, forward, residuals
     // over the descriptor estimate
     hipError_t e = launch_features(plan_cands(p), n, plan_halo(p), chain_estimates(sb->cross, n), sb->X, nullptr, s);
@@ -490,16 +489,7 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
     } else if (e == hipSuccess) {
         e = launch_select(sb->score, sb->seg, nseg, 0, topk, margin, nullptr, sb->sel, s);
     }
-    // the survivors' exact costs (their cost rows serve the gather as scratch first:
-    // 32 bytes per survivor, 16 used)
-    static_assert(sizeof(tm_stencil_cost) >= 2 * sizeof(int64_t), "gather scratch");
-    if (e == hipSuccess)
-        e = launch_gather(plan_cands(p), sb->sel, nsel, topk, plan_cells_per_item(p), sb->sub, sb->map, sb->sub_seg,
-                          sb->sub_hdr, plan_hdr(p), reinterpret_cast<int64_t*>(sb->sub_out), s);
-    if (e == hipSuccess) e = plan_eval_sub(p, sb, s);
-    if (e == hipSuccess) e = launch_select_segments(sb->sub_out, sb->sub_seg, nseg, sb->sub_best, s, sb->map);
-    if (e == hipSuccess)
-        e = launch_map_best(sb->sub_best, sb->sub_seg, sb->map, sb->sub_out, nseg, sb->seg, d_best, d_best_cost, s);
+    if (e == hipSuccess) e = plan_eval_chosen(p, sb, d_best, d_best_cost, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "ranked search: %s", hipGetErrorString(e));
     return TM_OK;
 }
