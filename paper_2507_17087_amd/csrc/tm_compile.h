@@ -89,6 +89,16 @@ __host__ __device__ inline bool is_bijective(const DevCand& d) {
     return true;
 }
 
+// Whether every launch dim is projected by blocks onto exactly one final dim.
+__host__ __device__ inline bool is_simple(const DevCand& d) {
+    uint32_t seen = 0;
+    for (int j = 0; j < d.frank; ++j) {
+        if (d.proj_mode[j] != TM_BLOCK || ((seen >> d.proj_src[j]) & 1u)) return false;
+        seen |= 1u << d.proj_src[j];
+    }
+    return d.frank == d.lrank;
+}
+
 // What a launch layout asks of a candidate: halos up to H, node-level counting, work
 // items of about per_item tuples (0: fill parts of at least kEvalPartTuples at most).
 struct EvalShape {
@@ -137,7 +147,7 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
     e->gpus = d.gpus;
     e->rgpus = 1.0f / (float)d.gpus;
     e->bij = is_bijective(d);
-    e->flags = 0;
+    e->flags = is_simple(d) ? kEvalSimple : 0;
     for (int j = 0; j < 5; ++j) e->pad[j] = 0;
     for (int t = 0; t < d.nops; ++t) fill_inverse(d, t, &e->inv[t]);
     int next = 0;

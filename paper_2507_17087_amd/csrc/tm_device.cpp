@@ -203,6 +203,7 @@ void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
         e.items += n.parts;
         e.parts = std::max(e.parts, n.parts);
         largest = std::max(largest, n.words);
+        e.all_simple = e.all_simple && is_simple(c);
         const int b = n.words > small ? 1 : 0;
         words[b] = std::max(words[b], n.words);
         whole[b] = std::max(whole[b], n.whole);
@@ -563,7 +564,7 @@ static void plan_drop_graphs(tm_plan* p) {
 }
 
 static void search_free(SearchBufs& b) {
-    void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.cross, b.seg, b.sel, b.sub_out, b.all_out};
+    void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.est, b.seg, b.sel, b.sub_out, b.all_out};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     b = SearchBufs{};
@@ -935,10 +936,9 @@ namespace tmk {
 
 int64_t plan_size(const tm_plan* p) { return p->cp.hdr.n; }
 const DevCand* plan_cands(const tm_plan* p) { return p->d_cands; }
-int32_t plan_max_vol(const tm_plan* p) { return p->cp.max_vol; }
 const int32_t* plan_halo(const tm_plan* p) { return p->d_hdr->halo; }
 
-// Ranker buffers: features and outputs of n rows; scores and chain statistics of
+// Ranker buffers: features and outputs of n rows; scores and estimates of
 // max(n, m) entries (m: the second stage's survivors of a ranked search).
 static int ensure_rank_bufs(SearchBufs& b, int64_t n, int64_t m, hipStream_t s) {
     const int64_t sc = std::max<int64_t>(std::max(n, m), 1);
@@ -957,11 +957,12 @@ static int ensure_rank_bufs(SearchBufs& b, int64_t n, int64_t m, hipStream_t s) 
     if (b.cap_sc < sc) {
         TM_HIP(hipStreamSynchronize(s));
         if (b.score) (void)hipFree(b.score);
-        if (b.cross) (void)hipFree(b.cross);
-        b.score = b.cross = nullptr;
+        if (b.est) (void)hipFree(b.est);
+        b.score = nullptr;
+        b.est = nullptr;
         b.cap_sc = 0;
         if (hipMalloc((void**)&b.score, (size_t)sc * 4) != hipSuccess ||
-            hipMalloc((void**)&b.cross, (size_t)sc * (kCrossFloats + 4) * 4) != hipSuccess)
+            hipMalloc((void**)&b.est, (size_t)sc * 2 * sizeof(double)) != hipSuccess)
             return set_error(TM_ENOMEM, "score buffers");
         b.cap_sc = sc;
     }
@@ -976,23 +977,21 @@ int plan_features(const tm_plan* p, float* d_feat, hipStream_t s) {
     const int64_t n = p->cp.hdr.n;
     const int rc = ensure_rank_bufs(b, n, 0, s);
     if (rc != TM_OK) return rc;
-    TM_HIP(launch_features(p->d_cands, n, p->d_hdr->halo, chain_estimates(b.cross, n), b.X, d_feat, s));
+    TM_HIP(launch_features(p->d_cands, n, p->d_hdr->halo, b.est, b.X, d_feat, s));
     return TM_OK;
 }
 
 int plan_block_estimates(const tm_plan* p, double* d_est, hipStream_t s) {
     if (!p || !p->loaded) return set_error(TM_EINVAL, "plan not loaded");
     if (!d_est) return set_error(TM_EINVAL, "null output");
-    tm_plan* q = const_cast<tm_plan*>(p);
-    SearchBufs& b = q->sb;
-    const int64_t n = p->cp.hdr.n;
-    const int rc = ensure_rank_bufs(b, n, 0, s);
-    if (rc != TM_OK) return rc;
-    TM_HIP(launch_chain_stats(p->d_cands, nullptr, n, p->cp.max_vol, p->d_hdr->halo, b.cross, s));
-    if (n > 0)
-        TM_HIP(hipMemcpyAsync(d_est, chain_estimates(b.cross, n), (size_t)n * 2 * sizeof(double),
-                              hipMemcpyDeviceToDevice, s));
+    TM_HIP(launch_estimates(plan_estimates(p), nullptr, p->cp.hdr.n, 0.f, d_est, nullptr, s));
     return TM_OK;
+}
+
+EstimateBatch plan_estimates(const tm_plan* p) {
+    const EvalPlan& e = p->cp.eval;
+    return EstimateBatch{p->d_cands, p->d_evals, p->cp.max_vol, {e.halo[0], e.halo[1], e.halo[2], e.halo[3]},
+                         p->d_hdr->halo, e.all_simple};
 }
 
 int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t prefilter, int32_t topk, bool ranked,

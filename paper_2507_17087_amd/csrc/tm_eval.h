@@ -33,6 +33,7 @@ struct EvalPlan {
     int32_t H = 0, parts = 1, node_level = 0;
     int32_t split = 0;          // candidates needing at most this many LDS words: the first launch
     int32_t words[2] = {0, 0};  // LDS words of the two launches (0: no such candidate)
+    bool all_simple = true;     // every candidate is simple (kEvalSimple)
     int32_t wg_per_cu = 0;      // at most this many workgroups per CU (0: one per item)
 };
 

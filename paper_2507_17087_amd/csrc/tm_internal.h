@@ -69,8 +69,9 @@ struct alignas(16) DevEval {
     DevOp inv[TM_MAX_OPS];
 };
 // kEvalCyclic: some launch dim has a cyclic projection; kEvalExtra: some has several
-// block or several cyclic ones
-constexpr int32_t kEvalCyclic = 1, kEvalExtra = 2;
+// block or several cyclic ones; kEvalSimple: every launch dim is projected by blocks onto
+// exactly one final dim
+constexpr int32_t kEvalCyclic = 1, kEvalExtra = 2, kEvalSimple = 4;
 static_assert(sizeof(DevEval) == 896, "staged by the first 56 lanes of a wave");
 
 // Compiled candidate as the kernels read it.  The host fills in the shapes of the

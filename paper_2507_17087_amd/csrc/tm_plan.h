@@ -8,6 +8,7 @@
 
 #include "tm_eval.h"
 #include "tm_internal.h"
+#include "tm_ranker.h"
 
 namespace tmk {
 
@@ -33,7 +34,7 @@ struct SearchBufs {
     uint16_t* X = nullptr;          // [n][kFeat] bf16 features
     float* Y = nullptr;             // [n][kOut] network outputs
     float* score = nullptr;         // [cap_sc] ranking scores (both stages)
-    float* cross = nullptr;         // [cap_sc][16] crossing fractions, then [cap_sc][2] fp64 estimates
+    double* est = nullptr;          // [cap_sc][2] the descriptor estimates
     int64_t* pre = nullptr;         // [nseg*prefilter] candidates kept by the network's scores
     int64_t* seg = nullptr;         // [nseg+1] instance segments
     int64_t* sel = nullptr;         // [nseg*k] chosen candidate indices
@@ -87,7 +88,7 @@ void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 
 int64_t plan_size(const tm_plan* p);
 const DevCand* plan_cands(const tm_plan* p);
-int32_t plan_max_vol(const tm_plan* p);
+EstimateBatch plan_estimates(const tm_plan* p);
 const int32_t* plan_halo(const tm_plan* p);
 int plan_features(const tm_plan* p, float* d_feat, hipStream_t s);
 int plan_block_estimates(const tm_plan* p, double* d_est, hipStream_t s);

@@ -79,21 +79,24 @@ constexpr int kMaxMrankCross = 8;  // node-crossing fractions kept per candidate
 // through bf16.
 constexpr int kBaseFeat[kOut] = {23, 60};
 constexpr float kBaseScale = 32.f;
-// Per-candidate chain statistics: 2 * kMaxMrankCross floats, then 2 doubles (estimates).
-constexpr int64_t kCrossFloats = 2 * kMaxMrankCross;
-inline double* chain_estimates(float* cross, int64_t n) {
-    return reinterpret_cast<double*>(cross + n * kCrossFloats);  // 64n bytes in: 8-byte aligned
-}
-
 // Features of n candidates: bf16 rows X, fp32 copies f32 (nullable), and the
 // descriptor estimate est[2i] (est[2i+1] = 0).
 hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_halo, double* est, uint16_t* X,
                            float* f32, hipStream_t s);
-// Chain statistics and block-model estimates of entries 0..n-1: candidate idx[i]
-// (negative: skipped) or i without idx; outputs at entry i of cross and
-// chain_estimates(cross, n).
-hipError_t launch_chain_stats(const DevCand* cands, const int64_t* idx, int64_t n, int32_t max_vol,
-                              const int32_t* d_halo, float* cross, hipStream_t s);
+// A loaded batch as the block-model estimates read it.
+struct EstimateBatch {
+    const DevCand* cands;
+    const DevEval* evals;
+    int32_t max_vol;
+    int32_t halo[TM_MAX_LRANK];
+    const int32_t* d_halo;
+    bool all_simple;
+};
+// Block-model estimates of entries 0..n-1: candidate idx[i] (negative: skipped) or i
+// without idx; to est[2i..] (nullable) and, as the second stage's score, score[i]
+// (nullable).
+hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t n, float lambda, double* est,
+                            float* score, hipStream_t s);
 hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, uint16_t* H1,
                               uint16_t* H2, uint16_t* H3, hipStream_t s);
 hipError_t launch_backward(const RankerBuffers& B, const RankerWeights& W, int64_t n, float s0, float s1,
@@ -107,7 +110,7 @@ hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W,
 // entry to the index written.
 hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t stride, int k, float margin,
                          const int64_t* remap, int64_t* sel, hipStream_t s);
-// Scores from the heads Y (nullable: the estimates alone) and the estimates est.
+// Scores from the heads Y and the descriptor estimates est.
 hipError_t launch_combine(const float* Y, const double* est, int64_t n, const float* mu, const float* sigma,
                           float lambda, float* s, hipStream_t st);
 

@@ -8,7 +8,10 @@
 // 8 * (l / 16); the result holds rows 4 * (l / 16) + r (r = 0..3) of column l % 16.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "tm_chain.h"
+#include "tm_groups.h"
 #include "tm_internal.h"
 #include "tm_ranker.h"
 
@@ -36,268 +39,239 @@ __device__ __forceinline__ f32x4 mfma16(u16x8 a, u16x8 b, f32x4 c) {
 
 __device__ __forceinline__ float lg2(double x) { return (float)log2(x); }
 
-// Per-candidate chain statistics (the second stage of a ranked search):
-//   cross[0..8)   per final dim j: fraction of adjacent coordinate pairs (a, a+e_j)
-//                 whose owners sit on different nodes (0 for a candidate whose
-//                 launch dims are each block-projected onto one final dim: its
-//                 estimate does not use them);
-//   cross[8..16)  the same for different processors;
-//   est[0..2)     block-model estimate of the ghost cells and of the inter-node
-//                 ones.  When every launch dim is projected (block) onto exactly one
-//                 final dim, each cell boundary b along a launch dim is seen by the
-//                 min(h, b) + min(h, l - b) cells within the halo of it, times the
-//                 area of the face (product of the block widths of the other dims),
-//                 counted where the owners (or nodes) on the two sides differ --
-//                 exact for bijective chains whose blocks are at least h wide.
-//                 Otherwise: per launch dim, the (cell, distinct foreign coordinate)
-//                 pairs along it times the other extents times the crossing fraction.
-// One workgroup per candidate; owners of all final coordinates staged in LDS, sized
-// for the batch's largest volume (volumes above kCrossMax give zeros).
+// ------------------------------------------------------------------ block-model estimates
+//
+// The second stage of a ranked search: per candidate the estimated ghost cells and
+// inter-node ghost cells (volumes above kCrossMax: 0, 0).  When every launch dim is
+// projected by blocks onto exactly one final dim (k_block_estimates), each cell boundary b
+// along a launch dim is seen by the min(h, b) + min(h, l - b) cells within the halo of it,
+// times the area of the face (the product of the other dims' block widths), counted where
+// the owners (or nodes) on its two sides differ -- exact for bijective chains whose blocks
+// are at least h wide.  Otherwise (k_crossing_estimates): per launch dim, the (cell,
+// distinct foreign coordinate) pairs along it times the other extents times the largest
+// fraction of adjacent final coordinates whose owners (nodes) differ.
 constexpr int kCrossMax = 16384;
 constexpr int kStatsStage = 1024;     // launch dims up to this extent have their contributions staged in LDS
 constexpr int kStatsSmallVol = 2048;  // owner-table words of the first (small-candidate) launch
-constexpr int kStatsTableCap = 4096;  // block-table entries per table (simple candidates)
 
-__device__ __forceinline__ int64_t block_first(int64_t a, int64_t S, int64_t l) { return div_nn(a * l + S - 1, S); }
+// The second stage's score of an estimate: log2(1 + cells) + lambda log2(1 + inter-node
+// cells); +inf when that is not finite.
+__device__ __forceinline__ float estimate_score(double e0, double e1, float lambda) {
+    const float b0 = kBaseScale * (lg2(1.0 + e0) / kBaseScale), b1 = kBaseScale * (lg2(1.0 + e1) / kBaseScale);
+    const float v = b0 + lambda * b1;
+    return __builtin_isfinite(v) ? v : INFINITY;
+}
 
-// Block-model terms of final coordinate v (digits a) for a candidate whose launch
-// dims are each projected (block) onto one final dim: along every dim j where v
-// starts a non-empty block (a_j >= 1), the boundary b = that block's first cell is
-// seen by the min(h, b) + min(h, l - b) cells within the halo of it, times the area
-// of the face (the product of the other dims' block widths), counted where the
-// owners (or nodes) of v and of the cell before b differ.  TAB: block bounds from
-// the LDS tables, else worked out.
-template <bool TAB>
-__device__ __forceinline__ void boundary_terms(int32_t v, const int32_t (&a)[kMaxMrankCross], int fr,
-                                               const int32_t (&fs)[kMaxMrankCross],
-                                               const int32_t (&fst)[kMaxMrankCross],
-                                               const int32_t (&toff)[TM_MAX_LRANK], const int32_t (&hj)[TM_MAX_LRANK],
-                                               const int64_t (&lj)[TM_MAX_LRANK], const int32_t* bft,
-                                               const int32_t* aLt, const int32_t* key, int gb, double& tot,
-                                               double& inter) {
-    int64_t bf0[TM_MAX_LRANK];
-    double wd[TM_MAX_LRANK];
+struct EstimateArgs {
+    const DevEval* evals;
+    const int64_t* idx;
+    int64_t n;
+    int32_t halo[TM_MAX_LRANK];
+    int32_t vmin, vmax;  // volumes this launch takes: above vmin, up to vmax (kCrossMax: zeros beyond)
+    int32_t cap;         // LDS words of keys: the largest volume it meets
+    float lambda;
+    double* est;
+    float* score;
+};
+
+// A workgroup per entry: the owner table in LDS, then a thread per final coordinate.  Its
+// block along a dim starts at cell ceil(a l / s), in closed form; every sum is of whole
+// numbers below 2^53, exact in any order.  Bound: VALU issue (as the stencil evaluation).
+// Measured on 116,992 kept candidates, against block tables in LDS and a descriptor of 960
+// bytes staged word by word before: 741 -> 270 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
+    extern __shared__ __attribute__((aligned(16))) int32_t key[];
+    __shared__ DevEval ev;
+    __shared__ double dred[NT / 64][2];
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int64_t i = blockIdx.x; i < A.n; i += gridDim.x) {
+        const int64_t ci = A.idx ? wave_uniform64(A.idx[i]) : i;
+        if (ci < 0) continue;
+        if (i != (int64_t)blockIdx.x) lds_sync(NW);  // the previous entry's LDS is no longer read
+        stage_eval(&ev, A.evals + ci, tid);
+        lds_sync(NW);
+        const int32_t vol = wave_uniform(ev.vol);
+        if (!(wave_uniform(ev.flags) & kEvalSimple)) continue;
+        const bool beyond = vol > kCrossMax && A.vmax == kCrossMax;
+        if (!beyond && (vol <= A.vmin || vol > A.vmax)) continue;
+        double tot = 0, inter = 0;
+        if (!beyond) {
+            const int K = wave_uniform(ev.lrank), gb = wave_uniform(ev.gbits);
+            owner_table(ev, key, 0, vol, -1, tid, NT);
+            // per launch dim: its final dim's size and stride (1 and no boundary for size 1)
+            uint32_t st[TM_MAX_LRANK], sz[TM_MAX_LRANK];
+            float rst[TM_MAX_LRANK], rsz[TM_MAX_LRANK];
+            double ld[TM_MAX_LRANK], sd[TM_MAX_LRANK], rs[TM_MAX_LRANK], rl[TM_MAX_LRANK];
 #pragma unroll
-    for (int j = 0; j < TM_MAX_LRANK; ++j) {
-        int64_t b0 = 0, b1 = 1;
-        if (j < fr) {
-            b0 = TAB ? bft[toff[j] + a[j]] : block_first(a[j], fs[j], lj[j]);
-            b1 = TAB ? bft[toff[j] + a[j] + 1] : block_first(a[j] + 1, fs[j], lj[j]);
+            for (int d = 0; d < TM_MAX_LRANK; ++d) {
+                const bool on = d < K && ev.dim[d].nblk > 0;
+                const DevProj& p = ev.pj[on ? ev.dim[d].first : 0];
+                sz[d] = on ? (uint32_t)p.s : 1u;
+                st[d] = on ? (uint32_t)p.stride : 1u;
+                rst[d] = 1.0f / (float)st[d];
+                rsz[d] = 1.0f / (float)sz[d];
+                ld[d] = d < K ? (double)ev.dim[d].l : 1.0;
+                sd[d] = (double)sz[d];
+                rs[d] = on ? p.rs : 1.0;
+                rl[d] = d < K ? ev.dim[d].rl : 1.0;
+            }
+            lds_sync(NW);
+            for (int32_t v = tid; v < vol; v += NT) {
+                const int32_t kv = key[v];
+                uint32_t a[TM_MAX_LRANK], x0[TM_MAX_LRANK];
+                double wd[TM_MAX_LRANK];
+#pragma unroll
+                for (int d = 0; d < TM_MAX_LRANK; ++d) {
+                    if (d >= K) {
+                        wd[d] = 1;
+                        continue;
+                    }
+                    const uint32_t q = div_small((uint32_t)v, rst[d]);
+                    a[d] = q - __umul24(div_small(q, rsz[d]), sz[d]);
+                    const double n0 = fma((double)a[d], ld[d], sd[d] - 1.0);
+                    x0[d] = div_wide(n0, rs[d]);
+                    wd[d] = (double)(div_wide(n0 + ld[d], rs[d]) - x0[d]);
+                }
+#pragma unroll
+                for (int d = 0; d < TM_MAX_LRANK; ++d) {
+                    const uint32_t h = (uint32_t)A.halo[d];
+                    if (d >= K || a[d] == 0 || h == 0 || wd[d] <= 0.0) continue;  // no boundary, or an empty block
+                    const uint32_t b = x0[d], r = (uint32_t)ld[d] - b;
+                    double w = (double)((h < b ? h : b) + (h < r ? h : r));
+#pragma unroll
+                    for (int e = 0; e < TM_MAX_LRANK; ++e)
+                        if (e != d) w *= wd[e];
+                    const uint32_t al = block_index(b - 1, sd[d], rl[d]);  // the block of the cell before b
+                    const int32_t kl = key[v - (int32_t)((a[d] - al) * st[d])];
+                    if (kl != kv) tot += w;
+                    if ((kl >> gb) != (kv >> gb)) inter += w;
+                }
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                tot += __shfl_xor(tot, o, 64);
+                inter += __shfl_xor(inter, o, 64);
+            }
+            if (NW > 1) {
+                if (lane == 0) {
+                    dred[tid >> 6][0] = tot;
+                    dred[tid >> 6][1] = inter;
+                }
+                __syncthreads();
+                for (int w = 1; w < NW; ++w) {
+                    tot += tid == 0 ? dred[w][0] : 0.0;
+                    inter += tid == 0 ? dred[w][1] : 0.0;
+                }
+            }
         }
-        bf0[j] = b0;
-        wd[j] = (double)(b1 - b0);
-    }
-    const int32_t kv = key[v];
-#pragma unroll
-    for (int j = 0; j < TM_MAX_LRANK; ++j) {
-        if (j >= fr || a[j] == 0 || hj[j] == 0) continue;
-        const int64_t b = bf0[j], l = lj[j];
-        if (b >= l || wd[j] <= 0.0) continue;  // empty block
-        double face = 1;
-#pragma unroll
-        for (int jj = 0; jj < TM_MAX_LRANK; ++jj)
-            if (jj != j && jj < fr) face *= wd[jj];
-        const int64_t h = hj[j];
-        const double w = (double)((h < b ? h : b) + (h < l - b ? h : l - b));
-        const int32_t aL = TAB ? aLt[toff[j] + a[j]] : (int32_t)div_nn((b - 1) * fs[j], l);
-        const int32_t kl = key[v - (a[j] - aL) * fst[j]];
-        if (kl != kv) tot += w * face;
-        if ((kl >> gb) != (kv >> gb)) inter += w * face;
+        if (tid == 0) {
+            if (A.est) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
+            if (A.score) A.score[i] = estimate_score(tot, inter, A.lambda);
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_chain_stats(const DevCand* __restrict__ cands,
-                                                     const int64_t* __restrict__ idx, int64_t n,
-                                                     const int32_t* __restrict__ halo, float* __restrict__ cross,
-                                                     double* __restrict__ est, int32_t vmin, int32_t vmax,
-                                                     int32_t vcap) {
+__global__ __launch_bounds__(256) void k_crossing_estimates(const DevCand* __restrict__ cands,
+                                                            const int32_t* __restrict__ d_halo, EstimateArgs A) {
     __shared__ DevCand sc;
-    // dynamic LDS: the owner keys (vcap words, the largest volume of this launch),
-    // then a region that holds either, for a simple candidate, its block tables
-    // (per final dim and block a = 0..S: the block's first cell; and the block
-    // holding the cell before it), tcap entries each -- the sum over dims of S + 1 is
-    // at most the volume plus twice the rank -- or, otherwise, a launch dim's
-    // coordinate contributions (kStatsStage entries)
+    // dynamic LDS: the owner keys (cap words), then a launch dim's contributions
     extern __shared__ __attribute__((aligned(16))) int32_t key[];
-    const int32_t tcap = vcap + 16 < kStatsTableCap ? vcap + 16 : kStatsTableCap;
-    int32_t* bft = key + ((vcap + 3) & ~3);
-    int32_t* aLt = bft + tcap;
-    int32_t* s_ct = bft;
+    int32_t* s_ct = key + A.cap;
     __shared__ int32_t red[kMaxMrankCross][4][2];  // per final dim and wave: node and owner changes
     __shared__ double dred[4][2];
     __shared__ float s_cross[2 * kMaxMrankCross];  // this candidate's crossing fractions
     __shared__ float s_rt[kRecipSlots];             // reciprocals of the inverse chain's divisors
-    const int nw = blockDim.x >> 6;
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        // entry i: candidate idx[i] (skipped when negative), or i without idx
-        const int64_t ci = idx ? wave_uniform64(idx[i]) : i;
-        if (ci < 0) continue;
-        // this launch takes the candidates of volume in (vmin, vmax]; the one whose
-        // vmax is kCrossMax also writes the zeros of those above it
-        const int32_t v0 = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)cands[ci].vol);
-        if (v0 > kCrossMax && vmax == kCrossMax) {
-            if (threadIdx.x < 2 * kMaxMrankCross) cross[i * 2 * kMaxMrankCross + threadIdx.x] = 0.f;
-            if (threadIdx.x < 2) est[i * 2 + threadIdx.x] = 0.0;
-            continue;
-        }
-        if (v0 <= vmin || v0 > vmax) continue;
-        lds_sync(nw);
-        stage_cand(&sc, &cands[ci]);
-        lds_sync(nw);
-        op_reciprocals(sc, s_rt, threadIdx.x, blockDim.x);
-        lds_sync(nw);
-        const int32_t vol = sc.vol;
-        const int K = wave_uniform(sc.lrank), gb = wave_uniform(sc.gbits), fr = wave_uniform(sc.frank);
-        const int nj = fr < kMaxMrankCross ? fr : kMaxMrankCross;
-        const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
-        // is every launch dim projected (block) onto exactly one final dim?
-        bool simple = fr == K;
-        uint32_t seen = 0;
-        for (int j = 0; j < fr; ++j) {
-            const int d = sc.proj_src[j];
-            simple = simple && sc.proj_mode[j] == TM_BLOCK && !((seen >> d) & 1u);
-            seen |= 1u << d;
-        }
-        // the final dims' extents and strides; with simple projections, each one's
-        // launch extent and halo and the offset of its block tables
-        int32_t fs[kMaxMrankCross], fst[kMaxMrankCross], toff[TM_MAX_LRANK], hj[TM_MAX_LRANK];
-        float rfs[kMaxMrankCross];
-        int64_t lj[TM_MAX_LRANK];
-#pragma unroll
-        for (int j = 0; j < kMaxMrankCross; ++j) {
-            fs[j] = j < fr ? wave_uniform(sc.fshape[j]) : 1;
-            fst[j] = j < fr ? wave_uniform(sc.fstride[j]) : 0;
-            rfs[j] = j < fr ? s_rt[kRecipFinal + j] : 1.0f;
-        }
-        int32_t off = 0;
-#pragma unroll
-        for (int j = 0; j < TM_MAX_LRANK; ++j) {
-            const int d = j < fr ? wave_uniform(sc.proj_src[j]) : 0;
-            toff[j] = off;
-            off += j < fr ? fs[j] + 1 : 0;
-            hj[j] = j < fr ? wave_uniform(halo[d]) : 0;
-            lj[j] = j < fr ? wave_uniform64(sc.extent[d]) : 1;
-        }
-        owner_keys_sized(sc, s_rt, key, 0, 0, vol, -1, tid, blockDim.x);
-        // the block tables fit when the blocks are few and the extents below 2^31
-        bool tab = simple && off <= tcap;
-#pragma unroll
-        for (int j = 0; j < TM_MAX_LRANK; ++j) tab = tab && lj[j] < INT32_MAX;
-        if (tab) {
-            // per final dim: block_first of every block a (0..S) and, for a >= 1, the
-            // block holding the cell before it
-            for (int j = 0; j < fr; ++j) {
-                const int64_t S = wave_uniform(sc.fshape[j]);
-                const int64_t l = sc.extent[sc.proj_src[j]];
-                int32_t o = 0;
-                for (int jj = 0; jj < j; ++jj) o += wave_uniform(sc.fshape[jj]) + 1;
-                for (int32_t aa = tid; aa <= (int32_t)S; aa += blockDim.x) {
-                    const int64_t b = block_first(aa, S, l);
-                    bft[o + aa] = (int32_t)b;
-                    aLt[o + aa] = (aa >= 1 && b >= 1) ? (int32_t)div_nn((b - 1) * S, l) : 0;
-                }
-            }
-        }
-        lds_sync(nw);  // owner keys and block tables ready
-        // one pass over the final coordinates: without simple projections, per final
-        // dim j, the adjacent pairs (v, v + e_j) and how many of them change owner /
-        // node (the crossing fractions, which only that estimate uses); with simple
-        // projections the block-model estimate: every v that starts
-        // a non-empty block along j (a_j >= 1) is a cell boundary b, seen by the
-        // min(h, b) + min(h, l - b) cells within the halo of it times the area of the
-        // face (the product of the other dims' block widths), counted where the owners
-        // (or nodes) of v and of the cell before b differ -- exact for bijective chains
-        // whose blocks are at least h wide.
-        // per final dim: owner changes << 16 | node changes (each at most the volume,
-        // below 2^16, also summed over a wave); the number of pairs is known
-        int32_t ch[kMaxMrankCross];
-#pragma unroll
-        for (int j = 0; j < kMaxMrankCross; ++j) ch[j] = 0;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
+    for (int64_t i = blockIdx.x; i < A.n; i += gridDim.x) {
+        const int64_t ci = A.idx ? wave_uniform64(A.idx[i]) : i;
+        if (ci < 0 || (wave_uniform(A.evals[ci].flags) & kEvalSimple)) continue;
+        const int32_t v0 = wave_uniform(cands[ci].vol);
+        const bool beyond = v0 > kCrossMax && A.vmax == kCrossMax;
+        if (!beyond && (v0 <= A.vmin || v0 > A.vmax)) continue;
         double tot = 0, inter = 0;
-        const bool need_cross = !simple;
-        for (int32_t v = tid; v < vol && (need_cross || tab); v += blockDim.x) {
-            int32_t a[kMaxMrankCross];
-            uint32_t rem = (uint32_t)v;
+        if (!beyond) {
+            lds_sync(nw);
+            stage_cand(&sc, &cands[ci]);
+            lds_sync(nw);
+            op_reciprocals(sc, s_rt, tid, blockDim.x);
+            lds_sync(nw);
+            const int32_t vol = sc.vol;
+            const int K = wave_uniform(sc.lrank), gb = wave_uniform(sc.gbits), fr = wave_uniform(sc.frank);
+            const int nj = fr < kMaxMrankCross ? fr : kMaxMrankCross;
+            int32_t fs[kMaxMrankCross], fst[kMaxMrankCross];
+            float rfs[kMaxMrankCross];
 #pragma unroll
-            for (int j = kMaxMrankCross - 1; j >= 0; --j) {
-                const uint32_t q = j < fr ? div24(rem, (uint32_t)fs[j], rfs[j]) : rem;
-                a[j] = j < fr ? (int32_t)(rem - __umul24(q, (uint32_t)fs[j])) : 0;
-                rem = q;
+            for (int j = 0; j < kMaxMrankCross; ++j) {
+                fs[j] = j < fr ? wave_uniform(sc.fshape[j]) : 1;
+                fst[j] = j < fr ? wave_uniform(sc.fstride[j]) : 0;
+                rfs[j] = j < fr ? s_rt[kRecipFinal + j] : 1.0f;
             }
-            if (need_cross) {
+            owner_keys_sized(sc, s_rt, key, 0, 0, vol, -1, tid, blockDim.x);
+            lds_sync(nw);
+            // per final dim the adjacent pairs (v, v + e_j) that change owner / node, as
+            // owner changes << 16 | node changes (each at most the volume, below 2^16,
+            // also summed over a wave)
+            int32_t ch[kMaxMrankCross];
+#pragma unroll
+            for (int j = 0; j < kMaxMrankCross; ++j) ch[j] = 0;
+            for (int32_t v = tid; v < vol; v += blockDim.x) {
+                uint32_t rem = (uint32_t)v;
                 const int32_t kv = key[v];
 #pragma unroll
-                for (int j = 0; j < kMaxMrankCross; ++j) {
-                    if (j < nj && a[j] < fs[j] - 1) {
+                for (int j = kMaxMrankCross - 1; j >= 0; --j) {
+                    const uint32_t q = j < fr ? div24(rem, (uint32_t)fs[j], rfs[j]) : rem;
+                    const int32_t a = j < fr ? (int32_t)(rem - __umul24(q, (uint32_t)fs[j])) : 0;
+                    rem = q;
+                    if (j < nj && a < fs[j] - 1) {
                         const int32_t kn = key[v + fst[j]];
                         ch[j] += ((kn != kv) << 16) | ((kn >> gb) != (kv >> gb));
                     }
                 }
             }
-            if (tab) boundary_terms<true>(v, a, fr, fs, fst, toff, hj, lj, bft, aLt, key, gb, tot, inter);
-        }
-        // the counts summed within each wave by shuffles, then over the waves
 #pragma unroll
-        for (int j = 0; j < kMaxMrankCross; ++j) {
-            if (j < nj && need_cross) {
+            for (int j = 0; j < kMaxMrankCross; ++j) {
+                if (j < nj) {
 #pragma unroll
-                for (int o2 = 32; o2 > 0; o2 >>= 1) ch[j] += __shfl_xor(ch[j], o2, 64);
-                if (lane == 0) {
-                    red[j][wv][0] = ch[j] & 0xffff;
-                    red[j][wv][1] = ch[j] >> 16;
+                    for (int o2 = 32; o2 > 0; o2 >>= 1) ch[j] += __shfl_xor(ch[j], o2, 64);
+                    if (lane == 0) {
+                        red[j][wv][0] = ch[j] & 0xffff;
+                        red[j][wv][1] = ch[j] >> 16;
+                    }
                 }
             }
-        }
-        if (simple && !tab) {  // the block tables did not fit: block bounds worked out per cell
-            for (int32_t v = tid; v < vol; v += blockDim.x) {
-                int32_t a[kMaxMrankCross];
-                uint32_t rem = (uint32_t)v;
-#pragma unroll
-                for (int j = kMaxMrankCross - 1; j >= 0; --j) {
-                    const uint32_t q = j < fr ? rem / (uint32_t)fs[j] : rem;
-                    a[j] = j < fr ? (int32_t)(rem - __umul24(q, (uint32_t)fs[j])) : 0;
-                    rem = q;
+            lds_sync(nw);
+            if (tid < kMaxMrankCross) {
+                float fn = 0.f, fp = 0.f;
+                if (tid < nj) {
+                    // pairs (v, v + e_j): the coordinates with a_j < S_j - 1
+                    const int32_t Sj = sc.fshape[tid];
+                    const int pairs = (Sj - 1) * (vol / Sj);
+                    int dn = 0, dp = 0;
+                    for (int w = 0; w < nw; ++w) {
+                        dn += red[tid][w][0];
+                        dp += red[tid][w][1];
+                    }
+                    const float inv = pairs ? 1.f / (float)pairs : 0.f;
+                    fn = (float)dn * inv;
+                    fp = (float)dp * inv;
                 }
-                boundary_terms<false>(v, a, fr, fs, fst, toff, hj, lj, bft, aLt, key, gb, tot, inter);
+                s_cross[tid] = fn;
+                s_cross[kMaxMrankCross + tid] = fp;
             }
-        }
-        lds_sync(nw);
-        if (tid < kMaxMrankCross) {
-            const int j = tid;
-            float fn = 0.f, fp = 0.f;
-            if (j < nj && need_cross) {
-                // pairs (v, v + e_j): the coordinates with a_j < S_j - 1
-                const int32_t Sj = sc.fshape[j];
-                const int pairs = (Sj - 1) * (vol / Sj);
-                int dn = 0, dp = 0;
-                for (int w = 0; w < nwv; ++w) {
-                    dn += red[j][w][0];
-                    dp += red[j][w][1];
-                }
-                const float inv = pairs ? 1.f / (float)pairs : 0.f;
-                fn = (float)dn * inv;
-                fp = (float)dp * inv;
-            }
-            cross[i * 2 * kMaxMrankCross + j] = fn;
-            cross[i * 2 * kMaxMrankCross + kMaxMrankCross + j] = fp;
-            s_cross[j] = fn;
-            s_cross[kMaxMrankCross + j] = fp;
-        }
-        lds_sync(nw);
-        if (!simple) {
-            // per launch dim, the (cell, distinct foreign coordinate) pairs along it
-            // times the other extents times the crossing fraction
+            lds_sync(nw);
             for (int d = 0; d < K; ++d) {
                 const int64_t l = sc.extent[d];
-                const int h = halo[d];
+                const int h = d_halo[d];
                 double part = 0;
                 if (h > 0 && l <= 65536) {
                     const bool staged = l <= kStatsStage;  // uniform
                     if (staged) {
-                        for (int32_t x = threadIdx.x; x < (int32_t)l; x += blockDim.x) s_ct[x] = coord_value(sc, d, x);
+                        for (int32_t x = tid; x < (int32_t)l; x += blockDim.x) s_ct[x] = coord_value(sc, d, x);
                         lds_sync(nw);
                     }
-                    for (int64_t x = threadIdx.x; x < l; x += blockDim.x) {
+                    for (int64_t x = tid; x < l; x += blockDim.x) {
                         const int32_t val = staged ? s_ct[x] : coord_value(sc, d, x);
                         int32_t found[2 * kMaxHalo];
                         int cnt = 0;
@@ -307,7 +281,7 @@ __global__ __launch_bounds__(256) void k_chain_stats(const DevCand* __restrict__
                                 if (xx < 0 || xx >= l) continue;
                                 const int32_t dv = (staged ? s_ct[xx] : coord_value(sc, d, xx)) - val;
                                 bool seen = dv == 0;
-                                for (int i = 0; i < cnt; ++i) seen = seen || found[i] == dv;
+                                for (int u = 0; u < cnt; ++u) seen = seen || found[u] == dv;
                                 if (!seen) found[cnt++] = dv;
                             }
                         part += cnt;
@@ -326,23 +300,60 @@ __global__ __launch_bounds__(256) void k_chain_stats(const DevCand* __restrict__
                 tot += part * pts * cp;
                 inter += part * pts * cn;
             }
-        }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            tot += __shfl_xor(tot, o, 64);
-            inter += __shfl_xor(inter, o, 64);
+            for (int o = 32; o > 0; o >>= 1) {
+                tot += __shfl_xor(tot, o, 64);
+                inter += __shfl_xor(inter, o, 64);
+            }
+            if (lane == 0) {
+                dred[wv][0] = tot;
+                dred[wv][1] = inter;
+            }
+            lds_sync(nw);
+            tot = inter = 0;
+            for (int w = 0; w < nw; ++w) {
+                tot += dred[w][0];
+                inter += dred[w][1];
+            }
         }
-        if (lane == 0) {
-            dred[wv][0] = tot;
-            dred[wv][1] = inter;
-        }
-        lds_sync(nw);
-        if (threadIdx.x < 2) {
-            double e = 0;
-            for (int w = 0; w < nwv; ++w) e += dred[w][threadIdx.x];
-            est[i * 2 + threadIdx.x] = e;
+        if (tid == 0) {
+            if (A.est) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
+            if (A.score) A.score[i] = estimate_score(tot, inter, A.lambda);
         }
     }
+}
+
+hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t n, float lambda, double* est,
+                            float* score, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const unsigned g = (unsigned)std::min<int64_t>(n, int64_t(1) << 20);
+    const int32_t top = std::max(1, std::min(b.max_vol, kCrossMax));
+    EstimateArgs A{};
+    A.evals = b.evals;
+    A.idx = idx;
+    A.n = n;
+    for (int d = 0; d < TM_MAX_LRANK; ++d) A.halo[d] = b.halo[d];
+    A.lambda = lambda;
+    A.est = est;
+    A.score = score;
+    // most candidates are small: a first launch with a small owner table in LDS (more
+    // workgroups per CU) takes the volumes up to kStatsSmallVol, a second one, sized for
+    // the batch's largest, the rest; large batches take one-wave workgroups
+    for (int pass = 0; pass < (top > kStatsSmallVol ? 2 : 1); ++pass) {
+        A.vmin = pass ? kStatsSmallVol : 0;
+        const bool last = pass || top <= kStatsSmallVol;
+        A.vmax = last ? kCrossMax : kStatsSmallVol;
+        A.cap = ((last ? top : kStatsSmallVol) + 3) & ~3;
+        const size_t lds = (size_t)A.cap * 4;
+        if (n >= kSmallBlockBatch)
+            hipLaunchKernelGGL(k_block_estimates<64>, dim3(g), dim3(64), lds, s, A);
+        else
+            hipLaunchKernelGGL(k_block_estimates<256>, dim3(g), dim3(256), lds, s, A);
+        if (!b.all_simple)
+            hipLaunchKernelGGL(k_crossing_estimates, dim3(g), dim3(n >= kSmallBlockBatch ? 64 : 256),
+                               lds + kStatsStage * 4, s, b.cands, b.d_halo, A);
+    }
+    return hipGetLastError();
 }
 
 // The descriptor fields the features read, fetched with 16-byte loads: each group
@@ -1150,14 +1161,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
 
 // Ranking score: predicted log2(1 + bytes) + lambda * predicted log2(1 + inter-node
 // bytes), each = estimate base (the same fp32 value training used) + un-standardised
-// residual head; without Y the estimates alone; +inf when that is not finite.
+// residual head; +inf when that is not finite.
 __global__ void k_combine(const float* __restrict__ Y, const double* __restrict__ est, int64_t n, float mu0,
                           float s0, float mu1, float s1, float lambda, float* __restrict__ s) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float b0 = kBaseScale * (lg2(1.0 + est[i * 2]) / kBaseScale);
     const float b1 = kBaseScale * (lg2(1.0 + est[i * 2 + 1]) / kBaseScale);
-    const float p0 = Y ? b0 + mu0 + s0 * Y[i * kOut] : b0, p1 = Y ? b1 + mu1 + s1 * Y[i * kOut + 1] : b1;
+    const float p0 = b0 + mu0 + s0 * Y[i * kOut], p1 = b1 + mu1 + s1 * Y[i * kOut + 1];
     const float v = p0 + lambda * p1;
     // a non-finite score (diverged or corrupt parameters) ranks last, by index, so
     // such candidates stay selectable and every instance keeps its survivors
@@ -1170,35 +1181,6 @@ hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_hal
                            float* f32, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_features, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cands, n, d_halo, est, X, f32);
-    return hipGetLastError();
-}
-
-hipError_t launch_chain_stats(const DevCand* cands, const int64_t* idx, int64_t n, int32_t max_vol,
-                              const int32_t* d_halo, float* cross, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int64_t g = n < 65536 ? n : 65536;
-    double* est = chain_estimates(cross, n);
-    // the owner table of a candidate lives in LDS: most candidates are small, so a
-    // first launch with a small table (more workgroups per CU) takes the volumes up to
-    // kStatsSmallVol, and a second one, sized for the batch's largest, the rest;
-    // large batches of small candidates: one-wave workgroups, four times as many
-    // candidates in flight per CU (each candidate's work is a few hundred keys)
-    const int bs = n >= kSmallBlockBatch ? 64 : 256;
-    const int32_t vtop = std::max(1, std::min(max_vol, kCrossMax));
-    // LDS words: the keys, then the two block tables or a launch dim's contributions
-    auto lds_bytes = [](int32_t vcap) {
-        const int32_t tcap = std::min(vcap + 16, kStatsTableCap);
-        return (size_t)(((vcap + 3) & ~3) + std::max(2 * tcap, kStatsStage)) * 4;
-    };
-    if (vtop <= kStatsSmallVol) {
-        hipLaunchKernelGGL(k_chain_stats, dim3((unsigned)g), dim3(bs), lds_bytes(vtop), s, cands, idx, n, d_halo,
-                           cross, est, 0, kCrossMax, vtop);
-    } else {
-        hipLaunchKernelGGL(k_chain_stats, dim3((unsigned)g), dim3(bs), lds_bytes(kStatsSmallVol), s, cands, idx, n,
-                           d_halo, cross, est, 0, kStatsSmallVol, kStatsSmallVol);
-        hipLaunchKernelGGL(k_chain_stats, dim3((unsigned)g), dim3(bs), lds_bytes(vtop), s, cands, idx, n, d_halo,
-                           cross, est, kStatsSmallVol, kCrossMax, vtop);
-    }
     return hipGetLastError();
 }
 

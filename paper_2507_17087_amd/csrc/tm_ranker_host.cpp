@@ -474,17 +474,15 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
     const int64_t n = plan_size(p);
     // the network's score of every candidate: descriptor features, forward, residuals
     // over the descriptor estimate
-    hipError_t e = launch_features(plan_cands(p), n, plan_halo(p), chain_estimates(sb->cross, n), sb->X, nullptr, s);
+    hipError_t e = launch_features(plan_cands(p), n, plan_halo(p), sb->est, sb->X, nullptr, s);
     if (e == hipSuccess) e = launch_mlp_forward(sb->X, n, r->W, sb->Y, nullptr, nullptr, nullptr, s);
-    if (e == hipSuccess) e = launch_combine(sb->Y, chain_estimates(sb->cross, n), n, r->mu, r->sigma, lambda, sb->score, s);
+    if (e == hipSuccess) e = launch_combine(sb->Y, sb->est, n, r->mu, r->sigma, lambda, sb->score, s);
     if (prefilter > 0) {
-        // the network keeps `prefilter` per instance; their block-model estimates (chain
-        // statistics) choose the topk
+        // the network keeps `prefilter` per instance; their block-model estimates
+        // choose the topk
         const int64_t m = nseg * (int64_t)prefilter;
         if (e == hipSuccess) e = launch_select(sb->score, sb->seg, nseg, 0, prefilter, 0.f, nullptr, sb->pre, s);
-        if (e == hipSuccess) e = launch_chain_stats(plan_cands(p), sb->pre, m, plan_max_vol(p), plan_halo(p), sb->cross, s);
-        if (e == hipSuccess)
-            e = launch_combine(nullptr, chain_estimates(sb->cross, m), m, r->mu, r->sigma, lambda, sb->score, s);
+        if (e == hipSuccess) e = launch_estimates(plan_estimates(p), sb->pre, m, lambda, nullptr, sb->score, s);
         if (e == hipSuccess) e = launch_select(sb->score, sb->seg, nseg, prefilter, topk, margin, sb->pre, sb->sel, s);
     } else if (e == hipSuccess) {
         e = launch_select(sb->score, sb->seg, nseg, 0, topk, margin, nullptr, sb->sel, s);
