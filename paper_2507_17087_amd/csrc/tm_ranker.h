@@ -11,7 +11,6 @@ namespace tmk {
 constexpr int kFeat = 64;    // features per candidate
 constexpr int kWidth = 256;  // hidden width (three hidden layers)
 constexpr int kOut = 2;      // heads: log2(1 + bytes), log2(1 + inter-node bytes), standardised
-constexpr int kSplits = 32;  // row splits of the weight-gradient reductions
 
 // Offsets (in floats) of each tensor in the flat fp32 parameter vector.
 struct RankerLayout {
@@ -32,10 +31,19 @@ constexpr RankerLayout ranker_layout() {
     return L;
 }
 
-// Device views of the weights: bf16 copies row-major (w*) and transposed (w*t);
+// bf16 matrices the MFMA kernels read lie in fragment order: a matrix of C columns with
+// the reduction index k as blocks of 16 columns x 32 k, each block the 1 KB that one
+// fragment load of a wave takes, lane l's 16 bytes (column l % 16, k 8 (l / 16) ..) at
+// 16 l.  A load then reads eight whole cache lines.
+__host__ __device__ inline int64_t frag_at(int64_t c, int64_t k, int64_t blocks_k) {
+    return ((c / 16 * blocks_k + k / 32) * 64 + (k % 32) / 8 * 16 + c % 16) * 8 + k % 8;
+}
+
+// Device views of the weights: bf16 fragments of each layer's product (f: output columns,
+// reduced over inputs) and of its transpose (g: input columns, reduced over outputs);
 // biases are read from the fp32 master vector.
 struct RankerWeights {
-    uint16_t *w1, *w1t, *w2, *w2t, *w3, *w3t, *w4;
+    uint16_t *f1, *f2, *f3, *g2, *g3, *w4;
     const float *b1, *b2, *b3, *b4;
     RankerLayout layout;
 };
@@ -48,27 +56,46 @@ __device__ __forceinline__ void publish_param(int64_t i, float v, const RankerWe
     const RankerLayout& L = W.layout;
     if (i >= L.w1 && i < L.b1) {
         const int64_t j = i - L.w1, r = j / kWidth, c = j % kWidth;
-        W.w1[j] = h;
-        W.w1t[c * kFeat + r] = h;
+        W.f1[frag_at(c, r, kFeat / 32)] = h;
     } else if (i >= L.w2 && i < L.b2) {
         const int64_t j = i - L.w2, r = j / kWidth, c = j % kWidth;
-        W.w2[j] = h;
-        W.w2t[c * kWidth + r] = h;
+        W.f2[frag_at(c, r, kWidth / 32)] = h;
+        W.g2[frag_at(r, c, kWidth / 32)] = h;
     } else if (i >= L.w3 && i < L.b3) {
         const int64_t j = i - L.w3, r = j / kWidth, c = j % kWidth;
-        W.w3[j] = h;
-        W.w3t[c * kWidth + r] = h;
+        W.f3[frag_at(c, r, kWidth / 32)] = h;
+        W.g3[frag_at(r, c, kWidth / 32)] = h;
     } else if (i >= L.w4 && i < L.b4) {
         W.w4[i - L.w4] = h;
     }
 }
 
-// Per-batch work buffers of training.
-struct RankerBuffers {
-    uint16_t *X, *H1, *H2, *H3, *dH1, *dH2, *dH3;  // bf16 [rows][width]
-    float *Y, *T, *dY;                             // fp32 [rows][kOut]
-    float* grad;                                   // fp32 [count]
-    float* part;                                   // fp32 [kSplits][kWidth * kWidth]
+// Row ranges of the weight gradients: about 512 rows each (288 workgroups on 4,096 rows),
+// at most 16 (their partial gradients are written and read back).
+constexpr int kMaxSplits = 16;
+inline int grad_splits(int64_t n) {
+    const int64_t s = (n + 511) / 512;
+    return (int)(s < 1 ? 1 : (s > kMaxSplits ? kMaxSplits : s));
+}
+// Batches up to this many rows run 16-row tiles.
+constexpr int64_t kTrainSmallRows = 4096;
+
+// A minibatch: rows first + i, or perm[first + i], of the features and targets.
+struct TrainBatch {
+    const float *feat, *target;
+    const int64_t* perm;
+    int64_t first, n;
+};
+// Per-batch work buffers, rows padded to npad (a multiple of 32): the features,
+// activations and their gradients in fragment order (their columns, reduced over rows);
+// fp32 rows; per tile of at least 16 rows its column sums [kColParts] (b1, b2, b3, w4,
+// b4); the matrices' gradients per row range [kMaxSplits][count].
+constexpr int kColParts = 3 * kWidth + kWidth * kOut + kOut;
+struct TrainBuffers {
+    uint16_t *X, *H1, *H2, *H3, *D1, *D2, *D3;
+    float *Y, *T;
+    float *colpart, *part;
+    int64_t npad;
 };
 
 constexpr int kMaxMrankCross = 8;  // node-crossing fractions kept per candidate
@@ -97,12 +124,16 @@ struct EstimateBatch {
 // (nullable).
 hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t n, float lambda, double* est,
                             float* score, hipStream_t s);
-hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, uint16_t* H1,
-                              uint16_t* H2, uint16_t* H3, hipStream_t s);
-hipError_t launch_backward(const RankerBuffers& B, const RankerWeights& W, int64_t n, float s0, float s1,
-                           hipStream_t s);
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t count, float lr, float b1, float b2,
-                       float eps, int64_t t, const RankerWeights& W, hipStream_t s);
+// Network outputs of n rows of bf16 features.
+hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, hipStream_t s);
+// Forward and backward of one batch (s0, s1: the heads' scale of Y - target): Y, T and the
+// columns; the bias and head gradients into grad, the matrices' into T.part.
+hipError_t launch_gradient(const TrainBatch& B, const RankerWeights& W, float s0, float s1, const TrainBuffers& T,
+                           float* grad, hipStream_t s);
+// The matrices' gradients into grad; or the Adam step from them.
+hipError_t launch_reduce_grad(const RankerLayout& L, const TrainBuffers& T, int64_t n, float* grad, hipStream_t s);
+hipError_t launch_reduce_adam(float* p, const TrainBuffers& T, int64_t n, const float* grad, float* m, float* v, float lr,
+                              float b1, float b2, float eps, int64_t t, const RankerWeights& W, hipStream_t s);
 hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W, hipStream_t s);
 // The k smallest (score, index) entries of each segment (k_select): sel[s*k ..)
 // in index order, -1 after; stride > 0 takes segment s as the first

@@ -1,11 +1,6 @@
 // tm_ranker.hip -- learned ranker kernels (gfx950): descriptor features, a 3-layer
-// BF16 MLP (MFMA v_mfma_f32_16x16x32_bf16, FP32 accumulation) inference / forward /
-// backward, Adam, the chain statistics and block-model estimates of a ranked
-// search's second stage, and per-segment k-smallest selection.
-//
-// MFMA fragment layout used throughout (16x16x32, one wave): lane l holds row
-// (l % 16) of A and column (l % 16) of B, eight consecutive k values starting at
-// 8 * (l / 16); the result holds rows 4 * (l / 16) + r (r = 0..3) of column l % 16.
+// BF16 MLP (MFMA v_mfma_f32_16x16x32_bf16, FP32 accumulation) inference, the block-model
+// estimates of a ranked search's second stage, and per-segment k-smallest selection.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -13,27 +8,10 @@
 #include "tm_chain.h"
 #include "tm_groups.h"
 #include "tm_internal.h"
+#include "tm_mfma.h"
 #include "tm_ranker.h"
 
 namespace tmk {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ uint16_t f2bf(float f) {
-    // round to nearest even (finite inputs)
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-__device__ __forceinline__ bf16x8 as_bf(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
-
-__device__ __forceinline__ f32x4 mfma16(u16x8 a, u16x8 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(a), as_bf(b), c, 0, 0, 0);
-}
 
 // ------------------------------------------------------------------ features
 
@@ -563,16 +541,15 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
 // A workgroup of the forward pass (8 waves) takes 64 rows.  Activations stay in LDS
 // (bf16, padded row stride); wave w computes output columns [32w, 32w + 32) of
 // each hidden layer as 4 x 2 MFMA tiles, reading weight fragments straight from
-// the transposed bf16 weights Wt[n][k] (16 contiguous bytes per lane).  Measured on
+// the bf16 weights in fragment order (16 contiguous bytes per lane).  Measured on
 // 1M rows: 8 waves of 32 columns 0.58 ms, 4 of 64 columns 0.63 ms, 16 of 16
 // columns 0.72 ms, 128-row workgroups 0.70 ms.  The tiles are computed
 // transposed (weights as the first operand), so a lane ends with four consecutive
 // columns of one row: the epilogue (bias, ReLU, round to bf16) writes them to LDS
-// as one 8-byte store; optionally the activations are stored for the backward pass.
+// as one 8-byte store.
 // The head (256 -> 2) is one more MFMA tile per wave against the two weight columns
 // staged in LDS (the other 14 columns zero): bf16 products summed in fp32.
 
-constexpr int kRowsFwd = 64;    // rows per workgroup of the backward-data kernel
 constexpr int kRowsMlp = 64;    // rows per workgroup of the forward pass
 constexpr int kMlpThreads = 512;
 constexpr int kMlpNB = kWidth / 16 / (kMlpThreads / 64);  // 16-column blocks per wave
@@ -581,7 +558,7 @@ constexpr int kLdsStride = kWidth + 8;  // bf16 elements per LDS row (breaks ban
 
 template <int KIN, int NB>
 __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, uint16_t* __restrict__ out_lds,
-                                          const uint16_t* __restrict__ Wt, const float* __restrict__ bias,
+                                          const uint16_t* __restrict__ F, const float* __restrict__ bias,
                                           int lane, int cbase) {
     f32x4 acc[4][NB];
 #pragma unroll
@@ -594,10 +571,8 @@ __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, u
     for (int k0 = 0; k0 < KIN; k0 += 32) {
         u16x8 bf[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int ncol = cbase + b * 16 + r16;
-            bf[b] = *reinterpret_cast<const u16x8*>(Wt + (size_t)ncol * KIN + k0 + kq);
-        }
+        for (int b = 0; b < NB; ++b)
+            bf[b] = *reinterpret_cast<const u16x8*>(F + (((cbase / 16 + b) * (KIN / 32) + k0 / 32) * 64 + lane) * 8);
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             const u16x8 af = *reinterpret_cast<const u16x8*>(in_lds + (a * 16 + r16) * kLdsStride + k0 + kq);
@@ -621,21 +596,8 @@ __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, u
     }
 }
 
-__device__ __forceinline__ void store_act(const uint16_t* __restrict__ lds_act, uint16_t* __restrict__ g,
-                                          int64_t row0, int64_t n, int tid) {
-    // kRowsMlp rows x 256 bf16: each thread moves 8 bf16 per step
-    for (int i = tid; i < kRowsMlp * (kWidth / 8); i += kMlpThreads) {
-        const int r = i / (kWidth / 8), c8 = (i % (kWidth / 8)) * 8;
-        if (row0 + r < n)
-            *reinterpret_cast<u16x8*>(g + (row0 + r) * kWidth + c8) =
-                *reinterpret_cast<const u16x8*>(lds_act + r * kLdsStride + c8);
-    }
-}
-
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __restrict__ X, int64_t n,
-                                                             const RankerWeights W, float* __restrict__ Y,
-                                                             uint16_t* __restrict__ H1, uint16_t* __restrict__ H2,
-                                                             uint16_t* __restrict__ H3) {
+                                                             const RankerWeights W, float* __restrict__ Y) {
     __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t sb[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];  // head weights, transposed
@@ -654,15 +616,12 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __r
             *reinterpret_cast<u16x8*>(sa + r * kLdsStride + c8) = v;
         }
         __syncthreads();
-        layer_fwd<kFeat, kMlpNB>(sa, sb, W.w1t, W.b1, lane, cbase);
+        layer_fwd<kFeat, kMlpNB>(sa, sb, W.f1, W.b1, lane, cbase);
         __syncthreads();
-        if (H1) store_act(sb, H1, row0, n, tid);
-        layer_fwd<kWidth, kMlpNB>(sb, sa, W.w2t, W.b2, lane, cbase);
+        layer_fwd<kWidth, kMlpNB>(sb, sa, W.f2, W.b2, lane, cbase);
         __syncthreads();
-        if (H2) store_act(sa, H2, row0, n, tid);
-        layer_fwd<kWidth, kMlpNB>(sa, sb, W.w3t, W.b3, lane, cbase);
+        layer_fwd<kWidth, kMlpNB>(sa, sb, W.f3, W.b3, lane, cbase);
         __syncthreads();
-        if (H3) store_act(sb, H3, row0, n, tid);
         // head: wave w < 4 takes rows 16w..16w+15; B columns 0, 1 are the two heads
         if (wid < kRowsMlp / 16) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -685,18 +644,17 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __r
     }
 }
 
-// Inference over many rows (no activations stored): a persistent workgroup per CU
+// Inference over many rows: a persistent workgroup per CU
 // keeps its waves' weight fragments in registers for every row tile it takes, so
 // the weights are read from L2 once per workgroup instead of once per tile.
 template <int KIN>
-__device__ __forceinline__ void load_wfrag(u16x8 (&wf)[KIN / 32][kMlpNB], const uint16_t* __restrict__ Wt, int lane,
+__device__ __forceinline__ void load_wfrag(u16x8 (&wf)[KIN / 32][kMlpNB], const uint16_t* __restrict__ F, int lane,
                                            int cbase) {
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
 #pragma unroll
-    for (int ks = 0; ks < KIN / 32; ++ks)
+    for (int b = 0; b < kMlpNB; ++b)
 #pragma unroll
-        for (int b = 0; b < kMlpNB; ++b)
-            wf[ks][b] = *reinterpret_cast<const u16x8*>(Wt + (size_t)(cbase + b * 16 + r16) * KIN + ks * 32 + kq);
+        for (int ks = 0; ks < KIN / 32; ++ks)
+            wf[ks][b] = *reinterpret_cast<const u16x8*>(F + (((cbase / 16 + b) * (KIN / 32) + ks) * 64 + lane) * 8);
 }
 
 template <int KIN>
@@ -742,9 +700,9 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __res
     const int cbase = wid * kMlpNB * 16;
     for (int i = tid; i < kOut * kWidth; i += kMlpThreads) s_w4[(i % kOut) * kWidth + i / kOut] = W.w4[i];
     u16x8 w1[kFeat / 32][kMlpNB], w2[kWidth / 32][kMlpNB], w3[kWidth / 32][kMlpNB];
-    load_wfrag<kFeat>(w1, W.w1t, lane, cbase);
-    load_wfrag<kWidth>(w2, W.w2t, lane, cbase);
-    load_wfrag<kWidth>(w3, W.w3t, lane, cbase);
+    load_wfrag<kFeat>(w1, W.f1, lane, cbase);
+    load_wfrag<kWidth>(w2, W.f2, lane, cbase);
+    load_wfrag<kWidth>(w3, W.f3, lane, cbase);
     const int r16 = lane & 15, kq = (lane >> 4) * 8;
     const float hb = r16 < kOut ? W.b4[r16] : 0.f;
     // one 16-byte piece of a 64 x 64 feature tile per thread; the next tile's piece is
@@ -786,238 +744,6 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __res
             }
         }
     }
-}
-
-// ------------------------------------------------------------------ backward pieces
-
-// dY = scale_h * (Y - T) (per head weights already in scale), and the head's input
-// gradient dH3 = (dY W4^T) * [H3 > 0], bf16.
-__global__ __launch_bounds__(256) void k_head_backward(const float* __restrict__ Y, const float* __restrict__ Tg,
-                                                       int64_t n, float s0, float s1, const RankerWeights W,
-                                                       const uint16_t* __restrict__ H3, float* __restrict__ dY,
-                                                       uint16_t* __restrict__ dH3) {
-    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx >= n * kWidth) return;
-    const int64_t r = idx / kWidth;
-    const int k = (int)(idx % kWidth);
-    const float d0 = s0 * (Y[r * kOut] - Tg[r * kOut]);
-    const float d1 = s1 * (Y[r * kOut + 1] - Tg[r * kOut + 1]);
-    if (k == 0) {
-        dY[r * kOut] = d0;
-        dY[r * kOut + 1] = d1;
-    }
-    const float g = d0 * bf2f(W.w4[k * kOut]) + d1 * bf2f(W.w4[k * kOut + 1]);
-    dH3[idx] = bf2f(H3[idx]) > 0.f ? f2bf(g) : (uint16_t)0;
-}
-
-// dIn = (dOut M) * [Act > 0] where the layer computed Out = In Wf: M = Wf^T, so
-// B-fragments come from Wf stored row-major [kin][kout] (k = kout contiguous).
-// 64 rows per workgroup, KOUT = 256 reduction, output columns KIN.
-template <int KIN>
-__global__ __launch_bounds__(256) void k_backward_data(const uint16_t* __restrict__ dOut, int64_t n,
-                                                       const uint16_t* __restrict__ Wf,
-                                                       const uint16_t* __restrict__ Act,
-                                                       uint16_t* __restrict__ dIn) {
-    __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsFwd * kLdsStride];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    constexpr int NT = KIN / 64;  // column tiles of 16 per wave
-    for (int64_t row0 = (int64_t)blockIdx.x * kRowsFwd; row0 < n; row0 += (int64_t)gridDim.x * kRowsFwd) {
-        __syncthreads();
-        for (int i = tid; i < kRowsFwd * (kWidth / 8); i += 256) {
-            const int r = i / (kWidth / 8), c8 = (i % (kWidth / 8)) * 8;
-            u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (row0 + r < n) v = *reinterpret_cast<const u16x8*>(dOut + (row0 + r) * kWidth + c8);
-            *reinterpret_cast<u16x8*>(sa + r * kLdsStride + c8) = v;
-        }
-        __syncthreads();
-        f32x4 acc[4][NT];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < NT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k0 = 0; k0 < kWidth; k0 += 32) {
-            u16x8 bf[NT];
-#pragma unroll
-            for (int b = 0; b < NT; ++b) {
-                const int ncol = wid * (KIN / 4) + b * 16 + r16;
-                bf[b] = *reinterpret_cast<const u16x8*>(Wf + (size_t)ncol * kWidth + k0 + kq);
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const u16x8 af = *reinterpret_cast<const u16x8*>(sa + (a * 16 + r16) * kLdsStride + k0 + kq);
-#pragma unroll
-                for (int b = 0; b < NT; ++b) acc[a][b] = mfma16(af, bf[b], acc[a][b]);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < NT; ++b) {
-            const int col = wid * (KIN / 4) + b * 16 + r16;
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row0 + a * 16 + (lane >> 4) * 4 + r;
-                    if (row < n) {
-                        const bool on = Act ? bf2f(Act[row * KIN + col]) > 0.f : true;
-                        dIn[row * KIN + col] = on ? f2bf(acc[a][b][r]) : (uint16_t)0;
-                    }
-                }
-        }
-    }
-}
-
-// Weight gradient partials: P[split][KIN][KOUT] = In[rows of split]^T dOut[rows].
-// Workgroup = (64 x 64 output tile, split).  Chunks of 32 rows are staged in LDS
-// transposed (k-major) so that both MFMA operands read 16 contiguous bytes.
-template <int KIN>
-__global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ In, const uint16_t* __restrict__ dOut,
-                                               int64_t n, int64_t rows_per_split, float* __restrict__ P) {
-    __shared__ __attribute__((aligned(16))) uint16_t sI[64][40];  // [kin][row] (32 rows + pad)
-    __shared__ __attribute__((aligned(16))) uint16_t sO[64][40];  // [kout][row]
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int tiles_n = kWidth / 64;
-    const int ti = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;  // output tile (kin, kout)
-    const int split = blockIdx.y;
-    const int64_t ra = split * rows_per_split;
-    const int64_t rb = ra + rows_per_split < n ? ra + rows_per_split : n;
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    const int wa = wid >> 1, wb = wid & 1;  // wave's 32 x 32 quadrant
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t r0 = ra; r0 < rb; r0 += 32) {
-        __syncthreads();
-        // 32 rows x 64 columns of each operand, transposed into LDS
-        for (int i = tid; i < 32 * 64; i += 256) {
-            const int rr = i / 64, cc = i % 64;
-            const int64_t row = r0 + rr;
-            uint16_t vi = 0, vo = 0;
-            if (row < rb) {
-                vi = In[row * KIN + ti * 64 + cc];
-                vo = dOut[row * kWidth + tn * 64 + cc];
-            }
-            sI[cc][rr] = vi;
-            sO[cc][rr] = vo;
-        }
-        __syncthreads();
-        const u16x8 a0 = *reinterpret_cast<const u16x8*>(&sI[wa * 32 + r16][kq]);
-        const u16x8 a1 = *reinterpret_cast<const u16x8*>(&sI[wa * 32 + 16 + r16][kq]);
-        const u16x8 b0 = *reinterpret_cast<const u16x8*>(&sO[wb * 32 + r16][kq]);
-        const u16x8 b1 = *reinterpret_cast<const u16x8*>(&sO[wb * 32 + 16 + r16][kq]);
-        acc[0][0] = mfma16(a0, b0, acc[0][0]);
-        acc[0][1] = mfma16(a0, b1, acc[0][1]);
-        acc[1][0] = mfma16(a1, b0, acc[1][0]);
-        acc[1][1] = mfma16(a1, b1, acc[1][1]);
-    }
-    float* out = P + (size_t)split * KIN * kWidth;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = ti * 64 + wa * 32 + a * 16 + (lane >> 4) * 4 + r;
-                const int col = tn * 64 + wb * 32 + b * 16 + r16;
-                out[row * kWidth + col] = acc[a][b][r];
-            }
-}
-
-// Column sums of a bf16 [n x N] matrix per split (bias gradients), fp32 partials.
-__global__ __launch_bounds__(256) void k_colsum(const uint16_t* __restrict__ A, int64_t n, int N,
-                                                int64_t rows_per_split, float* __restrict__ P) {
-    const int split = blockIdx.y;
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= N) return;
-    const int64_t ra = split * rows_per_split;
-    const int64_t rb = ra + rows_per_split < n ? ra + rows_per_split : n;
-    // eight partial sums (eight loads in flight), combined in a fixed order
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int64_t r = ra;
-    for (; r + 8 <= rb; r += 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] += bf2f(A[(r + u) * N + col]);
-    }
-    for (; r < rb; ++r) acc[0] += bf2f(A[r * N + col]);
-    P[(size_t)split * N + col] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-}
-
-// Head gradients: dW4[k][h] = sum_r H3[r][k] dY[r][h], db4[h] = sum_r dY[r][h].
-__global__ __launch_bounds__(256) void k_head_wgrad(const uint16_t* __restrict__ H3, const float* __restrict__ dY,
-                                                    int64_t n, int64_t rows_per_split, float* __restrict__ P) {
-    const int split = blockIdx.y;
-    const int t = threadIdx.x;  // k index
-    const int64_t ra = split * rows_per_split;
-    const int64_t rb = ra + rows_per_split < n ? ra + rows_per_split : n;
-    // four partial sums of each (four rows' loads in flight), combined in a fixed order
-    float s0[4] = {0.f, 0.f, 0.f, 0.f}, s1[4] = {0.f, 0.f, 0.f, 0.f};
-    float c0[4] = {0.f, 0.f, 0.f, 0.f}, c1[4] = {0.f, 0.f, 0.f, 0.f};
-    int64_t r = ra;
-    for (; r + 4 <= rb; r += 4) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float h = bf2f(H3[(r + u) * kWidth + t]);
-            const float y0 = dY[(r + u) * kOut], y1 = dY[(r + u) * kOut + 1];
-            s0[u] += h * y0;
-            s1[u] += h * y1;
-            c0[u] += y0;
-            c1[u] += y1;
-        }
-    }
-    for (; r < rb; ++r) {
-        const float h = bf2f(H3[r * kWidth + t]);
-        const float y0 = dY[r * kOut], y1 = dY[r * kOut + 1];
-        s0[0] += h * y0;
-        s1[0] += h * y1;
-        c0[0] += y0;
-        c1[0] += y1;
-    }
-    const float t0 = (s0[0] + s0[1]) + (s0[2] + s0[3]), t1 = (s1[0] + s1[1]) + (s1[2] + s1[3]);
-    const float b0 = (c0[0] + c0[1]) + (c0[2] + c0[3]), b1 = (c1[0] + c1[1]) + (c1[2] + c1[3]);
-    float* o = P + (size_t)split * (kWidth * kOut + kOut);
-    o[t * kOut] = t0;
-    o[t * kOut + 1] = t1;
-    if (t == 0) {
-        o[kWidth * kOut] = b0;
-        o[kWidth * kOut + 1] = b1;
-    }
-}
-
-// Sum split partials (fixed order: deterministic) into dst[count].
-__global__ __launch_bounds__(256) void k_reduce_splits(const float* __restrict__ P, int splits, int64_t count,
-                                                       float* __restrict__ dst) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    // four partial sums (four loads in flight), combined in a fixed order
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    int sp = 0;
-    for (; sp + 4 <= splits; sp += 4) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[u] += P[(size_t)(sp + u) * count + i];
-    }
-    for (; sp < splits; ++sp) acc[0] += P[(size_t)sp * count + i];
-    dst[i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-}
-
-// Adam on the fp32 master copy; refreshes the bf16 copies (row-major and
-// transposed) of the matrices.  Parameter layout: see RankerLayout.
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float* __restrict__ g,
-                                              float* __restrict__ m, float* __restrict__ v, int64_t count,
-                                              float lr, float b1, float b2, float eps, float c1, float c2,
-                                              const RankerWeights W) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    p[i] = pi;
-    publish_param(i, pi, W);
 }
 
 // Refresh all bf16 copies from the fp32 master (after loading or setting params).
@@ -1184,60 +910,15 @@ hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_hal
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, uint16_t* H1,
-                              uint16_t* H2, uint16_t* H3, hipStream_t s) {
+hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     int64_t grid = (n + kRowsMlp - 1) / kRowsMlp;
-    if (!H1 && !H2 && !H3 && grid > 4 * kMlpInferCus) {
-        // inference over many rows: persistent workgroups, weights in registers
+    if (grid > 4 * kMlpInferCus) {
+        // many rows: persistent workgroups, weights in registers
         hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)kMlpInferCus), dim3(kMlpThreads), 0, s, X, n, W, Y);
         return hipGetLastError();
     }
-    if (grid > 8192) grid = 8192;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)grid), dim3(kMlpThreads), 0, s, X, n, W, Y, H1, H2, H3);
-    return hipGetLastError();
-}
-
-hipError_t launch_backward(const RankerBuffers& B, const RankerWeights& W, int64_t n, float s0, float s1,
-                           hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int64_t rows_per_split = ((n + kSplits - 1) / kSplits + 31) / 32 * 32;
-    const int splits = (int)((n + rows_per_split - 1) / rows_per_split);
-    hipLaunchKernelGGL(k_head_backward, dim3((unsigned)((n * kWidth + 255) / 256)), dim3(256), 0, s, B.Y, B.T, n, s0,
-                       s1, W, B.H3, B.dY, B.dH3);
-    hipLaunchKernelGGL(k_head_wgrad, dim3(1, splits), dim3(kWidth), 0, s, B.H3, B.dY, n, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3((kWidth * kOut + kOut + 255) / 256), dim3(256), 0, s, B.part, splits,
-                       (int64_t)(kWidth * kOut + kOut), B.grad + W.layout.w4);
-    int64_t grid = (n + kRowsFwd - 1) / kRowsFwd;
-    if (grid > 8192) grid = 8192;
-    // layer 3
-    hipLaunchKernelGGL(k_wgrad<kWidth>, dim3(16, splits), dim3(256), 0, s, B.H2, B.dH3, n, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3((kWidth * kWidth + 255) / 256), dim3(256), 0, s, B.part, splits,
-                       (int64_t)kWidth * kWidth, B.grad + W.layout.w3);
-    hipLaunchKernelGGL(k_colsum, dim3(1, splits), dim3(kWidth), 0, s, B.dH3, n, kWidth, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3(1), dim3(256), 0, s, B.part, splits, (int64_t)kWidth, B.grad + W.layout.b3);
-    hipLaunchKernelGGL(k_backward_data<kWidth>, dim3((unsigned)grid), dim3(256), 0, s, B.dH3, n, W.w3, B.H2, B.dH2);
-    // layer 2
-    hipLaunchKernelGGL(k_wgrad<kWidth>, dim3(16, splits), dim3(256), 0, s, B.H1, B.dH2, n, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3((kWidth * kWidth + 255) / 256), dim3(256), 0, s, B.part, splits,
-                       (int64_t)kWidth * kWidth, B.grad + W.layout.w2);
-    hipLaunchKernelGGL(k_colsum, dim3(1, splits), dim3(kWidth), 0, s, B.dH2, n, kWidth, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3(1), dim3(256), 0, s, B.part, splits, (int64_t)kWidth, B.grad + W.layout.b2);
-    hipLaunchKernelGGL(k_backward_data<kWidth>, dim3((unsigned)grid), dim3(256), 0, s, B.dH2, n, W.w2, B.H1, B.dH1);
-    // layer 1
-    hipLaunchKernelGGL(k_wgrad<kFeat>, dim3(4, splits), dim3(256), 0, s, B.X, B.dH1, n, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3((kFeat * kWidth + 255) / 256), dim3(256), 0, s, B.part, splits,
-                       (int64_t)kFeat * kWidth, B.grad + W.layout.w1);
-    hipLaunchKernelGGL(k_colsum, dim3(1, splits), dim3(kWidth), 0, s, B.dH1, n, kWidth, rows_per_split, B.part);
-    hipLaunchKernelGGL(k_reduce_splits, dim3(1), dim3(256), 0, s, B.part, splits, (int64_t)kWidth, B.grad + W.layout.b1);
-    return hipGetLastError();
-}
-
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t count, float lr, float b1, float b2,
-                       float eps, int64_t t, const RankerWeights& W, hipStream_t s) {
-    const float c1 = 1.f - powf(b1, (float)t), c2 = 1.f - powf(b2, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, p, g, m, v, count, lr, b1, b2,
-                       eps, c1, c2, W);
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)grid), dim3(kMlpThreads), 0, s, X, n, W, Y);
     return hipGetLastError();
 }
 

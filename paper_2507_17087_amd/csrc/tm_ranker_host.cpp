@@ -41,9 +41,13 @@ struct tm_ranker {
     float mu[kOut] = {0, 0}, sigma[kOut] = {1, 1};   // target standardisation
     int64_t step = 0;
     // training buffers (grown on demand)
-    RankerBuffers B{};
+    TrainBuffers B{};
+    float* grad = nullptr;
     int64_t cap_rows = 0;
     void* bufmem = nullptr;
+    // bf16 features of a forward call (grown on demand)
+    uint16_t* X = nullptr;
+    int64_t cap_x = 0;
 };
 
 namespace tmk {
@@ -55,15 +59,14 @@ static int ranker_alloc_weights(tm_ranker* r) {
     TM_HIP(hipMalloc((void**)&r->v, n * 4));
     TM_HIP(hipMemset(r->m, 0, n * 4));
     TM_HIP(hipMemset(r->v, 0, n * 4));
-    const int64_t nb = 2 * (kFeat * kWidth) + 4 * (kWidth * kWidth) + kWidth * kOut;
+    const int64_t nb = kFeat * kWidth + 4 * (kWidth * kWidth) + kWidth * kOut;
     TM_HIP(hipMalloc((void**)&r->bf, nb * 2));
     uint16_t* q = r->bf;
-    r->W.w1 = q; q += kFeat * kWidth;
-    r->W.w1t = q; q += kFeat * kWidth;
-    r->W.w2 = q; q += kWidth * kWidth;
-    r->W.w2t = q; q += kWidth * kWidth;
-    r->W.w3 = q; q += kWidth * kWidth;
-    r->W.w3t = q; q += kWidth * kWidth;
+    r->W.f1 = q; q += kFeat * kWidth;
+    r->W.f2 = q; q += kWidth * kWidth;
+    r->W.f3 = q; q += kWidth * kWidth;
+    r->W.g3 = q; q += kWidth * kWidth;
+    r->W.g2 = q; q += kWidth * kWidth;
     r->W.w4 = q;
     r->W.b1 = r->p + r->L.b1;
     r->W.b2 = r->p + r->L.b2;
@@ -73,49 +76,53 @@ static int ranker_alloc_weights(tm_ranker* r) {
     return TM_OK;
 }
 
+static int64_t pad_rows(int64_t rows) { return (rows + 31) / 32 * 32; }
+
+// Buffers of a batch of `rows` rows.
 static int ranker_buffers(tm_ranker* r, int64_t rows) {
     if (rows <= r->cap_rows) return TM_OK;
     if (r->bufmem) TM_HIP(hipFree(r->bufmem));
     r->bufmem = nullptr;
-    rows = std::max<int64_t>(rows, 1024);
-    const size_t bf = (size_t)rows * (kFeat + 6 * kWidth) * 2;
-    const size_t f32 = (size_t)rows * 3 * kOut * 4 + (size_t)r->L.count * 4 + (size_t)kSplits * kWidth * kWidth * 4;
-    if (hipMalloc(&r->bufmem, bf + f32 + 1024) != hipSuccess) return set_error(TM_ENOMEM, "ranker buffers");
+    r->cap_rows = 0;
+    const int64_t cap = pad_rows(std::max<int64_t>(rows, 1024));
+    const size_t bytes = (size_t)cap * (kFeat + 6 * kWidth) * 2 + (size_t)cap * 2 * kOut * 4 + (size_t)(cap / 16) * kColParts * 4 +
+                         (size_t)r->L.count * (kMaxSplits + 1) * 4 + 16 * 256;
+    if (hipMalloc(&r->bufmem, bytes) != hipSuccess) return set_error(TM_ENOMEM, "ranker buffers");
     char* q = (char*)r->bufmem;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t n) {
         void* p = q;
-        q += (bytes + 255) & ~size_t(255);
+        q += (n + 255) & ~size_t(255);
         return p;
     };
-    r->B.X = (uint16_t*)take((size_t)rows * kFeat * 2);
-    r->B.H1 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.H2 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.H3 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.dH1 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.dH2 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.dH3 = (uint16_t*)take((size_t)rows * kWidth * 2);
-    r->B.Y = (float*)take((size_t)rows * kOut * 4);
-    r->B.T = (float*)take((size_t)rows * kOut * 4);
-    r->B.dY = (float*)take((size_t)rows * kOut * 4);
-    r->B.grad = (float*)take((size_t)r->L.count * 4);
-    r->B.part = (float*)take((size_t)kSplits * kWidth * kWidth * 4);
-    r->cap_rows = rows;
+    r->B.X = (uint16_t*)take((size_t)cap * kFeat * 2);
+    for (uint16_t** h : {&r->B.H1, &r->B.H2, &r->B.H3, &r->B.D1, &r->B.D2, &r->B.D3})
+        *h = (uint16_t*)take((size_t)cap * kWidth * 2);
+    for (float** f : {&r->B.Y, &r->B.T}) *f = (float*)take((size_t)cap * kOut * 4);
+    r->B.colpart = (float*)take((size_t)(cap / 16) * kColParts * 4);
+    r->grad = (float*)take((size_t)r->L.count * 4);
+    r->B.part = (float*)take((size_t)r->L.count * kMaxSplits * 4);
+    r->cap_rows = cap;
     return TM_OK;
 }
 
-// fp32 features -> bf16 rows, optionally gathered through a permutation; targets
-// gathered likewise.
-__global__ void k_pack_batch(const float* __restrict__ feat, const float* __restrict__ tgt,
-                             const int64_t* __restrict__ perm, int64_t first, int64_t rows,
-                             uint16_t* __restrict__ X, float* __restrict__ T) {
+// Features buffer of a forward call of `rows` rows at a time.
+static int forward_buffer(tm_ranker* r, int64_t rows) {
+    if (rows <= r->cap_x) return TM_OK;
+    if (r->X) TM_HIP(hipFree(r->X));
+    r->X = nullptr;
+    r->cap_x = 0;
+    if (hipMalloc((void**)&r->X, (size_t)rows * kFeat * 2) != hipSuccess) return set_error(TM_ENOMEM, "ranker features");
+    r->cap_x = rows;
+    return TM_OK;
+}
+
+// fp32 features -> bf16 rows.
+__global__ void k_pack_batch(const float* __restrict__ feat, int64_t first, int64_t rows, uint16_t* __restrict__ X) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= rows * kFeat) return;
-    const int64_t r = i / kFeat, c = i % kFeat;
-    const int64_t src = perm ? perm[first + r] : first + r;
-    uint32_t u = __float_as_uint(feat[src * kFeat + c]);
+    uint32_t u = __float_as_uint(feat[first * kFeat + i]);
     u += 0x7fffu + ((u >> 16) & 1u);
     X[i] = (uint16_t)(u >> 16);
-    if (c < kOut && T && tgt) T[r * kOut + c] = tgt[src * kOut + c];
 }
 
 // Standardised targets from exact costs: t_h = (log2(1 + x_h) - mu_h) / sigma_h.
@@ -179,20 +186,13 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ Y, const
     if (threadIdx.x == 0) part[blockIdx.x] = s[0];
 }
 
-static int ranker_forward_rows(tm_ranker* r, const uint16_t* X, int64_t rows, float* Y, bool keep, hipStream_t s) {
-    const hipError_t e = launch_mlp_forward(X, rows, r->W, Y, keep ? r->B.H1 : nullptr, keep ? r->B.H2 : nullptr,
-                                            keep ? r->B.H3 : nullptr, s);
-    if (e != hipSuccess) return set_error(TM_EDEVICE, "forward: %s", hipGetErrorString(e));
-    return TM_OK;
-}
-
-// Gradient of the mean squared error of one batch (rows already packed in B).
-static int ranker_batch_grad(tm_ranker* r, int64_t rows, hipStream_t s) {
-    int rc = ranker_forward_rows(r, r->B.X, rows, r->B.Y, true, s);
-    if (rc != TM_OK) return rc;
-    const float sc = 2.0f / (float)(rows * kOut);
-    const hipError_t e = launch_backward(r->B, r->W, rows, sc, sc, s);
-    if (e != hipSuccess) return set_error(TM_EDEVICE, "backward: %s", hipGetErrorString(e));
+// Gradient of the mean squared error of one batch: the bias and head gradients to grad,
+// the matrices' to the partial buffers.
+static int ranker_batch_grad(tm_ranker* r, const TrainBatch& b, float* grad, hipStream_t s) {
+    r->B.npad = pad_rows(b.n);
+    const float sc = 2.0f / (float)(b.n * kOut);
+    const hipError_t e = launch_gradient(b, r->W, sc, sc, r->B, grad, s);
+    if (e != hipSuccess) return set_error(TM_EDEVICE, "gradient: %s", hipGetErrorString(e));
     return TM_OK;
 }
 
@@ -244,6 +244,7 @@ int tm_ranker_destroy(tm_ranker* r) {
     if (r->v) (void)hipFree(r->v);
     if (r->bf) (void)hipFree(r->bf);
     if (r->bufmem) (void)hipFree(r->bufmem);
+    if (r->X) (void)hipFree(r->X);
     delete r;
     return TM_OK;
 }
@@ -274,14 +275,14 @@ int tm_ranker_forward(tm_ranker* r, const float* d_feat, int64_t n, float* d_out
     if (!r || n < 0 || (n > 0 && (!d_feat || !d_out))) return set_error(TM_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
     const int64_t chunk = 1 << 18;
-    int rc = ranker_buffers(r, std::min<int64_t>(n, chunk));
+    const int rc = forward_buffer(r, std::min<int64_t>(n, chunk));
     if (rc != TM_OK) return rc;
     for (int64_t a = 0; a < n; a += chunk) {
         const int64_t rows = std::min(chunk, n - a);
-        hipLaunchKernelGGL(k_pack_batch, dim3((unsigned)((rows * kFeat + 255) / 256)), dim3(256), 0, s, d_feat,
-                           nullptr, nullptr, a, rows, r->B.X, nullptr);
-        rc = ranker_forward_rows(r, r->B.X, rows, d_out + a * kOut, false, s);
-        if (rc != TM_OK) return rc;
+        hipLaunchKernelGGL(k_pack_batch, dim3((unsigned)((rows * kFeat + 255) / 256)), dim3(256), 0, s, d_feat, a, rows,
+                           r->X);
+        const hipError_t e = launch_mlp_forward(r->X, rows, r->W, d_out + a * kOut, s);
+        if (e != hipSuccess) return set_error(TM_EDEVICE, "forward: %s", hipGetErrorString(e));
     }
     return TM_OK;
 }
@@ -292,11 +293,9 @@ int tm_ranker_grad(tm_ranker* r, const float* d_feat, const float* d_target, int
     hipStream_t s = (hipStream_t)stream;
     int rc = ranker_buffers(r, n);
     if (rc != TM_OK) return rc;
-    hipLaunchKernelGGL(k_pack_batch, dim3((unsigned)((n * kFeat + 255) / 256)), dim3(256), 0, s, d_feat, d_target,
-                       nullptr, 0, n, r->B.X, r->B.T);
-    rc = ranker_batch_grad(r, n, s);
+    rc = ranker_batch_grad(r, TrainBatch{d_feat, d_target, nullptr, 0, n}, d_grad, s);
     if (rc != TM_OK) return rc;
-    TM_HIP(hipMemcpyAsync(d_grad, r->B.grad, r->L.count * 4, hipMemcpyDeviceToDevice, s));
+    TM_HIP(launch_reduce_grad(r->L, r->B, n, d_grad, s));
     return TM_OK;
 }
 
@@ -344,17 +343,15 @@ int tm_ranker_train(tm_ranker* r, const float* d_feat, const tm_stencil_cost* d_
         int64_t loss_rows = 0;
         for (int64_t first = 0; first + batch <= n || (first < n && first == 0); first += batch) {
             const int64_t rows = std::min<int64_t>(batch, n - first);
-            hipLaunchKernelGGL(k_pack_batch, dim3((unsigned)((rows * kFeat + 255) / 256)), dim3(256), 0, s, d_feat,
-                               d_T, d_perm, first, rows, r->B.X, r->B.T);
-            rc = ranker_batch_grad(r, rows, s);
+            rc = ranker_batch_grad(r, TrainBatch{d_feat, d_T, d_perm, first, rows}, r->grad, s);
             if (rc != TM_OK) break;
             ++r->step;
             // cosine decay over the run
             const double prog = (double)(ep * ((n + batch - 1) / batch) + first / batch) /
                                 (double)std::max<int64_t>(1, epochs * ((n + batch - 1) / batch));
             const float lr_t = (float)(lr * (0.05 + 0.95 * 0.5 * (1.0 + std::cos(3.141592653589793 * prog))));
-            if (launch_adam(r->p, r->B.grad, r->m, r->v, r->L.count, lr_t, 0.9f, 0.999f, 1e-8f, r->step, r->W, s) !=
-                hipSuccess) {
+            if (launch_reduce_adam(r->p, r->B, rows, r->grad, r->m, r->v, lr_t, 0.9f, 0.999f, 1e-8f, r->step, r->W,
+                                   s) != hipSuccess) {
                 rc = set_error(TM_EDEVICE, "adam");
                 break;
             }
@@ -475,7 +472,7 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
     // the network's score of every candidate: descriptor features, forward, residuals
     // over the descriptor estimate
     hipError_t e = launch_features(plan_cands(p), n, plan_halo(p), sb->est, sb->X, nullptr, s);
-    if (e == hipSuccess) e = launch_mlp_forward(sb->X, n, r->W, sb->Y, nullptr, nullptr, nullptr, s);
+    if (e == hipSuccess) e = launch_mlp_forward(sb->X, n, r->W, sb->Y, s);
     if (e == hipSuccess) e = launch_combine(sb->Y, sb->est, n, r->mu, r->sigma, lambda, sb->score, s);
     if (prefilter > 0) {
         // the network keeps `prefilter` per instance; their block-model estimates
