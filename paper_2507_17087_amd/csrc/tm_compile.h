@@ -148,7 +148,8 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
     e->rgpus = 1.0f / (float)d.gpus;
     e->bij = is_bijective(d);
     e->flags = is_simple(d) ? kEvalSimple : 0;
-    for (int j = 0; j < 5; ++j) e->pad[j] = 0;
+    e->pad = e->pad2[0] = e->pad2[1] = 0;
+    e->points = d.npoints;
     for (int t = 0; t < d.nops; ++t) fill_inverse(d, t, &e->inv[t]);
     int next = 0;
     for (int k = 0; k < d.lrank; ++k) {

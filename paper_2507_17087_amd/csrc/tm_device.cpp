@@ -9,6 +9,7 @@
 #include "tm_compile.h"
 #include "tm_eval.h"
 #include "tm_internal.h"
+#include "tm_map.h"
 #include "tm_plan.h"
 #include "tm_ranker.h"
 
@@ -31,14 +32,6 @@ static int64_t default_tuples_per_item(int64_t tuples) {
 }
 // Largest work item accepted from a caller.
 constexpr int64_t kMaxCellsPerItem = int64_t(1) << 26;
-// Map launches: one workgroup per block of map_rows_per_block(L) rows, up to this many
-// (more blocks are taken grid-stride).
-constexpr int64_t kMapMaxGrid = int64_t(1) << 20;
-static int map_grid(int64_t rows, int32_t L, int32_t lds_words) {
-    const int64_t rpb = map_rows_per_block(L, map_narrow(lds_words));
-    return (int)std::max<int64_t>(1, std::min<int64_t>((rows + rpb - 1) / rpb, kMapMaxGrid));
-}
-
 // ------------------------------------------------------------------ batch compilation
 
 static int64_t up4(int64_t x) { return (x + 3) & ~int64_t(3); }
@@ -336,15 +329,24 @@ extern "C" int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, v
         return set_error(TM_ECAPACITY, "map length %lld but the domain has %lld points", (long long)len,
                          (long long)cp.cands[0].npoints);
     if (!d_map) return set_error(TM_EINVAL, "null output");
-    DeviceBatch db;
-    rc = upload_batch(cp, db, s);
+    // one allocation: the descriptor, then the owner table as processor ids
+    const DevCand& c0 = cp.cands[0];
+    char* mem = nullptr;
+    TM_HIP(hipMallocAsync((void**)&mem, sizeof(DevEval) + (size_t)map_ids_words(c0.vol) * 4, s));
+    DevEval* d_eval = reinterpret_cast<DevEval*>(mem);
+    int32_t* ids = reinterpret_cast<int32_t*>(mem + sizeof(DevEval));
+    void* stg = nullptr;
+    rc = staging_acquire(sizeof(DevEval), &stg);
     if (rc == TM_OK) {
-        const int grid = map_grid(cp.cands[0].rows, cp.cands[0].L, cp.max_words);
-        hipError_t e = launch_build_tables(db.hdr, db.cands, 1, db.arena, 0, s);
-        if (e == hipSuccess) e = launch_map(db.cands, 1, db.arena, nullptr, 0, d_map, grid, cp.max_words, s);
-        if (e != hipSuccess) rc = set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
+        fill_eval(c0, EvalShape{1, 0, 0, 1}, static_cast<DevEval*>(stg));
+        hipError_t e = hipMemcpyAsync(d_eval, stg, sizeof(DevEval), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) rc = staging_release(s);
+        if (rc == TM_OK && e == hipSuccess) e = launch_map_ids(d_eval, 1, nullptr, 0, c0.vol, ids, s);
+        if (rc == TM_OK && e == hipSuccess)
+            e = launch_map(map_shape(c0.vol, c0.npoints, c0.L), d_eval, 1, nullptr, 0, ids, d_map, s);
+        if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
     }
-    free_batch(db, s);
+    (void)hipFreeAsync(mem, s);
     return rc;
 }
 
@@ -613,10 +615,10 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
     return TM_OK;
 }
 
-// Table words of the loaded batch's largest candidate, for the map of one candidate.
-static int64_t plan_map_words(const tm_plan* p) { return std::max<int64_t>(p->cp.max_all_words, 1); }
+// Words of the loaded batch's largest owner table, for the map of one candidate.
+static int64_t plan_map_words(const tm_plan* p) { return std::max<int64_t>(map_ids_words(p->cp.max_vol), 4); }
 
-// Device memory for one candidate's tables; grows (after draining `s`) when needed.
+// Device memory for one candidate's owner table; grows (after draining `s`) when needed.
 static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
     const int64_t words = plan_map_words(p);
     if (p->d_arena && p->cap_arena >= words) return TM_OK;
@@ -649,35 +651,28 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
 
 // Enqueues a run, or one stage of it, on stream s (direct launches; also used for
 // capture).  Stage 2 on its own repeats the selection (idempotent).
-static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, hipStream_t s) {
+static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, hipStream_t s,
+                               int32_t* best_ids = nullptr) {
     const Compiled& cp = p->cp;
     if (stage == 0) return launch_zero_costs(out, cp.hdr.n, s);
     if (stage == 2) return launch_bytes_select(out, cp.hdr.n, cp.hdr.elem_bytes, best, s);
-    return launch_eval_batch(cp.eval, p->d_evals, out, best, p->d_counter, num_cus(), s);
+    return launch_eval_batch(cp.eval, p->d_evals, out, best, p->d_counter, num_cus(), s, nullptr, 0, best_ids);
 }
 
-// Map grid for a device-side index: the largest over the loaded candidates.
-static int plan_map_grid(const tm_plan* p) {
-    int grid = 1;
-    for (auto& d : p->cp.cands) grid = std::max(grid, map_grid(d.rows, d.L, p->cp.max_words));
-    return grid;
-}
-
-// Tables, then the map, of candidate *d_index (or index).
-static hipError_t plan_enqueue_map(tm_plan* p, const int64_t* d_index, int64_t index, int32_t* map, int grid,
-                                   hipStream_t s) {
-    const int64_t n = p->cp.hdr.n;
-    hipError_t e = launch_build_one(p->d_hdr, p->d_cands, n, d_index, index, p->d_arena, s);
-    if (e == hipSuccess) e = launch_map(p->d_cands, n, p->d_arena, d_index, index, map, grid, p->cp.max_words, s);
-    return e;
+// Map launch for a device-side index: fits every loaded candidate.
+static MapShape plan_map_shape(const tm_plan* p) {
+    int64_t row = INT32_MAX;
+    for (auto& d : p->cp.cands) row = std::min<int64_t>(row, d.L);
+    return map_shape(p->cp.max_vol, p->cp.max_points, row);
 }
 
 // Captures a run (stage -1), a stage (0..2) or, with map, a run and the map of *best.
 static int capture(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, int32_t* map, hipGraphExec_t* exec) {
     hipGraph_t g = nullptr;
     TM_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = plan_enqueue(p, stage, out, best, p->cap_stream);
-    if (e == hipSuccess && map) e = plan_enqueue_map(p, best, 0, map, plan_map_grid(p), p->cap_stream);
+    hipError_t e = plan_enqueue(p, stage, out, best, p->cap_stream, map ? p->d_arena : nullptr);
+    if (e == hipSuccess && map)
+        e = launch_map(plan_map_shape(p), p->d_evals, p->cp.hdr.n, best, 0, p->d_arena, map, p->cap_stream);
     const hipError_t e2 = hipStreamEndCapture(p->cap_stream, &g);
     if (e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -815,20 +810,23 @@ extern "C" int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t h
     const Compiled& cp = p->cp;
     if (cp.hdr.n == 0) return set_error(TM_EINVAL, "empty batch");
     int64_t need = cp.max_points;
-    int grid = 1;
+    MapShape shape;
     if (!d_index) {
         if (host_index < 0 || host_index >= cp.hdr.n) return set_error(TM_EINVAL, "index %lld", (long long)host_index);
-        need = cp.cands[(size_t)host_index].npoints;
-        grid = map_grid(cp.cands[(size_t)host_index].rows, cp.cands[(size_t)host_index].L, cp.max_words);
+        const DevCand& c = cp.cands[(size_t)host_index];
+        need = c.npoints;
+        shape = map_shape(c.vol, c.npoints, c.L);
     } else {
-        grid = plan_map_grid(p);
+        shape = plan_map_shape(p);
     }
     if (cap < need) return set_error(TM_ECAPACITY, "map needs %lld entries", (long long)need);
     if (p->cap_words < cp.arena_words)
         return set_error(TM_EINVAL, "not run yet: run the plan before materialising a map");
     const int rc = plan_ensure_arena(p, (hipStream_t)stream);
     if (rc != TM_OK) return rc;
-    const hipError_t e = plan_enqueue_map(p, d_index, host_index, d_map, grid, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    hipError_t e = launch_map_ids(p->d_evals, cp.hdr.n, d_index, host_index, cp.max_vol, p->d_arena, s);
+    if (e == hipSuccess) e = launch_map(shape, p->d_evals, cp.hdr.n, d_index, host_index, p->d_arena, d_map, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
     return TM_OK;
 }

@@ -19,6 +19,7 @@ struct EvalArgs {
     int64_t n;
     tm_stencil_cost* out;
     int64_t* best;
+    int32_t* best_ids;  // nullable: the selected candidate's owner table, as processor ids
     unsigned long long* counter;
     int64_t elem_bytes;
     int32_t halo[TM_MAX_LRANK];
@@ -39,15 +40,17 @@ struct EvalPlan {
 
 // Evaluates the batch into out (n rows) and, with best, selects into *best.  counter: a
 // device word that holds 0 between launches.  With idx, the nidx candidates idx[i] instead
-// (whole ones; rows of negative entries are left alone).
+// (whole ones; rows of negative entries are left alone).  best_ids: the selected candidate's
+// owner table as processor ids (for its map), written by the workgroup that selects.
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
                              unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
-                             int64_t nidx = 0);
+                             int64_t nidx = 0, int32_t* best_ids = nullptr);
 // The evaluation's view of n compiled candidates.
 hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, hipStream_t s);
 // The rows zeroed; and the bytes of rows that hold cells, with the selection.
 hipError_t launch_zero_costs(tm_stencil_cost* out, int64_t n, hipStream_t s);
-hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s);
+hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s,
+                               const DevEval* evals = nullptr, int32_t* ids = nullptr);
 // Sum over the candidates of the product of their class counts (tm_plan_class_tuples).
 hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* halo, unsigned long long* total,
                                hipStream_t s);

@@ -310,10 +310,12 @@ __device__ __forceinline__ bool cost_less(int64_t b, int64_t i, int64_t x, int64
 }
 
 // The index minimising (bytes, inter_bytes, index) of n cost rows that other workgroups
-// of this launch wrote (read at device scope) -> *best.
+// of this launch wrote (read at device scope) -> *best; with ids, its owner table as
+// processor ids (ev: LDS for its descriptor).
 template <int NT>
-__device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best) {
-    __shared__ int64_t sb[NT / 64], si[NT / 64], sx[NT / 64];
+__device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best,
+                                            const DevEval* evals, int32_t* ids, DevEval& ev) {
+    __shared__ int64_t sb[NT / 64], si[NT / 64], sx[NT / 64], s_best;
     const int t = threadIdx.x;
     int64_t kb = INT64_MAX, ki = INT64_MAX, kx = INT64_MAX;
     for (int64_t i = t; i < n; i += NT) {
@@ -349,7 +351,13 @@ __device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t 
                 kx = sx[w];
             }
         *best = n > 0 ? kx : -1;
+        s_best = kx;
     }
+    if (!ids || n <= 0) return;
+    __syncthreads();
+    stage_eval(&ev, evals + wave_uniform64(s_best), t);
+    __syncthreads();
+    owner_table<true>(ev, ids, 0, wave_uniform(ev.vol), -1, t, NT);
 }
 
 constexpr int kOneRecord = 2 + 4 * kMaxHalo;  // words of the largest record without masks
@@ -420,7 +428,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : 
     __syncthreads();
     if (!s_last) return;
     __threadfence();
-    select_rows<NT>(A.out, A.n, A.best);
+    select_rows<NT>(A.out, A.n, A.best, A.evals, A.best_ids, ev);
     if (tid == 0) *A.counter = 0ull;
 }
 
@@ -476,25 +484,30 @@ __global__ __launch_bounds__(256) void k_cost_bytes(tm_stencil_cost* __restrict_
 }
 
 __global__ __launch_bounds__(1024) void k_select_rows(const tm_stencil_cost* __restrict__ out, int64_t n,
-                                                      int64_t* __restrict__ best) {
-    select_rows<1024>(out, n, best);
+                                                      int64_t* __restrict__ best, const DevEval* __restrict__ evals,
+                                                      int32_t* __restrict__ ids) {
+    __shared__ DevEval ev;
+    select_rows<1024>(out, n, best, evals, ids, ev);
 }
 
-static hipError_t launch_select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best, hipStream_t s) {
-    hipLaunchKernelGGL(k_select_rows, dim3(1), dim3(1024), 0, s, out, n, best);
+static hipError_t launch_select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best, const DevEval* evals,
+                                     int32_t* ids, hipStream_t s) {
+    hipLaunchKernelGGL(k_select_rows, dim3(1), dim3(1024), 0, s, out, n, best, evals, ids);
     return hipGetLastError();
 }
 
-hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s) {
+hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s,
+                               const DevEval* evals, int32_t* ids) {
     const int64_t g = std::min<int64_t>(std::max<int64_t>((n + 255) / 256, 1), 2048);
     hipLaunchKernelGGL(k_cost_bytes, dim3((unsigned)g), dim3(256), 0, s, out, n, elem_bytes);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && best) e = launch_select_rows(out, n, best, s);
+    if (e == hipSuccess && best) e = launch_select_rows(out, n, best, evals, ids, s);
     return e;
 }
 
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
-                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx, int64_t nidx) {
+                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx, int64_t nidx,
+                             int32_t* best_ids) {
     const int64_t n = idx ? nidx : p.n;
     if (n <= 0) return hipSuccess;
     const int32_t parts = idx ? 1 : p.parts;
@@ -511,6 +524,7 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
     // the last workgroup of a single launch over few rows selects; else a launch of its own
     const bool fin = best && parts == 1 && n <= kFinInCount && (p.words[0] == 0 || p.words[1] == 0);
     if (fin) A.best = best;
+    if (fin) A.best_ids = best_ids;
     hipError_t e = parts > 1 ? launch_zero_costs(out, n, s) : hipSuccess;
     int64_t grid = n * parts;
     if (p.wg_per_cu > 0) grid = std::min<int64_t>(grid, (int64_t)p.wg_per_cu * cus);
@@ -521,8 +535,8 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
         A.lds_words = p.words[b];
         e = launch_eval(A, p.H, grid, s);
     }
-    if (e == hipSuccess && parts > 1) return launch_bytes_select(out, n, p.elem_bytes, best, s);
-    if (e == hipSuccess && best && !fin) e = launch_select_rows(out, n, best, s);
+    if (e == hipSuccess && parts > 1) return launch_bytes_select(out, n, p.elem_bytes, best, s, evals, best_ids);
+    if (e == hipSuccess && best && !fin) e = launch_select_rows(out, n, best, evals, best_ids, s);
     return e;
 }
 

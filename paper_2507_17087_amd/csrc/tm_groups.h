@@ -47,11 +47,11 @@ __device__ __forceinline__ uint32_t div_wide(double n, double r) { return (uint3
 // ------------------------------------------------------------------ owner table
 
 // Owner keys (node << gbits) | gpu of the final-space coordinates [v0, v1) (v1 <= 2^15),
-// AND keep, written to out: each undoes the ops on the linear index, last op first, down
-// to Machine(GPU); uniform branches skip the divisions that an op's place makes trivial
+// AND keep, written to out (IDS: processor ids, node * gpus + gpu, instead): each undoes
+// the ops on the linear index, last op first, down to Machine(GPU); uniform branches skip the divisions that an op's place makes trivial
 // (nothing after or before its range, adjacent dims, factors of 1).  A thread takes KPT
 // coordinates per pass, so an op's constants are read once per pass.
-template <int KPT>
+template <int KPT, bool IDS>
 __device__ __forceinline__ void owner_table_pass(const DevEval& c, int32_t* __restrict__ out, int32_t v0, int32_t v1,
                                                  int32_t keep, int tid, int nt) {
     const uint32_t g = (uint32_t)c.gpus;
@@ -181,20 +181,21 @@ __device__ __forceinline__ void owner_table_pass(const DevEval& c, int32_t* __re
         for (int i = 0; i < KPT; ++i) {
             const int32_t v = base + i * nt;
             if (v < v1) {
-                const uint32_t node = div_small(L[i], rg);
-                out[v] = (int32_t)((node << gb) | (L[i] - __umul24(node, g))) & keep;
+                const uint32_t node = IDS ? 0 : div_small(L[i], rg);
+                out[v] = IDS ? (int32_t)L[i] : (int32_t)((node << gb) | (L[i] - __umul24(node, g))) & keep;
             }
         }
     }
 }
 
 // The whole range, keys per thread by its length (slots past the end repeat work).
+template <bool IDS = false>
 __device__ __forceinline__ void owner_table(const DevEval& c, int32_t* __restrict__ out, int32_t v0, int32_t v1,
                                             int32_t keep, int tid, int nt) {
     const int32_t len = v1 - v0;
-    if (len <= nt) owner_table_pass<1>(c, out, v0, v1, keep, tid, nt);
-    else if (len <= 2 * nt) owner_table_pass<2>(c, out, v0, v1, keep, tid, nt);
-    else owner_table_pass<4>(c, out, v0, v1, keep, tid, nt);
+    if (len <= nt) owner_table_pass<1, IDS>(c, out, v0, v1, keep, tid, nt);
+    else if (len <= 2 * nt) owner_table_pass<2, IDS>(c, out, v0, v1, keep, tid, nt);
+    else owner_table_pass<4, IDS>(c, out, v0, v1, keep, tid, nt);
 }
 
 // ------------------------------------------------------------------ coordinates

@@ -63,7 +63,9 @@ struct alignas(16) DevEval {
     int32_t bij;                  // every op is a bijection: distinct coordinates, distinct owners
     int32_t flags;                // kEval*
     int32_t words, parts, dim_d;  // LDS words the evaluation needs, its workgroups; the dim with the most groups
-    int32_t pad[5];
+    int32_t pad;
+    int64_t points;               // of the launch domain
+    int32_t pad2[2];
     DevDim dim[TM_MAX_LRANK];
     DevProj pj[TM_MAX_MRANK];
     DevOp inv[TM_MAX_OPS];
@@ -162,18 +164,6 @@ __host__ __device__ inline int64_t class_cap(const DevCand& c, int d, int h) {
     return r < l ? r : l;
 }
 
-// Map kernel: when the staged tables are small (many workgroups fit a CU), one-wave
-// workgroups taking blocks of about 1,024 points (4 KB of int32 map); else four-wave
-// workgroups taking about 4,096 points (16 KB).
-constexpr int32_t kMapMaxRowsPerBlock = 64;
-constexpr int32_t kMapNarrowWords = 2048;
-__host__ __device__ inline bool map_narrow(int32_t lds_words) { return lds_words <= kMapNarrowWords; }
-__host__ __device__ inline int32_t map_rows_per_block(int32_t L, bool narrow) {
-    const int32_t pts = narrow ? 1024 : 4096;
-    const int32_t r = (pts + (L > 0 ? L : 1) - 1) / (L > 0 ? L : 1);
-    return r < 1 ? 1 : (r > kMapMaxRowsPerBlock ? kMapMaxRowsPerBlock : r);
-}
-
 // Counting work items of a candidate: its class-tuple bound (product of the
 // capacities) split into items of about `per_item` tuples (at least one item).
 __host__ __device__ inline int32_t count_items(const DevCand& c, int64_t per_item) {
@@ -205,19 +195,12 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
 hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena,
                                int32_t mode_halo, hipStream_t s, tm_stencil_cost* out = nullptr,
                                unsigned long long* counter = nullptr);
-// Tables (owners and coordinates, no classes) of one candidate, *d_index or index, to
-// the start of `arena`.
-hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t n, const int64_t* d_index,
-                            int64_t index, int32_t* arena, hipStream_t s);
 // Batches up to this many candidates select inside the evaluation launch.
 constexpr int64_t kFinInCount = 2048;
 // Per segment the best cost row: of rows [seg[s], seg[s+1]), or with idx (row -> candidate,
 // negative: no row) of the k rows from s k; best_cost may be null.
 hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg, const int64_t* idx,
                                   int64_t k, int64_t* best, tm_stencil_cost* best_cost, hipStream_t s);
-// arena: the mapped candidate's tables.
-hipError_t launch_map(const DevCand* cands, int64_t n, const int32_t* arena, const int64_t* d_index,
-                      int64_t index, int32_t* out, int grid, int lds_words, hipStream_t s);
 hipError_t launch_chain_table(const DevCand* cand, const int32_t* arena, int32_t* out, hipStream_t s);
 // Batches of at least this many candidates run the per-candidate table and
 // statistics kernels with one-wave workgroups (more candidates in flight per CU).

@@ -108,23 +108,18 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
                                                       const DevCand* __restrict__ cands,
                                                       int32_t* __restrict__ arena, int use_halo,
                                                       tm_stencil_cost* __restrict__ out,
-                                                      unsigned long long* __restrict__ counter, int split,
-                                                      int64_t one, const int64_t* __restrict__ d_one) {
+                                                      unsigned long long* __restrict__ counter, int split) {
     __shared__ DevCand sc;
     __shared__ int32_t s_wt[4];
     __shared__ int32_t s_ct[kBuildStage];
     __shared__ float s_rt[kRecipSlots];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
     const int upc = split ? TM_MAX_LRANK : 1;  // units per candidate
-    // a single candidate (one or *d_one; its tables start the arena), or the whole batch
-    const bool single = one >= 0 || d_one;
-    if (d_one) one = uniform64(*d_one);
-    if (single && (one < 0 || one >= hdr->n)) return;  // no candidate selected
-    const int64_t units = (single ? 1 : hdr->n) * upc;
+    const int64_t units = hdr->n * upc;
     if (counter && blockIdx.x == 0 && tid < 2) counter[tid] = 0ull;
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const int64_t ui = u / upc, ci = single ? one : ui;
-        const int dlo = (int)(u - ui * upc);
+        const int64_t ci = u / upc;
+        const int dlo = (int)(u - ci * upc);
         const int K = (int)__builtin_amdgcn_readfirstlane((uint32_t)cands[ci].lrank);
         if (dlo >= K) continue;  // uniform
         const int dhi = split ? dlo + 1 : K;
@@ -133,7 +128,7 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
         lds_sync(nw);
         op_reciprocals(sc, s_rt, tid, blockDim.x);
         lds_sync(nw);
-        int32_t* base = arena + (single ? 0 : sc.arena_off);
+        int32_t* base = arena + sc.arena_off;
         if (dlo == 0) {
             if (out && tid < 4) reinterpret_cast<int64_t*>(&out[ci])[tid] = 0;
             if (use_halo)  // this candidate's entries of the item table (work item -> candidate)
@@ -230,16 +225,7 @@ hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64
     const int64_t grid = units < 131072 ? (units > 0 ? units : 1) : 131072;
     const int bs = n >= kSmallBlockBatch ? 64 : 256;
     hipLaunchKernelGGL(k_build_tables, dim3((unsigned)grid), dim3(bs), 0, s, hdr, cands, arena, use_halo, out,
-                       counter, split, (int64_t)-1, (const int64_t*)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_build_one(const DevHeader* hdr, const DevCand* cands, int64_t n, const int64_t* d_index,
-                            int64_t index, int32_t* arena, hipStream_t s) {
-    (void)n;
-    hipLaunchKernelGGL(k_build_tables, dim3(TM_MAX_LRANK), dim3(256), 0, s, hdr, cands, arena, 0,
-                       (tm_stencil_cost*)nullptr, (unsigned long long*)nullptr, 1, d_index ? (int64_t)-1 : index,
-                       d_index);
+                       counter, split);
     return hipGetLastError();
 }
 
@@ -294,106 +280,6 @@ hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* s
                                   int64_t k, int64_t* best, tm_stencil_cost* best_cost, hipStream_t s) {
     if (nseg <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_select_segments, dim3((unsigned)nseg), dim3(256), 0, s, costs, seg, idx, k, best, best_cost);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ processor map
-//
-// Each workgroup writes contiguous blocks of map_rows_per_block(L) rows (about 2,048
-// points, 8 KB), its 256 threads stepping through the block's 16-byte pieces in
-// order (one 16-byte store per thread and step when rows start 16-byte aligned, else
-// one point).  The owner table and (when it fits) the last dim's coordinate table
-// sit in LDS, and so do the block's row bases (sums of the outer dims' entries).
-// Measured on a 512^3 map: 8 KB blocks with plain stores
-// 6.80 TB/s, 16 KB 6.05, 4 KB 5.71, non-temporal stores 5.75 at 16 KB; a plain
-// device fill of the same bytes 6.58.
-
-template <int NT>
-__global__ __launch_bounds__(NT) void k_map(const DevCand* __restrict__ cands, int64_t n,
-                                            const int32_t* __restrict__ arena,
-                                            const int64_t* __restrict__ d_index, int64_t index,
-                                            int32_t* __restrict__ out) {
-    extern __shared__ __attribute__((aligned(16))) int32_t lds[];  // 16-byte aligned: ds_read_b128 of staged tables
-    // a short prologue (many small workgroups): the descriptor's fields are read in
-    // place; the tables and the first block's row bases are ready behind one barrier
-    __shared__ int32_t s_base[kMapMaxRowsPerBlock];
-    static_assert(NT >= kMapMaxRowsPerBlock, "a thread per row base");
-    const int64_t ci = d_index ? uniform64(*d_index) : index;
-    if (ci < 0 || ci >= n) return;  // no candidate selected (empty batch)
-    const DevCand* __restrict__ c = &cands[ci];
-    const int32_t words = uniform32(c->lds_words);
-    const int32_t* G = arena;  // this candidate's tables
-    {
-        const i32x4* s4 = reinterpret_cast<const i32x4*>(G);
-        i32x4* d4 = reinterpret_cast<i32x4*>(lds);
-        for (int32_t i = threadIdx.x; i < (words + 3) >> 2; i += NT) d4[i] = s4[i];
-    }
-    const int K = uniform32(c->lrank);
-    const int32_t L = uniform32(c->L);
-    const int64_t rows = uniform64(c->rows);
-    const int32_t gb = uniform32(c->gbits), g = uniform32(c->gpus), gmask = (1 << gb) - 1;
-    const int32_t* CL = uniform32(c->cl_lds) ? lds + uniform32(c->coord_off[K - 1]) : G + uniform32(c->coord_off[K - 1]);
-    int32_t co[TM_MAX_LRANK];
-    uint32_t ex[TM_MAX_LRANK];
-#pragma unroll
-    for (int d = 0; d < TM_MAX_LRANK; ++d) {
-        co[d] = d < K - 1 ? uniform32(c->coord_off[d]) : 0;
-        ex[d] = d < K - 1 ? (uint32_t)uniform64(c->extent[d]) : 1u;
-    }
-    const int32_t* T = lds;
-    const int tid = threadIdx.x;
-    const int32_t rpb = map_rows_per_block(L, NT == 64);
-    const bool vec = (L & 3) == 0 && ((reinterpret_cast<uintptr_t>(out) & 15) == 0);
-    const int64_t stride = (int64_t)gridDim.x * rpb;
-    for (int64_t r0 = (int64_t)blockIdx.x * rpb; r0 < rows; r0 += stride) {
-        const int32_t nr = (int32_t)(rows - r0 < rpb ? rows - r0 : rpb);
-        // the block's row bases: the sums of the outer dims' entries of its rows
-        if (tid < nr) {
-            uint32_t rr = (uint32_t)(r0 + tid);
-            int32_t bl = 0;
-            for (int d = K - 2; d >= 0; --d) {
-                bl += G[co[d] + (int32_t)(rr % ex[d])] & kValMask;
-                rr /= ex[d];
-            }
-            s_base[tid] = bl;
-        }
-        __syncthreads();  // tables (first block) and bases ready
-        int32_t* blk = out + r0 * (int64_t)L;
-        if (vec) {
-            const uint32_t pr = (uint32_t)L >> 2;  // 16-byte pieces per row
-            const uint32_t np = (uint32_t)nr * pr;
-            for (uint32_t j = tid; j < np; j += NT) {
-                const uint32_t rl = j / pr;
-                const int32_t x = (int32_t)(j - rl * pr) * 4;
-                const int32_t base = s_base[rl];
-                i32x4 key;
-                key.x = T[base + (CL[x] & kValMask)];
-                key.y = T[base + (CL[x + 1] & kValMask)];
-                key.z = T[base + (CL[x + 2] & kValMask)];
-                key.w = T[base + (CL[x + 3] & kValMask)];
-                reinterpret_cast<i32x4*>(blk)[j] = (key >> gb) * g + (key & gmask);
-            }
-        } else {
-            const uint32_t np = (uint32_t)nr * (uint32_t)L;
-            for (uint32_t j = tid; j < np; j += NT) {
-                const uint32_t rl = j / (uint32_t)L;
-                const int32_t x = (int32_t)(j - rl * (uint32_t)L);
-                const int32_t key = T[s_base[rl] + (CL[x] & kValMask)];
-                blk[j] = (key >> gb) * g + (key & gmask);
-            }
-        }
-        if (r0 + stride < rows) __syncthreads();  // the next block rewrites the bases
-    }
-}
-
-hipError_t launch_map(const DevCand* cands, int64_t n, const int32_t* arena, const int64_t* d_index,
-                      int64_t index, int32_t* out, int grid, int lds_words, hipStream_t s) {
-    if (map_narrow(lds_words))
-        hipLaunchKernelGGL(k_map<64>, dim3(grid), dim3(64), (size_t)lds_words * 4, s, cands, n, arena, d_index,
-                           index, out);
-    else
-        hipLaunchKernelGGL(k_map<256>, dim3(grid), dim3(256), (size_t)lds_words * 4, s, cands, n, arena, d_index,
-                           index, out);
     return hipGetLastError();
 }
 

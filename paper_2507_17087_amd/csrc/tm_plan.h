@@ -52,7 +52,7 @@ struct tm_plan {
     int64_t cap_arena = 0;            // words of d_arena
     tmk::DevCand* d_cands = nullptr;
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
-    int32_t* d_arena = nullptr;       // tables of the candidate being mapped
+    int32_t* d_arena = nullptr;       // owner table (processor ids) of the candidate being mapped
     tmk::DevHeader* d_hdr = nullptr;
     unsigned long long* d_counter = nullptr;
     tmk::DevCand* h_cands = nullptr;  // pinned staging
