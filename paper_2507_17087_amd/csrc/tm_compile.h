@@ -148,8 +148,10 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
     e->rgpus = 1.0f / (float)d.gpus;
     e->bij = is_bijective(d);
     e->flags = is_simple(d) ? kEvalSimple : 0;
-    e->pad = e->pad2[0] = e->pad2[1] = 0;
+    e->procs = d.nodes * d.gpus;
     e->points = d.npoints;
+    e->first_proc = 0;
+    bool distinct = e->bij;
     for (int t = 0; t < d.nops; ++t) fill_inverse(d, t, &e->inv[t]);
     int next = 0;
     for (int k = 0; k < d.lrank; ++k) {
@@ -166,8 +168,10 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
                 p.stride = d.fstride[j];
                 p.rs = 1.0 / (double)p.s;
             }
+        distinct = distinct && !(g.ident && g.nblk > 1);
         e->flags |= (g.ncyc ? kEvalCyclic : 0) | (g.nblk > 1 || g.ncyc > 1 ? kEvalExtra : 0);
     }
+    e->flags |= distinct ? kEvalDistinct : 0;
     const EvalNeed n = eval_need(e->dim, d.lrank, d.vol, e->flags & kEvalCyclic, e->bij, shape);
     e->words = n.words;
     e->parts = n.parts;

@@ -12,6 +12,7 @@
 #include "tm_map.h"
 #include "tm_plan.h"
 #include "tm_ranker.h"
+#include "tm_volume.h"
 
 namespace tmk {
 
@@ -387,6 +388,65 @@ extern "C" int tm_eval_stencil_node_batch(const tm_candidate* c, int64_t n, cons
     return eval_stencil(c, n, st, d_out, (hipStream_t)stream, true);
 }
 
+// One upload of `bytes` of descriptors that fill writes to the staging buffer; false from
+// it: nothing is uploaded, *taken stays false.  launch runs with their device copy.
+template <class Fill, class Launch>
+static int with_descriptors(size_t bytes, hipStream_t s, bool* taken, const char* what, Fill fill, Launch launch) {
+    void* stg = nullptr;
+    int rc = staging_acquire(bytes, &stg);
+    if (rc != TM_OK || !fill(stg)) return rc;
+    *taken = true;
+    void* d = nullptr;
+    TM_HIP(hipMallocAsync(&d, bytes, s));
+    hipError_t e = hipMemcpyAsync(d, stg, bytes, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) rc = staging_release(s);
+    if (rc == TM_OK && e == hipSuccess) e = launch(d);
+    if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "%s launch: %s", what, hipGetErrorString(e));
+    (void)hipFreeAsync(d, s);
+    return rc;
+}
+
+// Pairs (i, n + i) over joint groups, when the tables of all of them fit a workgroup's LDS.
+static int redistribution_groups(const Compiled& cp, int64_t n, int64_t elem_bytes, tm_redist_cost* d_out,
+                                 hipStream_t s, bool* taken) {
+    int32_t words = 0, parts = 1;
+    auto fill = [&](void* stg) {
+        DevPair* p = static_cast<DevPair*>(stg);
+        for (int64_t i = 0; i < n; ++i, ++p) {
+            int32_t w = 0;
+            if (!fill_pair(cp.cands[(size_t)i], cp.cands[(size_t)(n + i)], p, &w)) return false;
+            words = std::max(words, w);
+            parts = std::max(parts, p->parts);
+        }
+        return n * parts <= INT32_MAX;
+    };
+    return with_descriptors((size_t)n * sizeof(DevPair), s, taken, "redistribution", fill, [&](void* d) {
+        return launch_pairs(static_cast<const DevPair*>(d), n, parts, words, elem_bytes, d_out, s);
+    });
+}
+
+// Matmul tiles over coordinate groups, when all candidates are for that kernel.
+static int matmul_groups(const Compiled& cp, const int64_t* proc_off, int64_t tile_bytes, int64_t* d_per_proc,
+                         tm_matmul_cost* d_out, hipStream_t s, bool* taken) {
+    const int64_t n = (int64_t)cp.cands.size();
+    int32_t words = 0;
+    auto fill = [&](void* stg) {
+        DevEval* e = static_cast<DevEval*>(stg);
+        for (int64_t i = 0; i < n; ++i, ++e) {
+            if (cp.cands[(size_t)i].vol > kMaxLdsWords) return false;
+            fill_eval(cp.cands[(size_t)i], EvalShape{1, 0, 0, 1}, e);
+            e->first_proc = proc_off[i];
+            const int32_t w = matmul_words(*e);
+            if (w == 0) return false;
+            words = std::max(words, w);
+        }
+        return n <= INT32_MAX;
+    };
+    return with_descriptors((size_t)n * sizeof(DevEval), s, taken, "matmul", fill, [&](void* d) {
+        return launch_matmul_groups(static_cast<const DevEval*>(d), n, words, tile_bytes, d_out, d_per_proc, s);
+    });
+}
+
 extern "C" int tm_eval_redistribution_batch(const tm_candidate* src, const tm_candidate* dst, int64_t n,
                                             int64_t elem_bytes, tm_redist_cost* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
@@ -409,6 +469,9 @@ extern "C" int tm_eval_redistribution_batch(const tm_candidate* src, const tm_ca
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
+    bool taken = false;
+    rc = redistribution_groups(cp, n, elem_bytes, d_out, s, &taken);
+    if (rc != TM_OK || taken) return rc;
     // each pair's joint-class block goes into its a-side table block: the record, then
     // per dim the a entries, the b entries and the run starts of its classes; a dim's
     // joint classes start where either mapping's contribution changes, so there are at
@@ -490,6 +553,9 @@ extern "C" int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_m
     }
     proc_off[(size_t)n] = procs;
     block_first[(size_t)n] = blocks;
+    bool taken = false;
+    rc = matmul_groups(cp, proc_off.data(), mm->tile_bytes, d_per_proc, d_out, s, &taken);
+    if (rc != TM_OK || taken) return rc;
     DeviceBatch db;
     rc = upload_batch(cp, db, s);
     int64_t *d_off = nullptr, *d_bf = nullptr;

@@ -63,9 +63,9 @@ struct alignas(16) DevEval {
     int32_t bij;                  // every op is a bijection: distinct coordinates, distinct owners
     int32_t flags;                // kEval*
     int32_t words, parts, dim_d;  // LDS words the evaluation needs, its workgroups; the dim with the most groups
-    int32_t pad;
+    int32_t procs;                // nodes * gpus
     int64_t points;               // of the launch domain
-    int32_t pad2[2];
+    int64_t first_proc;           // matmul batches: processors of the candidates before this one
     DevDim dim[TM_MAX_LRANK];
     DevProj pj[TM_MAX_MRANK];
     DevOp inv[TM_MAX_OPS];
@@ -73,7 +73,7 @@ struct alignas(16) DevEval {
 // kEvalCyclic: some launch dim has a cyclic projection; kEvalExtra: some has several
 // block or several cyclic ones; kEvalSimple: every launch dim is projected by blocks onto
 // exactly one final dim
-constexpr int32_t kEvalCyclic = 1, kEvalExtra = 2, kEvalSimple = 4;
+constexpr int32_t kEvalCyclic = 1, kEvalExtra = 2, kEvalSimple = 4, kEvalDistinct = 8;
 static_assert(sizeof(DevEval) == 896, "staged by the first 56 lanes of a wave");
 
 // Compiled candidate as the kernels read it.  The host fills in the shapes of the
