@@ -306,7 +306,7 @@ def tm_eval_matmul_batch(c, tile_bytes, per_proc=True):
     out = torch.empty((n, 7), dtype=torch.int64, device="cuda")
     pp = None
     if per_proc:
-        P = int(sum(int(x["nodes"]) * int(x["gpus"]) for x in a))
+        P = int(np.dot(a["nodes"].astype(np.int64), a["gpus"].astype(np.int64)))
         pp = torch.empty((max(P, 1), 3), dtype=torch.int64, device="cuda")
     _check(lib().tm_eval_matmul_batch(a.ctypes.data, n, mm.ctypes.data,
                                       _dev_ptr(pp, torch.int64) if pp is not None else None,

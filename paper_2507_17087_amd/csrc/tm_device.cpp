@@ -171,45 +171,65 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
 // The evaluation's launches.  One launch takes all candidates when the largest need
 // (eval_need) is small, else those above kEvalSmall* go in a launch of their own, so that
 // they do not cost the others their occupancy; a candidate gets as many more records than
-// it needs as fit its launch's words.
-void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
-    EvalPlan& e = cp.eval;
-    e = EvalPlan{};
-    e.n = (int64_t)cp.cands.size();
-    e.elem_bytes = cp.hdr.elem_bytes;
-    for (int k = 0; k < TM_MAX_LRANK; ++k) e.halo[k] = cp.hdr.halo[k];
-    e.H = cp.H;
-    e.node_level = node_level ? 1 : 0;
-    e.per_item = tuples_per_item;
-    e.fill = std::max<int64_t>(1, kEvalFill / std::max<int64_t>(e.n, 1));
-    const bool wave = e.n >= kEvalWaveBatch;
-    const int32_t small = wave ? kEvalSmallWave : kEvalSmallBlock, most = wave ? kEvalMostWave : kEvalMostBlock;
-    const EvalShape shape{e.H, e.node_level, e.per_item, e.fill};
+// it needs as fit its launch's words.  Candidates are added one by one.
+struct EvalLayout {
+    EvalPlan& e;
+    int32_t small, most;
     int32_t words[2] = {0, 0}, whole[2] = {0, 0}, largest = 0;  // of the needs up to small, above it
-    for (auto& c : cp.cands) {
-        DevDim dim[TM_MAX_LRANK];
-        bool cyclic = false;
-        for (int k = 0; k < c.lrank; ++k) {
-            count_groups(c, k, &dim[k]);
-            cyclic = cyclic || dim[k].ncyc > 0;
-        }
-        const EvalNeed n = eval_need(dim, c.lrank, c.vol, cyclic, is_bijective(c), shape);
+
+    EvalLayout(EvalPlan& plan, int64_t n, const tm_stencil& st, int H, int64_t tuples_per_item, bool node_level) : e(plan) {
+        e = EvalPlan{};
+        e.n = n;
+        e.elem_bytes = st.elem_bytes;
+        for (int k = 0; k < TM_MAX_LRANK; ++k) e.halo[k] = k < st.lrank ? st.halo[k] : 0;
+        e.H = H;
+        e.node_level = node_level ? 1 : 0;
+        e.per_item = tuples_per_item;
+        e.fill = std::max<int64_t>(1, kEvalFill / std::max<int64_t>(n, 1));
+        const bool wave = n >= kEvalWaveBatch;
+        small = wave ? kEvalSmallWave : kEvalSmallBlock;
+        most = wave ? kEvalMostWave : kEvalMostBlock;
+    }
+    EvalShape shape() const { return EvalShape{e.H, e.node_level, e.per_item, e.fill}; }
+    void add(const EvalNeed& n, bool simple) {
         e.items += n.parts;
         e.parts = std::max(e.parts, n.parts);
         largest = std::max(largest, n.words);
-        e.all_simple = e.all_simple && is_simple(c);
+        e.all_simple = e.all_simple && simple;
         const int b = n.words > small ? 1 : 0;
         words[b] = std::max(words[b], n.words);
         whole[b] = std::max(whole[b], n.whole);
     }
-    if (largest <= most) {
-        e.split = largest;
-        e.words[0] = std::max(largest, std::min(std::max(whole[0], whole[1]), small));
-    } else {
-        e.split = small;
-        e.words[0] = std::max(words[0], std::min(whole[0], small));
-        e.words[1] = words[1];
+    void finish() {
+        if (largest <= most) {
+            e.split = largest;
+            e.words[0] = std::max(largest, std::min(std::max(whole[0], whole[1]), small));
+        } else {
+            e.split = small;
+            e.words[0] = std::max(words[0], std::min(whole[0], small));
+            e.words[1] = words[1];
+        }
     }
+};
+
+void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
+    tm_stencil st{};
+    st.lrank = TM_MAX_LRANK;
+    st.elem_bytes = cp.hdr.elem_bytes;
+    for (int k = 0; k < TM_MAX_LRANK; ++k) st.halo[k] = cp.hdr.halo[k];
+    EvalLayout lay(cp.eval, (int64_t)cp.cands.size(), st, cp.H, tuples_per_item, node_level);
+    const EvalShape shape = lay.shape();
+    for (auto& c : cp.cands) {
+        DevDim dim[TM_MAX_LRANK];
+        bool cyclic = false;
+        const uint64_t bits = projection_bits(c);
+        for (int k = 0; k < c.lrank; ++k) {
+            count_groups(c, k, bits, &dim[k]);
+            cyclic = cyclic || dim[k].ncyc > 0;
+        }
+        lay.add(eval_need(dim, c.lrank, c.vol, cyclic, is_bijective(c), shape), is_simple(c));
+    }
+    lay.finish();
 }
 
 // ------------------------------------------------------------------ staging
@@ -255,6 +275,112 @@ static int staging_release(hipStream_t s) {
     TM_HIP(hipEventRecord(g_stage.ev, s));
     g_stage.pending = true;
     return TM_OK;
+}
+
+// Per-thread slots of pinned memory that kernels read descriptors from in place, and a
+// piece of device scratch each: a call takes the next one once the work that used it last
+// is done.  Bounded (kSlots x kSlotBytes a thread) and freed with the thread.  A small
+// call's allocation, copy and free cost more than its kernel: 300 descriptors (269 KB) read
+// in place 11.8 us a call (launch, event, GPU time of the reads), copied into a
+// stream-ordered allocation 61.5 us.
+constexpr int kSlots = 4;
+constexpr size_t kSlotBytes = size_t(1) << 20;
+constexpr size_t kSlotScratch = sizeof(DevEval) + (size_t)kMaxLdsWords * 4;  // a descriptor, an owner table
+
+struct SlotRing {
+    int device = -1;
+    char* host = nullptr;
+    char* scratch = nullptr;
+    hipEvent_t ev[kSlots] = {};
+    bool pending[kSlots] = {};
+    int next = 0;
+
+    void drop() {
+        for (int i = 0; i < kSlots; ++i) {
+            if (pending[i]) (void)hipEventSynchronize(ev[i]);
+            if (ev[i]) (void)hipEventDestroy(ev[i]);
+            ev[i] = nullptr;
+            pending[i] = false;
+        }
+        if (host) (void)hipHostFree(host);
+        if (scratch) (void)hipFree(scratch);
+        host = scratch = nullptr;
+        device = -1;
+    }
+    ~SlotRing() { drop(); }
+};
+static thread_local SlotRing g_ring;
+
+struct Slot {
+    int index;
+    char* host;
+    char* scratch;
+};
+
+static int slot_acquire(bool scratch, Slot* out) {
+    int dev = 0;
+    TM_HIP(hipGetDevice(&dev));
+    SlotRing& r = g_ring;
+    if (r.device != dev) r.drop();
+    r.device = dev;
+    if (!r.host && hipHostMalloc((void**)&r.host, kSlots * kSlotBytes, hipHostMallocDefault) != hipSuccess) {
+        r.host = nullptr;
+        return set_error(TM_ENOMEM, "pinned staging of %zu bytes", kSlots * kSlotBytes);
+    }
+    if (scratch && !r.scratch && hipMalloc((void**)&r.scratch, kSlots * kSlotScratch) != hipSuccess) {
+        r.scratch = nullptr;
+        return set_error(TM_ENOMEM, "scratch of %zu bytes", kSlots * kSlotScratch);
+    }
+    const int i = r.next;
+    if (!r.ev[i]) TM_HIP(hipEventCreateWithFlags(&r.ev[i], hipEventDisableTiming));
+    if (r.pending[i]) TM_HIP(hipEventSynchronize(r.ev[i]));
+    r.pending[i] = false;
+    *out = Slot{i, r.host + (size_t)i * kSlotBytes, r.scratch ? r.scratch + (size_t)i * kSlotScratch : nullptr};
+    return TM_OK;
+}
+
+// After the last launch that uses the slot.
+static int slot_release(const Slot& slot, hipStream_t s) {
+    SlotRing& r = g_ring;
+    if (hipEventRecord(r.ev[slot.index], s) == hipSuccess) r.pending[slot.index] = true;
+    else TM_HIP(hipStreamSynchronize(s));
+    r.next = (slot.index + 1) % kSlots;
+    return TM_OK;
+}
+
+// A capture's replays would find other descriptors in a slot.
+static bool slots_fit(size_t bytes, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return bytes <= kSlotBytes && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+}
+
+// Descriptors that fill writes, for launch to read: in a slot, or larger ones in a device
+// copy.  fill's result: TM_OK, an error, or kGeneral (nothing is launched).
+constexpr int kGeneral = 1;
+template <class Fill, class Launch>
+static int with_descriptors(size_t bytes, hipStream_t s, const char* what, Fill fill, Launch launch) {
+    hipError_t e = hipSuccess;
+    int rc;
+    if (slots_fit(bytes, s)) {
+        Slot slot;
+        rc = slot_acquire(false, &slot);
+        if (rc == TM_OK) rc = fill((void*)slot.host);
+        if (rc != TM_OK) return rc;
+        e = launch((const void*)slot.host);
+        rc = slot_release(slot, s);
+    } else {
+        void *stg = nullptr, *d = nullptr;
+        rc = staging_acquire(bytes, &stg);
+        if (rc == TM_OK) rc = fill(stg);
+        if (rc != TM_OK) return rc;
+        TM_HIP(hipMallocAsync(&d, bytes, s));
+        e = hipMemcpyAsync(d, stg, bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) rc = staging_release(s);
+        if (rc == TM_OK && e == hipSuccess) e = launch((const void*)d);
+        (void)hipFreeAsync(d, s);
+    }
+    if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "%s launch: %s", what, hipGetErrorString(e));
+    return rc;
 }
 
 // Device copies of a compiled batch in stream-ordered allocations.
@@ -326,56 +452,91 @@ extern "C" int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, v
     Compiled cp;
     int rc = compile_batch(c, 1, nullptr, 0, true, cp);
     if (rc != TM_OK) return rc;
-    if (len != cp.cands[0].npoints)
-        return set_error(TM_ECAPACITY, "map length %lld but the domain has %lld points", (long long)len,
-                         (long long)cp.cands[0].npoints);
-    if (!d_map) return set_error(TM_EINVAL, "null output");
-    // one allocation: the descriptor, then the owner table as processor ids
     const DevCand& c0 = cp.cands[0];
-    char* mem = nullptr;
-    TM_HIP(hipMallocAsync((void**)&mem, sizeof(DevEval) + (size_t)map_ids_words(c0.vol) * 4, s));
-    DevEval* d_eval = reinterpret_cast<DevEval*>(mem);
-    int32_t* ids = reinterpret_cast<int32_t*>(mem + sizeof(DevEval));
-    void* stg = nullptr;
-    rc = staging_acquire(sizeof(DevEval), &stg);
-    if (rc == TM_OK) {
-        fill_eval(c0, EvalShape{1, 0, 0, 1}, static_cast<DevEval*>(stg));
-        hipError_t e = hipMemcpyAsync(d_eval, stg, sizeof(DevEval), hipMemcpyHostToDevice, s);
+    if (len != c0.npoints)
+        return set_error(TM_ECAPACITY, "map length %lld but the domain has %lld points", (long long)len,
+                         (long long)c0.npoints);
+    if (!d_map) return set_error(TM_EINVAL, "null output");
+    const EvalShape shape{1, 0, 0, 1};
+    const MapShape m = map_shape(c0.vol, c0.npoints, c0.L);
+    hipError_t e = hipSuccess;
+    if (slots_fit(sizeof(DevEval), s)) {
+        Slot slot;
+        rc = slot_acquire(true, &slot);
+        if (rc != TM_OK) return rc;
+        DevEval *h = reinterpret_cast<DevEval*>(slot.host), *d = reinterpret_cast<DevEval*>(slot.scratch);
+        int32_t* ids = reinterpret_cast<int32_t*>(d + 1);
+        fill_eval(c0, shape, h);
+        // every workgroup of the map reads the descriptor: it goes to device memory on the way
+        e = launch_map_ids(h, 1, nullptr, 0, c0.vol, ids, s, d);
+        if (e == hipSuccess) e = launch_map(m, d, 1, nullptr, 0, ids, d_map, s);
+        rc = slot_release(slot, s);
+    } else {
+        void* stg = nullptr;
+        DevEval* d = nullptr;
+        rc = staging_acquire(sizeof(DevEval), &stg);
+        if (rc != TM_OK) return rc;
+        fill_eval(c0, shape, static_cast<DevEval*>(stg));
+        TM_HIP(hipMallocAsync((void**)&d, sizeof(DevEval) + (size_t)map_ids_words(c0.vol) * 4, s));
+        int32_t* ids = reinterpret_cast<int32_t*>(d + 1);
+        e = hipMemcpyAsync(d, stg, sizeof(DevEval), hipMemcpyHostToDevice, s);
         if (e == hipSuccess) rc = staging_release(s);
-        if (rc == TM_OK && e == hipSuccess) e = launch_map_ids(d_eval, 1, nullptr, 0, c0.vol, ids, s);
-        if (rc == TM_OK && e == hipSuccess)
-            e = launch_map(map_shape(c0.vol, c0.npoints, c0.L), d_eval, 1, nullptr, 0, ids, d_map, s);
-        if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
+        if (rc == TM_OK && e == hipSuccess) e = launch_map_ids(d, 1, nullptr, 0, c0.vol, ids, s);
+        if (rc == TM_OK && e == hipSuccess) e = launch_map(m, d, 1, nullptr, 0, ids, d_map, s);
+        (void)hipFreeAsync(d, s);
     }
-    (void)hipFreeAsync(mem, s);
+    if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
     return rc;
+}
+
+// The halo slots of a stencil the kernels take (0: none; compile_batch tells why).
+static int stencil_slots(const tm_stencil& st) {
+    if (st.lrank < 1 || st.lrank > TM_MAX_LRANK || st.elem_bytes < 0) return 0;
+    int h = 1;
+    for (int d = 0; d < st.lrank; ++d) {
+        if (st.halo[d] < 0) return 0;
+        h = std::max(h, (int)st.halo[d]);
+    }
+    return h <= kMaxHalo ? h : 0;
 }
 
 static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, tm_stencil_cost* d_out,
                         hipStream_t s, bool node_level) {
     if (!st) return set_error(TM_EINVAL, "null stencil");
+    EvalPlan plan;
+    auto launch = [&](const void* d) {
+        return launch_eval_batch(plan, static_cast<const DevEval*>(d), d_out, nullptr, nullptr, num_cus(), s);
+    };
+    const int H = stencil_slots(*st);
+    if (H > 0 && c && n > 0) {
+        // straight from the records to the evaluation's descriptors
+        const int rc = with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", [&](void* stg) {
+            DevEval* e = static_cast<DevEval*>(stg);
+            EvalLayout lay(plan, n, *st, H, 0, node_level);
+            const EvalShape shape = lay.shape();
+            for (int64_t i = 0; i < n; ++i, ++e) {
+                CandView v;
+                EvalNeed need;
+                if (c[i].lrank > st->lrank || !compile_eval(&c[i], shape, &v, e, &need)) return kGeneral;
+                lay.add(need, e->flags & kEvalSimple);
+            }
+            lay.finish();
+            return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
+        }, launch);
+        if (rc != kGeneral) return rc;
+    }
     Compiled cp;
     int rc = compile_batch(c, n, st, 0, true, cp);
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
     layout_eval(cp, 0, node_level);
-    const EvalShape shape{cp.eval.H, cp.eval.node_level, cp.eval.per_item, cp.eval.fill};
-    DevEval* d_evals = nullptr;
-    const size_t bytes = (size_t)n * sizeof(DevEval);
-    TM_HIP(hipMallocAsync((void**)&d_evals, bytes, s));
-    void* stg = nullptr;
-    rc = staging_acquire(bytes, &stg);
-    if (rc == TM_OK) {
+    plan = cp.eval;
+    return with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", [&](void* stg) {
+        const EvalShape shape{plan.H, plan.node_level, plan.per_item, plan.fill};
         for (int64_t i = 0; i < n; ++i) fill_eval(cp.cands[(size_t)i], shape, static_cast<DevEval*>(stg) + i);
-        hipError_t e = hipMemcpyAsync(d_evals, stg, bytes, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) rc = staging_release(s);
-        if (rc == TM_OK && e == hipSuccess)
-            e = launch_eval_batch(cp.eval, d_evals, d_out, nullptr, nullptr, num_cus(), s);
-        if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "stencil launch: %s", hipGetErrorString(e));
-    }
-    (void)hipFreeAsync(d_evals, s);
-    return rc;
+        return TM_OK;
+    }, launch);
 }
 
 extern "C" int tm_eval_stencil_batch(const tm_candidate* c, int64_t n, const tm_stencil* st,
@@ -388,61 +549,62 @@ extern "C" int tm_eval_stencil_node_batch(const tm_candidate* c, int64_t n, cons
     return eval_stencil(c, n, st, d_out, (hipStream_t)stream, true);
 }
 
-// One upload of `bytes` of descriptors that fill writes to the staging buffer; false from
-// it: nothing is uploaded, *taken stays false.  launch runs with their device copy.
-template <class Fill, class Launch>
-static int with_descriptors(size_t bytes, hipStream_t s, bool* taken, const char* what, Fill fill, Launch launch) {
-    void* stg = nullptr;
-    int rc = staging_acquire(bytes, &stg);
-    if (rc != TM_OK || !fill(stg)) return rc;
-    *taken = true;
-    void* d = nullptr;
-    TM_HIP(hipMallocAsync(&d, bytes, s));
-    hipError_t e = hipMemcpyAsync(d, stg, bytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) rc = staging_release(s);
-    if (rc == TM_OK && e == hipSuccess) e = launch(d);
-    if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "%s launch: %s", what, hipGetErrorString(e));
-    (void)hipFreeAsync(d, s);
-    return rc;
-}
-
-// Pairs (i, n + i) over joint groups, when the tables of all of them fit a workgroup's LDS.
-static int redistribution_groups(const Compiled& cp, int64_t n, int64_t elem_bytes, tm_redist_cost* d_out,
-                                 hipStream_t s, bool* taken) {
+// Pairs (src[i], dst[i]) over joint groups, when the tables of all of them fit a
+// workgroup's LDS (else kGeneral).
+static int redistribution_groups(const tm_candidate* src, const tm_candidate* dst, int64_t n, int64_t elem_bytes,
+                                 tm_redist_cost* d_out, hipStream_t s) {
     int32_t words = 0, parts = 1;
     auto fill = [&](void* stg) {
+        const EvalShape shape{1, 0, 0, 1};
         DevPair* p = static_cast<DevPair*>(stg);
         for (int64_t i = 0; i < n; ++i, ++p) {
+            CandView a, b;
+            EvalNeed need;
             int32_t w = 0;
-            if (!fill_pair(cp.cands[(size_t)i], cp.cands[(size_t)(n + i)], p, &w)) return false;
+            if (!compile_eval(&src[i], shape, &a, &p->a, &need) || !compile_eval(&dst[i], shape, &b, &p->b, &need) ||
+                !fill_pair(a, b, p, &w))
+                return kGeneral;
             words = std::max(words, w);
             parts = std::max(parts, p->parts);
         }
-        return n * parts <= INT32_MAX;
+        if (n * parts > INT32_MAX) return kGeneral;
+        return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
     };
-    return with_descriptors((size_t)n * sizeof(DevPair), s, taken, "redistribution", fill, [&](void* d) {
+    return with_descriptors((size_t)n * sizeof(DevPair), s, "redistribution", fill, [&](const void* d) {
         return launch_pairs(static_cast<const DevPair*>(d), n, parts, words, elem_bytes, d_out, s);
     });
 }
 
-// Matmul tiles over coordinate groups, when all candidates are for that kernel.
-static int matmul_groups(const Compiled& cp, const int64_t* proc_off, int64_t tile_bytes, int64_t* d_per_proc,
-                         tm_matmul_cost* d_out, hipStream_t s, bool* taken) {
-    const int64_t n = (int64_t)cp.cands.size();
+// Whether a matrix of the domain has more tiles than its counts hold.
+static bool tiles_overflow(const int64_t* extent) {
+    return extent[0] * extent[1] > INT32_MAX || extent[1] * extent[2] > INT32_MAX || extent[0] * extent[2] > INT32_MAX;
+}
+constexpr int64_t kMatmulProcs = 1024;
+
+// Matmul tiles over coordinate groups, when all candidates are for that kernel (else
+// kGeneral).
+static int matmul_groups(const tm_candidate* c, int64_t n, int64_t tile_bytes, int64_t* d_per_proc,
+                         tm_matmul_cost* d_out, hipStream_t s) {
     int32_t words = 0;
+    int64_t procs = 0;
     auto fill = [&](void* stg) {
         DevEval* e = static_cast<DevEval*>(stg);
         for (int64_t i = 0; i < n; ++i, ++e) {
-            if (cp.cands[(size_t)i].vol > kMaxLdsWords) return false;
-            fill_eval(cp.cands[(size_t)i], EvalShape{1, 0, 0, 1}, e);
-            e->first_proc = proc_off[i];
+            CandView v;
+            EvalNeed need;
+            if (!compile_eval(&c[i], EvalShape{1, 0, 0, 1}, &v, e, &need) || v.lrank != 3 ||
+                e->procs > kMatmulProcs || tiles_overflow(v.extent))
+                return kGeneral;
+            e->first_proc = procs;
+            procs += e->procs;
             const int32_t w = matmul_words(*e);
-            if (w == 0) return false;
+            if (w == 0) return kGeneral;
             words = std::max(words, w);
         }
-        return n <= INT32_MAX;
+        if (n > INT32_MAX) return kGeneral;
+        return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
     };
-    return with_descriptors((size_t)n * sizeof(DevEval), s, taken, "matmul", fill, [&](void* d) {
+    return with_descriptors((size_t)n * sizeof(DevEval), s, "matmul", fill, [&](const void* d) {
         return launch_matmul_groups(static_cast<const DevEval*>(d), n, words, tile_bytes, d_out, d_per_proc, s);
     });
 }
@@ -459,6 +621,10 @@ extern "C" int tm_eval_redistribution_batch(const tm_candidate* src, const tm_ca
         for (int d = 0; same && d < a.lrank && d < TM_MAX_LRANK; ++d) same = a.extent[d] == b.extent[d];
         if (!same) return set_error(TM_EINVAL, "pair %lld: different launch domains or machines", (long long)i);
     }
+    if (n > 0) {
+        const int rc = redistribution_groups(src, dst, n, elem_bytes, d_out, s);
+        if (rc != kGeneral) return rc;
+    }
     std::vector<tm_candidate> both((size_t)(2 * n));
     if (n > 0) {
         std::memcpy(both.data(), src, (size_t)n * sizeof(tm_candidate));
@@ -469,9 +635,6 @@ extern "C" int tm_eval_redistribution_batch(const tm_candidate* src, const tm_ca
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
-    bool taken = false;
-    rc = redistribution_groups(cp, n, elem_bytes, d_out, s, &taken);
-    if (rc != TM_OK || taken) return rc;
     // each pair's joint-class block goes into its a-side table block: the record, then
     // per dim the a entries, the b entries and the run starts of its classes; a dim's
     // joint classes start where either mapping's contribution changes, so there are at
@@ -526,6 +689,10 @@ extern "C" int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_m
                                     tm_matmul_cost* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     if (!mm || mm->tile_bytes < 0) return set_error(TM_EINVAL, "bad matmul descriptor");
+    if (c && n > 0) {
+        const int rc = matmul_groups(c, n, mm->tile_bytes, d_per_proc, d_out, s);
+        if (rc != kGeneral) return rc;
+    }
     // coordinate classes with a zero halo: runs of coordinates with equal contributions
     tm_stencil zs{};
     zs.lrank = TM_MAX_LRANK;
@@ -541,9 +708,10 @@ extern "C" int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_m
         const DevCand& d = cp.cands[(size_t)i];
         if (d.lrank != 3) return set_error(TM_EINVAL, "candidate %lld: matmul needs launch rank 3", (long long)i);
         const int64_t P = (int64_t)d.nodes * d.gpus;
-        if (P > 1024) return set_error(TM_ENOTSUP, "candidate %lld: %lld processors (limit 1024)", (long long)i, (long long)P);
-        if (d.extent[0] * d.extent[1] > INT32_MAX || d.extent[1] * d.extent[2] > INT32_MAX ||
-            d.extent[0] * d.extent[2] > INT32_MAX)
+        if (P > kMatmulProcs)
+            return set_error(TM_ENOTSUP, "candidate %lld: %lld processors (limit %lld)", (long long)i, (long long)P,
+                             (long long)kMatmulProcs);
+        if (tiles_overflow(d.extent))
             return set_error(TM_ENOTSUP, "candidate %lld: more than 2^31 tiles in a matrix", (long long)i);
         pmax = std::max<int>(pmax, (int)P);
         proc_off[(size_t)i] = procs;
@@ -553,9 +721,6 @@ extern "C" int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_m
     }
     proc_off[(size_t)n] = procs;
     block_first[(size_t)n] = blocks;
-    bool taken = false;
-    rc = matmul_groups(cp, proc_off.data(), mm->tile_bytes, d_per_proc, d_out, s, &taken);
-    if (rc != TM_OK || taken) return rc;
     DeviceBatch db;
     rc = upload_batch(cp, db, s);
     int64_t *d_off = nullptr, *d_bf = nullptr;

@@ -12,6 +12,7 @@
 #include <utility>
 #include <vector>
 
+#include "tm_compile.h"
 #include "tm_internal.h"
 
 namespace tmk {
@@ -48,60 +49,64 @@ int validate_shapes(const tm_candidate* c, Shapes* sh) {
     for (int d = 0; d < c->lrank; ++d) {
         const int64_t l = c->extent[d];
         if (l < 1 || l > TM_MAX_EXTENT) return set_error(TM_EINVAL, "extent[%d] = %lld", d, (long long)l);
-        if (pts > TM_MAX_POINTS / l) return set_error(TM_EOVERFLOW, "more than 2^40 points");
-        pts *= l;
+        int64_t p;
+        if (__builtin_mul_overflow(pts, l, &p) || p > TM_MAX_POINTS)
+            return set_error(TM_EOVERFLOW, "more than 2^40 points");
+        pts = p;
     }
-    sh->rank[0] = 2;
-    sh->size[0][0] = c->nodes;
-    sh->size[0][1] = c->gpus_per_node;
+    // every row holds ones past its rank: rows are copied and shifted whole
+    int r = 2;
+    sh->rank[0] = r;
+    int32_t* s = sh->size[0];
+    s[0] = c->nodes;
+    s[1] = c->gpus_per_node;
+    for (int u = 2; u < TM_MAX_MRANK; ++u) s[u] = 1;
     for (int t = 0; t < c->nops; ++t) {
         const tm_op& op = c->ops[t];
-        const int r = sh->rank[t];
-        const int64_t* s = sh->size[t];
-        int64_t* o = sh->size[t + 1];
-        int nr = r;
+        s = sh->size[t];
+        int32_t* o = sh->size[t + 1];
+        std::memcpy(o, s, sizeof(sh->size[0]));
         switch (op.kind) {
             case TM_SPLIT: {
-                const int i = op.a;
-                const int64_t d = op.b;
+                const int i = op.a, d = op.b;
                 if (i < 0 || i >= r) return set_error(TM_EINVAL, "op %d: split dim %d of rank %d", t, i, r);
-                if (d < 1 || s[i] % d) return set_error(TM_EINVAL, "op %d: split factor %lld does not divide %lld", t, (long long)d, (long long)s[i]);
+                if (d < 1 || s[i] % d) return set_error(TM_EINVAL, "op %d: split factor %d does not divide %d", t, d, s[i]);
                 if (r + 1 > TM_MAX_MRANK) return set_error(TM_EINVAL, "op %d: rank above 8", t);
-                nr = r + 1;
-                for (int u = 0; u < i; ++u) o[u] = s[u];
+                for (int u = TM_MAX_MRANK - 1; u > 0; --u) o[u] = u > i ? s[u - 1] : s[u];
                 o[i] = d;
                 o[i + 1] = s[i] / d;
-                for (int u = i + 1; u < r; ++u) o[u + 1] = s[u];
+                ++r;
                 break;
             }
             case TM_MERGE: {
                 const int p = op.a, q = op.b;
                 if (p < 0 || p >= q || q >= r) return set_error(TM_EINVAL, "op %d: merge(%d,%d) on rank %d", t, p, q, r);
-                nr = r - 1;
-                int w = 0;
-                for (int u = 0; u < r; ++u)
-                    if (u != q) o[w++] = u == p ? s[p] * s[q] : s[u];
+                for (int u = 0; u + 1 < TM_MAX_MRANK; ++u) o[u] = u < q ? s[u] : s[u + 1];
+                o[TM_MAX_MRANK - 1] = 1;
+                o[p] = s[p] * s[q];
+                --r;
                 break;
             }
             case TM_SWAP: {
                 const int p = op.a, q = op.b;
                 if (p < 0 || q < 0 || p >= r || q >= r || p == q)
                     return set_error(TM_EINVAL, "op %d: swap(%d,%d) on rank %d", t, p, q, r);
-                for (int u = 0; u < r; ++u) o[u] = s[u];
                 std::swap(o[p], o[q]);
                 break;
             }
             case TM_BALANCE_SPLIT: {
-                const int i = op.a;
-                const int64_t d = op.b;
-                if (i < 0 || i >= r || d < 1) return set_error(TM_EINVAL, "op %d: balance_split(%d,%lld)", t, i, (long long)d);
+                const int i = op.a, d = op.b;
+                if (i < 0 || i >= r || d < 1) return set_error(TM_EINVAL, "op %d: balance_split(%d,%d)", t, i, d);
                 if (d > TM_MAX_VOLUME) return set_error(TM_EOVERFLOW, "op %d: balance_split factor too large", t);
                 if (r + 1 > TM_MAX_MRANK) return set_error(TM_EINVAL, "op %d: rank above 8", t);
-                nr = r + 1;
-                for (int u = 0; u < i; ++u) o[u] = s[u];
+                for (int u = TM_MAX_MRANK - 1; u > 0; --u) o[u] = u > i ? s[u - 1] : s[u];
                 o[i] = d;
                 o[i + 1] = (s[i] + d - 1) / d;
-                for (int u = i + 1; u < r; ++u) o[u + 1] = s[u];
+                ++r;
+                // the only op that changes the volume (at most 2^24 before it, 2^48 after)
+                int64_t vol = 1;
+                for (int u = 0; u < r; ++u) vol *= o[u];
+                if (vol > TM_MAX_VOLUME) return set_error(TM_EOVERFLOW, "op %d: processor space volume above 2^24", t);
                 break;
             }
             case TM_DECOMPOSE: {
@@ -113,22 +118,18 @@ int validate_shapes(const tm_candidate* c, Shapes* sh) {
                 for (int m = 0; m < k; ++m) {
                     if (op.f[m] < 1) return set_error(TM_EINVAL, "op %d: factor %d", t, op.f[m]);
                     prod *= op.f[m];
-                    if (prod > s[i]) return set_error(TM_EINVAL, "op %d: factors exceed %lld", t, (long long)s[i]);
+                    if (prod > s[i]) return set_error(TM_EINVAL, "op %d: factors exceed %d", t, s[i]);
                 }
-                if (prod != s[i]) return set_error(TM_EINVAL, "op %d: factor product %lld != %lld", t, (long long)prod, (long long)s[i]);
-                nr = r + k - 1;
-                for (int u = 0; u < i; ++u) o[u] = s[u];
+                if (prod != s[i]) return set_error(TM_EINVAL, "op %d: factor product %lld != %d", t, (long long)prod, s[i]);
+                for (int u = i + k; u < TM_MAX_MRANK; ++u) o[u] = s[u - k + 1];
                 for (int m = 0; m < k; ++m) o[i + m] = op.f[m];
-                for (int u = i + 1; u < r; ++u) o[u + k - 1] = s[u];
+                r += k - 1;
                 break;
             }
             default:
                 return set_error(TM_EINVAL, "op %d: unknown kind %d", t, op.kind);
         }
-        sh->rank[t + 1] = nr;
-        int64_t vol = 1;
-        for (int u = 0; u < nr; ++u) vol *= o[u];
-        if (vol > TM_MAX_VOLUME) return set_error(TM_EOVERFLOW, "op %d: processor space volume above 2^24", t);
+        sh->rank[t + 1] = r;
     }
     const int fr = sh->rank[c->nops];
     if (c->mrank != fr) return set_error(TM_EINVAL, "mrank %d but the final rank is %d", c->mrank, fr);
@@ -158,7 +159,7 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d) {
     d->frank = fr;
     int64_t vol = 1;
     for (int j = fr - 1; j >= 0; --j) {
-        d->fshape[j] = (int32_t)sh.size[c->nops][j];
+        d->fshape[j] = sh.size[c->nops][j];
         d->fstride[j] = (int32_t)vol;
         vol *= sh.size[c->nops][j];
     }
@@ -180,14 +181,14 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d) {
     }
     for (int t = 0; t < c->nops; ++t) {
         d->rank[t] = sh.rank[t];
-        for (int u = 0; u < sh.rank[t]; ++u) d->shape[t][u] = (int32_t)sh.size[t][u];
+        for (int u = 0; u < sh.rank[t]; ++u) d->shape[t][u] = sh.size[t][u];
         d->op_kind[t] = c->ops[t].kind;
         d->op_a[t] = c->ops[t].a;
         d->op_b[t] = c->ops[t].b;
         d->op_nf[t] = c->ops[t].nf;
         for (int m = 0; m < TM_MAX_LRANK; ++m) d->op_f[t][m] = c->ops[t].f[m];
         // the op's range [lo, hi] in its input shape and the products around it
-        const int64_t* s = sh.size[t];
+        const int32_t* s = sh.size[t];
         const int r = sh.rank[t], pa = c->ops[t].a, pb = c->ops[t].b;
         const int kind = c->ops[t].kind;
         const bool pair = kind == TM_MERGE || kind == TM_SWAP;
@@ -200,7 +201,7 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d) {
         if (kind == TM_SPLIT) sc = s[pa] / pb;
         if (kind == TM_BALANCE_SPLIT) {
             sc = (s[pa] + pb - 1) / pb;
-            wout = (int64_t)pb * sc;
+            wout = pb * sc;
         }
         d->inv_lo[t] = (int32_t)after;
         d->inv_win[t] = (int32_t)win;
@@ -209,6 +210,72 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d) {
         d->inv_c[t] = (int32_t)sc;
     }
     return words > INT32_MAX ? TM_EOVERFLOW : TM_OK;
+}
+
+bool compile_eval(const tm_candidate* c, const EvalShape& shape, CandView* v, DevEval* e, EvalNeed* need) {
+    Shapes sh;
+    if (validate_shapes(c, &sh) != TM_OK) return false;
+    const int nops = c->nops, K = c->lrank;
+    v->lrank = K;
+    v->nops = nops;
+    v->frank = sh.rank[nops];
+    std::memcpy(v->fshape, sh.size[nops], sizeof(v->fshape));
+    int32_t vol = 1;
+    for (int j = TM_MAX_MRANK - 1; j >= 0; --j) {
+        v->fstride[j] = vol;
+        vol *= v->fshape[j];
+    }
+    v->vol = vol;
+    std::memcpy(v->proj_src, c->proj_src, sizeof(v->proj_src));
+    std::memcpy(v->proj_mode, c->proj_mode, sizeof(v->proj_mode));
+    int64_t pts = 1, rows = 1, cells = 0;
+    for (int k = 0; k < K; ++k) {
+        v->extent[k] = c->extent[k];
+        rows = pts;
+        pts *= c->extent[k];
+        cells += c->extent[k];
+    }
+    v->npoints = pts;
+    v->rows = rows;
+    // the owner table in a workgroup's LDS, 32-bit rows, and tables (of the general path)
+    // that 32-bit offsets reach whatever the halo: 20 words a coordinate at most
+    if (((vol + 3) & ~3) + 4 > kMaxLdsWords || rows > (int64_t(1) << 30) || cells > (int64_t(1) << 26)) return false;
+    e->gpus = c->gpus_per_node;
+    e->gbits = bits_for(c->gpus_per_node);
+    e->rgpus = 1.0f / (float)e->gpus;
+    e->procs = c->nodes * c->gpus_per_node;
+    bool bij = true;
+    for (int t = 0; t < nops; ++t) {
+        const tm_op& op = c->ops[t];
+        const int32_t* s = sh.size[t];
+        int32_t after[TM_MAX_MRANK + 1];  // products of the dims from u on
+        after[TM_MAX_MRANK] = 1;
+        for (int u = TM_MAX_MRANK - 1; u >= 0; --u) after[u] = s[u] * after[u + 1];
+        OpView o;
+        o.kind = op.kind;
+        o.a = op.a;
+        o.b = op.b;
+        o.nf = op.nf;
+        o.f = op.f;
+        const bool pair = op.kind == TM_MERGE || op.kind == TM_SWAP;
+        const int lo = pair && op.b < op.a ? op.b : op.a, hi = pair ? op.a + op.b - lo : op.a;
+        o.sa = s[op.a];
+        o.sb = pair ? s[op.b] : 1;
+        o.lo = after[hi + 1];
+        o.mid = pair ? after[lo + 1] / after[hi] : 1;
+        o.wi = pair ? o.sa * o.mid * o.sb : o.sa;
+        o.wo = o.wi;
+        o.c = 1;
+        if (op.kind == TM_SPLIT || op.kind == TM_BALANCE_SPLIT) {
+            o.c = sh.size[t + 1][op.a + 1];
+            o.wo = op.b * o.c;
+            bij = bij && o.wo == o.wi;
+        }
+        o.first = after[0] == after[lo];
+        fill_inverse(o, &e->inv[t]);
+    }
+    *need = fill_dims(*v, bij, shape, e);
+    return true;
 }
 
 // ------------------------------------------------------------------ decompose's search

@@ -123,10 +123,11 @@ struct DevHeader {
     int64_t item_tab;      // arena word offset of the item table (candidate of every counting work item)
 };
 
-// Host-side result of validation.
+// Host-side result of validation: the rank and the extents (with ones up to 8) before
+// each op and after the last.
 struct Shapes {
     int32_t rank[TM_MAX_OPS + 1];
-    int64_t size[TM_MAX_OPS + 1][TM_MAX_MRANK];
+    int32_t size[TM_MAX_OPS + 1][TM_MAX_MRANK];
 };
 
 // An entry of a per-dim coordinate table holds the contribution of that coordinate

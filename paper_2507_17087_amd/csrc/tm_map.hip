@@ -26,21 +26,22 @@ namespace tmk {
 // Processor ids of the candidate's final coordinates (*d_index, or index), written to ids.
 __global__ __launch_bounds__(256) void k_map_ids(const DevEval* __restrict__ evals, int64_t n,
                                                  const int64_t* __restrict__ d_index, int64_t index,
-                                                 int32_t* __restrict__ ids) {
+                                                 int32_t* __restrict__ ids, DevEval* __restrict__ copy) {
     __shared__ DevEval ev;
     const int64_t ci = d_index ? wave_uniform64(*d_index) : index;
     if (ci < 0 || ci >= n) return;  // no candidate selected (empty batch)
     stage_eval(&ev, evals + ci, threadIdx.x);
     __syncthreads();
+    if (copy && blockIdx.x == 0) stage_eval(copy, &ev, threadIdx.x);
     const int32_t vol = wave_uniform(ev.vol), per = ((vol + (int)gridDim.x - 1) / (int)gridDim.x + 255) & ~255;
     const int32_t v0 = (int32_t)blockIdx.x * per, v1 = v0 + per < vol ? v0 + per : vol;
     if (v0 < v1) owner_table<true>(ev, ids, v0, v1, -1, threadIdx.x, 256);
 }
 
 hipError_t launch_map_ids(const DevEval* evals, int64_t n, const int64_t* d_index, int64_t index, int32_t max_vol,
-                          int32_t* ids, hipStream_t s) {
+                          int32_t* ids, hipStream_t s, DevEval* copy) {
     const int grid = std::max(1, std::min(16, (max_vol + 1023) / 1024));
-    hipLaunchKernelGGL(k_map_ids, dim3(grid), dim3(256), 0, s, evals, n, d_index, index, ids);
+    hipLaunchKernelGGL(k_map_ids, dim3(grid), dim3(256), 0, s, evals, n, d_index, index, ids, copy);
     return hipGetLastError();
 }
 

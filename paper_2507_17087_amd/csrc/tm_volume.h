@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tm_compile.h"
 #include "tm_internal.h"
 
 namespace tmk {
@@ -39,9 +40,9 @@ constexpr int64_t kPairWide = 512;
 // Most tuples of one group of dim_d (they are indexed in floats, see div_small).
 constexpr int64_t kPairRowTuples = int64_t(1) << 20;
 
-// Joint dims, parts and LDS words of candidates a, b (same domain).  False: not for this
-// kernel (the general one takes it).
-bool fill_pair(const DevCand& a, const DevCand& b, DevPair* p, int32_t* words);
+// Joint dims, parts and LDS words of candidates a, b (same domain; p->a and p->b are
+// filled).  False: not for this kernel (the general one takes it).
+bool fill_pair(const CandView& a, const CandView& b, DevPair* p, int32_t* words);
 hipError_t launch_pairs(const DevPair* pairs, int64_t n, int32_t parts, int32_t lds_words, int64_t elem_bytes,
                         tm_redist_cost* out, hipStream_t s);
 

@@ -323,26 +323,15 @@ __global__ void k_zero_moves(tm_redist_cost* __restrict__ out, int64_t n) {
 }
 
 // Joint dim k of candidates a and b; false: more block sizes than JointDim lists.
-static bool fill_joint(const DevCand& a, const DevCand& b, int k, JointDim* g) {
+static bool fill_joint(const CandView& a, const CandView& b, int k, JointDim* g) {
     const int64_t l = a.extent[k];
     int64_t m = 1, sizes[2 * TM_MAX_MRANK];
     int ns = 0;
-    for (const DevCand* c : {&a, &b})
-        for (int j = 0; j < c->frank; ++j) {
-            const int64_t s = c->fshape[j];
-            if (c->proj_src[j] != k || s == 1) continue;
-            if (c->proj_mode[j] == TM_CYCLIC) {
-                int64_t x = m, y = s;
-                while (y) {
-                    const int64_t r = x % y;
-                    x = y;
-                    y = r;
-                }
-                if (m < l) m = std::min(m / x * s, l);  // from l on every coordinate is its own residue
-            } else {
-                sizes[ns++] = s;
-            }
-        }
+    for (const CandView* c : {&a, &b}) {
+        const uint64_t bits = projection_bits(*c);
+        for (uint32_t m8 = cyclics_of(bits, k); m8; m8 &= m8 - 1) m = lcm_upto(m, c->fshape[__builtin_ctz(m8)], l);
+        for (uint32_t m8 = blocks_of(bits, k); m8; m8 &= m8 - 1) sizes[ns++] = c->fshape[__builtin_ctz(m8)];
+    }
     int64_t changes = 0, sum = 0;
     g->nblk = 0;
     for (int i = 0; i < ns; ++i) {
@@ -372,8 +361,7 @@ static bool fill_joint(const DevCand& a, const DevCand& b, int k, JointDim* g) {
     return true;
 }
 
-bool fill_pair(const DevCand& a, const DevCand& b, DevPair* p, int32_t* words) {
-    if (a.vol > kMaxLdsWords || b.vol > kMaxLdsWords) return false;
+bool fill_pair(const CandView& a, const CandView& b, DevPair* p, int32_t* words) {
     int64_t groups = 0, tuples = 1;
     p->dim_d = 0;
     for (int k = 0; k < a.lrank; ++k) {
@@ -387,9 +375,6 @@ bool fill_pair(const DevCand& a, const DevCand& b, DevPair* p, int32_t* words) {
     if (w > kMaxLdsWords || tuples / g > kPairRowTuples) return false;
     p->parts = (int32_t)std::max<int64_t>(1, std::min<int64_t>((tuples + kPairTuples - 1) / kPairTuples, g));
     p->pad[0] = p->pad[1] = 0;
-    const EvalShape shape{1, 0, 0, 1};
-    fill_eval(a, shape, &p->a);
-    fill_eval(b, shape, &p->b);
     *words = (int32_t)w;
     return true;
 }
