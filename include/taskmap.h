@@ -303,9 +303,10 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
 /* ---------------------------------------------------------------- batch plans
  * A plan owns device memory for up to max_cands candidates and, for the map of one of
  * them, max_words table words (both grow).  tm_plan_load validates a batch on the host
- * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run replays one
- * hipGraph: one evaluation launch whatever the candidates' launch ranks (two when their
- * LDS needs differ much), which also selects for batches of at most 2048 candidates.
+ * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run is one evaluation
+ * launch whatever the candidates' launch ranks (two when their LDS needs differ much),
+ * which also selects for batches of at most 2048 candidates.  It makes no host
+ * synchronisation and can be captured in the caller's own graph.
  * d_out: tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  A work item is a workgroup:
  * a candidate, or a part of one holding about cells_per_item of its group tuples (0 = a
  * default: whole candidates, but parts where they are too few to fill the GPU; at most
@@ -318,7 +319,7 @@ int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const tm_stencil*
 int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, void* stream);
 /* stage 0: zeroes d_out; 1: the evaluation (which also selects, for batches of at most
  * 2048 candidates in one launch); 2: bytes + selection (together the work of tm_plan_run,
- * one stage at a time, in this order, each replayed from its own graph). */
+ * one stage at a time, in this order). */
 int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t* d_best,
                       void* stream);
 /* Processor map of candidate *d_index (device int64; index into the loaded batch),
@@ -327,9 +328,8 @@ int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t
 int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t host_index, int32_t* d_map,
                         int64_t cap, void* stream);
 /* tm_plan_run, then the processor map of the selected candidate (*d_best) into
- * d_map (device int32[cap], cap holding the batch's largest candidate), replayed as
- * one hipGraph: Sec. 4.2's choice and the map Sec. 3.2 defines for it, with no host
- * step between them.  d_out, d_best and d_map must not be NULL (TM_EINVAL); an empty
+ * d_map (device int32[cap], cap holding the batch's largest candidate): Sec. 4.2's
+ * choice and the map Sec. 3.2 defines for it, with no host step between them.  d_out, d_best and d_map must not be NULL (TM_EINVAL); an empty
  * batch is TM_EINVAL, a short map TM_ECAPACITY. */
 int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, int32_t* d_map, int64_t cap,
                     void* stream);

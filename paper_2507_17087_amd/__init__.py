@@ -103,7 +103,7 @@ def _cands(c):
 
 def _stream():
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev_ptr(t, dtype, numel=None):
@@ -327,7 +327,7 @@ def tm_select_best(costs, seg):
 
 
 class Plan:
-    """tm_plan: batch evaluation replayed from hipGraphs (see taskmap.h)."""
+    """tm_plan: batch evaluation of descriptors kept on the device (see taskmap.h)."""
 
     def __init__(self, max_cands=1, max_words=1):
         self._p = ctypes.c_void_p()
@@ -355,7 +355,7 @@ class Plan:
 
     def run_map(self, out, best, pmap):
         """run(out, best), then the map of the selected candidate into pmap (int32
-        device tensor), as one graph."""
+        device tensor), with no host step between them."""
         import torch
         _check(lib().tm_plan_run_map(self._p, _dev_ptr(out, torch.int64, 4 * self.n), _dev_ptr(best, torch.int64, 1),
                                      _dev_ptr(pmap, torch.int32), pmap.numel(), _stream()))

@@ -159,6 +159,7 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
         cp.points += d.npoints;
         cp.max_points = std::max(cp.max_points, d.npoints);
         cp.max_vol = std::max(cp.max_vol, d.vol);
+        cp.min_row = std::min(cp.min_row, d.L);
     }
     cp.tables_words = words;
     cp.arena_words = words;
@@ -355,23 +356,25 @@ static bool slots_fit(size_t bytes, hipStream_t s) {
 }
 
 // Descriptors that fill writes, for launch to read: in a slot, or larger ones in a device
-// copy.  fill's result: TM_OK, an error, or kGeneral (nothing is launched).
+// copy.  fill's result: TM_OK, an error, or kGeneral (nothing is launched).  *memory: the
+// error of getting the memory; then the result is kGeneral, since the records come first
+// (the general path has them validated before it meets the same error).
 constexpr int kGeneral = 1;
 template <class Fill, class Launch>
-static int with_descriptors(size_t bytes, hipStream_t s, const char* what, Fill fill, Launch launch) {
+static int with_descriptors(size_t bytes, hipStream_t s, const char* what, int* memory, Fill fill, Launch launch) {
     hipError_t e = hipSuccess;
     int rc;
     if (slots_fit(bytes, s)) {
         Slot slot;
-        rc = slot_acquire(false, &slot);
-        if (rc == TM_OK) rc = fill((void*)slot.host);
+        *memory = slot_acquire(false, &slot);
+        rc = *memory == TM_OK ? fill((void*)slot.host) : kGeneral;
         if (rc != TM_OK) return rc;
         e = launch((const void*)slot.host);
         rc = slot_release(slot, s);
     } else {
         void *stg = nullptr, *d = nullptr;
-        rc = staging_acquire(bytes, &stg);
-        if (rc == TM_OK) rc = fill(stg);
+        *memory = staging_acquire(bytes, &stg);
+        rc = *memory == TM_OK ? fill(stg) : kGeneral;
         if (rc != TM_OK) return rc;
         TM_HIP(hipMallocAsync(&d, bytes, s));
         e = hipMemcpyAsync(d, stg, bytes, hipMemcpyHostToDevice, s);
@@ -508,9 +511,10 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
         return launch_eval_batch(plan, static_cast<const DevEval*>(d), d_out, nullptr, nullptr, num_cus(), s);
     };
     const int H = stencil_slots(*st);
+    int memory = TM_OK;
     if (H > 0 && c && n > 0) {
         // straight from the records to the evaluation's descriptors
-        const int rc = with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", [&](void* stg) {
+        const int rc = with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", &memory, [&](void* stg) {
             DevEval* e = static_cast<DevEval*>(stg);
             EvalLayout lay(plan, n, *st, H, 0, node_level);
             const EvalShape shape = lay.shape();
@@ -532,11 +536,12 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
     if (!d_out) return set_error(TM_EINVAL, "null output");
     layout_eval(cp, 0, node_level);
     plan = cp.eval;
-    return with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", [&](void* stg) {
+    rc = with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", &memory, [&](void* stg) {
         const EvalShape shape{plan.H, plan.node_level, plan.per_item, plan.fill};
         for (int64_t i = 0; i < n; ++i) fill_eval(cp.cands[(size_t)i], shape, static_cast<DevEval*>(stg) + i);
         return TM_OK;
     }, launch);
+    return rc == kGeneral ? memory : rc;
 }
 
 extern "C" int tm_eval_stencil_batch(const tm_candidate* c, int64_t n, const tm_stencil* st,
@@ -553,7 +558,8 @@ extern "C" int tm_eval_stencil_node_batch(const tm_candidate* c, int64_t n, cons
 // workgroup's LDS (else kGeneral).
 static int redistribution_groups(const tm_candidate* src, const tm_candidate* dst, int64_t n, int64_t elem_bytes,
                                  tm_redist_cost* d_out, hipStream_t s) {
-    int32_t words = 0, parts = 1;
+    int memory, parts = 1;
+    int32_t words = 0;
     auto fill = [&](void* stg) {
         const EvalShape shape{1, 0, 0, 1};
         DevPair* p = static_cast<DevPair*>(stg);
@@ -570,7 +576,7 @@ static int redistribution_groups(const tm_candidate* src, const tm_candidate* ds
         if (n * parts > INT32_MAX) return kGeneral;
         return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
     };
-    return with_descriptors((size_t)n * sizeof(DevPair), s, "redistribution", fill, [&](const void* d) {
+    return with_descriptors((size_t)n * sizeof(DevPair), s, "redistribution", &memory, fill, [&](const void* d) {
         return launch_pairs(static_cast<const DevPair*>(d), n, parts, words, elem_bytes, d_out, s);
     });
 }
@@ -585,6 +591,7 @@ constexpr int64_t kMatmulProcs = 1024;
 // kGeneral).
 static int matmul_groups(const tm_candidate* c, int64_t n, int64_t tile_bytes, int64_t* d_per_proc,
                          tm_matmul_cost* d_out, hipStream_t s) {
+    int memory;
     int32_t words = 0;
     int64_t procs = 0;
     auto fill = [&](void* stg) {
@@ -604,7 +611,7 @@ static int matmul_groups(const tm_candidate* c, int64_t n, int64_t tile_bytes, i
         if (n > INT32_MAX) return kGeneral;
         return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
     };
-    return with_descriptors((size_t)n * sizeof(DevEval), s, "matmul", fill, [&](const void* d) {
+    return with_descriptors((size_t)n * sizeof(DevEval), s, "matmul", &memory, fill, [&](const void* d) {
         return launch_matmul_groups(static_cast<const DevEval*>(d), n, words, tile_bytes, d_out, d_per_proc, s);
     });
 }
@@ -784,18 +791,6 @@ extern "C" int tm_select_best(const tm_stencil_cost* d_costs, const int64_t* seg
 
 namespace tmk {
 
-static void plan_drop_graphs(tm_plan* p) {
-    if (p->g_full) (void)hipGraphExecDestroy(p->g_full);
-    if (p->g_map) (void)hipGraphExecDestroy(p->g_map);
-    for (auto& g : p->g_stage)
-        if (g) (void)hipGraphExecDestroy(g);
-    p->g_full = nullptr;
-    p->g_map = nullptr;
-    p->g_map_ptr = nullptr;
-    for (auto& g : p->g_stage) g = nullptr;
-    p->g_valid = false;
-}
-
 static void search_free(SearchBufs& b) {
     void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.est, b.seg, b.sel, b.sub_out, b.all_out};
     for (void* q : ptrs)
@@ -804,7 +799,6 @@ static void search_free(SearchBufs& b) {
 }
 
 static void plan_free(tm_plan* p) {
-    plan_drop_graphs(p);
     search_free(p->sb);
     if (p->d_cands) (void)hipFree(p->d_cands);
     if (p->d_evals) (void)hipFree(p->d_evals);
@@ -857,7 +851,6 @@ static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
     if (p->d_arena) (void)hipFree(p->d_arena);
     p->d_arena = nullptr;
     p->cap_arena = 0;
-    plan_drop_graphs(p);
     if (hipMalloc((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
         return set_error(TM_ENOMEM, "table arena of %lld words", (long long)words);
     p->cap_arena = words;
@@ -880,8 +873,10 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
     return TM_OK;
 }
 
-// Enqueues a run, or one stage of it, on stream s (direct launches; also used for
-// capture).  Stage 2 on its own repeats the selection (idempotent).
+// Enqueues a run (stage -1) or one stage of it on stream s: one launch up to kFinInCount
+// candidates, else two or three.  A launch costs the host 2.4 us; replaying a graph of one
+// 18.2 us (and its capture at every change of an output).  Stage 2 on its own repeats the
+// selection (idempotent).
 static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, hipStream_t s,
                                int32_t* best_ids = nullptr) {
     const Compiled& cp = p->cp;
@@ -891,39 +886,7 @@ static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int6
 }
 
 // Map launch for a device-side index: fits every loaded candidate.
-static MapShape plan_map_shape(const tm_plan* p) {
-    int64_t row = INT32_MAX;
-    for (auto& d : p->cp.cands) row = std::min<int64_t>(row, d.L);
-    return map_shape(p->cp.max_vol, p->cp.max_points, row);
-}
-
-// Captures a run (stage -1), a stage (0..2) or, with map, a run and the map of *best.
-static int capture(tm_plan* p, int stage, tm_stencil_cost* out, int64_t* best, int32_t* map, hipGraphExec_t* exec) {
-    hipGraph_t g = nullptr;
-    TM_HIP(hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = plan_enqueue(p, stage, out, best, p->cap_stream, map ? p->d_arena : nullptr);
-    if (e == hipSuccess && map)
-        e = launch_map(plan_map_shape(p), p->d_evals, p->cp.hdr.n, best, 0, p->d_arena, map, p->cap_stream);
-    const hipError_t e2 = hipStreamEndCapture(p->cap_stream, &g);
-    if (e != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return set_error(TM_EDEVICE, "capture: %s", hipGetErrorString(e));
-    }
-    TM_HIP(e2);
-    const hipError_t e3 = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    TM_HIP(e3);
-    return TM_OK;
-}
-
-// The graphs of the last (out, best): dropped when either changes, captured on first use.
-static void plan_graphs(tm_plan* p, tm_stencil_cost* out, int64_t* best) {
-    if (p->g_valid && p->g_out == out && p->g_best == best) return;
-    plan_drop_graphs(p);
-    p->g_valid = true;
-    p->g_out = out;
-    p->g_best = best;
-}
+static MapShape plan_map_shape(const tm_plan* p) { return map_shape(p->cp.max_vol, p->cp.max_points, p->cp.min_row); }
 
 }  // namespace tmk
 
@@ -940,8 +903,6 @@ extern "C" int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** ou
     }
     if (rc == TM_OK && hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming) != hipSuccess)
         rc = set_error(TM_EDEVICE, "event");
-    if (rc == TM_OK && hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking) != hipSuccess)
-        rc = set_error(TM_EDEVICE, "capture stream");
     if (rc != TM_OK) {
         tm_plan_destroy(p);
         return rc;
@@ -956,7 +917,6 @@ extern "C" int tm_plan_destroy(tm_plan* p) {
     (void)hipDeviceSynchronize();
     plan_free(p);
     if (p->up_ev) (void)hipEventDestroy(p->up_ev);
-    if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
     delete p;
     return TM_OK;
 }
@@ -983,7 +943,6 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
     cp.eval.wg_per_cu = p->wg_per_cu;
     p->cp = std::move(cp);
     p->loaded = true;
-    plan_drop_graphs(p);
     return plan_upload(p, s);
 }
 
@@ -991,11 +950,8 @@ extern "C" int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, 
     if (!p || !p->loaded) return set_error(TM_EINVAL, "plan not loaded");
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
-    plan_graphs(p, d_out, d_best);
-    const int rc = p->g_full ? TM_OK : capture(p, -1, d_out, d_best, nullptr, &p->g_full);
-    if (rc != TM_OK) return rc;
+    TM_HIP(plan_enqueue(p, -1, d_out, d_best, (hipStream_t)stream));
     p->cap_words = std::max(p->cap_words, p->cp.arena_words);
-    TM_HIP(hipGraphLaunch(p->g_full, (hipStream_t)stream));
     return TM_OK;
 }
 
@@ -1005,18 +961,12 @@ extern "C" int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_be
     if (p->cp.hdr.n == 0) return set_error(TM_EINVAL, "empty batch");
     if (!d_out || !d_best || !d_map) return set_error(TM_EINVAL, "null output");
     if (cap < p->cp.max_points) return set_error(TM_ECAPACITY, "map needs %lld entries", (long long)p->cp.max_points);
-    int rc = plan_ensure_arena(p, (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    const int rc = plan_ensure_arena(p, s);
     if (rc != TM_OK) return rc;
-    plan_graphs(p, d_out, d_best);
-    if (!p->g_map || p->g_map_ptr != d_map) {
-        if (p->g_map) (void)hipGraphExecDestroy(p->g_map);
-        p->g_map = nullptr;
-        rc = capture(p, -1, d_out, d_best, d_map, &p->g_map);
-        p->g_map_ptr = rc == TM_OK ? d_map : nullptr;
-    }
-    if (rc != TM_OK) return rc;
+    TM_HIP(plan_enqueue(p, -1, d_out, d_best, s, p->d_arena));
+    TM_HIP(launch_map(plan_map_shape(p), p->d_evals, p->cp.hdr.n, d_best, 0, p->d_arena, d_map, s));
     p->cap_words = std::max(p->cap_words, p->cp.arena_words);
-    TM_HIP(hipGraphLaunch(p->g_map, (hipStream_t)stream));
     return TM_OK;
 }
 
@@ -1026,11 +976,8 @@ extern "C" int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_o
     if (stage < 0 || stage > 2) return set_error(TM_EINVAL, "stage %d", stage);
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
-    plan_graphs(p, d_out, d_best);
-    const int rc = p->g_stage[stage] ? TM_OK : capture(p, stage, d_out, d_best, nullptr, &p->g_stage[stage]);
-    if (rc != TM_OK) return rc;
+    TM_HIP(plan_enqueue(p, stage, d_out, d_best, (hipStream_t)stream));
     p->cap_words = std::max(p->cap_words, p->cp.arena_words);
-    TM_HIP(hipGraphLaunch(p->g_stage[stage], (hipStream_t)stream));
     return TM_OK;
 }
 
@@ -1098,7 +1045,6 @@ static int plan_relayout(tm_plan* p, int64_t cells_per_item, int wg_per_cu, hipS
     layout_items(p->cp, cells_per_item > 0 ? cells_per_item : default_tuples_per_item(p->cp.tuples));
     layout_eval(p->cp, cells_per_item, false);
     p->cp.eval.wg_per_cu = wg_per_cu;
-    plan_drop_graphs(p);
     return plan_upload(p, s);
 }
 

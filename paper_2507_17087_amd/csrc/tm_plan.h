@@ -20,6 +20,7 @@ struct Compiled {
     int32_t max_words = 0;      // largest LDS-staged prefix
     int32_t max_all_words = 0;  // largest whole table block of one candidate
     int32_t max_vol = 0;        // largest final-space volume
+    int32_t min_row = INT32_MAX;  // shortest row (last extent)
     int32_t cnt_words = 0;      // LDS words of the counting launch (largest staged owner table + class blocks)
     int64_t tuples = 0;         // class-tuple bound of the batch (sum of the candidates')
     int64_t tables_words = 0;   // arena words of the tables (the item table follows)
@@ -61,18 +62,10 @@ struct tm_plan {
     int64_t cap_hseg = 0;
     hipEvent_t up_ev = nullptr;
     bool up_pending = false;
-    hipStream_t cap_stream = nullptr;
     tmk::Compiled cp;  // the loaded batch
     bool loaded = false;
     int64_t cells_per_item = 0;
     int wg_per_cu = 0;
-    // graph cache: one entry
-    bool g_valid = false;
-    void* g_out = nullptr;
-    void* g_best = nullptr;
-    hipGraphExec_t g_full = nullptr, g_stage[3] = {nullptr, nullptr, nullptr};
-    hipGraphExec_t g_map = nullptr;  // the whole run, then the map of the selected candidate
-    void* g_map_ptr = nullptr;
     tmk::SearchBufs sb;
 };
 
