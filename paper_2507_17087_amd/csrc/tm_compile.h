@@ -230,6 +230,30 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
     fill_dims(d, is_bijective(d), shape, e);
 }
 
+__host__ __device__ inline void fill_feat(const DevCand& d, DevFeat* f) {
+    uint32_t kinds = 0, opa = 0, proj = 0;
+    int first = -1;  // decompose
+    for (int t = 0; t < d.nops; ++t) {
+        kinds |= (uint32_t)d.op_kind[t] << (4 * t);
+        if (t < 3) opa |= (uint32_t)d.op_a[t] << (8 * t);
+        if (first < 0 && d.op_kind[t] == TM_DECOMPOSE) first = t;
+    }
+    for (int j = 0; j < d.frank; ++j)
+        proj |= ((uint32_t)d.proj_src[j] | (d.proj_mode[j] == TM_BLOCK ? 0u : 8u)) << (4 * j);
+    f->nodes = d.nodes;
+    f->gpus = d.gpus;
+    f->counts = (uint32_t)d.lrank | (uint32_t)d.nops << 8 | (uint32_t)d.gbits << 16 | (uint32_t)d.frank << 24;
+    f->kinds = kinds;
+    f->opa = opa;
+    f->proj = proj;
+    for (int k = 0; k < TM_MAX_LRANK; ++k) {
+        f->ext[k] = (int32_t)d.extent[k];
+        f->F[k] = first >= 0 && k < d.op_nf[first] ? d.op_f[first][k] : 1;
+    }
+    for (int j = 0; j < TM_MAX_MRANK; ++j) f->fshape[j] = d.fshape[j];
+    for (int t = 0; t < 6; ++t) f->opb[t] = d.op_b[t];
+}
+
 // A validated candidate without the tables' layout: what the calls that go straight to
 // DevEval need of it.
 struct CandView {

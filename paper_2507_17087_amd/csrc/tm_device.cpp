@@ -792,7 +792,7 @@ extern "C" int tm_select_best(const tm_stencil_cost* d_costs, const int64_t* seg
 namespace tmk {
 
 static void search_free(SearchBufs& b) {
-    void* ptrs[] = {b.X, b.Y, b.score, b.pre, b.est, b.seg, b.sel, b.sub_out, b.all_out};
+    void* ptrs[] = {b.X, b.base, b.score, b.pre, b.seg, b.sel, b.sub_out, b.all_out};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     b = SearchBufs{};
@@ -802,6 +802,7 @@ static void plan_free(tm_plan* p) {
     search_free(p->sb);
     if (p->d_cands) (void)hipFree(p->d_cands);
     if (p->d_evals) (void)hipFree(p->d_evals);
+    if (p->d_feats) (void)hipFree(p->d_feats);
     if (p->d_arena) (void)hipFree(p->d_arena);
     if (p->d_hdr) (void)hipFree(p->d_hdr);
     if (p->d_counter) (void)hipFree(p->d_counter);
@@ -810,6 +811,7 @@ static void plan_free(tm_plan* p) {
     if (p->h_seg) (void)hipHostFree(p->h_seg);
     p->d_cands = nullptr;
     p->d_evals = nullptr;
+    p->d_feats = nullptr;
     p->d_arena = nullptr;
     p->d_hdr = nullptr;
     p->d_counter = nullptr;
@@ -829,6 +831,7 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
     cands = std::max<int64_t>(cands, 1);
     if (hipMalloc((void**)&p->d_cands, (size_t)cands * sizeof(DevCand)) != hipSuccess ||
         hipMalloc((void**)&p->d_evals, (size_t)cands * sizeof(DevEval)) != hipSuccess ||
+        hipMalloc((void**)&p->d_feats, (size_t)cands * sizeof(DevFeat)) != hipSuccess ||
         hipMalloc((void**)&p->d_hdr, sizeof(DevHeader)) != hipSuccess ||
         hipMalloc((void**)&p->d_counter, 256) != hipSuccess || hipMemset(p->d_counter, 0, 256) != hipSuccess ||
         hipHostMalloc((void**)&p->h_cands, (size_t)cands * sizeof(DevCand), hipHostMallocDefault) != hipSuccess ||
@@ -869,7 +872,7 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
     if (nc) TM_HIP(hipMemcpyAsync(p->d_cands, p->h_cands, nc, hipMemcpyHostToDevice, s));
     TM_HIP(hipEventRecord(p->up_ev, s));
     p->up_pending = true;
-    TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, s));
+    TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, p->d_feats, s));
     return TM_OK;
 }
 
@@ -1110,34 +1113,34 @@ extern "C" int tm_plan_set_launch(tm_plan* p, int64_t cells_per_item, int32_t wg
 namespace tmk {
 
 int64_t plan_size(const tm_plan* p) { return p->cp.hdr.n; }
-const DevCand* plan_cands(const tm_plan* p) { return p->d_cands; }
-const int32_t* plan_halo(const tm_plan* p) { return p->d_hdr->halo; }
+const DevFeat* plan_feats(const tm_plan* p) { return p->d_feats; }
+FeatHalo plan_halo(const tm_plan* p) {
+    const int32_t* h = p->cp.hdr.halo;
+    return FeatHalo{{h[0], h[1], h[2], h[3]}};
+}
 
-// Ranker buffers: features and outputs of n rows; scores and estimates of
-// max(n, m) entries (m: the second stage's survivors of a ranked search).
+// Ranker buffers: features and bases of n rows; scores of max(n, m) entries (m: the
+// second stage's survivors of a ranked search).
 static int ensure_rank_bufs(SearchBufs& b, int64_t n, int64_t m, hipStream_t s) {
     const int64_t sc = std::max<int64_t>(std::max(n, m), 1);
     if (b.cap_n < n) {
         TM_HIP(hipStreamSynchronize(s));
         if (b.X) (void)hipFree(b.X);
-        if (b.Y) (void)hipFree(b.Y);
+        if (b.base) (void)hipFree(b.base);
         b.X = nullptr;
-        b.Y = nullptr;
+        b.base = nullptr;
         b.cap_n = 0;
         if (hipMalloc((void**)&b.X, (size_t)std::max<int64_t>(n, 1) * kFeat * 2) != hipSuccess ||
-            hipMalloc((void**)&b.Y, (size_t)std::max<int64_t>(n, 1) * kOut * 4) != hipSuccess)
+            hipMalloc((void**)&b.base, (size_t)std::max<int64_t>(n, 1) * 4) != hipSuccess)
             return set_error(TM_ENOMEM, "feature buffers");
         b.cap_n = n;
     }
     if (b.cap_sc < sc) {
         TM_HIP(hipStreamSynchronize(s));
         if (b.score) (void)hipFree(b.score);
-        if (b.est) (void)hipFree(b.est);
         b.score = nullptr;
-        b.est = nullptr;
         b.cap_sc = 0;
-        if (hipMalloc((void**)&b.score, (size_t)sc * 4) != hipSuccess ||
-            hipMalloc((void**)&b.est, (size_t)sc * 2 * sizeof(double)) != hipSuccess)
+        if (hipMalloc((void**)&b.score, (size_t)sc * 4) != hipSuccess)
             return set_error(TM_ENOMEM, "score buffers");
         b.cap_sc = sc;
     }
@@ -1152,7 +1155,7 @@ int plan_features(const tm_plan* p, float* d_feat, hipStream_t s) {
     const int64_t n = p->cp.hdr.n;
     const int rc = ensure_rank_bufs(b, n, 0, s);
     if (rc != TM_OK) return rc;
-    TM_HIP(launch_features(p->d_cands, n, p->d_hdr->halo, b.est, b.X, d_feat, s));
+    TM_HIP(launch_features(p->d_feats, n, plan_halo(p), b.base, b.X, d_feat, s));
     return TM_OK;
 }
 

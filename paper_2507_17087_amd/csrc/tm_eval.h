@@ -46,7 +46,7 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
                              unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
                              int64_t nidx = 0, int32_t* best_ids = nullptr);
 // The evaluation's view of n compiled candidates.
-hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, hipStream_t s);
+hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats, hipStream_t s);
 // The rows zeroed; and the bytes of rows that hold cells, with the selection.
 hipError_t launch_zero_costs(tm_stencil_cost* out, int64_t n, hipStream_t s);
 hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s,

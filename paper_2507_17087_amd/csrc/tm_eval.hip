@@ -451,15 +451,18 @@ static hipError_t launch_eval(const EvalArgs& A, int H, int64_t grid, hipStream_
 // ------------------------------------------------------------------ the evaluation's descriptors
 
 __global__ __launch_bounds__(64) void k_fill_evals(const DevCand* __restrict__ cands, int64_t n, EvalShape shape,
-                                                   DevEval* __restrict__ evals) {
+                                                   DevEval* __restrict__ evals, DevFeat* __restrict__ feats) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) fill_eval(cands[i], shape, &evals[i]);
+    if (i >= n) return;
+    fill_eval(cands[i], shape, &evals[i]);
+    fill_feat(cands[i], &feats[i]);
 }
 
-hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, hipStream_t s) {
+hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats, hipStream_t s) {
     if (p.n <= 0) return hipSuccess;
     const EvalShape shape{p.H, p.node_level, p.per_item, p.fill};
-    hipLaunchKernelGGL(k_fill_evals, dim3((unsigned)((p.n + 63) / 64)), dim3(64), 0, s, cands, p.n, shape, evals);
+    hipLaunchKernelGGL(k_fill_evals, dim3((unsigned)((p.n + 63) / 64)), dim3(64), 0, s, cands, p.n, shape, evals,
+                       feats);
     return hipGetLastError();
 }
 

@@ -111,6 +111,20 @@ struct DevCand {
         inv_c[TM_MAX_OPS];
 };
 
+// What the ranker's features read of a candidate: one cache line.
+struct alignas(16) DevFeat {
+    int32_t ext[TM_MAX_LRANK];  // 0 past the launch rank
+    int32_t nodes, gpus;
+    uint32_t counts;            // launch rank | ops << 8 | gpu bits << 16 | final rank << 24
+    uint32_t kinds;             // of op t: bits 4 t
+    int32_t fshape[TM_MAX_MRANK];
+    int32_t opb[6];
+    uint32_t opa;               // of op t < 3: bits 8 t
+    uint32_t proj;              // of final dim j: source in bits 4 j, cyclic in bit 4 j + 3
+    int32_t F[TM_MAX_LRANK];    // the factors of the first decompose (1 past them)
+    int32_t pad[4];
+};
+
 // Batch header: one per plan, in device memory, read by every kernel of a replay.
 struct DevHeader {
     int64_t n;            // candidates

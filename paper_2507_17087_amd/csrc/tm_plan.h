@@ -33,9 +33,8 @@ struct Compiled {
 struct SearchBufs {
     int64_t cap_n = 0, cap_sc = 0, cap_pre = 0, cap_sel = 0, cap_seg = 0, cap_all = 0;
     uint16_t* X = nullptr;          // [n][kFeat] bf16 features
-    float* Y = nullptr;             // [n][kOut] network outputs
+    float* base = nullptr;          // [n] the scores' bases
     float* score = nullptr;         // [cap_sc] ranking scores (both stages)
-    double* est = nullptr;          // [cap_sc][2] the descriptor estimates
     int64_t* pre = nullptr;         // [nseg*prefilter] candidates kept by the network's scores
     int64_t* seg = nullptr;         // [nseg+1] instance segments
     int64_t* sel = nullptr;         // [nseg*k] chosen candidate indices
@@ -53,6 +52,7 @@ struct tm_plan {
     int64_t cap_arena = 0;            // words of d_arena
     tmk::DevCand* d_cands = nullptr;
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
+    tmk::DevFeat* d_feats = nullptr;  // the features'
     int32_t* d_arena = nullptr;       // owner table (processor ids) of the candidate being mapped
     tmk::DevHeader* d_hdr = nullptr;
     unsigned long long* d_counter = nullptr;
@@ -80,9 +80,9 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 
 int64_t plan_size(const tm_plan* p);
-const DevCand* plan_cands(const tm_plan* p);
+const DevFeat* plan_feats(const tm_plan* p);
 EstimateBatch plan_estimates(const tm_plan* p);
-const int32_t* plan_halo(const tm_plan* p);
+FeatHalo plan_halo(const tm_plan* p);
 int plan_features(const tm_plan* p, float* d_feat, hipStream_t s);
 int plan_block_estimates(const tm_plan* p, double* d_est, hipStream_t s);
 int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t prefilter, int32_t topk, bool ranked,

@@ -106,10 +106,13 @@ constexpr int kMaxMrankCross = 8;  // node-crossing fractions kept per candidate
 // through bf16.
 constexpr int kBaseFeat[kOut] = {23, 60};
 constexpr float kBaseScale = 32.f;
-// Features of n candidates: bf16 rows X, fp32 copies f32 (nullable), and the
-// descriptor estimate est[2i] (est[2i+1] = 0).
-hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_halo, double* est, uint16_t* X,
-                           float* f32, hipStream_t s);
+struct FeatHalo {
+    int32_t h[TM_MAX_LRANK];
+};
+// Features of n candidates: bf16 rows X, fp32 copies f32 (nullable), and the fp32 base of
+// each one's score.
+hipError_t launch_features(const DevFeat* feats, int64_t n, const FeatHalo& halo, float* base, uint16_t* X, float* f32,
+                           hipStream_t s);
 // A loaded batch as the block-model estimates read it.
 struct EstimateBatch {
     const DevCand* cands;
@@ -124,8 +127,15 @@ struct EstimateBatch {
 // (nullable).
 hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t n, float lambda, double* est,
                             float* score, hipStream_t s);
-// Network outputs of n rows of bf16 features.
-hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, hipStream_t s);
+// The ranking scores of rows with these bases (score == nullptr: outputs instead).
+struct RankScore {
+    const float* base;
+    float mu[kOut], sigma[kOut], lambda;
+    float* score;
+};
+// Network outputs Y, or scores, of n rows of bf16 features.
+hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, const RankScore& S,
+                              hipStream_t s);
 // Forward and backward of one batch (s0, s1: the heads' scale of Y - target): Y, T and the
 // columns; the bias and head gradients into grad, the matrices' into T.part.
 hipError_t launch_gradient(const TrainBatch& B, const RankerWeights& W, float s0, float s1, const TrainBuffers& T,
@@ -141,8 +151,5 @@ hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W,
 // entry to the index written.
 hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t stride, int k, float margin,
                          const int64_t* remap, int64_t* sel, hipStream_t s);
-// Scores from the heads Y and the descriptor estimates est.
-hipError_t launch_combine(const float* Y, const double* est, int64_t n, const float* mu, const float* sigma,
-                          float lambda, float* s, hipStream_t st);
 
 }  // namespace tmk

@@ -334,75 +334,32 @@ hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t 
     return hipGetLastError();
 }
 
-// The descriptor fields the features read, fetched with 16-byte loads: each group
-// below starts at a 16-byte aligned offset of DevCand (checked here), so a thread
-// issues 15 vector loads per candidate instead of one load per field.
-static_assert(offsetof(DevCand, lrank) == 0 && offsetof(DevCand, nops) == 4 && offsetof(DevCand, nodes) == 8 &&
-                  offsetof(DevCand, gpus) == 12 && offsetof(DevCand, gbits) == 16 && offsetof(DevCand, frank) == 20,
-              "descriptor header");
-static_assert(offsetof(DevCand, extent) == 32, "extents");
-static_assert(offsetof(DevCand, fshape) % 16 == 0 && TM_MAX_MRANK == 8, "final shape");
-static_assert(offsetof(DevCand, proj_mode) == offsetof(DevCand, proj_src) + 8 && offsetof(DevCand, proj_src) % 16 == 0,
-              "projections");
-static_assert(offsetof(DevCand, op_kind) % 16 == 0 && offsetof(DevCand, op_a) % 16 == 0 &&
-                  offsetof(DevCand, op_b) % 16 == 0 && offsetof(DevCand, op_nf) % 16 == 0 &&
-                  offsetof(DevCand, op_f) % 16 == 0 && TM_MAX_OPS == 8 && TM_MAX_LRANK == 4,
-              "ops");
-
+// A candidate's DevFeat unpacked.
 struct FeatDesc {
     int k, nops, nodes, gpus, gbits, fr;
-    int64_t ext[TM_MAX_LRANK];
+    int32_t ext[TM_MAX_LRANK];
     int32_t fsh[TM_MAX_MRANK];
-    int32_t psrc[TM_MAX_MRANK], pmode[TM_MAX_MRANK];
-    int32_t kind[TM_MAX_OPS], opa[4], opb[TM_MAX_OPS];
-    int tdec, nf;
-    int32_t F[TM_MAX_LRANK];  // the factors of the first decompose (1 past nf)
+    uint32_t proj, kinds, opa;
+    int32_t opb[6];
+    int32_t F[TM_MAX_LRANK];
+    __device__ __forceinline__ int src(int j) const { return (int)(proj >> (4 * j)) & 7; }
+    __device__ __forceinline__ bool cyclic(int j) const { return (proj >> (4 * j + 3)) & 1u; }
+    __device__ __forceinline__ int kind(int t) const { return (int)(kinds >> (4 * t)) & 15; }
 };
 
-__device__ __forceinline__ FeatDesc load_feat_desc(const DevCand* c) {
-    const int4* q = reinterpret_cast<const int4*>(c);
-    auto at = [&](size_t off) { return q[off / 16]; };
+__device__ __forceinline__ FeatDesc unpack_feat(const int4* q) {
     FeatDesc d;
-    const int4 h0 = at(0), h1 = at(16);
-    d.k = h0.x, d.nops = h0.y, d.nodes = h0.z, d.gpus = h0.w, d.gbits = h1.x, d.fr = h1.y;
-    const int4 e0 = at(32), e1 = at(48);
-    d.ext[0] = (int64_t)(((uint64_t)(uint32_t)e0.y << 32) | (uint32_t)e0.x);
-    d.ext[1] = (int64_t)(((uint64_t)(uint32_t)e0.w << 32) | (uint32_t)e0.z);
-    d.ext[2] = (int64_t)(((uint64_t)(uint32_t)e1.y << 32) | (uint32_t)e1.x);
-    d.ext[3] = (int64_t)(((uint64_t)(uint32_t)e1.w << 32) | (uint32_t)e1.z);
-    const int4 f0 = at(offsetof(DevCand, fshape)), f1 = at(offsetof(DevCand, fshape) + 16);
-    const int32_t fs[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-    const int4 pj = at(offsetof(DevCand, proj_src));
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        d.fsh[j] = fs[j];
-        d.psrc[j] = (int32_t)(int8_t)(((j < 4 ? pj.x : pj.y) >> (8 * (j & 3))) & 0xff);
-        d.pmode[j] = (int32_t)(int8_t)(((j < 4 ? pj.z : pj.w) >> (8 * (j & 3))) & 0xff);
-    }
-    const int4 k0 = at(offsetof(DevCand, op_kind)), k1 = at(offsetof(DevCand, op_kind) + 16);
-    const int4 b0 = at(offsetof(DevCand, op_b)), b1 = at(offsetof(DevCand, op_b) + 16);
-    const int4 n0 = at(offsetof(DevCand, op_nf)), n1 = at(offsetof(DevCand, op_nf) + 16);
-    const int4 a0 = at(offsetof(DevCand, op_a));
-    const int32_t kk[8] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w};
-    const int32_t bb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-    const int32_t nn[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
-    d.opa[0] = a0.x, d.opa[1] = a0.y, d.opa[2] = a0.z, d.opa[3] = a0.w;
-    d.tdec = -1;
-    d.nf = 0;
-#pragma unroll
-    for (int t = TM_MAX_OPS - 1; t >= 0; --t) {
-        d.kind[t] = kk[t];
-        d.opb[t] = bb[t];
-        if (t < d.nops && kk[t] == TM_DECOMPOSE) {
-            d.tdec = t;
-            d.nf = nn[t];
-        }
-    }
-    const int4 fv = q[(offsetof(DevCand, op_f) + 16 * (d.tdec >= 0 ? d.tdec : 0)) / 16];
-    d.F[0] = 0 < d.nf ? fv.x : 1;
-    d.F[1] = 1 < d.nf ? fv.y : 1;
-    d.F[2] = 2 < d.nf ? fv.z : 1;
-    d.F[3] = 3 < d.nf ? fv.w : 1;
+    const int4 e = q[0], m = q[1], s0 = q[2], s1 = q[3], b0 = q[4], b1 = q[5], f = q[6];
+    d.ext[0] = e.x, d.ext[1] = e.y, d.ext[2] = e.z, d.ext[3] = e.w;
+    d.nodes = m.x, d.gpus = m.y;
+    d.k = m.z & 255, d.nops = (m.z >> 8) & 255, d.gbits = (m.z >> 16) & 255, d.fr = (m.z >> 24) & 255;
+    d.kinds = (uint32_t)m.w;
+    d.fsh[0] = s0.x, d.fsh[1] = s0.y, d.fsh[2] = s0.z, d.fsh[3] = s0.w;
+    d.fsh[4] = s1.x, d.fsh[5] = s1.y, d.fsh[6] = s1.z, d.fsh[7] = s1.w;
+    d.opb[0] = b0.x, d.opb[1] = b0.y, d.opb[2] = b0.z, d.opb[3] = b0.w, d.opb[4] = b1.x, d.opb[5] = b1.y;
+    d.opa = (uint32_t)b1.z;
+    d.proj = (uint32_t)b1.w;
+    d.F[0] = f.x, d.F[1] = f.y, d.F[2] = f.z, d.F[3] = f.w;
     return d;
 }
 
@@ -414,7 +371,7 @@ __device__ __forceinline__ FeatDesc load_feat_desc(const DevCand* c) {
 // the sum of their sizes less one each, and at most l - 1); every boundary puts 2h
 // cells of each cross-section into the halo.  Exact for bijective chains with one
 // final dim per launch dim whose blocks are at least h wide.
-__device__ __forceinline__ double descriptor_estimate(const FeatDesc& c, const int32_t* __restrict__ halo) {
+__device__ __forceinline__ double descriptor_estimate(const FeatDesc& c, const int32_t (&halo)[TM_MAX_LRANK]) {
     double cells = 0;
 #pragma unroll
     for (int d = 0; d < TM_MAX_LRANK; ++d) {
@@ -424,8 +381,8 @@ __device__ __forceinline__ double descriptor_estimate(const FeatDesc& c, const i
         bool cyc = false;
 #pragma unroll
         for (int j = 0; j < TM_MAX_MRANK; ++j) {
-            if (j >= c.fr || c.psrc[j] != d) continue;
-            if (c.pmode[j] != TM_BLOCK) cyc = cyc || c.fsh[j] > 1;
+            if (j >= c.fr || c.src(j) != d) continue;
+            if (c.cyclic(j)) cyc = cyc || c.fsh[j] > 1;
             else nb += c.fsh[j] - 1;
         }
         nb = cyc ? l - 1 : (nb < l - 1 ? nb : l - 1);
@@ -442,22 +399,39 @@ __device__ __forceinline__ double descriptor_estimate(const FeatDesc& c, const i
 // the fp64 reference at 1e-5 and stored in bf16)
 __device__ __forceinline__ float lg2f(float x) { return log2f(x); }
 
-// One thread per candidate; writes kFeat bf16 values (row of X, eight 16-byte
-// stores), the descriptor estimate (est[2i]; est[2i+1] = 0: no inter-node base)
-// and, when feat_f32 is given, the features in fp32.
-__global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ cands, int64_t n,
-                                                  const int32_t* __restrict__ halo, double* __restrict__ est,
-                                                  uint16_t* __restrict__ X, float* __restrict__ feat_f32) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const FeatDesc c = load_feat_desc(cands + i);
+// A thread per candidate: kFeat bf16 values (a row of X), the base of its score (the
+// descriptor estimate in the target's log space; the inter-node head has none) and, when
+// feat_f32 is given, the features in fp32.  A wave's descriptors come in, and its rows go
+// out, as whole lines through LDS.
+//
+// Bound: HBM bytes, 260 a candidate.  1.04M candidates: 57 us (4.7 TB/s); reading the
+// fields where they lie in the 960-byte descriptors, five to six lines of each, 162 us.
+constexpr int kFeatStride = 36;  // LDS words of a row: 16-byte pieces of eight lanes on distinct banks
+__global__ __launch_bounds__(64) void k_features(const DevFeat* __restrict__ feats, int64_t n, const FeatHalo halo,
+                                                 float* __restrict__ base, uint16_t* __restrict__ X,
+                                                 float* __restrict__ feat_f32) {
+    __shared__ __attribute__((aligned(16))) int32_t rows[64 * kFeatStride];
+    const int tid = threadIdx.x;
+    const int64_t first = blockIdx.x * (int64_t)64, i = first + tid;
+    const int here = (int)(n - first < 64 ? n - first : 64);
+    constexpr int kPieces = (int)sizeof(DevFeat) / 16;
+    static_assert(sizeof(DevFeat) == 128 && kFeat * 2 == 128, "a descriptor and a row of X are eight 16-byte pieces");
+    const int4* src = reinterpret_cast<const int4*>(feats + first);
+#pragma unroll
+    for (int t = 0; t < kPieces; ++t) {
+        const int p = t * 64 + tid;
+        if (p < here * kPieces) *reinterpret_cast<int4*>(rows + (p >> 3) * kFeatStride + (p & 7) * 4) = src[p];
+    }
+    lds_sync(1);
+    const FeatDesc c = unpack_feat(reinterpret_cast<const int4*>(rows + (tid < here ? tid : 0) * kFeatStride));
+    lds_sync(1);
     // every index into f and the small arrays below is static once the loops are
     // unrolled (bounded by the ABI's maxima, the candidate's counts as predicates), so
     // all of them live in registers
     float f[kFeat];
 #pragma unroll
     for (int t = 0; t < kFeat; ++t) f[t] = 0.f;
-    const int k = c.k, fr = c.fr, nops = c.nops, nf = c.nf;
+    const int k = c.k, fr = c.fr, nops = c.nops;
 #pragma unroll
     for (int d = 0; d < TM_MAX_LRANK; ++d) f[d] = d == k - 1 ? 1.f : 0.f;
     // blocks per launch dim: the product of the final extents it projects onto
@@ -465,7 +439,7 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
 #pragma unroll
     for (int j = 0; j < TM_MAX_MRANK; ++j) {
         if (j < fr) {
-            const int src = c.psrc[j];
+            const int src = c.src(j);
             const double sh = (double)c.fsh[j];
 #pragma unroll
             for (int d = 0; d < TM_MAX_LRANK; ++d) blocks[d] *= src == d ? sh : 1.0;
@@ -473,7 +447,7 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
     }
     int32_t hl[TM_MAX_LRANK];
 #pragma unroll
-    for (int d = 0; d < TM_MAX_LRANK; ++d) hl[d] = d < k ? halo[d] : 0;
+    for (int d = 0; d < TM_MAX_LRANK; ++d) hl[d] = d < k ? halo.h[d] : 0;
     double vol_f = 0;
 #pragma unroll
     for (int d = 0; d < TM_MAX_LRANK; ++d) {
@@ -483,7 +457,7 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
             f[4 + d] = ll / 10.f;
             f[15 + d] = lb / 9.f;
             f[19 + d] = (ll - lb) / 10.f;
-            if (d < nf) vol_f += 2.0 * hl[d] * (c.F[d] - 1.0) / l;
+            vol_f += 2.0 * hl[d] * (c.F[d] - 1.0) / l;
             f[54 + d] = hl[d] / 4.f;
         }
     }
@@ -492,34 +466,32 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
     f[10] = lg2f((float)c.nodes * (float)c.gpus) / 9.f;
 #pragma unroll
     for (int m = 0; m < TM_MAX_LRANK; ++m)
-        if (m < nf) f[11 + m] = lg2f((float)c.F[m]) / 9.f;
+        f[11 + m] = lg2f((float)c.F[m]) / 9.f;
     f[24] = lg2f((float)(1.0 + vol_f)) / 4.f;
 #pragma unroll
     for (int t = 0; t < TM_MAX_OPS; ++t) {
         if (t < nops) {
-            const int kd = c.kind[t];
+            const int kd = c.kind(t);
 #pragma unroll
             for (int q = 0; q < 5; ++q) f[25 + q] += kd == q + 1 ? 0.25f : 0.f;
             if (t < 6) {
                 f[30 + t] = kd / 5.f;
-                if (t < 3) f[39 + t] = c.opa[t] / 8.f;
-                f[42 + t] = kd == TM_DECOMPOSE ? 0.f : lg2f(1.f + (float)c.opb[t]) / 9.f;
+                if (t < 3) f[39 + t] = (float)((c.opa >> (8 * t)) & 255u) / 8.f;
+                f[42 + t] = kd == TM_DECOMPOSE ? 0.f : lg2f(1.f + (float)c.opb[t < 6 ? t : 0]) / 9.f;
             }
         }
     }
-    f[48] = (nops > 0 && c.kind[0] == TM_SWAP) ? 1.f : 0.f;
+    f[48] = (nops > 0 && c.kind(0) == TM_SWAP) ? 1.f : 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        if (j < fr) f[49 + j] = c.pmode[j] ? 1.f : 0.f;
+        if (j < fr) f[49 + j] = c.cyclic(j) ? 1.f : 0.f;
     f[53] = fr / 8.f;
     f[58] = c.gbits / 3.f;
     f[59] = 1.f;
     // the descriptor estimate of the ghost cells in the log space of the target (the
     // inter-node head has no base: feature kBaseFeat[1] stays 0)
-    const double e0 = descriptor_estimate(c, hl);
-    *reinterpret_cast<double2*>(est + i * 2) = make_double2(e0, 0.0);
-    f[kBaseFeat[0]] = lg2(1.0 + e0) / kBaseScale;
-    uint4* row = reinterpret_cast<uint4*>(X + i * kFeat);
+    f[kBaseFeat[0]] = lg2(1.0 + descriptor_estimate(c, hl)) / kBaseScale;
+    if (tid < here) base[i] = f[kBaseFeat[0]];
 #pragma unroll
     for (int t = 0; t < kFeat / 8; ++t) {
         uint4 w;
@@ -527,9 +499,16 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
         w.y = (uint32_t)f2bf(f[8 * t + 2]) | ((uint32_t)f2bf(f[8 * t + 3]) << 16);
         w.z = (uint32_t)f2bf(f[8 * t + 4]) | ((uint32_t)f2bf(f[8 * t + 5]) << 16);
         w.w = (uint32_t)f2bf(f[8 * t + 6]) | ((uint32_t)f2bf(f[8 * t + 7]) << 16);
-        row[t] = w;
+        *reinterpret_cast<uint4*>(rows + tid * kFeatStride + t * 4) = w;
     }
-    if (feat_f32) {
+    lds_sync(1);
+    int4* dst = reinterpret_cast<int4*>(X + first * kFeat);
+#pragma unroll
+    for (int t = 0; t < kPieces; ++t) {
+        const int p = t * 64 + tid;
+        if (p < here * kPieces) dst[p] = *reinterpret_cast<const int4*>(rows + (p >> 3) * kFeatStride + (p & 7) * 4);
+    }
+    if (feat_f32 && tid < here) {
         float4* fo = reinterpret_cast<float4*>(feat_f32 + i * kFeat);
 #pragma unroll
         for (int t = 0; t < kFeat / 4; ++t) fo[t] = make_float4(f[4 * t], f[4 * t + 1], f[4 * t + 2], f[4 * t + 3]);
@@ -549,6 +528,46 @@ __global__ __launch_bounds__(256) void k_features(const DevCand* __restrict__ ca
 // as one 8-byte store.
 // The head (256 -> 2) is one more MFMA tile per wave against the two weight columns
 // staged in LDS (the other 14 columns zero): bf16 products summed in fp32.
+
+// What becomes of a row's two outputs: written to Y, or combined into a ranking score,
+// predicted log2(1 + bytes) + lambda * predicted log2(1 + inter-node bytes), each the
+// estimate's base (the same fp32 value training used; the inter-node head has none) plus
+// the un-standardised residual; +inf when that is not finite: a score of diverged or
+// corrupt parameters ranks last, by index, so that such candidates stay selectable and
+// every instance keeps its survivors.  acc: rows row .. row + 3, output r16.
+__device__ __forceinline__ void put_outputs(const f32x4& acc, float hb, int r16, const f32x4& base, int64_t row,
+                                            int64_t n, float* __restrict__ Y, const RankScore& S) {
+    if (S.score) {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float y = acc[r] + hb, y1 = __shfl_down(y, 1, 64);
+            const float b0 = kBaseScale * base[r], b1 = 0.f;
+            const float p0 = b0 + S.mu[0] + S.sigma[0] * y, p1 = b1 + S.mu[1] + S.sigma[1] * y1;
+            const float sc = p0 + S.lambda * p1;
+            v[r] = __builtin_isfinite(sc) ? sc : INFINITY;
+        }
+        if (r16 == 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (row + r < n) S.score[row + r] = v[r];
+        }
+    } else if (r16 < kOut) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (row + r < n) Y[(row + r) * kOut + r16] = acc[r] + hb;
+    }
+}
+
+// The bases of rows row .. row + 3.
+__device__ __forceinline__ f32x4 score_bases(const RankScore& S, int64_t row, int64_t n) {
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (S.score) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b[r] = S.base[row + r < n ? row + r : n - 1];
+    }
+    return b;
+}
 
 constexpr int kRowsMlp = 64;    // rows per workgroup of the forward pass
 constexpr int kMlpThreads = 512;
@@ -597,7 +616,7 @@ __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, u
 }
 
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __restrict__ X, int64_t n,
-                                                             const RankerWeights W, float* __restrict__ Y) {
+                                                             const RankerWeights W, float* __restrict__ Y, const RankScore S) {
     __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t sb[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];  // head weights, transposed
@@ -615,6 +634,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __r
             if (row0 + r < n) v = *reinterpret_cast<const u16x8*>(X + (row0 + r) * kFeat + c8);
             *reinterpret_cast<u16x8*>(sa + r * kLdsStride + c8) = v;
         }
+        const f32x4 base = score_bases(S, row0 + (wid % 4) * 16 + (lane >> 4) * 4, n);
         __syncthreads();
         layer_fwd<kFeat, kMlpNB>(sa, sb, W.f1, W.b1, lane, cbase);
         __syncthreads();
@@ -632,14 +652,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __r
                 const u16x8 wf = *reinterpret_cast<const u16x8*>(s_w4 + (r16 < kOut ? r16 : 0) * kWidth + k0 + kq);
                 acc = mfma16(af, r16 < kOut ? wf : zero, acc);
             }
-            // acc[r]: row wid*16 + (lane>>4)*4 + r, output r16
-            if (r16 < kOut) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row0 + wid * 16 + (lane >> 4) * 4 + r;
-                    if (row < n) Y[row * kOut + r16] = acc[r] + hb;
-                }
-            }
+            put_outputs(acc, hb, r16, base, row0 + wid * 16 + (lane >> 4) * 4, n, Y, S);
         }
     }
 }
@@ -692,7 +705,7 @@ __device__ __forceinline__ void layer_reg(const uint16_t* __restrict__ in_lds, u
 }
 
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __restrict__ X, int64_t n,
-                                                           const RankerWeights W, float* __restrict__ Y) {
+                                                           const RankerWeights W, float* __restrict__ Y, const RankScore S) {
     __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t sb[kRowsMlp * kLdsStride];
     __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];
@@ -719,6 +732,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __res
     for (int64_t row0 = (int64_t)blockIdx.x * kRowsMlp; row0 < n; row0 += step) {
         __syncthreads();  // this tile's features in sa; the previous head is done with sb
         const u16x8 xn = x_piece(row0 + step);
+        const f32x4 base = score_bases(S, row0 + (wid % 4) * 16 + (lane >> 4) * 4, n);
         layer_reg<kFeat>(sa, sb, w1, W.b1, lane, cbase);
         __syncthreads();
         layer_reg<kWidth>(sb, sa, w2, W.b2, lane, cbase);
@@ -735,13 +749,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __res
                 const u16x8 wf = *reinterpret_cast<const u16x8*>(s_w4 + (r16 < kOut ? r16 : 0) * kWidth + k0 + kq);
                 acc = mfma16(af, r16 < kOut ? wf : zero, acc);
             }
-            if (r16 < kOut) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row0 + wid * 16 + (lane >> 4) * 4 + r;
-                    if (row < n) Y[row * kOut + r16] = acc[r] + hb;
-                }
-            }
+            put_outputs(acc, hb, r16, base, row0 + wid * 16 + (lane >> 4) * 4, n, Y, S);
         }
     }
 }
@@ -885,40 +893,25 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
     for (int64_t r = (int64_t)written + tid; r < k; r += kSelThreads) out[r] = -1;
 }
 
-// Ranking score: predicted log2(1 + bytes) + lambda * predicted log2(1 + inter-node
-// bytes), each = estimate base (the same fp32 value training used) + un-standardised
-// residual head; +inf when that is not finite.
-__global__ void k_combine(const float* __restrict__ Y, const double* __restrict__ est, int64_t n, float mu0,
-                          float s0, float mu1, float s1, float lambda, float* __restrict__ s) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float b0 = kBaseScale * (lg2(1.0 + est[i * 2]) / kBaseScale);
-    const float b1 = kBaseScale * (lg2(1.0 + est[i * 2 + 1]) / kBaseScale);
-    const float p0 = b0 + mu0 + s0 * Y[i * kOut], p1 = b1 + mu1 + s1 * Y[i * kOut + 1];
-    const float v = p0 + lambda * p1;
-    // a non-finite score (diverged or corrupt parameters) ranks last, by index, so
-    // such candidates stay selectable and every instance keeps its survivors
-    s[i] = __builtin_isfinite(v) ? v : INFINITY;
-}
-
 // ------------------------------------------------------------------ launchers
 
-hipError_t launch_features(const DevCand* cands, int64_t n, const int32_t* d_halo, double* est, uint16_t* X,
+hipError_t launch_features(const DevFeat* feats, int64_t n, const FeatHalo& halo, float* base, uint16_t* X,
                            float* f32, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_features, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cands, n, d_halo, est, X, f32);
+    hipLaunchKernelGGL(k_features, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, feats, n, halo, base, X, f32);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, hipStream_t s) {
+hipError_t launch_mlp_forward(const uint16_t* X, int64_t n, const RankerWeights& W, float* Y, const RankScore& S,
+                              hipStream_t s) {
     if (n <= 0) return hipSuccess;
     int64_t grid = (n + kRowsMlp - 1) / kRowsMlp;
     if (grid > 4 * kMlpInferCus) {
         // many rows: persistent workgroups, weights in registers
-        hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)kMlpInferCus), dim3(kMlpThreads), 0, s, X, n, W, Y);
+        hipLaunchKernelGGL(k_mlp_infer, dim3((unsigned)kMlpInferCus), dim3(kMlpThreads), 0, s, X, n, W, Y, S);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)grid), dim3(kMlpThreads), 0, s, X, n, W, Y);
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)grid), dim3(kMlpThreads), 0, s, X, n, W, Y, S);
     return hipGetLastError();
 }
 
@@ -932,14 +925,6 @@ hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, i
     if (nseg <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_select, dim3((unsigned)nseg), dim3(kSelThreads), 0, s, score, seg, stride, k, margin, remap,
                        sel);
-    return hipGetLastError();
-}
-
-hipError_t launch_combine(const float* Y, const double* est, int64_t n, const float* mu, const float* sigma,
-                          float lambda, float* s, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Y, est, n, mu[0], sigma[0],
-                       mu[1], sigma[1], lambda, s);
     return hipGetLastError();
 }
 

@@ -281,7 +281,7 @@ int tm_ranker_forward(tm_ranker* r, const float* d_feat, int64_t n, float* d_out
         const int64_t rows = std::min(chunk, n - a);
         hipLaunchKernelGGL(k_pack_batch, dim3((unsigned)((rows * kFeat + 255) / 256)), dim3(256), 0, s, d_feat, a, rows,
                            r->X);
-        const hipError_t e = launch_mlp_forward(r->X, rows, r->W, d_out + a * kOut, s);
+        const hipError_t e = launch_mlp_forward(r->X, rows, r->W, d_out + a * kOut, RankScore{}, s);
         if (e != hipSuccess) return set_error(TM_EDEVICE, "forward: %s", hipGetErrorString(e));
     }
     return TM_OK;
@@ -471,9 +471,9 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
     const int64_t n = plan_size(p);
     // the network's score of every candidate: descriptor features, forward, residuals
     // over the descriptor estimate
-    hipError_t e = launch_features(plan_cands(p), n, plan_halo(p), sb->est, sb->X, nullptr, s);
-    if (e == hipSuccess) e = launch_mlp_forward(sb->X, n, r->W, sb->Y, s);
-    if (e == hipSuccess) e = launch_combine(sb->Y, sb->est, n, r->mu, r->sigma, lambda, sb->score, s);
+    hipError_t e = launch_features(plan_feats(p), n, plan_halo(p), sb->base, sb->X, nullptr, s);
+    const RankScore score{sb->base, {r->mu[0], r->mu[1]}, {r->sigma[0], r->sigma[1]}, lambda, sb->score};
+    if (e == hipSuccess) e = launch_mlp_forward(sb->X, n, r->W, nullptr, score, s);
     if (prefilter > 0) {
         // the network keeps `prefilter` per instance; their block-model estimates
         // choose the topk
