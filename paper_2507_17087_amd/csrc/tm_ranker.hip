@@ -404,7 +404,7 @@ __device__ __forceinline__ float lg2f(float x) { return log2f(x); }
 // feat_f32 is given, the features in fp32.  A wave's descriptors come in, and its rows go
 // out, as whole lines through LDS.
 //
-// Bound: HBM bytes, 260 a candidate.  1.04M candidates: 57 us (4.7 TB/s); reading the
+// Bound: HBM bytes, 260 a candidate.  1.03M candidates: 57 us (4.7 TB/s); reading the
 // fields where they lie in the 960-byte descriptors, five to six lines of each, 162 us.
 constexpr int kFeatStride = 36;  // LDS words of a row: 16-byte pieces of eight lanes on distinct banks
 __global__ __launch_bounds__(64) void k_features(const DevFeat* __restrict__ feats, int64_t n, const FeatHalo halo,
@@ -495,10 +495,10 @@ __global__ __launch_bounds__(64) void k_features(const DevFeat* __restrict__ fea
 #pragma unroll
     for (int t = 0; t < kFeat / 8; ++t) {
         uint4 w;
-        w.x = (uint32_t)f2bf(f[8 * t]) | ((uint32_t)f2bf(f[8 * t + 1]) << 16);
-        w.y = (uint32_t)f2bf(f[8 * t + 2]) | ((uint32_t)f2bf(f[8 * t + 3]) << 16);
-        w.z = (uint32_t)f2bf(f[8 * t + 4]) | ((uint32_t)f2bf(f[8 * t + 5]) << 16);
-        w.w = (uint32_t)f2bf(f[8 * t + 6]) | ((uint32_t)f2bf(f[8 * t + 7]) << 16);
+        w.x = pack_bf16(f[8 * t], f[8 * t + 1]);
+        w.y = pack_bf16(f[8 * t + 2], f[8 * t + 3]);
+        w.z = pack_bf16(f[8 * t + 4], f[8 * t + 5]);
+        w.w = pack_bf16(f[8 * t + 6], f[8 * t + 7]);
         *reinterpret_cast<uint4*>(rows + tid * kFeatStride + t * 4) = w;
     }
     lds_sync(1);
@@ -608,8 +608,8 @@ __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, u
         for (int a = 0; a < 4; ++a) {
             const int row = a * 16 + r16;
             uint2 w;
-            w.x = (uint32_t)f2bf(fmaxf(acc[a][b][0] + b0, 0.f)) | ((uint32_t)f2bf(fmaxf(acc[a][b][1] + b1, 0.f)) << 16);
-            w.y = (uint32_t)f2bf(fmaxf(acc[a][b][2] + b2, 0.f)) | ((uint32_t)f2bf(fmaxf(acc[a][b][3] + b3, 0.f)) << 16);
+            w.x = pack_bf16(fmaxf(acc[a][b][0] + b0, 0.f), fmaxf(acc[a][b][1] + b1, 0.f));
+            w.y = pack_bf16(fmaxf(acc[a][b][2] + b2, 0.f), fmaxf(acc[a][b][3] + b3, 0.f));
             *reinterpret_cast<uint2*>(out_lds + row * kLdsStride + col0) = w;
         }
     }
@@ -697,8 +697,8 @@ __device__ __forceinline__ void layer_reg(const uint16_t* __restrict__ in_lds, u
         for (int a = 0; a < 4; ++a) {
             const int row = a * 16 + r16;
             uint2 w;
-            w.x = (uint32_t)f2bf(fmaxf(acc[a][b][0] + b0, 0.f)) | ((uint32_t)f2bf(fmaxf(acc[a][b][1] + b1, 0.f)) << 16);
-            w.y = (uint32_t)f2bf(fmaxf(acc[a][b][2] + b2, 0.f)) | ((uint32_t)f2bf(fmaxf(acc[a][b][3] + b3, 0.f)) << 16);
+            w.x = pack_bf16(fmaxf(acc[a][b][0] + b0, 0.f), fmaxf(acc[a][b][1] + b1, 0.f));
+            w.y = pack_bf16(fmaxf(acc[a][b][2] + b2, 0.f), fmaxf(acc[a][b][3] + b3, 0.f));
             *reinterpret_cast<uint2*>(out_lds + row * kLdsStride + col0) = w;
         }
     }

@@ -64,7 +64,7 @@ __device__ __forceinline__ void tile_product(f32x4 (&acc)[RT][2], const uint16_t
 }
 
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
-    return make_uint2((uint32_t)f2bf(a) | (uint32_t)f2bf(b) << 16, (uint32_t)f2bf(c) | (uint32_t)f2bf(d) << 16);
+    return make_uint2(pack_bf16(a, b), pack_bf16(c, d));
 }
 
 // This lane's biases of a layer: columns c0 + 16b + 4 (lane / 16) ..
