@@ -148,8 +148,8 @@ hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W,
 // The k smallest (score, index) entries of each segment (k_select): sel[s*k ..)
 // in index order, -1 after; stride > 0 takes segment s as the first
 // min(stride, seg[s+1] - seg[s]) entries from s * stride; remap (nullable) maps an
-// entry to the index written.
-hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t stride, int k, float margin,
-                         const int64_t* remap, int64_t* sel, hipStream_t s);
+// entry to the index written; n: entries of all segments.
+hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t n, int64_t stride, int k,
+                         float margin, const int64_t* remap, int64_t* sel, hipStream_t s);
 
 }  // namespace tmk

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(64) void k_features(const DevFeat* __restrict__ fea
 // ------------------------------------------------------------------ fused forward
 //
 // A workgroup of the forward pass (8 waves) takes 64 rows.  Activations stay in LDS
-// (bf16, padded row stride); wave w computes output columns [32w, 32w + 32) of
+// (bf16); wave w computes output columns [32w, 32w + 32) of
 // each hidden layer as 4 x 2 MFMA tiles, reading weight fragments straight from
 // the bf16 weights in fragment order (16 contiguous bytes per lane).  Measured on
 // 1M rows: 8 waves of 32 columns 0.58 ms, 4 of 64 columns 0.63 ms, 16 of 16
@@ -573,93 +573,155 @@ constexpr int kRowsMlp = 64;    // rows per workgroup of the forward pass
 constexpr int kMlpThreads = 512;
 constexpr int kMlpNB = kWidth / 16 / (kMlpThreads / 64);  // 16-column blocks per wave
 constexpr int kMlpInferCus = 256;  // persistent inference workgroups (one per CU)
-constexpr int kLdsStride = kWidth + 8;  // bf16 elements per LDS row (breaks bank aliasing)
 
-template <int KIN, int NB>
+// Activations lie in LDS in fragment order too: row r, reduction index k of a tile at
+// frag_at(r, k, blocks of k).  A fragment read and a wave's epilogue write (one 16-byte
+// piece a lane) are then 1 KB in lane order, and no bank is asked twice in a cycle; rows of
+// a padded stride cannot do that, since a 16-byte read takes its lanes in groups that mix
+// the quarters of a fragment: half of the LDS cycles were conflicts.
+constexpr int kActElems = kRowsMlp * kWidth;
+
+// Row block a's fragment of reduction block ks, of nk.
+__device__ __forceinline__ u16x8 act_frag(const uint16_t* __restrict__ lds, int a, int ks, int nk, int lane) {
+    return *reinterpret_cast<const u16x8*>(lds + ((a * nk + ks) * 64 + lane) * 8);
+}
+
+// A wave's 32 output columns are dealt to its two column blocks in fours, so that a lane
+// (quarter q of the fragment) ends with the eight columns cbase + 8 q ..: position i of
+// block b is column cbase + 8 (i / 4) + 4 b + i % 4.
+static_assert(kMlpNB == 2, "two blocks of 16 columns a wave");
+__device__ __forceinline__ const uint16_t* weight_frag(const uint16_t* __restrict__ F, int b, int ks, int nk, int lane,
+                                                       int cbase) {
+    const int c = cbase + (lane & 12) * 2 + b * 4 + (lane & 3);
+    return F + frag_at(c, ks * 32 + (lane >> 4) * 8, nk);
+}
+
+// max(x, 0), NaN -> 0, as fmaxf has it, in one instruction: fmaxf quiets its operand in
+// another, and so does a median whose bound the compiler knows to be infinite.
+__device__ __forceinline__ float relu(float x) {
+    float top = INFINITY;
+    asm("" : "+s"(top));
+    return __builtin_amdgcn_fmed3f(x, 0.f, top);
+}
+
+// acc[a][b][r] (row a*16 + lane%16, column cbase + 8 (lane / 16) + 4 b + r) -> ReLU, bf16,
+// to the next layer's activations, one 16-byte piece a row block.
+__device__ __forceinline__ void layer_out(const f32x4 (&acc)[4][kMlpNB], uint16_t* __restrict__ out_lds, int lane,
+                                          int cbase) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        uint4 w;
+        w.x = pack_bf16(relu(acc[a][0][0]), relu(acc[a][0][1]));
+        w.y = pack_bf16(relu(acc[a][0][2]), relu(acc[a][0][3]));
+        w.z = pack_bf16(relu(acc[a][1][0]), relu(acc[a][1][1]));
+        w.w = pack_bf16(relu(acc[a][1][2]), relu(acc[a][1][3]));
+        *reinterpret_cast<uint4*>(out_lds + ((a * (kWidth / 32) + cbase / 32) * 64 + lane) * 8) = w;
+    }
+}
+
+// The sums start from the biases (LDS).
+__device__ __forceinline__ void layer_start(f32x4 (&acc)[4][kMlpNB], const float* __restrict__ bias, int lane,
+                                            int cbase) {
+#pragma unroll
+    for (int b = 0; b < kMlpNB; ++b) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(bias + cbase + (lane >> 4) * 8 + b * 4);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) acc[a][b] = v;
+    }
+}
+
+template <int KIN>
 __device__ __forceinline__ void layer_fwd(const uint16_t* __restrict__ in_lds, uint16_t* __restrict__ out_lds,
                                           const uint16_t* __restrict__ F, const float* __restrict__ bias,
                                           int lane, int cbase) {
-    f32x4 acc[4][NB];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+    f32x4 acc[4][kMlpNB];
+    layer_start(acc, bias, lane, cbase);
     // two k-steps in flight
 #pragma unroll 2
-    for (int k0 = 0; k0 < KIN; k0 += 32) {
-        u16x8 bf[NB];
+    for (int ks = 0; ks < KIN / 32; ++ks) {
+        u16x8 bf[kMlpNB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-            bf[b] = *reinterpret_cast<const u16x8*>(F + (((cbase / 16 + b) * (KIN / 32) + k0 / 32) * 64 + lane) * 8);
+        for (int b = 0; b < kMlpNB; ++b)
+            bf[b] = *reinterpret_cast<const u16x8*>(weight_frag(F, b, ks, KIN / 32, lane, cbase));
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const u16x8 af = *reinterpret_cast<const u16x8*>(in_lds + (a * 16 + r16) * kLdsStride + k0 + kq);
+            const u16x8 af = act_frag(in_lds, a, ks, KIN / 32, lane);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[a][b] = mfma16(bf[b], af, acc[a][b]);
+            for (int b = 0; b < kMlpNB; ++b) acc[a][b] = mfma16(bf[b], af, acc[a][b]);
         }
     }
-    // acc[a][b][r]: row a*16 + r16, column cbase + b*16 + (lane>>4)*4 + r
+    layer_out(acc, out_lds, lane, cbase);
+}
+
+// The head over 16 rows: B columns 0, 1 are the two heads.
+__device__ __forceinline__ f32x4 head_rows(const uint16_t* __restrict__ h3, const uint16_t* __restrict__ w4, int rb,
+                                           int lane) {
+    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int col0 = cbase + b * 16 + (lane >> 4) * 4;
-        const float b0 = bias[col0], b1 = bias[col0 + 1], b2 = bias[col0 + 2], b3 = bias[col0 + 3];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int row = a * 16 + r16;
-            uint2 w;
-            w.x = pack_bf16(fmaxf(acc[a][b][0] + b0, 0.f), fmaxf(acc[a][b][1] + b1, 0.f));
-            w.y = pack_bf16(fmaxf(acc[a][b][2] + b2, 0.f), fmaxf(acc[a][b][3] + b3, 0.f));
-            *reinterpret_cast<uint2*>(out_lds + row * kLdsStride + col0) = w;
-        }
+    for (int ks = 0; ks < kWidth / 32; ++ks) {
+        const u16x8 af = act_frag(h3, rb, ks, kWidth / 32, lane);
+        const u16x8 wf = *reinterpret_cast<const u16x8*>(w4 + (r16 < kOut ? r16 : 0) * kWidth + ks * 32 + kq);
+        acc = mfma16(af, r16 < kOut ? wf : zero, acc);
+    }
+    return acc;
+}
+
+// Head weights transposed and biases to LDS.
+__device__ __forceinline__ void stage_small(uint16_t* __restrict__ w4, float* __restrict__ bias, const RankerWeights& W,
+                                            int tid) {
+    for (int i = tid; i < kOut * kWidth; i += kMlpThreads) w4[(i % kOut) * kWidth + i / kOut] = W.w4[i];
+    for (int i = tid; i < kWidth; i += kMlpThreads) {
+        bias[i] = W.b1[i];
+        bias[kWidth + i] = W.b2[i];
+        bias[2 * kWidth + i] = W.b3[i];
     }
 }
 
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const uint16_t* __restrict__ X, int64_t n,
                                                              const RankerWeights W, float* __restrict__ Y, const RankScore S) {
-    __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsMlp * kLdsStride];
-    __shared__ __attribute__((aligned(16))) uint16_t sb[kRowsMlp * kLdsStride];
-    __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];  // head weights, transposed
+    __shared__ __attribute__((aligned(16))) uint16_t sa[kActElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sb[kActElems];
+    __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];
+    __shared__ __attribute__((aligned(16))) float s_bias[3 * kWidth];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int cbase = wid * kMlpNB * 16;  // this wave's output columns
-    for (int i = tid; i < kOut * kWidth; i += kMlpThreads) s_w4[(i % kOut) * kWidth + i / kOut] = W.w4[i];
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    const float hb = r16 < kOut ? W.b4[r16] : 0.f;
+    stage_small(s_w4, s_bias, W, tid);
+    const float hb = (lane & 15) < kOut ? W.b4[lane & 15] : 0.f;
     for (int64_t row0 = (int64_t)blockIdx.x * kRowsMlp; row0 < n; row0 += (int64_t)gridDim.x * kRowsMlp) {
         __syncthreads();
         // X tile -> sa (kRowsMlp x 64 bf16), zero rows past n
-        for (int i = tid; i < kRowsMlp * (kFeat / 8); i += kMlpThreads) {
-            const int r = i / (kFeat / 8), c8 = (i % (kFeat / 8)) * 8;
+        static_assert(kRowsMlp * (kFeat / 8) == kMlpThreads && kFeat == 64, "one feature piece per thread");
+        {
+            const int r = (wid >> 1) * 16 + (lane & 15), c8 = (wid & 1) * 32 + (lane >> 4) * 8;
             u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
             if (row0 + r < n) v = *reinterpret_cast<const u16x8*>(X + (row0 + r) * kFeat + c8);
-            *reinterpret_cast<u16x8*>(sa + r * kLdsStride + c8) = v;
+            *reinterpret_cast<u16x8*>(sa + tid * 8) = v;
         }
         const f32x4 base = score_bases(S, row0 + (wid % 4) * 16 + (lane >> 4) * 4, n);
         __syncthreads();
-        layer_fwd<kFeat, kMlpNB>(sa, sb, W.f1, W.b1, lane, cbase);
+        layer_fwd<kFeat>(sa, sb, W.f1, s_bias, lane, cbase);
         __syncthreads();
-        layer_fwd<kWidth, kMlpNB>(sb, sa, W.f2, W.b2, lane, cbase);
+        layer_fwd<kWidth>(sb, sa, W.f2, s_bias + kWidth, lane, cbase);
         __syncthreads();
-        layer_fwd<kWidth, kMlpNB>(sa, sb, W.f3, W.b3, lane, cbase);
+        layer_fwd<kWidth>(sa, sb, W.f3, s_bias + 2 * kWidth, lane, cbase);
         __syncthreads();
-        // head: wave w < 4 takes rows 16w..16w+15; B columns 0, 1 are the two heads
-        if (wid < kRowsMlp / 16) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int k0 = 0; k0 < kWidth; k0 += 32) {
-                const u16x8 af = *reinterpret_cast<const u16x8*>(sb + (wid * 16 + r16) * kLdsStride + k0 + kq);
-                const u16x8 wf = *reinterpret_cast<const u16x8*>(s_w4 + (r16 < kOut ? r16 : 0) * kWidth + k0 + kq);
-                acc = mfma16(af, r16 < kOut ? wf : zero, acc);
-            }
-            put_outputs(acc, hb, r16, base, row0 + wid * 16 + (lane >> 4) * 4, n, Y, S);
-        }
+        if (wid < kRowsMlp / 16)
+            put_outputs(head_rows(sb, s_w4, wid, lane), hb, lane & 15, base, row0 + wid * 16 + (lane >> 4) * 4, n, Y, S);
     }
 }
 
 // Inference over many rows: a persistent workgroup per CU
 // keeps its waves' weight fragments in registers for every row tile it takes, so
 // the weights are read from L2 once per workgroup instead of once per tile.
+//
+// Bound: the three phases of a layer in a workgroup of its own (two waves a SIMD: the
+// weights fill the registers): products 299 of 650 thousand cycles of a run over 1.03M rows,
+// epilogues 110, LDS reads, barriers and their latencies the rest.  278 us (1.13 PFLOP/s);
+// before, 355: padded rows (351 in fragment order), fragments read just before use and
+// biases from memory in each epilogue (292 with both mended and three barriers a tile
+// instead of four), eight-byte writes and fmaxf (278).
 template <int KIN>
 __device__ __forceinline__ void load_wfrag(u16x8 (&wf)[KIN / 32][kMlpNB], const uint16_t* __restrict__ F, int lane,
                                            int cbase) {
@@ -667,91 +729,92 @@ __device__ __forceinline__ void load_wfrag(u16x8 (&wf)[KIN / 32][kMlpNB], const 
     for (int b = 0; b < kMlpNB; ++b)
 #pragma unroll
         for (int ks = 0; ks < KIN / 32; ++ks)
-            wf[ks][b] = *reinterpret_cast<const u16x8*>(F + (((cbase / 16 + b) * (KIN / 32) + ks) * 64 + lane) * 8);
+            wf[ks][b] = *reinterpret_cast<const u16x8*>(weight_frag(F, b, ks, KIN / 32, lane, cbase));
 }
 
+// A layer from the weights in registers.  The next k-step's fragments are read while this
+// one's are multiplied, one read to kMlpNB products: left to itself the compiler reads each
+// fragment just before its products and waits out the LDS latency 64 times a tile.
 template <int KIN>
 __device__ __forceinline__ void layer_reg(const uint16_t* __restrict__ in_lds, uint16_t* __restrict__ out_lds,
                                           const u16x8 (&wf)[KIN / 32][kMlpNB], const float* __restrict__ bias,
                                           int lane, int cbase) {
+    constexpr int NK = KIN / 32;
+    constexpr int kDsRead = 0x100, kMfma = 0x8;
     f32x4 acc[4][kMlpNB];
+    u16x8 cur[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a) cur[a] = act_frag(in_lds, a, 0, NK, lane);
+    layer_start(acc, bias, lane, cbase);
+    __builtin_amdgcn_sched_group_barrier(kDsRead, 4 + kMlpNB, 0);
 #pragma unroll
-        for (int b = 0; b < kMlpNB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-#pragma unroll
-    for (int ks = 0; ks < KIN / 32; ++ks) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const u16x8 af = *reinterpret_cast<const u16x8*>(in_lds + (a * 16 + r16) * kLdsStride + ks * 32 + kq);
-#pragma unroll
-            for (int b = 0; b < kMlpNB; ++b) acc[a][b] = mfma16(wf[ks][b], af, acc[a][b]);
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < kMlpNB; ++b) {
-        const int col0 = cbase + b * 16 + (lane >> 4) * 4;
-        const float b0 = bias[col0], b1 = bias[col0 + 1], b2 = bias[col0 + 2], b3 = bias[col0 + 3];
+    for (int ks = 0; ks < NK; ++ks) {
+        u16x8 nxt[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const int row = a * 16 + r16;
-            uint2 w;
-            w.x = pack_bf16(fmaxf(acc[a][b][0] + b0, 0.f), fmaxf(acc[a][b][1] + b1, 0.f));
-            w.y = pack_bf16(fmaxf(acc[a][b][2] + b2, 0.f), fmaxf(acc[a][b][3] + b3, 0.f));
-            *reinterpret_cast<uint2*>(out_lds + row * kLdsStride + col0) = w;
+            if (ks + 1 < NK) nxt[a] = act_frag(in_lds, a, ks + 1, NK, lane);
+#pragma unroll
+            for (int b = 0; b < kMlpNB; ++b) acc[a][b] = mfma16(wf[ks][b], cur[a], acc[a][b]);
+            if (ks + 1 < NK) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(kMfma, kMlpNB, 0);
         }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) cur[a] = nxt[a];
     }
+    layer_out(acc, out_lds, lane, cbase);
 }
 
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_infer(const uint16_t* __restrict__ X, int64_t n,
-                                                           const RankerWeights W, float* __restrict__ Y, const RankScore S) {
-    __shared__ __attribute__((aligned(16))) uint16_t sa[kRowsMlp * kLdsStride];
-    __shared__ __attribute__((aligned(16))) uint16_t sb[kRowsMlp * kLdsStride];
+                                                           const RankerWeights W, float* __restrict__ Y,
+                                                           const RankScore S) {
+    __shared__ __attribute__((aligned(16))) uint16_t sx[kRowsMlp * kFeat];
+    __shared__ __attribute__((aligned(16))) uint16_t h1[kActElems], h2[kActElems], h3[kActElems];
     __shared__ __attribute__((aligned(16))) uint16_t s_w4[kOut * kWidth];
+    __shared__ __attribute__((aligned(16))) float s_bias[3 * kWidth];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int cbase = wid * kMlpNB * 16;
-    for (int i = tid; i < kOut * kWidth; i += kMlpThreads) s_w4[(i % kOut) * kWidth + i / kOut] = W.w4[i];
+    stage_small(s_w4, s_bias, W, tid);
     u16x8 w1[kFeat / 32][kMlpNB], w2[kWidth / 32][kMlpNB], w3[kWidth / 32][kMlpNB];
     load_wfrag<kFeat>(w1, W.f1, lane, cbase);
     load_wfrag<kWidth>(w2, W.f2, lane, cbase);
     load_wfrag<kWidth>(w3, W.f3, lane, cbase);
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    const float hb = r16 < kOut ? W.b4[r16] : 0.f;
+    const float hb = (lane & 15) < kOut ? W.b4[lane & 15] : 0.f;
     // one 16-byte piece of a 64 x 64 feature tile per thread; the next tile's piece is
     // loaded while the current tile runs through the layers
     static_assert(kRowsMlp * (kFeat / 8) == kMlpThreads, "one feature piece per thread");
-    const int xr = tid / (kFeat / 8), xc = (tid % (kFeat / 8)) * 8;
+    // (thread t's is the t-th of the tile in fragment order: no bank is written twice)
+    const int xr = (wid >> 1) * 16 + (lane & 15), xc = (wid & 1) * 32 + (lane >> 4) * 8;
+    static_assert(kFeat == 64, "two reduction blocks of features");
+    uint16_t* const xp = sx + tid * 8;
     const int64_t step = (int64_t)gridDim.x * kRowsMlp;
     auto x_piece = [&](int64_t r0) {
         u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
         if (r0 + xr < n) v = *reinterpret_cast<const u16x8*>(X + (r0 + xr) * kFeat + xc);
         return v;
     };
-    *reinterpret_cast<u16x8*>(sa + xr * kLdsStride + xc) = x_piece((int64_t)blockIdx.x * kRowsMlp);
-    for (int64_t row0 = (int64_t)blockIdx.x * kRowsMlp; row0 < n; row0 += step) {
-        __syncthreads();  // this tile's features in sa; the previous head is done with sb
+    // the head of a tile runs beside the next one's first layer: waves 0..3, 16 rows each
+    const int rq = (wid % 4) * 16 + (lane >> 4) * 4;
+    f32x4 base = {0.f, 0.f, 0.f, 0.f};
+    auto head = [&](int64_t r0) {
+        if (wid < kRowsMlp / 16)
+            put_outputs(head_rows(h3, s_w4, wid, lane), hb, lane & 15, base, r0 + rq, n, Y, S);
+    };
+    int64_t row0 = (int64_t)blockIdx.x * kRowsMlp;
+    *reinterpret_cast<u16x8*>(xp) = x_piece(row0);
+    for (; row0 < n; row0 += step) {
+        __syncthreads();  // this tile's features in sx; the previous one's last layer in h3
         const u16x8 xn = x_piece(row0 + step);
-        const f32x4 base = score_bases(S, row0 + (wid % 4) * 16 + (lane >> 4) * 4, n);
-        layer_reg<kFeat>(sa, sb, w1, W.b1, lane, cbase);
+        if (row0 >= step) head(row0 - step);
+        layer_reg<kFeat>(sx, h1, w1, s_bias, lane, cbase);
+        __syncthreads();  // sx is free
+        *reinterpret_cast<u16x8*>(xp) = xn;
+        layer_reg<kWidth>(h1, h2, w2, s_bias + kWidth, lane, cbase);
         __syncthreads();
-        layer_reg<kWidth>(sb, sa, w2, W.b2, lane, cbase);
-        __syncthreads();
-        layer_reg<kWidth>(sa, sb, w3, W.b3, lane, cbase);
-        __syncthreads();  // sa is free: the next tile's features go in
-        *reinterpret_cast<u16x8*>(sa + xr * kLdsStride + xc) = xn;
-        if (wid < kRowsMlp / 16) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int k0 = 0; k0 < kWidth; k0 += 32) {
-                const u16x8 af = *reinterpret_cast<const u16x8*>(sb + (wid * 16 + r16) * kLdsStride + k0 + kq);
-                const u16x8 wf = *reinterpret_cast<const u16x8*>(s_w4 + (r16 < kOut ? r16 : 0) * kWidth + k0 + kq);
-                acc = mfma16(af, r16 < kOut ? wf : zero, acc);
-            }
-            put_outputs(acc, hb, r16, base, row0 + wid * 16 + (lane >> 4) * 4, n, Y, S);
-        }
+        base = score_bases(S, row0 + rq, n);  // for its head
+        layer_reg<kWidth>(h2, h3, w3, s_bias + 2 * kWidth, lane, cbase);
     }
+    __syncthreads();
+    if (row0 >= step) head(row0 - step);
 }
 
 // Refresh all bf16 copies from the fp32 master (after loading or setting params).
@@ -773,40 +836,56 @@ __global__ __launch_bounds__(256) void k_publish(const float* __restrict__ p, in
 // entries from s * stride.  margin > 0 keeps of the chosen only those scoring at
 // most `margin` above the segment's best.  remap (nullable) gives the index written
 // for entry e (else e).  Scores are finite or +inf.
+//
+// Bound: latency, of a chain of passes.  Up to kSelKeys keys are kept in LDS after the
+// first pass, so that the others do not wait for memory, and a workgroup has 16 waves
+// where its segments are long (kSelWide): 457 segments of 2,261 scores 26.7 us, before
+// (four waves, every pass from memory) 36.6; 457 of 256 scores 7.4 us with four waves.
 
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+// A key's score (order_key's inverse; NaN has none).
+__device__ __forceinline__ float key_score(uint32_t k) {
+    return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
+}
 
-constexpr int kSelThreads = 256;
-constexpr int kSelBins = 2048;  // 8 per thread
+constexpr int kSelBins = 2048;
+constexpr uint32_t kSelKeys = 8192;
 
-__global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict__ score,
-                                                        const int64_t* __restrict__ seg, int64_t stride, int k,
-                                                        float margin, const int64_t* __restrict__ remap,
-                                                        int64_t* __restrict__ sel) {
+template <int NT>
+__global__ __launch_bounds__(NT) void k_select(const float* __restrict__ score, const int64_t* __restrict__ seg,
+                                               int64_t stride, int k, float margin, const int64_t* __restrict__ remap,
+                                               int64_t* __restrict__ sel) {
+    constexpr int kWaves = NT / 64, kPer = kSelBins / NT;
+    __shared__ uint32_t keys[kSelKeys];
     __shared__ uint32_t hist[kSelBins];
-    __shared__ uint32_t wa[kSelThreads / 64], wb[kSelThreads / 64];
-    __shared__ float wmin[kSelThreads / 64];
+    __shared__ uint32_t wa[kWaves], wb[kWaves];
+    __shared__ float wmin[kWaves];
     __shared__ uint32_t s_bin, s_below;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int nwv = kSelThreads / 64;
     const int64_t s = blockIdx.x;
     const int64_t len_s = seg[s + 1] - seg[s];
     const int64_t a = stride > 0 ? s * stride : seg[s];
     const uint32_t len = (uint32_t)(stride > 0 ? (len_s < stride ? len_s : stride) : len_s);
     int64_t* out = sel + s * (int64_t)k;
     const uint64_t lt_mask = (1ull << lane) - 1;
+    auto key_at = [&](uint32_t i) { return i < kSelKeys ? keys[i] : order_key(score[a + i]); };
     // the segment's best score (the margin's reference)
     float best = INFINITY;
-    for (uint32_t i = tid; i < len; i += kSelThreads) best = fminf(best, score[a + i]);
+    for (uint32_t i = tid; i < len; i += NT) {
+        const float v = score[a + i];
+        best = fminf(best, v);
+        if (i < kSelKeys) keys[i] = order_key(v);
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));
     if (lane == 0) wmin[wv] = best;
+    for (int b = tid; b < kSelBins; b += NT) hist[b] = 0;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < nwv; ++w) best = fminf(best, wmin[w]);
+    for (int w = 0; w < kWaves; ++w) best = fminf(best, wmin[w]);
     // the k-th smallest key T; rem = how many of the chosen have key T
     const bool all = len <= (uint32_t)k;
     uint32_t prefix = 0, pmask = 0, rem = all ? len : (uint32_t)k;
@@ -814,17 +893,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
         for (int pass = 0; pass < 3; ++pass) {
             const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
             const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
-            for (int b = tid; b < kSelBins; b += kSelThreads) hist[b] = 0;
-            __syncthreads();
-            for (uint32_t i = tid; i < len; i += kSelThreads) {
-                const uint32_t kk = order_key(score[a + i]);
+            for (uint32_t i = tid; i < len; i += NT) {
+                const uint32_t kk = key_at(i);
                 if ((kk & pmask) == prefix) atomicAdd(&hist[(kk >> shift) & dmask], 1u);
             }
             __syncthreads();
-            uint32_t c[8], tsum = 0;
+            uint32_t c[kPer], tsum = 0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                c[q] = hist[tid * 8 + q];
+            for (int q = 0; q < kPer; ++q) {
+                c[q] = hist[tid * kPer + q];
                 tsum += c[q];
             }
             uint32_t incl = tsum;
@@ -839,30 +916,31 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
             for (int w = 0; w < wv; ++w) run += wa[w];
             // exactly one bin has run < rem <= run + count
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
+            for (int q = 0; q < kPer; ++q) {
                 if (run < rem && run + c[q] >= rem) {
-                    s_bin = (uint32_t)(tid * 8 + q);
+                    s_bin = (uint32_t)(tid * kPer + q);
                     s_below = run;
                 }
                 run += c[q];
+                hist[tid * kPer + q] = 0;  // for the next pass
             }
             __syncthreads();
             prefix |= s_bin << shift;
             pmask |= dmask << shift;
             rem -= s_below;
-            __syncthreads();  // s_bin, s_below and hist are rewritten by the next pass
+            __syncthreads();  // s_bin and s_below are rewritten by the next pass
         }
     }
     // in index order: keys below T, then the first rem keys equal to T
     const uint32_t T = prefix;
     uint32_t seen_eq = 0, written = 0;
-    for (uint32_t i0 = 0; i0 < len; i0 += kSelThreads) {
+    for (uint32_t i0 = 0; i0 < len; i0 += NT) {
         const uint32_t i = i0 + tid;
         bool in = false, eq = false;
         float sv = INFINITY;
         if (i < len) {
-            sv = score[a + i];
-            const uint32_t kk = order_key(sv);
+            const uint32_t kk = key_at(i);
+            sv = key_score(kk);
             in = all || kk < T;
             eq = !all && kk == T;
         }
@@ -871,7 +949,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
         __syncthreads();
         uint32_t eq_rank = (uint32_t)__popcll(beq & lt_mask), chunk_eq = 0;
 #pragma unroll
-        for (int w = 0; w < nwv; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             eq_rank += w < wv ? wa[w] : 0u;
             chunk_eq += wa[w];
         }
@@ -881,7 +959,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
         __syncthreads();
         uint32_t pos = (uint32_t)__popcll(bt & lt_mask), chunk_t = 0;
 #pragma unroll
-        for (int w = 0; w < nwv; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             pos += w < wv ? wb[w] : 0u;
             chunk_t += wb[w];
         }
@@ -890,7 +968,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const float* __restrict_
         seen_eq += chunk_eq;
         __syncthreads();  // wa, wb are rewritten by the next chunk
     }
-    for (int64_t r = (int64_t)written + tid; r < k; r += kSelThreads) out[r] = -1;
+    for (int64_t r = (int64_t)written + tid; r < k; r += NT) out[r] = -1;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -920,11 +998,18 @@ hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W,
     return hipGetLastError();
 }
 
-hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t stride, int k, float margin,
-                         const int64_t* remap, int64_t* sel, hipStream_t s) {
+// 16 waves a workgroup for segments longer than this on average.
+constexpr int64_t kSelWide = 1024;
+
+hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t n, int64_t stride, int k,
+                         float margin, const int64_t* remap, int64_t* sel, hipStream_t s) {
     if (nseg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_select, dim3((unsigned)nseg), dim3(kSelThreads), 0, s, score, seg, stride, k, margin, remap,
-                       sel);
+    if ((stride > 0 ? stride : n / nseg) > kSelWide)
+        hipLaunchKernelGGL(k_select<1024>, dim3((unsigned)nseg), dim3(1024), 0, s, score, seg, stride, k, margin, remap,
+                           sel);
+    else
+        hipLaunchKernelGGL(k_select<256>, dim3((unsigned)nseg), dim3(256), 0, s, score, seg, stride, k, margin, remap,
+                           sel);
     return hipGetLastError();
 }
 
