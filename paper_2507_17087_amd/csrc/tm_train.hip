@@ -5,7 +5,7 @@
 // inputs give the same bits.
 //
 // Measured against the 22 launches before (per layer a data and a weight gradient, column
-// sums and reductions, activations row-major between them): 4,096 rows 165 -> 26 us (15,
+// sums and reductions, activations row-major between them): 4,096 rows 165 -> 25 us (14,
 // 10 and 3), 34,833 rows 751 -> 137 us.  With weights and columns row-major (64-byte pieces
 // of 16 lines per load) the two large launches took 25 and 16 us.
 #include <hip/hip_runtime.h>
@@ -53,14 +53,20 @@ __device__ __forceinline__ void tile_product(f32x4 (&acc)[RT][2], const uint16_t
     for (int a = 0; a < RT; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // all activations are requested before the first product waits for one
+    u16x8 x[K / 32][RT];
 #pragma unroll
     for (int ks = 0; ks < K / 32; ++ks)
 #pragma unroll
-        for (int a = 0; a < RT; ++a) {
-            const u16x8 x = *reinterpret_cast<const u16x8*>(in + (a * 16 + r16) * ld + ks * 32 + kq);
+        for (int a = 0; a < RT; ++a)
+            x[ks][a] = *reinterpret_cast<const u16x8*>(in + (a * 16 + r16) * ld + ks * 32 + kq);
+    if (RT == 1) __builtin_amdgcn_sched_group_barrier(0x100, K / 32, 0);
 #pragma unroll
-            for (int b = 0; b < 2; ++b) acc[a][b] = mfma16(w[ks][b], x, acc[a][b]);
-        }
+    for (int ks = 0; ks < K / 32; ++ks)
+#pragma unroll
+        for (int a = 0; a < RT; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] = mfma16(w[ks][b], x[ks][a], acc[a][b]);
 }
 
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
@@ -181,6 +187,7 @@ __global__ __launch_bounds__(kTrainThreads) void k_forward_backward(const TrainB
     load_bias(bias1, W.b1, lane, c0);
     load_bias(bias2, W.b2, lane, c0);
     load_bias(bias3, W.b3, lane, c0);
+    const float hb = W.b4[r16 < kOut ? r16 : 0];
     for (int i = tid; i < kOut * kWidth; i += kTrainThreads) s_w4[(i % kOut) * kWidth + i / kOut] = W.w4[i];
     // features (rows through the permutation when there is one) and targets
     for (int i = tid; i < R * (kFeat / 4); i += kTrainThreads) {
@@ -224,7 +231,6 @@ __global__ __launch_bounds__(kTrainThreads) void k_forward_backward(const TrainB
             y = mfma16(af, r16 < kOut ? hw : zero, y);
         }
         if (r16 < kOut) {
-            const float hb = W.b4[r16];
 #pragma unroll
             for (int r = 0; r < 4; ++r) s_y[wid * 16 + (lane >> 4) * 4 + r][r16] = y[r] + hb;
         }
@@ -263,10 +269,16 @@ __global__ __launch_bounds__(kTrainThreads) void k_forward_backward(const TrainB
         part[5 * kWidth + tid] = p;
     }
     // dH3 = (dY W4^T) where H3 > 0
-    for (int i = tid; i < R * kWidth; i += kTrainThreads) {
-        const int r = i / kWidth, k = i % kWidth;
-        const float g = s_y[r][0] * bf2f(s_w4[k]) + s_y[r][1] * bf2f(s_w4[kWidth + k]);
-        da[r * kLd + k] = (h3[r * kLd + k] & 0x7fffu) ? f2bf(g) : (uint16_t)0;
+    for (int i = tid; i < R * (kWidth / 8); i += kTrainThreads) {
+        const int r = i / (kWidth / 8), k = i % (kWidth / 8) * 8;
+        const float y0 = s_y[r][0], y1 = s_y[r][1];
+        const u16x8 u = *reinterpret_cast<const u16x8*>(s_w4 + k), v = *reinterpret_cast<const u16x8*>(s_w4 + kWidth + k);
+        const u16x8 h = *reinterpret_cast<const u16x8*>(h3 + r * kLd + k);
+        float g[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g[j] = (h[j] & 0x7fffu) ? y0 * bf2f(u[j]) + y1 * bf2f(v[j]) : 0.f;
+        *reinterpret_cast<uint4*>(da + r * kLd + k) = make_uint4(pack_bf16(g[0], g[1]), pack_bf16(g[2], g[3]),
+                                                                 pack_bf16(g[4], g[5]), pack_bf16(g[6], g[7]));
     }
     lds_barrier();
     tile_product<kWidth, RT>(acc, da, kLd, wa, lane);
