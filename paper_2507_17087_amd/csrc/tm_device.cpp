@@ -83,6 +83,14 @@ static int layout_tables(DevCand& d, int H, const int32_t* halo) {
     return TM_OK;
 }
 
+// Blocks of all launch dims where each is projected onto at most one final dim, one for a
+// dim without a projection.
+static int32_t blocks_and_dims(const DevCand& d) {
+    int64_t n = d.lrank;
+    for (int j = 0; j < d.frank; ++j) n += d.fshape[j];
+    return (int32_t)std::min<int64_t>(n, INT32_MAX);
+}
+
 // Counting work items of every candidate, and the item table (the candidate of each
 // item, written by the table build) after the tables in the arena.
 static void layout_items(Compiled& cp, int64_t tuples_per_item) {
@@ -159,6 +167,7 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
         cp.points += d.npoints;
         cp.max_points = std::max(cp.max_points, d.npoints);
         cp.max_vol = std::max(cp.max_vol, d.vol);
+        cp.max_blocks = std::max(cp.max_blocks, blocks_and_dims(d));
         cp.min_row = std::min(cp.min_row, d.L);
     }
     cp.tables_words = words;
@@ -792,7 +801,7 @@ extern "C" int tm_select_best(const tm_stencil_cost* d_costs, const int64_t* seg
 namespace tmk {
 
 static void search_free(SearchBufs& b) {
-    void* ptrs[] = {b.X, b.base, b.score, b.pre, b.seg, b.sel, b.sub_out, b.all_out};
+    void* ptrs[] = {b.X, b.base, b.score, b.est, b.pre, b.seg, b.sel, b.sub_out, b.all_out};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     b = SearchBufs{};
@@ -1168,7 +1177,7 @@ int plan_block_estimates(const tm_plan* p, double* d_est, hipStream_t s) {
 
 EstimateBatch plan_estimates(const tm_plan* p) {
     const EvalPlan& e = p->cp.eval;
-    return EstimateBatch{p->d_cands, p->d_evals, p->cp.max_vol, {e.halo[0], e.halo[1], e.halo[2], e.halo[3]},
+    return EstimateBatch{p->d_cands, p->d_evals, p->cp.max_vol, p->cp.max_blocks, {e.halo[0], e.halo[1], e.halo[2], e.halo[3]},
                          p->d_hdr->halo, e.all_simple};
 }
 
@@ -1199,9 +1208,12 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
         if (b.cap_pre < npre) {
             TM_HIP(hipStreamSynchronize(s));
             if (b.pre) (void)hipFree(b.pre);
+            if (b.est) (void)hipFree(b.est);
             b.pre = nullptr;
+            b.est = nullptr;
             b.cap_pre = 0;
-            if (hipMalloc((void**)&b.pre, (size_t)npre * 8) != hipSuccess)
+            if (hipMalloc((void**)&b.pre, (size_t)npre * 8) != hipSuccess ||
+                hipMalloc((void**)&b.est, (size_t)npre * 2 * sizeof(double)) != hipSuccess)
                 return set_error(TM_ENOMEM, "prefilter buffer");
             b.cap_pre = npre;
         }

@@ -20,6 +20,7 @@ struct Compiled {
     int32_t max_words = 0;      // largest LDS-staged prefix
     int32_t max_all_words = 0;  // largest whole table block of one candidate
     int32_t max_vol = 0;        // largest final-space volume
+    int32_t max_blocks = 0;     // most blocks of all launch dims of a candidate (estimates' records)
     int32_t min_row = INT32_MAX;  // shortest row (last extent)
     int32_t cnt_words = 0;      // LDS words of the counting launch (largest staged owner table + class blocks)
     int64_t tuples = 0;         // class-tuple bound of the batch (sum of the candidates')
@@ -35,6 +36,7 @@ struct SearchBufs {
     uint16_t* X = nullptr;          // [n][kFeat] bf16 features
     float* base = nullptr;          // [n] the scores' bases
     float* score = nullptr;         // [cap_sc] ranking scores (both stages)
+    double* est = nullptr;          // [nseg*prefilter][2] their block-model estimates
     int64_t* pre = nullptr;         // [nseg*prefilter] candidates kept by the network's scores
     int64_t* seg = nullptr;         // [nseg+1] instance segments
     int64_t* sel = nullptr;         // [nseg*k] chosen candidate indices

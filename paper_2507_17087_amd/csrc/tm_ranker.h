@@ -118,13 +118,13 @@ struct EstimateBatch {
     const DevCand* cands;
     const DevEval* evals;
     int32_t max_vol;
+    int32_t max_blocks;  // most blocks of all launch dims of a simple candidate
     int32_t halo[TM_MAX_LRANK];
     const int32_t* d_halo;
     bool all_simple;
 };
 // Block-model estimates of entries 0..n-1: candidate idx[i] (negative: skipped) or i
-// without idx; to est[2i..] (nullable) and, as the second stage's score, score[i]
-// (nullable).
+// without idx; to est[2i..] and, as the second stage's score, score[i] (nullable).
 hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t n, float lambda, double* est,
                             float* score, hipStream_t s);
 // The ranking scores of rows with these bases (score == nullptr: outputs instead).

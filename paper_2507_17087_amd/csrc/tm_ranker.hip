@@ -29,15 +29,21 @@ __device__ __forceinline__ float lg2(double x) { return (float)log2(x); }
 // distinct foreign coordinate) pairs along it times the other extents times the largest
 // fraction of adjacent final coordinates whose owners (nodes) differ.
 constexpr int kCrossMax = 16384;
+constexpr int kEstRecords = 4096;     // most block records in LDS (of the dims but the largest there are at most 129)
 constexpr int kStatsStage = 1024;     // launch dims up to this extent have their contributions staged in LDS
 constexpr int kStatsSmallVol = 2048;  // owner-table words of the first (small-candidate) launch
 
-// The second stage's score of an estimate: log2(1 + cells) + lambda log2(1 + inter-node
-// cells); +inf when that is not finite.
-__device__ __forceinline__ float estimate_score(double e0, double e1, float lambda) {
-    const float b0 = kBaseScale * (lg2(1.0 + e0) / kBaseScale), b1 = kBaseScale * (lg2(1.0 + e1) / kBaseScale);
+// The second stage's scores of n estimates: log2(1 + cells) + lambda log2(1 + inter-node
+// cells); +inf when that is not finite.  A launch of its own: in the estimates' workgroups
+// one lane would run the two 64-bit logarithms for all.
+__global__ __launch_bounds__(256) void k_estimate_scores(const double2* __restrict__ est, int64_t n, float lambda,
+                                                         float* __restrict__ score) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double2 e = est[i];
+    const float b0 = kBaseScale * (lg2(1.0 + e.x) / kBaseScale), b1 = kBaseScale * (lg2(1.0 + e.y) / kBaseScale);
     const float v = b0 + lambda * b1;
-    return __builtin_isfinite(v) ? v : INFINITY;
+    score[i] = __builtin_isfinite(v) ? v : INFINITY;
 }
 
 struct EstimateArgs {
@@ -47,23 +53,26 @@ struct EstimateArgs {
     int32_t halo[TM_MAX_LRANK];
     int32_t vmin, vmax;  // volumes this launch takes: above vmin, up to vmax (kCrossMax: zeros beyond)
     int32_t cap;         // LDS words of keys: the largest volume it meets
-    float lambda;
+    int32_t records;     // block records there is room for
     double* est;
-    float* score;
 };
 
-// A workgroup per entry: the owner table in LDS, then a thread per final coordinate.  Its
-// block along a dim starts at cell ceil(a l / s), in closed form; every sum is of whole
-// numbers below 2^53, exact in any order.  Bound: VALU issue (as the stencil evaluation).
-// Measured on 116,992 kept candidates, against block tables in LDS and a descriptor of 960
-// bytes staged word by word before: 741 -> 270 us.
+// A workgroup per entry: the owner table and, per launch dim and block of it, a record in
+// LDS -- cells of the block; offset to the final coordinate of the cell before it, and cells
+// that see its boundary (none before the first block) -- then a thread per tuple of blocks.
+// A block starts at cell ceil(a l / s), in closed form; every sum is of whole numbers below
+// 2^53, exact in any order.  Bound: VALU issue (as the stencil evaluation).  Measured on
+// 116,992 kept candidates, against block tables in LDS and a descriptor of 960 bytes staged
+// word by word 741 us, against blocks and boundaries computed per final coordinate 285 us:
+// EST_US us.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
-    extern __shared__ __attribute__((aligned(16))) int32_t key[];
+    extern __shared__ __attribute__((aligned(16))) int32_t key[];  // owners, then the records
     __shared__ DevEval ev;
     __shared__ double dred[NT / 64][2];
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x, lane = tid & 63;
+    i32x2* rec = reinterpret_cast<i32x2*>(key + A.cap);
     for (int64_t i = blockIdx.x; i < A.n; i += gridDim.x) {
         const int64_t ci = A.idx ? wave_uniform64(A.idx[i]) : i;
         if (ci < 0) continue;
@@ -78,53 +87,90 @@ __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
         if (!beyond) {
             const int K = wave_uniform(ev.lrank), gb = wave_uniform(ev.gbits);
             owner_table(ev, key, 0, vol, -1, tid, NT);
-            // per launch dim: its final dim's size and stride (1 and no boundary for size 1)
-            uint32_t st[TM_MAX_LRANK], sz[TM_MAX_LRANK];
-            float rst[TM_MAX_LRANK], rsz[TM_MAX_LRANK];
-            double ld[TM_MAX_LRANK], sd[TM_MAX_LRANK], rs[TM_MAX_LRANK], rl[TM_MAX_LRANK];
+            // per launch dim: its final dim's size and stride (one block without a projection)
+            int32_t st[TM_MAX_LRANK], size[TM_MAX_LRANK], rest = 0, most = 0, D = 0;
 #pragma unroll
             for (int d = 0; d < TM_MAX_LRANK; ++d) {
-                const bool on = d < K && ev.dim[d].nblk > 0;
-                const DevProj& p = ev.pj[on ? ev.dim[d].first : 0];
-                sz[d] = on ? (uint32_t)p.s : 1u;
-                st[d] = on ? (uint32_t)p.stride : 1u;
-                rst[d] = 1.0f / (float)st[d];
-                rsz[d] = 1.0f / (float)sz[d];
-                ld[d] = d < K ? (double)ev.dim[d].l : 1.0;
-                sd[d] = (double)sz[d];
-                rs[d] = on ? p.rs : 1.0;
-                rl[d] = d < K ? ev.dim[d].rl : 1.0;
-            }
-            lds_sync(NW);
-            for (int32_t v = tid; v < vol; v += NT) {
-                const int32_t kv = key[v];
-                uint32_t a[TM_MAX_LRANK], x0[TM_MAX_LRANK];
-                double wd[TM_MAX_LRANK];
-#pragma unroll
-                for (int d = 0; d < TM_MAX_LRANK; ++d) {
-                    if (d >= K) {
-                        wd[d] = 1;
-                        continue;
-                    }
-                    const uint32_t q = div_small((uint32_t)v, rst[d]);
-                    a[d] = q - __umul24(div_small(q, rsz[d]), sz[d]);
-                    const double n0 = fma((double)a[d], ld[d], sd[d] - 1.0);
-                    x0[d] = div_wide(n0, rs[d]);
-                    wd[d] = (double)(div_wide(n0 + ld[d], rs[d]) - x0[d]);
+                const bool on = d < K && wave_uniform(ev.dim[d].nblk) > 0;
+                const int j = on ? wave_uniform(ev.dim[d].first) : 0;
+                size[d] = on ? wave_uniform(ev.pj[j].s) : 1;
+                st[d] = on ? wave_uniform(ev.pj[j].stride) : 0;
+                rest += d < K ? size[d] : 0;
+                if (d < K && size[d] > most) {
+                    most = size[d];
+                    D = d;
                 }
+            }
+            rest -= most;
+            // the records of every dim, of the largest (D) as many at a time as there is room
+            // for (A.records; all of them below kEstRecords)
+            const int32_t room = A.records - rest;
+            for (int32_t g0 = 0; g0 < most; g0 += room) {
+                if (g0 > 0) lds_sync(NW);  // the previous range's are no longer read
+                int32_t sz[TM_MAX_LRANK], lo[TM_MAX_LRANK], first[TM_MAX_LRANK], all = 0;
+                uint32_t tuples = 1;
+                float rsz[TM_MAX_LRANK];
 #pragma unroll
                 for (int d = 0; d < TM_MAX_LRANK; ++d) {
-                    const uint32_t h = (uint32_t)A.halo[d];
-                    if (d >= K || a[d] == 0 || h == 0 || wd[d] <= 0.0) continue;  // no boundary, or an empty block
-                    const uint32_t b = x0[d], r = (uint32_t)ld[d] - b;
-                    double w = (double)((h < b ? h : b) + (h < r ? h : r));
+                    lo[d] = d == D ? g0 : 0;
+                    sz[d] = d == D ? (most - g0 < room ? most - g0 : room) : size[d];
+                    rsz[d] = 1.0f / (float)sz[d];
+                    first[d] = all;
+                    all += d < K ? sz[d] : 0;
+                    tuples *= (uint32_t)sz[d];
+                }
+                for (int32_t r = tid; r < all; r += NT) {
+                    int d = 0;
+                    int32_t f = -lo[0];
+                    uint32_t h = (uint32_t)A.halo[0];
 #pragma unroll
-                    for (int e = 0; e < TM_MAX_LRANK; ++e)
-                        if (e != d) w *= wd[e];
-                    const uint32_t al = block_index(b - 1, sd[d], rl[d]);  // the block of the cell before b
-                    const int32_t kl = key[v - (int32_t)((a[d] - al) * st[d])];
-                    if (kl != kv) tot += w;
-                    if ((kl >> gb) != (kv >> gb)) inter += w;
+                    for (int e = 1; e < TM_MAX_LRANK; ++e)
+                        if (e < K && r >= first[e]) {
+                            d = e;
+                            f = first[e] - lo[e];
+                            h = (uint32_t)A.halo[e];
+                        }
+                    const LaneDim ld = lane_dim(ev, d, false);
+                    const uint32_t x = (uint32_t)(r - f);
+                    const double rs = ld.nblk ? ld.brs : 1.0, n0 = fma((double)x, (double)ld.l, ld.bs - 1.0);
+                    const uint32_t x0 = div_wide(n0, rs), cells = div_wide(n0 + (double)ld.l, rs) - x0;
+                    uint32_t seen = 0, off = 0;
+                    if (x > 0 && cells > 0) {  // else no boundary, or an empty block
+                        const uint32_t after = ld.l - x0;
+                        seen = (h < x0 ? h : x0) + (h < after ? h : after);
+                        off = (x - block_index(x0 - 1, ld.bs, ld.rl)) * ld.bst;
+                    }
+                    rec[r] = i32x2{(int32_t)cells, (int32_t)(off | seen << 16)};
+                }
+                lds_sync(NW);
+                for (uint32_t t = tid; t < tuples; t += NT) {
+                    uint32_t q = t;
+                    int32_t v = 0;
+                    i32x2 e[TM_MAX_LRANK];
+                    double wd[TM_MAX_LRANK];
+#pragma unroll
+                    for (int d = TM_MAX_LRANK - 1; d >= 0; --d) {
+                        wd[d] = 1;
+                        if (d >= K) continue;
+                        const uint32_t hi = d > 0 ? div_small(q, rsz[d]) : 0, x = q - __umul24(hi, (uint32_t)sz[d]);
+                        q = hi;
+                        e[d] = rec[first[d] + (int32_t)x];
+                        v += (int32_t)__umul24(x + (uint32_t)lo[d], (uint32_t)st[d]);
+                        wd[d] = (double)(uint32_t)e[d].x;
+                    }
+                    const int32_t kv = key[v];
+#pragma unroll
+                    for (int d = 0; d < TM_MAX_LRANK; ++d) {
+                        if (d >= K) continue;
+                        const int32_t kl = key[v - (e[d].y & 0xffff)];
+                        const uint32_t seen = (uint32_t)e[d].y >> 16;
+                        double w = 1;
+#pragma unroll
+                        for (int f = 0; f < TM_MAX_LRANK; ++f)
+                            if (f != d && f < K) w *= wd[f];
+                        tot = fma((double)(kl != kv ? seen : 0u), w, tot);
+                        inter = fma((double)((kl >> gb) != (kv >> gb) ? seen : 0u), w, inter);
+                    }
                 }
             }
 #pragma unroll
@@ -144,10 +190,7 @@ __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
                 }
             }
         }
-        if (tid == 0) {
-            if (A.est) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
-            if (A.score) A.score[i] = estimate_score(tot, inter, A.lambda);
-        }
+        if (tid == 0) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
     }
 }
 
@@ -294,10 +337,7 @@ __global__ __launch_bounds__(256) void k_crossing_estimates(const DevCand* __res
                 inter += dred[w][1];
             }
         }
-        if (tid == 0) {
-            if (A.est) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
-            if (A.score) A.score[i] = estimate_score(tot, inter, A.lambda);
-        }
+        if (tid == 0) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
     }
 }
 
@@ -311,9 +351,7 @@ hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t 
     A.idx = idx;
     A.n = n;
     for (int d = 0; d < TM_MAX_LRANK; ++d) A.halo[d] = b.halo[d];
-    A.lambda = lambda;
     A.est = est;
-    A.score = score;
     // most candidates are small: a first launch with a small owner table in LDS (more
     // workgroups per CU) takes the volumes up to kStatsSmallVol, a second one, sized for
     // the batch's largest, the rest; large batches take one-wave workgroups
@@ -323,14 +361,19 @@ hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t 
         A.vmax = last ? kCrossMax : kStatsSmallVol;
         A.cap = ((last ? top : kStatsSmallVol) + 3) & ~3;
         const size_t lds = (size_t)A.cap * 4;
+        A.records = std::min({b.max_blocks, A.cap + TM_MAX_LRANK, kEstRecords});
+        const size_t records = (size_t)A.records * 8;
         if (n >= kSmallBlockBatch)
-            hipLaunchKernelGGL(k_block_estimates<64>, dim3(g), dim3(64), lds, s, A);
+            hipLaunchKernelGGL(k_block_estimates<64>, dim3(g), dim3(64), lds + records, s, A);
         else
-            hipLaunchKernelGGL(k_block_estimates<256>, dim3(g), dim3(256), lds, s, A);
+            hipLaunchKernelGGL(k_block_estimates<256>, dim3(g), dim3(256), lds + records, s, A);
         if (!b.all_simple)
             hipLaunchKernelGGL(k_crossing_estimates, dim3(g), dim3(n >= kSmallBlockBatch ? 64 : 256),
                                lds + kStatsStage * 4, s, b.cands, b.d_halo, A);
     }
+    if (score)
+        hipLaunchKernelGGL(k_estimate_scores, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           reinterpret_cast<const double2*>(est), n, lambda, score);
     return hipGetLastError();
 }
 

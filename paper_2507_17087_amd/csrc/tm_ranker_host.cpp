@@ -479,7 +479,7 @@ int plan_ranked_search(tm_plan* p, tm_ranker* r, const int64_t* seg, int64_t nse
         // choose the topk
         const int64_t m = nseg * (int64_t)prefilter;
         if (e == hipSuccess) e = launch_select(sb->score, sb->seg, nseg, n, 0, prefilter, 0.f, nullptr, sb->pre, s);
-        if (e == hipSuccess) e = launch_estimates(plan_estimates(p), sb->pre, m, lambda, nullptr, sb->score, s);
+        if (e == hipSuccess) e = launch_estimates(plan_estimates(p), sb->pre, m, lambda, sb->est, sb->score, s);
         if (e == hipSuccess) e = launch_select(sb->score, sb->seg, nseg, n, prefilter, topk, margin, sb->pre, sb->sel, s);
     } else if (e == hipSuccess) {
         e = launch_select(sb->score, sb->seg, nseg, n, 0, topk, margin, nullptr, sb->sel, s);
