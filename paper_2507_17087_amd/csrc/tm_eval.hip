@@ -234,7 +234,7 @@ __device__ __forceinline__ void count_general(const int32_t* lds, const GroupDim
     }
 }
 
-// Counts one part of candidate c: owner table, records, tuples.  LDS: the owner table,
+// Counts one part of candidate c: records, tuples.  LDS: the owner table (being written),
 // the records of every dim but D, then a range of D's.  Launch ranks below the tuple
 // loop's K take dims of one group of one coordinate (the record at `one`).
 template <int NT, int H, bool CYC>
@@ -255,8 +255,6 @@ __device__ __forceinline__ void eval_part(const DevEval& c, const EvalArgs& A, i
     int32_t GD = G[0];
 #pragma unroll
     for (int d = 1; d < TM_MAX_LRANK; ++d) GD = d == D ? G[d] : GD;
-    // node-level tables keep the node of each owner (GPU bits cleared)
-    owner_table(c, lds, 0, vol, A.node_level ? ~((1 << gb) - 1) : -1, tid, NT);
     const int32_t ga = parts > 1 ? (int32_t)((int64_t)GD * part / parts) : 0,
                   gz = parts > 1 ? (int32_t)((int64_t)GD * (part + 1) / parts) : GD;
     const int32_t fit = (A.lds_words - t0) / stride - rest, room = fit > 1 ? fit : 1;
@@ -318,15 +316,22 @@ __device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t 
     __shared__ int64_t sb[NT / 64], si[NT / 64], sx[NT / 64], s_best;
     const int t = threadIdx.x;
     int64_t kb = INT64_MAX, ki = INT64_MAX, kx = INT64_MAX;
-    for (int64_t i = t; i < n; i += NT) {
-        int64_t* o = reinterpret_cast<int64_t*>(const_cast<tm_stencil_cost*>(&out[i]));
-        const int64_t b = __hip_atomic_load(o + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t ib = __hip_atomic_load(o + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cost_less(b, ib, i, kb, ki, kx)) {
-            kb = b;
-            ki = ib;
-            kx = i;
+    for (int64_t i0 = t; i0 < n; i0 += 4 * NT) {  // four rows in flight; past the end the last one again
+        int64_t b[4], ib[4], x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = i0 + u * NT < n ? i0 + u * NT : n - 1;
+            int64_t* o = reinterpret_cast<int64_t*>(const_cast<tm_stencil_cost*>(&out[x[u]]));
+            b[u] = __hip_atomic_load(o + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ib[u] = __hip_atomic_load(o + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (cost_less(b[u], ib[u], x[u], kb, ki, kx)) {
+                kb = b[u];
+                ki = ib[u];
+                kx = x[u];
+            }
     }
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1) {
@@ -357,7 +362,17 @@ __device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t 
     __syncthreads();
     stage_eval(&ev, evals + wave_uniform64(s_best), t);
     __syncthreads();
-    owner_table<true>(ev, ids, 0, wave_uniform(ev.vol), -1, t, NT);
+    owner_ids(ev, ids, wave_uniform(ev.vol), t, NT);
+}
+
+// The item of a workgroup's turn.  Workgroups go to the eight XCDs in turn, and batches are
+// often menus of chains whose length is a multiple of eight, so that an XCD would take the
+// same few chains of every menu, cheap or expensive ones: each group of eight is rotated by
+// its place.  219,424 search candidates (menus of 32): 893 us in order (the CUs busy 62% of
+// it), 598 rotated.
+__device__ __forceinline__ int64_t spread_item(int64_t turn, int64_t items) {
+    if (turn >= (items & ~int64_t(7))) return turn;
+    return (turn & ~int64_t(7)) | ((turn + (turn >> 3) + (turn >> 6) + (turn >> 9)) & 7);
 }
 
 constexpr int kOneRecord = 2 + 4 * kMaxHalo;  // words of the largest record without masks
@@ -373,18 +388,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : 
     const int64_t items = A.n * A.parts;
     // the record of a dim of one coordinate: {0, 1}, no offsets
     if (tid < kOneRecord) lds[A.lds_words + tid] = tid == 1 ? 1 : 0;
-    for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    for (int64_t turn = blockIdx.x; turn < items; turn += gridDim.x) {
+        const int64_t item = spread_item(turn, items);
         const int64_t row = A.parts == 1 ? item : item / A.parts;
         const int part = (int)(item - row * A.parts);
         const int64_t ci = A.idx ? wave_uniform64(A.idx[row]) : row;
         if (ci < 0) continue;
-        if (item != (int64_t)blockIdx.x) lds_sync(NW);  // the previous item's LDS is no longer read
+        if (turn != (int64_t)blockIdx.x) lds_sync(NW);  // the previous item's LDS is no longer read
         stage_eval(&ev, A.evals + ci, tid);
         lds_sync(NW);
         const int32_t words = wave_uniform(ev.words), own = wave_uniform(ev.parts);
         const int parts = own < A.parts ? own : A.parts;
         if (words <= A.min_words || words > A.max_words || part >= parts) continue;  // another launch's, or no such part
         double tot = 0, inter = 0;
+        // node-level tables keep the node of each owner (GPU bits cleared)
+        owner_table(ev, lds, 0, wave_uniform(ev.vol), A.node_level ? ~((1 << wave_uniform(ev.gbits)) - 1) : -1, tid, NT);
         if (wave_uniform(ev.flags) & kEvalCyclic)
             eval_part<NT, H, true>(ev, A, lds, A.lds_words, part, parts, tid, tot, inter);
         else

@@ -57,23 +57,20 @@ __device__ __forceinline__ void owner_table_pass(const DevEval& c, int32_t* __re
     const uint32_t g = (uint32_t)c.gpus;
     const int gb = wave_uniform(c.gbits), nops = wave_uniform(c.nops);
     const float rg = c.rgpus;
-    for (int32_t base = v0 + tid; base < v1; base += KPT * nt) {
-        uint32_t L[KPT];
+    {
+        uint32_t m[KPT], l0[KPT], h[KPT];
 #pragma unroll
         for (int i = 0; i < KPT; ++i) {
-            const int32_t v = base + i * nt;
-            L[i] = (uint32_t)(v < v1 ? v : v1 - 1);  // out-of-range slots repeat a valid index
+            const int32_t v = v0 + tid + i * nt;
+            m[i] = (uint32_t)(v < v1 ? v : v1 - 1);  // out-of-range slots repeat a valid index
+            l0[i] = h[i] = 0;
         }
-        for (int t = nops - 1; t >= 0; --t) {
+        // op 0 reaches Machine(GPU) = (nodes, gpus), so a merge there is of its two dims
+        const bool fused = nops > 0 && (wave_uniform(c.inv[0].kind) & kOpKind) == TM_MERGE;
+        for (int t = nops - 1; t >= (fused ? 1 : 0); --t) {
             const DevOp& op = c.inv[t];
             const int32_t kf = wave_uniform(op.kind), kind = kf & kOpKind;
             const uint32_t lo = op.lo, wi = op.wi, wo = op.wo;
-            uint32_t l0[KPT], h[KPT], m[KPT];
-#pragma unroll
-            for (int i = 0; i < KPT; ++i) {
-                l0[i] = h[i] = 0;
-                m[i] = L[i];
-            }
             if (!(kf & kOpNoLo)) {
                 const float rlo = op.rlo;
 #pragma unroll
@@ -174,28 +171,51 @@ __device__ __forceinline__ void owner_table_pass(const DevEval& c, int32_t* __re
 #pragma unroll
                 for (int i = 0; i < KPT; ++i) m[i] += r[i];
             }
+            if (!(kf & kOpNoHi)) {
 #pragma unroll
-            for (int i = 0; i < KPT; ++i) L[i] = __umul24(__umul24(h[i], wi) + m[i], lo) + l0[i];
+                for (int i = 0; i < KPT; ++i) m[i] += __umul24(h[i], wi);
+            }
+            if (!(kf & kOpNoLo)) {
+#pragma unroll
+                for (int i = 0; i < KPT; ++i) m[i] = __umul24(m[i], lo) + l0[i];
+            }
         }
+        // m: the processor, or where the merge is fused its index with the node fastest
+        const uint32_t d = fused ? c.inv[0].u[1] : g;
+        const float rd = fused ? c.inv[0].f[1] : rg;
 #pragma unroll
         for (int i = 0; i < KPT; ++i) {
-            const int32_t v = base + i * nt;
-            if (v < v1) {
-                const uint32_t node = IDS ? 0 : div_small(L[i], rg);
-                out[v] = IDS ? (int32_t)L[i] : (int32_t)((node << gb) | (L[i] - __umul24(node, g))) & keep;
+            const int32_t v = v0 + tid + i * nt;
+            if (IDS && !fused) {
+                if (v < v1) out[v] = (int32_t)m[i];
+                continue;
             }
+            const uint32_t q = div_small(m[i], rd), r = m[i] - __umul24(q, d);
+            const uint32_t node = fused ? r : q, gpu = fused ? q : r;
+            if (v < v1) out[v] = IDS ? (int32_t)(__umul24(node, g) + gpu) : (int32_t)((node << gb) | gpu) & keep;
         }
     }
 }
 
-// The whole range, keys per thread by its length (slots past the end repeat work).
+// The whole range: passes of four coordinates a thread, the rest in one of as many as are
+// left (on 219,424 search candidates of 245 coordinates each 4.5 a thread on average; with
+// passes of one, two or four 5.2).
 template <bool IDS = false>
 __device__ __forceinline__ void owner_table(const DevEval& c, int32_t* __restrict__ out, int32_t v0, int32_t v1,
                                             int32_t keep, int tid, int nt) {
-    const int32_t len = v1 - v0;
-    if (len <= nt) owner_table_pass<1, IDS>(c, out, v0, v1, keep, tid, nt);
-    else if (len <= 2 * nt) owner_table_pass<2, IDS>(c, out, v0, v1, keep, tid, nt);
-    else owner_table_pass<4, IDS>(c, out, v0, v1, keep, tid, nt);
+    for (; v0 < v1; v0 += 4 * nt) {
+        const int32_t len = v1 - v0;
+        if (len <= nt) owner_table_pass<1, IDS>(c, out, v0, v1, keep, tid, nt);
+        else if (len <= 2 * nt) owner_table_pass<2, IDS>(c, out, v0, v1, keep, tid, nt);
+        else if (len <= 3 * nt) owner_table_pass<3, IDS>(c, out, v0, v1, keep, tid, nt);
+        else owner_table_pass<4, IDS>(c, out, v0, v1, keep, tid, nt);
+    }
+}
+
+// Processor ids of all coordinates, in little code (beside another table in a kernel: the
+// instruction cache holds 64 KB).
+__device__ __forceinline__ void owner_ids(const DevEval& c, int32_t* __restrict__ out, int32_t vol, int tid, int nt) {
+    for (int32_t v0 = 0; v0 < vol; v0 += nt) owner_table_pass<1, true>(c, out, v0, vol, -1, tid, nt);
 }
 
 // ------------------------------------------------------------------ coordinates

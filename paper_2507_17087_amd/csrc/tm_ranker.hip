@@ -29,7 +29,9 @@ __device__ __forceinline__ float lg2(double x) { return (float)log2(x); }
 // distinct foreign coordinate) pairs along it times the other extents times the largest
 // fraction of adjacent final coordinates whose owners (nodes) differ.
 constexpr int kCrossMax = 16384;
-constexpr int kEstRecords = 4096;     // most block records in LDS (of the dims but the largest there are at most 129)
+// Most block records in LDS, of one-wave and of four-wave workgroups (of the dims but the
+// largest there are at most 130): few, so that workgroups are many.
+constexpr int kEstRecordsWave = 256, kEstRecords = 4096;
 constexpr int kStatsStage = 1024;     // launch dims up to this extent have their contributions staged in LDS
 constexpr int kStatsSmallVol = 2048;  // owner-table words of the first (small-candidate) launch
 
@@ -62,9 +64,9 @@ struct EstimateArgs {
 // that see its boundary (none before the first block) -- then a thread per tuple of blocks.
 // A block starts at cell ceil(a l / s), in closed form; every sum is of whole numbers below
 // 2^53, exact in any order.  Bound: VALU issue (as the stencil evaluation).  Measured on
-// 116,992 kept candidates, against block tables in LDS and a descriptor of 960 bytes staged
-// word by word 741 us, against blocks and boundaries computed per final coordinate 285 us:
-// EST_US us.
+// 116,992 kept candidates: block tables in LDS and a descriptor of 960 bytes staged word by
+// word 741 us, blocks and boundaries computed per final coordinate 285, these records 248,
+// with 256 of them at most (six workgroups a CU more) and a shorter owner table 203.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
     extern __shared__ __attribute__((aligned(16))) int32_t key[];  // owners, then the records
@@ -103,7 +105,7 @@ __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
             }
             rest -= most;
             // the records of every dim, of the largest (D) as many at a time as there is room
-            // for (A.records; all of them below kEstRecords)
+            // for (A.records)
             const int32_t room = A.records - rest;
             for (int32_t g0 = 0; g0 < most; g0 += room) {
                 if (g0 > 0) lds_sync(NW);  // the previous range's are no longer read
@@ -361,7 +363,7 @@ hipError_t launch_estimates(const EstimateBatch& b, const int64_t* idx, int64_t 
         A.vmax = last ? kCrossMax : kStatsSmallVol;
         A.cap = ((last ? top : kStatsSmallVol) + 3) & ~3;
         const size_t lds = (size_t)A.cap * 4;
-        A.records = std::min({b.max_blocks, A.cap + TM_MAX_LRANK, kEstRecords});
+        A.records = std::min({b.max_blocks, A.cap + TM_MAX_LRANK, n >= kSmallBlockBatch ? kEstRecordsWave : kEstRecords});
         const size_t records = (size_t)A.records * 8;
         if (n >= kSmallBlockBatch)
             hipLaunchKernelGGL(k_block_estimates<64>, dim3(g), dim3(64), lds + records, s, A);
