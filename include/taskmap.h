@@ -305,7 +305,7 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
  * them, max_words table words (both grow).  tm_plan_load validates a batch on the host
  * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run is one evaluation
  * launch whatever the candidates' launch ranks (two when their LDS needs differ much),
- * which also selects for batches of at most 2048 candidates.  It makes no host
+ * which also selects for batches of at most 128 candidates.  It makes no host
  * synchronisation and can be captured in the caller's own graph.
  * d_out: tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  A work item is a workgroup:
  * a candidate, or a part of one holding about cells_per_item of its group tuples (0 = a
@@ -317,9 +317,8 @@ int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** out);
 int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const tm_stencil* st,
                  int64_t cells_per_item, void* stream);
 int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, void* stream);
-/* stage 0: zeroes d_out; 1: the evaluation (which also selects, for batches of at most
- * 2048 candidates in one launch); 2: bytes + selection (together the work of tm_plan_run,
- * one stage at a time, in this order). */
+/* stage 0: zeroes d_out; 1: the evaluation and the selection; 2: bytes + selection
+ * (together the work of tm_plan_run, one stage at a time, in this order). */
 int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t* d_best,
                       void* stream);
 /* Processor map of candidate *d_index (device int64; index into the loaded batch),

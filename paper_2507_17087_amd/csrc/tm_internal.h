@@ -210,8 +210,12 @@ int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
 hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena,
                                int32_t mode_halo, hipStream_t s, tm_stencil_cost* out = nullptr,
                                unsigned long long* counter = nullptr);
-// Batches up to this many candidates select inside the evaluation launch.
-constexpr int64_t kFinInCount = 2048;
+// Batches up to this many candidates select inside the evaluation launch: its last
+// workgroup finds the best row, for which every workgroup makes its row visible to the other
+// XCDs, some 20 ns each; a launch of its own costs about as much as 100 of that.  With the
+// selection inside and in its own launch: 64 candidates 10.9 and 11.8 us, 128 12.0 and 11.7,
+// 216 14.0 and 12.0, 1,440 35.2 and 16.2, 2,000 46.4 and 20.1.
+constexpr int64_t kFinInCount = 128;
 // Per segment the best cost row: of rows [seg[s], seg[s+1]), or with idx (row -> candidate,
 // negative: no row) of the k rows from s k; best_cost may be null.
 hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg, const int64_t* idx,
