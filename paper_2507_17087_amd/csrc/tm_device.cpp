@@ -187,7 +187,10 @@ struct EvalLayout {
     int32_t small, most;
     int32_t words[2] = {0, 0}, whole[2] = {0, 0}, largest = 0;  // of the needs up to small, above it
 
-    EvalLayout(EvalPlan& plan, int64_t n, const tm_stencil& st, int H, int64_t tuples_per_item, bool node_level) : e(plan) {
+    // max_vol: of all candidates, or more where that is not known yet
+    EvalLayout(EvalPlan& plan, int64_t n, int32_t max_vol, const tm_stencil& st, int H, int64_t tuples_per_item,
+               bool node_level)
+        : e(plan) {
         e = EvalPlan{};
         e.n = n;
         e.elem_bytes = st.elem_bytes;
@@ -196,9 +199,9 @@ struct EvalLayout {
         e.node_level = node_level ? 1 : 0;
         e.per_item = tuples_per_item;
         e.fill = std::max<int64_t>(1, kEvalFill / std::max<int64_t>(n, 1));
-        const bool wave = n >= kEvalWaveBatch;
-        small = wave ? kEvalSmallWave : kEvalSmallBlock;
-        most = wave ? kEvalMostWave : kEvalMostBlock;
+        e.wave = n >= kEvalWaveBatch || (n >= kEvalWaveSmall && max_vol <= kEvalWaveVol);
+        small = e.wave ? kEvalSmallWave : kEvalSmallBlock;
+        most = e.wave ? kEvalMostWave : kEvalMostBlock;
     }
     EvalShape shape() const { return EvalShape{e.H, e.node_level, e.per_item, e.fill}; }
     void add(const EvalNeed& n, bool simple) {
@@ -227,7 +230,7 @@ void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
     st.lrank = TM_MAX_LRANK;
     st.elem_bytes = cp.hdr.elem_bytes;
     for (int k = 0; k < TM_MAX_LRANK; ++k) st.halo[k] = cp.hdr.halo[k];
-    EvalLayout lay(cp.eval, (int64_t)cp.cands.size(), st, cp.H, tuples_per_item, node_level);
+    EvalLayout lay(cp.eval, (int64_t)cp.cands.size(), cp.max_vol, st, cp.H, tuples_per_item, node_level);
     const EvalShape shape = lay.shape();
     for (auto& c : cp.cands) {
         DevDim dim[TM_MAX_LRANK];
@@ -525,7 +528,7 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
         // straight from the records to the evaluation's descriptors
         const int rc = with_descriptors((size_t)n * sizeof(DevEval), s, "stencil", &memory, [&](void* stg) {
             DevEval* e = static_cast<DevEval*>(stg);
-            EvalLayout lay(plan, n, *st, H, 0, node_level);
+            EvalLayout lay(plan, n, INT32_MAX, *st, H, 0, node_level);
             const EvalShape shape = lay.shape();
             for (int64_t i = 0; i < n; ++i, ++e) {
                 CandView v;

@@ -34,6 +34,7 @@ struct EvalPlan {
     int32_t H = 0, parts = 1, node_level = 0;
     int32_t split = 0;          // candidates needing at most this many LDS words: the first launch
     int32_t words[2] = {0, 0};  // LDS words of the two launches (0: no such candidate)
+    bool wave = false;          // one-wave workgroups
     bool all_simple = true;     // every candidate is simple (kEvalSimple)
     int32_t wg_per_cu = 0;      // at most this many workgroups per CU (0: one per item)
 };
@@ -55,8 +56,14 @@ hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_byt
 hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* halo, unsigned long long* total,
                                hipStream_t s);
 
-// Batches of at least this many candidates run one-wave workgroups.
-constexpr int64_t kEvalWaveBatch = 2048;
+// Batches of at least kEvalWaveBatch candidates run one-wave workgroups, of at least
+// kEvalWaveSmall where no owner table is larger than kEvalWaveVol: with few candidates the
+// largest one's latency decides.  One wave and four, us: random ones (tables to 900) 3,000
+// candidates 27.3 and 25.7, 4,096 27.6 and 30.8; the search's (to 512) 3,000 42 and 31, 4,096
+// 42.6 and 38.0, 6,000 44 and 51; the 2-D study's (to 128) 512 10.7 and 10.5, 1,024 11.8 and
+// 12.6, 1,440 12.5 and 16.2.
+constexpr int64_t kEvalWaveBatch = 4096, kEvalWaveSmall = 1024;
+constexpr int32_t kEvalWaveVol = 128;
 
 // LDS words of a launch: records share the LDS up to kEvalSmall* words (5 KB per one-wave
 // workgroup keeps 26 of them on a CU, 20 KB per four-wave one 8); all candidates go in one

@@ -450,7 +450,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : 
     if (tid == 0) *A.counter = 0ull;
 }
 
-static hipError_t launch_eval(const EvalArgs& A, int H, int64_t grid, hipStream_t s) {
+static hipError_t launch_eval(const EvalArgs& A, int H, bool wave, int64_t grid, hipStream_t s) {
     const size_t lds = (size_t)(A.lds_words + kOneRecord + 2) * 4;
 #define TM_EVAL(nt, h) hipLaunchKernelGGL((k_eval<nt, h>), dim3((unsigned)grid), dim3(nt), lds, s, A)
 #define TM_EVAL_H(nt)                   \
@@ -459,7 +459,7 @@ static hipError_t launch_eval(const EvalArgs& A, int H, int64_t grid, hipStream_
         else if (H <= 2) TM_EVAL(nt, 2); \
         else TM_EVAL(nt, 4);            \
     } while (0)
-    if (A.n >= kEvalWaveBatch) TM_EVAL_H(64);
+    if (wave) TM_EVAL_H(64);
     else TM_EVAL_H(256);
 #undef TM_EVAL_H
 #undef TM_EVAL
@@ -554,7 +554,7 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
         A.min_words = b == 0 ? 0 : p.split;
         A.max_words = b == 0 ? p.split : INT32_MAX;
         A.lds_words = p.words[b];
-        e = launch_eval(A, p.H, grid, s);
+        e = launch_eval(A, p.H, idx ? n >= kEvalWaveBatch : p.wave, grid, s);
     }
     if (e == hipSuccess && parts > 1) return launch_bytes_select(out, n, p.elem_bytes, best, s, evals, best_ids);
     if (e == hipSuccess && best && !fin) e = launch_select_rows(out, n, best, evals, best_ids, s);
