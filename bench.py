@@ -7,13 +7,13 @@ decompose's enumeration) under 6 transformation chains = 216 candidate mappings;
 candidate exactly (processor of each of the 216 x 134,217,728 launch points, and
 the distinct-owner ghost volume with its intra/inter-node split), selects the
 cheapest by (bytes, inter-node bytes, index), and materialises the selected
-candidate's int32 processor map (512 MiB), all in one graph replay; consecutive steps
+candidate's int32 processor map (512 MiB), with no host step in between; consecutive steps
 run round-robin on three streams (a plan and outputs each), so a step's evaluation
 overlaps the previous step's map write.  Inputs (candidate descriptors) are
 resident on the device before timing starts.  The ghost volume of a candidate is
-counted exactly over its coordinate classes (runs of coordinates with the same
-contribution and neighbour offsets along each launch dim), so the counting work is
-its class tuples, not its points; the map is written point by point.
+counted exactly over tuples of coordinate groups (the coordinates of a launch dim with the
+same contribution to the final index), so the counting work is
+its tuples, not its points; the map is written point by point.
 
 The metric's second part -- candidates ranked per second by the learned ranker vs
 exhaustive exact evaluation, at the exhaustive optimum -- is the "search" object of
@@ -39,10 +39,9 @@ if ROOT not in sys.path:
 
 METRIC = "mapping point-evals/sec; candidates ranked/sec surrogate vs exhaustive at =opt"
 PEAK_LANE_OPS = 256 * 64 * 2.4e9      # 32-bit VALU lane-ops/s: 256 CUs x 64 lanes x 2.4 GHz
-# Integer operations of one exact cell evaluation for a 3-D halo-2 star: one owner
-# lookup, up to 2 * sum(h) = 12 neighbour lookups, compares and the de-duplication of
-# a small set -- about 50 to 70; the midpoint prices one class-tuple evaluation (a
-# class tuple is evaluated exactly like one of its cells).
+# Integer operations of one tuple of coordinate groups: its owner, up to 2 * sum(h) = 12
+# neighbouring owners, their compares and counts -- about 50 to 70, as for one cell of a
+# 3-D halo-2 star; the midpoint.
 OPS_PER_TUPLE = 60
 PEAK_HBM = 8.0e12                     # bytes/s
 
@@ -50,8 +49,8 @@ PEAK_HBM = 8.0e12                     # bytes/s
 # reference kernels' readings: reads x2.000 as a copy, writes x1.000 as a fill), valid only for the kernel
 # sources they were taken on (hash of the files below); see
 # profiles/c2_512cube_hbm_traffic.txt.
-KERNEL_SOURCES = ["paper_2507_17087_amd/csrc/tm_kernels.hip", "paper_2507_17087_amd/csrc/tm_chain.h",
-                  "paper_2507_17087_amd/csrc/tm_internal.h"]
+KERNEL_SOURCES = ["paper_2507_17087_amd/csrc/tm_map.hip", "paper_2507_17087_amd/csrc/tm_map.h",
+                  "paper_2507_17087_amd/csrc/tm_groups.h"]
 TRAFFIC_SOURCE_HASH = "8f383901c5ebc06f"
 TRAFFIC_BYTES = {"k_map": 537.05e6}
 
@@ -422,11 +421,16 @@ def transpose_leg(tm, W, reps=3):
     return res
 
 
+def group_tuples(tm, cs):
+    """Tuples of coordinate groups of a batch, at most: one per final coordinate."""
+    return int(sum(np.prod(tm.tm_validate(cs[i:i + 1])[1], dtype=np.int64) for i in range(len(cs))))
+
+
 def c3_leg(tm, W, reps=20, cyclic_pct=0):
     """The batched workload: 4,096 random candidates (seed 17087; launch ranks 2 and 3
     mixed, extents log-uniform 32..1023, 1..64 nodes x {1,2,4,8} GPUs, 0-4 random
-    transformations), halo 1, in one plan (one counting launch), autotuned, timed as
-    graph replays of the whole evaluation (reset, tables, counting, selection) with
+    transformations), halo 1, in one plan (one counting launch), autotuned, timed stage by
+    stage (reset, evaluation, bytes and selection) with
     HIP events on the plan's stream.  cyclic_pct: the share of projections drawn
     cyclic (the coverage variant)."""
     import torch
@@ -456,14 +460,15 @@ def c3_leg(tm, W, reps=20, cyclic_pct=0):
     tuples = plan.class_tuples()
     plan.close()
     ms, cms = float(np.median(ts)), float(np.median(tc))
-    ach = OPS_PER_TUPLE * tuples / (cms * 1e-3)
+    work = group_tuples(tm, cs)
+    ach = OPS_PER_TUPLE * work / (cms * 1e-3)
     return {"candidates": int(len(cs)), "ranks": sorted(int(k) for k in set(cs["lrank"])), "points": int(pts),
             "ms": ms, "ms_spread": [float(min(ts)), float(max(ts))], "point_evals_per_s": pts / (ms * 1e-3),
             "count_ms": cms, "class_tuples": int(tuples), "work_items": int(items),
             "tuples_per_item": cpi, "wg_per_cu": wg,
             "roofline_count": {"bound": "alu", "achieved": ach / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                               "unit": "Tlane-op/s", "frac": ach / PEAK_LANE_OPS, "kernel": "k_count",
-                               "ops_per_tuple": OPS_PER_TUPLE}}
+                               "unit": "Tlane-op/s", "frac": ach / PEAK_LANE_OPS, "kernel": "k_eval",
+                               "group_tuples": work, "ops_per_tuple": OPS_PER_TUPLE}}
 
 
 def c4_leg(tm, W, reps=10):
@@ -536,12 +541,11 @@ def main():
         tuned = plan.autotune(out)
     _, items, _ = plan.info()
 
-    # A step: one graph replay -- the evaluation (tables and classes, counting, bytes
-    # + selection) and then the map of the selected candidate, with no host step in
-    # between.  The timed steps are issued round-robin on `--streams` streams, each
+    # A step: the evaluation, the selection and then the map of the selected candidate,
+    # three launches with no host step in between.  The timed steps are issued round-robin on `--streams` streams, each
     # with its own plan (the same batch) and its own outputs, so that one step's
     # evaluation (latency-bound) overlaps the previous step's map write (HBM-bound);
-    # every step is a whole pass.  Events around each replay on its stream.
+    # every step is a whole pass.  Events around each step on its stream.
     ns = max(1, args.streams)
     lanes = [(plan, out, best, pmap, torch.cuda.current_stream())]
     for _ in range(ns - 1):
@@ -568,7 +572,7 @@ def main():
     lanes_agree = all(bool(torch.equal(lanes[i][1], out)) and bool(torch.equal(lanes[i][2], best)) and
                       bool(torch.equal(lanes[i][3], pmap)) for i in range(ns))
     # the same steps on one stream (one step at a time), for comparison; then once more
-    # with events around each replay for the per-step GPU time
+    # with events around each step for the per-step GPU time
     torch.cuda.synchronize()
     t2 = time.perf_counter()
     for k in range(args.steps):
@@ -583,8 +587,8 @@ def main():
     torch.cuda.synchronize()
     step_gpu = np.array([evs[k][0].elapsed_time(evs[k][1]) for k in range(args.steps)])
     # breakdown (second and third passes over the same steps; not part of `value`):
-    # the evaluation graph and the map launch with events between them, then the
-    # evaluation one stage graph at a time
+    # the evaluation and the map (its owner table and its points) with events between
+    # them, then the evaluation one stage at a time
     mev = [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(args.steps)]
     for k in range(args.steps):
         mev[k][0].record()
@@ -609,14 +613,15 @@ def main():
     b = int(best.cpu()[0])
     tuples = plan.class_tuples()
     value = points / (ms_step * 1e-3)
-    cnt_ach = OPS_PER_TUPLE * tuples / (count * 1e-3)
+    work = group_tuples(tm, cands)
+    cnt_ach = OPS_PER_TUPLE * work / (count * 1e-3)
     map_bw = 4.0 * L ** 3 / (mapk * 1e-3)
     roof_map = {"bound": "hbm", "achieved": map_bw / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
                 "frac": map_bw / PEAK_HBM, "traffic": measured_traffic("k_map"), "kernel": "k_map",
                 "bytes_per_point": 4, "kernel_ms": mapk}
     roof_count = {"bound": "alu", "achieved": cnt_ach / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                  "unit": "Tlane-op/s", "frac": cnt_ach / PEAK_LANE_OPS, "traffic": measured_traffic("k_count"),
-                  "kernel": "k_count", "class_tuples": tuples, "ops_per_tuple": OPS_PER_TUPLE, "kernel_ms": count}
+                  "unit": "Tlane-op/s", "frac": cnt_ach / PEAK_LANE_OPS, "traffic": measured_traffic("k_eval"),
+                  "kernel": "k_eval", "group_tuples": work, "class_tuples": tuples, "ops_per_tuple": OPS_PER_TUPLE, "kernel_ms": count}
     res = {
         "metric": METRIC,
         "value": value,

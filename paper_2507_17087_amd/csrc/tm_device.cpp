@@ -38,12 +38,10 @@ constexpr int64_t kMaxCellsPerItem = int64_t(1) << 26;
 static int64_t up4(int64_t x) { return (x + 3) & ~int64_t(3); }
 
 // Arena layout of one candidate: owner table T, the last dim's coordinate table
-// (16-byte aligned, zero-padded to whole 512-entry chunks), the other dims'
-// coordinate tables, then (stencil batches: halo != nullptr) the class record (the
+// (16-byte aligned, padded to whole 512-entry chunks), the other dims'
+// coordinate tables, then (halo != nullptr) the class record (the
 // class count of each dim, written by the table build) and each dim's class block
-// (entries, starts, offset lists of 2H words; capacities from class_cap).  The map
-// and redistribution kernels stage the prefix T + last dim's table in LDS when it
-// fits (else T only); the counting kernel stages T and the class blocks.
+// (entries, starts, and the room of offset lists of 2H words; capacities from class_cap).
 static int layout_tables(DevCand& d, int H, const int32_t* halo) {
     const int K = d.lrank;
     int64_t off = up4(d.vol);
@@ -56,7 +54,6 @@ static int layout_tables(DevCand& d, int H, const int32_t* halo) {
         d.coord_off[k] = (int32_t)std::min<int64_t>(off, INT32_MAX);
         off += d.extent[k];
     }
-    d.hstride = 2 * H;
     for (int k = 0; k < TM_MAX_LRANK; ++k) d.cls_off[k] = d.cls_cap[k] = 0;
     d.cls_base = d.cls_words = 0;
     if (halo) {
@@ -74,8 +71,7 @@ static int layout_tables(DevCand& d, int H, const int32_t* halo) {
         d.cls_base = (int32_t)cb;
         d.cls_words = (int32_t)(off - cb);
     }
-    d.cl_lds = c_end <= kMaxLdsWords ? 1 : 0;
-    const int64_t staged = d.cl_lds ? c_end : t_end;
+    const int64_t staged = c_end <= kMaxLdsWords ? c_end : t_end;
     const int64_t words = up4(std::max(off, staged));  // the next candidate's tables start 16-byte aligned
     if (words > INT32_MAX) return TM_EOVERFLOW;
     d.lds_words = (int32_t)staged;
@@ -91,20 +87,15 @@ static int32_t blocks_and_dims(const DevCand& d) {
     return (int32_t)std::min<int64_t>(n, INT32_MAX);
 }
 
-// Counting work items of every candidate, and the item table (the candidate of each
-// item, written by the table build) after the tables in the arena.
+// Counting work items of every candidate, a word of the arena each.
 static void layout_items(Compiled& cp, int64_t tuples_per_item) {
     int64_t items = 0;
-    cp.max_citems = 0;
     for (auto& d : cp.cands) {
         d.citems = count_items(d, tuples_per_item);
         d.item_first = items;
         items += d.citems;
-        cp.max_citems = std::max(cp.max_citems, d.citems);
     }
     cp.items = items;
-    cp.hdr.total_items = items;
-    cp.hdr.item_tab = cp.tables_words;
     cp.arena_words = cp.tables_words + up4(items);
 }
 
@@ -131,7 +122,6 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
         cp.H = std::max(1, hmax);
         cp.hdr.elem_bytes = st->elem_bytes;
         cp.hdr.lrank = st->lrank;
-        cp.hdr.H = cp.H;
     }
     int64_t words = 0;
     for (int64_t i = 0; i < n; ++i) {
@@ -172,8 +162,6 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
     }
     cp.tables_words = words;
     cp.arena_words = words;
-    cp.hdr.max_words = cp.max_words;
-    cp.hdr.cnt_words = cp.cnt_words;
     layout_items(cp, tuples_per_item > 0 ? tuples_per_item : default_tuples_per_item(cp.tuples));
     return TM_OK;
 }

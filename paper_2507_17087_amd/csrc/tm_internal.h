@@ -92,8 +92,8 @@ struct DevCand {
     int32_t cls_off[TM_MAX_LRANK];      // table offsets of the per-dim coordinate-class blocks
     int32_t cls_cap[TM_MAX_LRANK];      // class capacity of each dim (an upper bound on the class count)
     int32_t cls_base, cls_words;        // class record (four class counts) + the blocks: offset and words
-    int32_t lds_words, hstride;         // leading words staged in LDS by the map kernel; offset-list stride (2*H)
-    int32_t citems, cl_lds;             // counting work items; last dim's coordinate table is in the staged prefix
+    int32_t lds_words, pad2;            // owner table and, where it fits the LDS, the last dim's coordinate table
+    int32_t citems, pad3;               // counting work items
     int32_t fshape[TM_MAX_MRANK], fstride[TM_MAX_MRANK];
     int8_t proj_src[TM_MAX_MRANK], proj_mode[TM_MAX_MRANK];
     int32_t rank[TM_MAX_OPS];                    // rank before op t
@@ -125,16 +125,11 @@ struct alignas(16) DevFeat {
     int32_t pad[4];
 };
 
-// Batch header: one per plan, in device memory, read by every kernel of a replay.
+// Batch header: one per plan, in device memory.
 struct DevHeader {
     int64_t n;            // candidates
-    int64_t total_items;  // work items over all candidates
     int32_t halo[TM_MAX_LRANK];
     int32_t elem_bytes, lrank;
-    int32_t max_words, H;  // largest table prefix staged by the map kernel; max halo (offset-list stride 2H)
-    int32_t node_level;    // owner tables hold nodes only (node-level exchange volume)
-    int32_t cnt_words;     // LDS words of the counting launch (owner table + class blocks staged)
-    int64_t item_tab;      // arena word offset of the item table (candidate of every counting work item)
 };
 
 // Host-side result of validation: the rank and the extents (with ones up to 8) before
@@ -147,17 +142,14 @@ struct Shapes {
 // An entry of a per-dim coordinate table holds the contribution of that coordinate
 // to the linear final-space index (volumes are at most 2^24).
 //
-// Coordinate classes (stencil batches).  Along launch dim d, coordinate x has a
+// Coordinate classes.  Along launch dim d, coordinate x has a
 // contribution C_d[x] and a set of distinct non-zero index offsets C_d[x +- s] -
-// C_d[x] to its in-domain star neighbours (1 <= s <= h_d).  The distinct foreign
-// owners of a cell depend on nothing else: cells whose coordinates fall in the same
-// class along every dim have equal counts.  A class is a maximal run of consecutive
-// coordinates with equal contribution and equal offset set; its block stores, for
-// class k, the entry (contribution | offset count << kCntShift), the first
-// coordinate (k = R is the extent, so the run length is start[k+1] - start[k]) and
-// the sorted offsets (2*H words, zero-padded).
-constexpr int32_t kValMask = 0x00ffffff;
-constexpr int kCntShift = 24;
+// C_d[x] to its in-domain star neighbours (1 <= s <= h_d).  A class is a maximal run of
+// consecutive coordinates with equal contribution and equal offset set.  Matmul batches
+// too large for the LDS build them with a zero halo (runs of equal contribution): class k's
+// entry and first coordinate (k = R is the extent, so the run length is start[k+1] -
+// start[k]).  For stencil batches the layout with classes is only a measure: of the scratch
+// that tm_eval_stencil_batch_noalloc counts and of the run that a map needs before it.
 constexpr int32_t kMaxLdsWords = 32768;
 constexpr int kMaxHalo = 4;
 
@@ -205,11 +197,9 @@ int validate_shapes(const tm_candidate* c, Shapes* sh);
 int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
 
 // Kernel launchers (tm_kernels.hip).  All enqueue on `s` and return hipError_t.
-// Table build; with out/counter (stencil batches) it also zeroes the outputs and the
-// counting kernel's work and completion counters (counter[0], counter[1]).
-hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena,
-                               int32_t mode_halo, hipStream_t s, tm_stencil_cost* out = nullptr,
-                               unsigned long long* counter = nullptr);
+// Owner and coordinate tables; with runs also the coordinates' runs of equal contribution.
+hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena, int32_t runs,
+                               hipStream_t s);
 // Batches up to this many candidates select inside the evaluation launch: its last
 // workgroup finds the best row, for which every workgroup makes its row visible to the other
 // XCDs, some 20 ns each; a launch of its own costs about as much as 100 of that.  With the

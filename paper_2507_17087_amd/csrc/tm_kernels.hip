@@ -1,4 +1,6 @@
-// tm_kernels.hip -- gfx950 kernels of libtaskmap.
+// tm_kernels.hip -- gfx950 kernels of libtaskmap that work on tables in device memory: the
+// chain table; matmul tiles and redistribution volumes of mappings whose owner tables do
+// not fit a workgroup's LDS (tm_volume.hip takes the others); selection per segment.
 //
 // Data layout.  For each candidate the table-build kernel writes, into a device
 // arena, (1) the chain table T[v]: the owner of every coordinate v of the final
@@ -7,17 +9,10 @@
 // as the fold described in taskmap.h), stored as the key (node << gbits) | gpu so
 // that owner identity and node are both one integer operation away; and (2) one
 // coordinate table per launch dim d: C_d[x] = sum over final dims j projected
-// from d of a_j(x) * stride_j (block: floor(x*s_j/l_d), cyclic: x mod s_j), with
-// the number of distinct non-zero index offsets to the star neighbours within the
-// halo along d in bits 24..27 (and, for the last dim, the offsets themselves in a
-// list beside it and the flags described in tm_internal.h in bits 28..29).
+// from d of a_j(x) * stride_j (block: floor(x*s_j/l_d), cyclic: x mod s_j), and for
+// matmul batches its runs of equal entries.
 // The linear final coordinate of point q is then v(q) = sum_d C_d[q_d] and its
 // owner is T[v(q)]: the chain is evaluated once per coordinate, not per point.
-//
-// Kernels: table build; processor map (streaming int32 writes); stencil counting
-// (persistent, work queue over (candidate, row block) items, tables in LDS); bytes
-// and selection; matmul tile bitmaps; redistribution counting.  All arithmetic is
-// exact integer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -60,55 +55,18 @@ __device__ __forceinline__ void stage_words(int32_t* __restrict__ dst, const int
 
 // ------------------------------------------------------------------ table build
 
-// Sorted distinct non-zero offsets C[x +- s] - C[x] (1 <= s <= h, in-domain
-// neighbours) of coordinate x, in slots o[0..n); unused slots hold INT32_MAX.
-__device__ __forceinline__ int coord_offsets(const int32_t* __restrict__ C, int64_t x, int64_t l, int h,
-                                             int32_t (&o)[2 * kMaxHalo]) {
-#pragma unroll
-    for (int i = 0; i < 2 * kMaxHalo; ++i) o[i] = INT32_MAX;
-    const int32_t cv = C[x];
-    int n = 0;
-#pragma unroll
-    for (int s = 1; s <= kMaxHalo; ++s) {
-#pragma unroll
-        for (int dir = 0; dir < 2; ++dir) {
-            const int64_t xx = dir ? x + s : x - s;
-            if (s > h || xx < 0 || xx >= l) continue;
-            const int32_t dv = C[xx] - cv;
-            bool seen = dv == 0;
-#pragma unroll
-            for (int i = 0; i < 2 * kMaxHalo; ++i) seen = seen || o[i] == dv;
-            if (seen) continue;
-            // insert into the sorted slots (static indices only: no scratch)
-#pragma unroll
-            for (int i = 2 * kMaxHalo - 1; i >= 0; --i) {
-                const bool shift = i > 0 && o[i - 1] > dv;
-                const bool here = i == 0 ? o[0] > dv : (o[i - 1] <= dv && o[i] > dv);
-                o[i] = shift ? o[i - 1] : (here ? dv : o[i]);
-            }
-            ++n;
-        }
-    }
-    return n;
-}
-
 constexpr int kBuildStage = 2048;  // coordinate-table entries staged in LDS for the class build
 
 // The owner table T[v] (one key per final-space coordinate), the coordinate tables
-// C_d and, with halos (use_halo), the coordinate classes of every launch dim (see
-// tm_internal.h): a coordinate starts a class when its contribution or offset set
-// differs from its left neighbour's; class indices come from a workgroup prefix
+// C_d and, with runs, the coordinate classes of every launch dim: maximal runs of equal
+// contribution; run indices come from a workgroup prefix
 // count of the starts.  With split, one workgroup per (candidate, launch dim) --
-// workgroup d writes the d-th K-th of T, C_d and dim d's classes (small batches:
+// workgroup d writes the d-th K-th of T, C_d and dim d's runs (small batches:
 // more workgroups in flight) -- else one per candidate, all dims in turn (grid-
-// stride in both cases).  The first workgroup of a candidate also writes its
-// entries of the item table and, with out/counter, zeroes its outputs (workgroup 0
-// of the launch the counting kernel's counters).
+// stride in both cases).
 __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restrict__ hdr,
                                                       const DevCand* __restrict__ cands,
-                                                      int32_t* __restrict__ arena, int use_halo,
-                                                      tm_stencil_cost* __restrict__ out,
-                                                      unsigned long long* __restrict__ counter, int split) {
+                                                      int32_t* __restrict__ arena, int runs, int split) {
     __shared__ DevCand sc;
     __shared__ int32_t s_wt[4];
     __shared__ int32_t s_ct[kBuildStage];
@@ -116,7 +74,6 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, nw = blockDim.x >> 6;
     const int upc = split ? TM_MAX_LRANK : 1;  // units per candidate
     const int64_t units = hdr->n * upc;
-    if (counter && blockIdx.x == 0 && tid < 2) counter[tid] = 0ull;
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
         const int64_t ci = u / upc;
         const int dlo = (int)(u - ci * upc);
@@ -129,25 +86,16 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
         op_reciprocals(sc, s_rt, tid, blockDim.x);
         lds_sync(nw);
         int32_t* base = arena + sc.arena_off;
-        if (dlo == 0) {
-            if (out && tid < 4) reinterpret_cast<int64_t*>(&out[ci])[tid] = 0;
-            if (use_halo)  // this candidate's entries of the item table (work item -> candidate)
-                for (int32_t j = tid; j < sc.citems; j += blockDim.x)
-                    arena[hdr->item_tab + sc.item_first + j] = (int32_t)ci;
-        }
-        // node-level tables keep the node of each owner (GPU bits cleared): the
-        // counting kernel then counts distinct other nodes per cell
-        const int32_t keep = hdr->node_level ? ~((1 << sc.gbits) - 1) : -1;
         const int32_t v0 = split ? (int32_t)((int64_t)sc.vol * dlo / K) : 0;
         const int32_t v1 = split ? (int32_t)((int64_t)sc.vol * (dlo + 1) / K) : sc.vol;
-        owner_keys_sized(sc, s_rt, base, 0, v0, v1, keep, tid, blockDim.x);
+        owner_keys_sized(sc, s_rt, base, 0, v0, v1, -1, tid, blockDim.x);
         for (int d = dlo; d < dhi; ++d) {
             if (d > dlo) lds_sync(nw);  // the previous dim's staged table is no longer read
             const int64_t l = sc.extent[d];
             int32_t* ct = base + sc.coord_off[d];
             // the dim's coordinate table; kept in LDS too when it fits (the class build
-            // reads it 2 (2h + 1) times per coordinate)
-            const bool staged = use_halo && l <= kBuildStage;
+            // reads it twice per coordinate)
+            const bool staged = runs && l <= kBuildStage;
             for (int64_t x = tid; x < l; x += blockDim.x) {
                 const int32_t cv = coord_value(sc, d, x);
                 ct[x] = cv;
@@ -155,35 +103,23 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
             }
             if (d == K - 1)  // zero entries up to a multiple of 512 (read in whole chunks)
                 for (int64_t x = l + tid; x < ((l + 511) & ~int64_t(511)); x += blockDim.x) ct[x] = 0;
-            if (!use_halo) continue;
+            if (!runs) continue;
             // the coordinate table complete (read from LDS when staged, else from global memory)
             if (staged) lds_sync(nw);
             else __syncthreads();
             const int32_t* cr = staged ? s_ct : ct;
-            const int hs = sc.hstride;
             int32_t* rec = base + sc.cls_base;
-            const int h = hdr->halo[d];
             const int64_t cap = sc.cls_cap[d];
             int32_t* ce = base + sc.cls_off[d];
             int32_t* cs = ce + ((cap + 3) & ~int64_t(3));
-            int32_t* co = cs + ((cap + 4) & ~int64_t(3));
             int64_t run = 0;  // classes so far (the same in every thread)
             for (int64_t x0 = 0; x0 < l; x0 += blockDim.x) {
                 const int64_t x = x0 + tid;
                 bool start = false;
-                int32_t val = 0, o[2 * kMaxHalo];
-                int no = 0;
+                int32_t val = 0;
                 if (x < l) {
                     val = cr[x];
-                    no = coord_offsets(cr, x, l, h, o);
-                    start = x == 0;
-                    if (!start) {
-                        int32_t pv[2 * kMaxHalo];
-                        (void)coord_offsets(cr, x - 1, l, h, pv);
-                        start = cr[x - 1] != val;
-#pragma unroll
-                        for (int i = 0; i < 2 * kMaxHalo; ++i) start = start || pv[i] != o[i];
-                    }
+                    start = x == 0 || cr[x - 1] != val;
                 }
                 const uint64_t m = __ballot(start);
                 int64_t below = 0, tot = __popcll(m);
@@ -200,9 +136,8 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
                     const int64_t idx = run + below + __builtin_amdgcn_mbcnt_hi(
                                                               (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
                     if (idx < cap) {  // the capacity bounds the count (class_cap); never exceeded
-                        ce[idx] = val | (no << kCntShift);
+                        ce[idx] = val;
                         cs[idx] = (int32_t)x;
-                        for (int i = 0; i < hs; ++i) co[idx * hs + i] = i < no ? o[i] : 0;
                     }
                 }
                 run += tot;
@@ -216,16 +151,14 @@ __global__ __launch_bounds__(256) void k_build_tables(const DevHeader* __restric
     }
 }
 
-hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena,
-                               int32_t use_halo, hipStream_t s, tm_stencil_cost* out,
-                               unsigned long long* counter) {
+hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64_t n, int32_t* arena, int32_t runs,
+                               hipStream_t s) {
     // small batches: a workgroup per (candidate, launch dim); large ones: per candidate
     const int split = n <= kSplitBuildBatch ? 1 : 0;
     const int64_t units = n * (split ? TM_MAX_LRANK : 1);
     const int64_t grid = units < 131072 ? (units > 0 ? units : 1) : 131072;
     const int bs = n >= kSmallBlockBatch ? 64 : 256;
-    hipLaunchKernelGGL(k_build_tables, dim3((unsigned)grid), dim3(bs), 0, s, hdr, cands, arena, use_halo, out,
-                       counter, split);
+    hipLaunchKernelGGL(k_build_tables, dim3((unsigned)grid), dim3(bs), 0, s, hdr, cands, arena, runs, split);
     return hipGetLastError();
 }
 
@@ -347,9 +280,9 @@ __global__ __launch_bounds__(256) void k_pair_classes(const DevCand* __restrict_
                 int32_t va = 0, vb = 0;
                 bool start = false;
                 if (x < l) {
-                    va = ca[x] & kValMask;
-                    vb = cb[x] & kValMask;
-                    start = x == 0 || (ca[x - 1] & kValMask) != va || (cb[x - 1] & kValMask) != vb;
+                    va = ca[x];
+                    vb = cb[x];
+                    start = x == 0 || ca[x - 1] != va || cb[x - 1] != vb;
                 }
                 const uint64_t m = __ballot(start);
                 if (lane == 0) s_wt[wid] = __popcll(m);
@@ -541,8 +474,7 @@ hipError_t launch_redist(const DevCand* cands, int64_t npair, int32_t* arena, in
 //
 // A tile of A (i, k) is fetched by every processor that owns some task (i, j, k),
 // and the owners along j depend only on the classes of i and k (runs of coordinates
-// with the same contribution to the final index, built by the table build with a
-// zero halo): all tiles of one pair of classes have the same owner set, and each
+// with the same contribution to the final index, built by the table build): all tiles of one pair of classes have the same owner set, and each
 // processor of it counts the pair's tiles, the product of the two run lengths.  The
 // same holds for B (k, j) over i and C (i, j) over k.  Work block = (candidate,
 // matrix m in {A, B, C}, kMatmulTiles class pairs of the candidate's bound); a
@@ -629,14 +561,14 @@ __global__ __launch_bounds__(256) void k_matmul(const DevCand* __restrict__ cand
         const uint32_t ntile = (uint32_t)Ra * (uint32_t)Rb, t1 = (uint32_t)(local + 1) * kMatmulTiles;
         for (uint32_t t = (uint32_t)local * kMatmulTiles + tid; t < t1 && t < ntile; t += 256) {
             const int32_t ca = (int32_t)(t / (uint32_t)Rb), cbx = (int32_t)(t - (uint32_t)ca * (uint32_t)Rb);
-            const int32_t fixed = (Ea[ca] & kValMask) + (Eb[cbx] & kValMask);
+            const int32_t fixed = Ea[ca] + Eb[cbx];
             const unsigned long long w =
                 (unsigned long long)(Sa[ca + 1] - Sa[ca]) * (unsigned long long)(Sb[cbx + 1] - Sb[cbx]);
             uint64_t bm[W];
 #pragma unroll
             for (int u = 0; u < W; ++u) bm[u] = 0;
             for (int32_t r = 0; r < Rr; ++r) {
-                const int32_t key = T[fixed + (Er[r] & kValMask)];
+                const int32_t key = T[fixed + Er[r]];
                 const int32_t p = (key >> gb) * g + (key & ((1 << gb) - 1));
                 const uint64_t bit = 1ull << (p & 63);
                 if (W == 1) {
