@@ -202,10 +202,10 @@ hipError_t launch_build_tables(const DevHeader* hdr, const DevCand* cands, int64
                                hipStream_t s);
 // Batches up to this many candidates select inside the evaluation launch: its last
 // workgroup finds the best row, for which every workgroup makes its row visible to the other
-// XCDs, some 20 ns each; a launch of its own costs about as much as 100 of that.  With the
-// selection inside and in its own launch: 64 candidates 10.9 and 11.8 us, 128 12.0 and 11.7,
-// 216 14.0 and 12.0, 1,440 35.2 and 16.2, 2,000 46.4 and 20.1.
-constexpr int64_t kFinInCount = 128;
+// XCDs, some 20 ns each; a launch of its own costs about as much as 80 of that.  With the
+// selection inside and in its own launch: 1 candidate 7.9 and 9.3 us, 64 8.9 and 9.7, 96 9.4
+// and 9.6, 128 9.9 and 9.5.
+constexpr int64_t kFinInCount = 96;
 // Per segment the best cost row: of rows [seg[s], seg[s+1]), or with idx (row -> candidate,
 // negative: no row) of the k rows from s k; best_cost may be null.
 hipError_t launch_select_segments(const tm_stencil_cost* costs, const int64_t* seg, int64_t nseg, const int64_t* idx,
