@@ -24,10 +24,10 @@
 // candidate, 8 us.  One-wave workgroups for large batches keep 20 candidates in flight per
 // CU, and persistent ones taking several candidates in turn were slower (1.03-1.1 ms
 // against 0.90 on the search).  Measured, against a table build into memory and a count
-// over runs of equal coordinates read back from it: 219,424 search candidates 0.88 ms
-// (6.30), 4,096 random ones 32 us (150), with a quarter of the projections cyclic 38 us
+// over runs of equal coordinates read back from it: 219,424 search candidates 0.58 ms
+// (6.30), 4,096 random ones 27 us (150), with a quarter of the projections cyclic 36 us
 // (3,200), 300 two-level mappings of 512^3 at halo 2 20 us (23,350), 1,440 2-D mappings
-// with rows of up to 640,000 cells 35 us (5,100), 216 mappings of 512^3 13 us (51).
+// with rows of up to 640,000 cells 12 us (5,100), 216 mappings of 512^3 10.5 us (51).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -135,7 +135,7 @@ __device__ __forceinline__ double cells_seeing(const int32_t* lds, const int32_t
 }
 
 // Slots whose owners are compared in registers: one-wave workgroups (large batches) keep
-// five waves per SIMD, four-wave ones four.
+// five waves per SIMD, four-wave ones three or four.
 constexpr int owners_in_regs(int nt) { return nt == 64 ? 12 : 24; }
 
 // The general case.  A foreign owner of one slot counts that slot's members, as above;
@@ -169,7 +169,12 @@ __device__ __forceinline__ void count_general(const int32_t* lds, const GroupDim
             const int d = i / U;
             int32_t rd = r[0];
 #pragma unroll
-            for (int e = 1; e < K; ++e) rd = d == e ? r[e] : rd;
+            for (int e = 1; e < K; ++e) {
+                rd = d == e ? r[e] : rd;
+                // else r[] lies in scratch memory, stored on every tuple (8,192 random candidates:
+                // 38.5 us, 37.4 without)
+                asm("" : "+v"(rd));
+            }
             return T[v + low16(lds[rd + 2 + i - d * U])];
         };
         if (S <= owners_in_regs(NT)) {
@@ -377,8 +382,14 @@ __device__ __forceinline__ int64_t spread_item(int64_t turn, int64_t items) {
 
 constexpr int kOneRecord = 2 + 4 * kMaxHalo;  // words of the largest record without masks
 
+// Waves a SIMD: the registers of an instance without scratch memory.  At four, the four-wave
+// one of halo 2 (256 work items or so: one workgroup a CU) kept 21 registers there: 216
+// mappings of 512^3 with their selection 11.6 us at four and 10.5 at three, 300 random ones
+// 17.9 and 16.5, 3,000 33.9 and 33.5.
+constexpr int waves_per_simd(int nt, int h) { return nt == 64 && h <= 2 ? 5 : (h == 1 ? 4 : 3); }
+
 template <int NT, int H>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(H > 2 ? 3 : (NT == 64 ? 5 : 4)))) void k_eval(const EvalArgs A) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT, H)))) void k_eval(const EvalArgs A) {
     extern __shared__ __attribute__((aligned(16))) int32_t lds[];
     __shared__ DevEval ev;
     __shared__ double s_sum[NT / 64][2];
