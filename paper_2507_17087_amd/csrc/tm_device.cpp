@@ -187,7 +187,7 @@ struct EvalLayout {
         e.node_level = node_level ? 1 : 0;
         e.per_item = tuples_per_item;
         e.fill = std::max<int64_t>(1, kEvalFill / std::max<int64_t>(n, 1));
-        e.wave = n >= kEvalWaveBatch || (n >= kEvalWaveSmall && max_vol <= kEvalWaveVol);
+        e.wave = n >= eval_wave_batch(H) || (n >= kEvalWaveSmall && max_vol <= kEvalWaveVol);
         small = e.wave ? kEvalSmallWave : kEvalSmallBlock;
         most = e.wave ? kEvalMostWave : kEvalMostBlock;
     }

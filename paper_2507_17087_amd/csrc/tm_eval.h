@@ -56,13 +56,17 @@ hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_byt
 hipError_t launch_class_tuples(const DevCand* cands, int64_t n, const int32_t* halo, unsigned long long* total,
                                hipStream_t s);
 
-// Batches of at least kEvalWaveBatch candidates run one-wave workgroups, of at least
+// Batches of at least eval_wave_batch candidates run one-wave workgroups, of at least
 // kEvalWaveSmall where no owner table is larger than kEvalWaveVol: with few candidates the
-// largest one's latency decides.  One wave and four, us: random ones (tables to 900) 3,000
-// candidates 27.3 and 25.7, 4,096 27.6 and 30.8; the search's (to 512) 3,000 42 and 31, 4,096
-// 42.6 and 38.0, 6,000 44 and 51; the 2-D study's (to 128) 512 10.7 and 10.5, 1,024 11.8 and
-// 12.6, 1,440 12.5 and 16.2.
-constexpr int64_t kEvalWaveBatch = 4096, kEvalWaveSmall = 1024;
+// largest one's latency decides, the longer the more slots a tuple has.  One wave and four,
+// us.  Halo 1: random ones (tables to 900) 2,048 candidates 26.6 and 21.2, 4,096 27.0 and 30.3;
+// the search's (to 512) 4,096 39.5 and 36.1, 8,192 44 and 61.  Halo 2: random 4,096 49 and 44,
+// 6,144 62 and 58, 8,192 62 and 72; the search's 4,096 78 and 57, 8,192 79 and 90.  Halo 4:
+// random 8,192 144 and 103, 16,384 171 and 174, 24,576 255 and 250; the search's 16,384 333 and
+// 239.  The 2-D study's (to 128) at halos 1, 2 and 4: 512 10.1 and 10.0, 11.1 and 10.7, 13.3
+// and 11.8; 1,024 11.2 and 11.9, 12.2 and 16.1, 14.3 and 18.2.
+constexpr int64_t eval_wave_batch(int H) { return H <= 1 ? 4096 : (H <= 2 ? 8192 : 24576); }
+constexpr int64_t kEvalWaveSmall = 1024;
 constexpr int32_t kEvalWaveVol = 128;
 
 // LDS words of a launch: records share the LDS up to kEvalSmall* words (5 KB per one-wave

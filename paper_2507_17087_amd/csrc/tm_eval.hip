@@ -135,14 +135,16 @@ __device__ __forceinline__ double cells_seeing(const int32_t* lds, const int32_t
 }
 
 // Slots whose owners are compared in registers: one-wave workgroups (large batches) keep
-// five waves per SIMD, four-wave ones three or four.
-constexpr int owners_in_regs(int nt) { return nt == 64 ? 12 : 24; }
+// five waves per SIMD up to halo 2, where 24 slots would spill (non-cyclic 2-D mappings 16.0
+// and 18.3 us); at halos of 3 and 4, 4,096 random candidates take 251 us with 12 slots and
+// 100 with 24.
+constexpr int owners_in_regs(int nt, int h) { return nt == 64 && h <= 2 ? 12 : 24; }
 
 // The general case.  A foreign owner of one slot counts that slot's members, as above;
-// one of several slots counts, at its first slot, the cells that see any of them.  With
-// few slots their owners are compared in registers (on the search's chains few tuples
+// one of several slots counts, at its first slot, the cells that see any of them.  Up to R
+// slots their owners are compared in registers (on the search's chains few tuples
 // have such owners); else every slot looks at all the others.
-template <int K, int U, int NT>
+template <int K, int U, int NT, int R>
 __device__ __forceinline__ void count_general(const int32_t* lds, const GroupDims& D, int32_t stride, int gb,
                                               uint32_t n, int tid, double& tot, double& inter) {
     const int32_t* T = lds;
@@ -177,7 +179,7 @@ __device__ __forceinline__ void count_general(const int32_t* lds, const GroupDim
             }
             return T[v + low16(lds[rd + 2 + i - d * U])];
         };
-        if (S <= owners_in_regs(NT)) {
+        if (S <= R) {
             int32_t p[S];
 #pragma unroll
             for (int d = 0; d < K; ++d)
@@ -245,7 +247,7 @@ __device__ __forceinline__ void count_general(const int32_t* lds, const GroupDim
 template <int NT, int H, bool CYC>
 __device__ __forceinline__ void eval_part(const DevEval& c, const EvalArgs& A, int32_t* lds, int32_t one, int part,
                                           int parts, int tid, double& tot, double& inter) {
-    constexpr int NW = NT / 64, U = CYC ? 4 * H : 2 * H;
+    constexpr int NW = NT / 64, U = CYC ? 4 * H : 2 * H, R = owners_in_regs(NT, H);
     const int32_t vol = wave_uniform(c.vol);
     const int gb = wave_uniform(c.gbits), K = wave_uniform(c.lrank), D = wave_uniform(c.dim_d);
     const int32_t flags = wave_uniform(c.flags);
@@ -299,9 +301,9 @@ __device__ __forceinline__ void eval_part(const DevEval& c, const EvalArgs& A, i
             n *= (uint32_t)g.G[d];
         }
         if (masks) {
-            if (K <= 2) count_general<2, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
-            else if (K == 3) count_general<3, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
-            else count_general<4, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
+            if (K <= 2) count_general<2, U, NT, R>(lds, g, stride, gb, n, tid, tot, inter);
+            else if (K == 3) count_general<3, U, NT, R>(lds, g, stride, gb, n, tid, tot, inter);
+            else count_general<4, U, NT, R>(lds, g, stride, gb, n, tid, tot, inter);
         } else if (K <= 2) count_bijective<2, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
         else if (K == 3) count_bijective<3, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
         else count_bijective<4, U, NT>(lds, g, stride, gb, n, tid, tot, inter);
@@ -611,7 +613,7 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
         A.min_words = b == 0 ? 0 : p.split;
         A.max_words = b == 0 ? p.split : INT32_MAX;
         A.lds_words = p.words[b];
-        e = launch_eval(A, p.H, idx ? n >= kEvalWaveBatch : p.wave, grid, s);
+        e = launch_eval(A, p.H, idx ? n >= eval_wave_batch(p.H) : p.wave, grid, s);
     }
     if (e == hipSuccess && parts > 1) return launch_bytes_select(out, n, p.elem_bytes, best, s, evals, best_ids);
     if (e == hipSuccess && best && !fin) e = launch_select_rows(out, n, best, evals, best_ids, s);

@@ -114,3 +114,20 @@ def test_two_launches(tm):
     assert (got[cands["lrank"] == 3] == oracle.stencil_cost_batch(cands[cands["lrank"] == 3], st)).all()
     assert int(best.cpu()[0]) == oracle.select_best(got)
     plan.close()
+
+
+@pytest.mark.parametrize("halo, n", [(1, 4095), (1, 4096), (2, 8191), (2, 8192), (3, 24575), (3, 24576), (4, 24576)])
+def test_workgroups_by_batch(tm, halo, n):
+    """Both sides of the batch sizes from which workgroups have one wave, which keep another
+    number of slots in registers."""
+    say("batch of", n, "halo", halo)
+    wide = W.candidate((40, 30), 64, 4, [merge(0, 1), decompose(0, (16, 16))])  # a table above 128
+    forms = W.batch([wide] + [c for k in (2, 3) for c in random_forms(150, 40 + halo, k, 14)])
+    pick = np.random.default_rng(n).integers(0, len(forms), n)
+    pick[n // 2] = 0
+    st = W.stencil((halo, halo, halo), 8)
+    exp = np.zeros((len(forms), 4), np.int64)
+    for k in (2, 3):
+        of = forms["lrank"] == k
+        exp[of] = oracle.stencil_cost_batch(forms[of], W.stencil((halo,) * k, 8))
+    assert (tm.tm_eval_stencil_batch(forms[pick], st).cpu().numpy() == exp[pick]).all()
