@@ -301,8 +301,8 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
                             int32_t nodes, int32_t gpus_per_node, const int32_t* halo, tm_candidate* out);
 
 /* ---------------------------------------------------------------- batch plans
- * A plan owns device memory for up to max_cands candidates and, for the map of one of
- * them, max_words table words (both grow).  tm_plan_load validates a batch on the host
+ * A plan owns device memory for up to max_cands candidates and, once a map is asked for,
+ * a place for each candidate's owner table (max_words words reserved; both grow).  tm_plan_load validates a batch on the host
  * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run is one evaluation
  * launch whatever the candidates' launch ranks (two when their LDS needs differ much),
  * which also selects for batches of at most 128 candidates.  It makes no host

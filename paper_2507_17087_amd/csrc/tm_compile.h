@@ -191,7 +191,7 @@ __host__ __device__ inline EvalNeed fill_dims(const C& d, bool bij, const EvalSh
     e->bij = bij;
     int flags = is_simple(d) ? kEvalSimple : 0;
     e->points = d.npoints;
-    e->first_proc = 0;
+    e->offset = 0;
     bool distinct = bij;
     const uint64_t bits = projection_bits(d);
     int next = 0;
@@ -228,6 +228,7 @@ __host__ __device__ inline void fill_eval(const DevCand& d, const EvalShape& sha
     e->procs = d.nodes * d.gpus;
     for (int t = 0; t < d.nops; ++t) fill_inverse(op_view(d, t), &e->inv[t]);
     fill_dims(d, is_bijective(d), shape, e);
+    e->offset = d.arena_off;
 }
 
 __host__ __device__ inline void fill_feat(const DevCand& d, DevFeat* f) {

@@ -602,7 +602,7 @@ static int matmul_groups(const tm_candidate* c, int64_t n, int64_t tile_bytes, i
             if (!compile_eval(&c[i], EvalShape{1, 0, 0, 1}, &v, e, &need) || v.lrank != 3 ||
                 e->procs > kMatmulProcs || tiles_overflow(v.extent))
                 return kGeneral;
-            e->first_proc = procs;
+            e->offset = procs;
             procs += e->procs;
             const int32_t w = matmul_words(*e);
             if (w == 0) return kGeneral;
@@ -843,12 +843,20 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
     return TM_OK;
 }
 
-// Words of the loaded batch's largest owner table, for the map of one candidate.
-static int64_t plan_map_words(const tm_plan* p) { return std::max<int64_t>(map_ids_words(p->cp.max_vol), 4); }
+// A place for every candidate's owner table: a map writes its candidate's, and maps of
+// several candidates may be in flight on several streams.
+static void layout_maps(Compiled& cp) {
+    int64_t words = 0;
+    for (auto& d : cp.cands) {
+        d.arena_off = words;
+        words += map_ids_words(d.vol);
+    }
+    cp.map_words = words;
+}
 
-// Device memory for one candidate's owner table; grows (after draining `s`) when needed.
+// Device memory for the batch's owner tables; grows (after draining `s`) when needed.
 static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
-    const int64_t words = plan_map_words(p);
+    const int64_t words = std::max<int64_t>(p->cp.map_words, 4);
     if (p->d_arena && p->cap_arena >= words) return TM_OK;
     TM_HIP(hipStreamSynchronize(s));
     if (p->d_arena) (void)hipFree(p->d_arena);
@@ -943,6 +951,7 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
     }
     if (cells_per_item > 0) p->cells_per_item = cells_per_item;
     layout_eval(cp, p->cells_per_item, false);
+    layout_maps(cp);
     cp.eval.wg_per_cu = p->wg_per_cu;
     p->cp = std::move(cp);
     p->loaded = true;

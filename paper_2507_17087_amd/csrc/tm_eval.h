@@ -19,7 +19,7 @@ struct EvalArgs {
     int64_t n;
     tm_stencil_cost* out;
     int64_t* best;
-    int32_t* best_ids;  // nullable: the selected candidate's owner table, as processor ids
+    int32_t* best_ids;  // nullable: the selected candidate's owner table, as processor ids, goes to its DevEval::offset here
     unsigned long long* counter;
     int64_t elem_bytes;
     int32_t halo[TM_MAX_LRANK];
@@ -42,7 +42,7 @@ struct EvalPlan {
 // Evaluates the batch into out (n rows) and, with best, selects into *best.  counter: a
 // device word that holds 0 between launches.  With idx, the nidx candidates idx[i] instead
 // (whole ones; rows of negative entries are left alone).  best_ids: the selected candidate's
-// owner table as processor ids (for its map), written by the workgroup that selects.
+// owner table as processor ids (for its map), written at its offset by the workgroup that selects.
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
                              unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
                              int64_t nidx = 0, int32_t* best_ids = nullptr);

@@ -316,7 +316,7 @@ __device__ __forceinline__ bool cost_less(int64_t b, int64_t i, int64_t x, int64
 
 // The index minimising (bytes, inter_bytes, index) of n cost rows that other workgroups
 // of this launch wrote (read at device scope) -> *best; with ids, its owner table as
-// processor ids (ev: LDS for its descriptor).
+// processor ids, at its place there (ev: LDS for its descriptor).
 template <int NT>
 __device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best,
                                             const DevEval* evals, int32_t* ids, DevEval& ev) {
@@ -369,7 +369,7 @@ __device__ __forceinline__ void select_rows(const tm_stencil_cost* out, int64_t 
     __syncthreads();
     stage_eval(&ev, evals + wave_uniform64(s_best), t);
     __syncthreads();
-    owner_ids(ev, ids, wave_uniform(ev.vol), t, NT);
+    owner_ids(ev, ids + wave_uniform64(ev.offset), wave_uniform(ev.vol), t, NT);
 }
 
 // The item of a workgroup's turn.  Workgroups go to the eight XCDs in turn, and batches are
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(1024) void k_select_rows(const tm_stencil_cost* __r
     if (!ids || n <= 0) return;
     stage_eval(&ev, evals + wave_uniform64(kx), t);
     __syncthreads();
-    owner_ids(ev, ids, wave_uniform(ev.vol), t, NT);
+    owner_ids(ev, ids + wave_uniform64(ev.offset), wave_uniform(ev.vol), t, NT);
 }
 
 static hipError_t launch_select_rows(const tm_stencil_cost* out, int64_t n, int64_t* best, const DevEval* evals,

@@ -65,7 +65,8 @@ struct alignas(16) DevEval {
     int32_t words, parts, dim_d;  // LDS words the evaluation needs, its workgroups; the dim with the most groups
     int32_t procs;                // nodes * gpus
     int64_t points;               // of the launch domain
-    int64_t first_proc;           // matmul batches: processors of the candidates before this one
+    int64_t offset;               // matmul batches: processors of the candidates before this one;
+                                  // plans: its owner table's first word among the batch's (maps)
     DevDim dim[TM_MAX_LRANK];
     DevProj pj[TM_MAX_MRANK];
     DevOp inv[TM_MAX_OPS];

@@ -25,11 +25,11 @@ struct MapShape {
 // For candidates of volume up to max_vol, max_points points and rows of at least min_row.
 MapShape map_shape(int32_t max_vol, int64_t max_points, int64_t min_row);
 
-// Words of an ids buffer: whole 16-byte pieces.
+// Words of a candidate's ids: whole 16-byte pieces.
 inline int64_t map_ids_words(int32_t vol) { return (vol + 3) & ~3; }
 
-// Candidate *d_index (or index): its owner table as processor ids (and with copy its
-// descriptor, to device memory), then its map.
+// Candidate *d_index (or index): its owner table as processor ids, to ids + its offset (and
+// with copy its descriptor, to device memory), then its map.
 hipError_t launch_map_ids(const DevEval* evals, int64_t n, const int64_t* d_index, int64_t index, int32_t max_vol,
                           int32_t* ids, hipStream_t s, DevEval* copy = nullptr);
 hipError_t launch_map(const MapShape& m, const DevEval* evals, int64_t n, const int64_t* d_index, int64_t index,

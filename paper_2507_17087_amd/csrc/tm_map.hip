@@ -23,7 +23,9 @@ namespace tmk {
 
 // ------------------------------------------------------------------ the owner table
 
-// Processor ids of the candidate's final coordinates (*d_index, or index), written to ids.
+// Processor ids of the candidate's final coordinates (*d_index, or index), written to ids at
+// its offset: every candidate of a plan has a place of its own there, so that the maps of two
+// of them (on two streams) do not disturb each other, and two of one write the same words.
 __global__ __launch_bounds__(256) void k_map_ids(const DevEval* __restrict__ evals, int64_t n,
                                                  const int64_t* __restrict__ d_index, int64_t index,
                                                  int32_t* __restrict__ ids, DevEval* __restrict__ copy) {
@@ -35,7 +37,7 @@ __global__ __launch_bounds__(256) void k_map_ids(const DevEval* __restrict__ eva
     if (copy && blockIdx.x == 0) stage_eval(copy, &ev, threadIdx.x);
     const int32_t vol = wave_uniform(ev.vol), per = ((vol + (int)gridDim.x - 1) / (int)gridDim.x + 255) & ~255;
     const int32_t v0 = (int32_t)blockIdx.x * per, v1 = v0 + per < vol ? v0 + per : vol;
-    if (v0 < v1) owner_table<true>(ev, ids, v0, v1, -1, threadIdx.x, 256);
+    if (v0 < v1) owner_table<true>(ev, ids + wave_uniform64(ev.offset), v0, v1, -1, threadIdx.x, 256);
 }
 
 hipError_t launch_map_ids(const DevEval* evals, int64_t n, const int64_t* d_index, int64_t index, int32_t max_vol,
@@ -77,6 +79,7 @@ __global__ __launch_bounds__(NT) void k_map(const DevEval* __restrict__ evals, i
     const int32_t vol = e->vol;
     const int K = e->lrank;
     const int64_t points = e->points;
+    ids += e->offset;
     if ((int64_t)blockIdx.x * kBlock >= points) return;  // the grid fits the batch's largest domain
     for (int32_t i = tid * 4; i < vol; i += NT * 4) *reinterpret_cast<i32x4v*>(T + i) = *reinterpret_cast<const i32x4v*>(ids + i);
     const uint32_t L = (uint32_t)e->dim[K - 1].l;

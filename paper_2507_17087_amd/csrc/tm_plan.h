@@ -25,6 +25,7 @@ struct Compiled {
     int32_t cnt_words = 0;      // LDS words of the counting launch (largest staged owner table + class blocks)
     int64_t tuples = 0;         // class-tuple bound of the batch (sum of the candidates')
     int64_t tables_words = 0;   // arena words of the tables (the item table follows)
+    int64_t map_words = 0;      // plans: words of all owner tables (each candidate's arena_off is among them)
     EvalPlan eval;              // the evaluation's launches
     int K = 0, H = 1;
 };
@@ -54,7 +55,7 @@ struct tm_plan {
     tmk::DevCand* d_cands = nullptr;
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
     tmk::DevFeat* d_feats = nullptr;  // the features'
-    int32_t* d_arena = nullptr;       // owner table (processor ids) of the candidate being mapped
+    int32_t* d_arena = nullptr;       // owner tables (processor ids) of the candidates mapped so far
     tmk::DevHeader* d_hdr = nullptr;
     unsigned long long* d_counter = nullptr;
     tmk::DevCand* h_cands = nullptr;  // pinned staging

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kMatmulThreads) void k_matmul_groups(const DevEval*
         }
     }
     lds_sync(NW);
-    const int64_t first = wave_uniform64(ev.first_proc);
+    const int64_t first = wave_uniform64(ev.offset);
     if (per_proc)
         for (int32_t i = tid; i < 3 * P; i += NT) {
             const uint32_t p = div_small((uint32_t)i, 1.0f / 3.0f);
