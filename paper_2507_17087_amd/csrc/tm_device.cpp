@@ -833,7 +833,7 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
         hipMalloc((void**)&p->d_evals, (size_t)cands * sizeof(DevEval)) != hipSuccess ||
         hipMalloc((void**)&p->d_feats, (size_t)cands * sizeof(DevFeat)) != hipSuccess ||
         hipMalloc((void**)&p->d_hdr, sizeof(DevHeader)) != hipSuccess ||
-        hipMalloc((void**)&p->d_counter, 256) != hipSuccess || hipMemset(p->d_counter, 0, 256) != hipSuccess ||
+        hipMalloc((void**)&p->d_counter, kCounters * sizeof(unsigned int)) != hipSuccess ||
         hipHostMalloc((void**)&p->h_cands, (size_t)cands * sizeof(DevCand), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&p->h_hdr, sizeof(DevHeader), hipHostMallocDefault) != hipSuccess) {
         plan_free(p);
@@ -880,8 +880,19 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
     if (nc) TM_HIP(hipMemcpyAsync(p->d_cands, p->h_cands, nc, hipMemcpyHostToDevice, s));
     TM_HIP(hipEventRecord(p->up_ev, s));
     p->up_pending = true;
-    TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, p->d_feats, s));
+    TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, p->d_feats, p->d_counter, s));
     return TM_OK;
+}
+
+// The word in which a run counts its finished workgroups.  Runs of one plan may overlap on
+// several streams, so each takes the next one; the replays of a graph keep the word of its
+// capture, which no run outside a graph takes.
+static unsigned int* plan_counter(tm_plan* p, hipStream_t s) {
+    constexpr unsigned int kHalf = kCounters / 2;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return p->d_counter + kHalf + p->captured++ % kHalf;
+    return p->d_counter + p->runs++ % kHalf;
 }
 
 // Enqueues a run (stage -1) or one stage of it on stream s: one launch up to kFinInCount
@@ -893,7 +904,8 @@ static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int6
     const Compiled& cp = p->cp;
     if (stage == 0) return launch_zero_costs(out, cp.hdr.n, s);
     if (stage == 2) return launch_bytes_select(out, cp.hdr.n, cp.hdr.elem_bytes, best, s);
-    return launch_eval_batch(cp.eval, p->d_evals, out, best, p->d_counter, num_cus(), s, nullptr, 0, best_ids);
+    return launch_eval_batch(cp.eval, p->d_evals, out, best, best ? plan_counter(p, s) : nullptr, num_cus(), s, nullptr,
+                             0, best_ids);
 }
 
 // Map launch for a device-side index: fits every loaded candidate.
@@ -1277,7 +1289,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
 // The best of the candidates chosen in sb (sb->sel), by their exact costs.
 hipError_t plan_eval_chosen(tm_plan* p, SearchBufs* sb, int64_t* d_best, tm_stencil_cost* d_best_cost, hipStream_t s) {
     const int64_t nsel = sb->nseg * sb->k;
-    const hipError_t e = launch_eval_batch(p->cp.eval, p->d_evals, sb->sub_out, nullptr, p->d_counter, num_cus(), s,
+    const hipError_t e = launch_eval_batch(p->cp.eval, p->d_evals, sb->sub_out, nullptr, nullptr, num_cus(), s,
                                            sb->sel, nsel);
     if (e != hipSuccess) return e;
     return launch_select_segments(sb->sub_out, sb->seg, sb->nseg, sb->sel, sb->k, d_best, d_best_cost, s);

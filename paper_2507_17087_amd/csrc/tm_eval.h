@@ -12,7 +12,7 @@ namespace tmk {
 // in up to `parts` workgroups each.  parts == 1: whole cost rows are stored; else the cells are added to
 // rows the caller zeroed (bytes follow in another launch).  best (parts == 1, one launch
 // for all candidates): the last workgroup also selects; counter starts at 0 and is left
-// so.
+// so, each launch in flight having one of its own.
 struct EvalArgs {
     const DevEval* evals;
     const int64_t* idx;  // row i evaluates candidate idx[i] (negative: no row); null: i
@@ -20,7 +20,7 @@ struct EvalArgs {
     tm_stencil_cost* out;
     int64_t* best;
     int32_t* best_ids;  // nullable: the selected candidate's owner table, as processor ids, goes to its DevEval::offset here
-    unsigned long long* counter;
+    unsigned int* counter;
     int64_t elem_bytes;
     int32_t halo[TM_MAX_LRANK];
     int32_t node_level, parts, min_words, max_words, lds_words;
@@ -40,14 +40,16 @@ struct EvalPlan {
 };
 
 // Evaluates the batch into out (n rows) and, with best, selects into *best.  counter: a
-// device word that holds 0 between launches.  With idx, the nidx candidates idx[i] instead
+// device word of this launch's own that holds 0 before it (and after it).  With idx, the nidx candidates idx[i] instead
 // (whole ones; rows of negative entries are left alone).  best_ids: the selected candidate's
 // owner table as processor ids (for its map), written at its offset by the workgroup that selects.
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
-                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
+                             unsigned int* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
                              int64_t nidx = 0, int32_t* best_ids = nullptr);
-// The evaluation's view of n compiled candidates.
-hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats, hipStream_t s);
+// The evaluation's view of n compiled candidates; and a plan's counters set to 0.
+constexpr int kCounters = 64;
+hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats,
+                             unsigned int* counters, hipStream_t s);
 // The rows zeroed; and the bytes of rows that hold cells, with the selection.
 hipError_t launch_zero_costs(tm_stencil_cost* out, int64_t n, hipStream_t s);
 hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_bytes, int64_t* best, hipStream_t s,

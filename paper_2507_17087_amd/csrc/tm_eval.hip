@@ -450,17 +450,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_si
         }
     }
     if (!A.best) return;
-    // the last workgroup to finish selects and leaves the counter as it found it
+    // the last workgroup to finish selects; the count wraps to the 0 it started from
     __syncthreads();
     if (tid == 0) {
         __threadfence();  // this workgroup's rows are visible before it reports done
-        s_last = atomicAdd(A.counter, 1ull) == (unsigned long long)gridDim.x - 1;
+        s_last = atomicInc(A.counter, gridDim.x - 1) == gridDim.x - 1;
     }
     __syncthreads();
     if (!s_last) return;
     __threadfence();
     select_rows<NT>(A.out, A.n, A.best, A.evals, A.best_ids, ev);
-    if (tid == 0) *A.counter = 0ull;
 }
 
 static hipError_t launch_eval(const EvalArgs& A, int H, bool wave, int64_t grid, hipStream_t s) {
@@ -482,18 +481,22 @@ static hipError_t launch_eval(const EvalArgs& A, int H, bool wave, int64_t grid,
 // ------------------------------------------------------------------ the evaluation's descriptors
 
 __global__ __launch_bounds__(64) void k_fill_evals(const DevCand* __restrict__ cands, int64_t n, EvalShape shape,
-                                                   DevEval* __restrict__ evals, DevFeat* __restrict__ feats) {
+                                                   DevEval* __restrict__ evals, DevFeat* __restrict__ feats,
+                                                   unsigned int* __restrict__ counters) {
+    static_assert(kCounters == 64, "one a thread of the first workgroup");
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0) counters[threadIdx.x] = 0;
     if (i >= n) return;
     fill_eval(cands[i], shape, &evals[i]);
     fill_feat(cands[i], &feats[i]);
 }
 
-hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats, hipStream_t s) {
+hipError_t launch_fill_evals(const EvalPlan& p, const DevCand* cands, DevEval* evals, DevFeat* feats,
+                             unsigned int* counters, hipStream_t s) {
     if (p.n <= 0) return hipSuccess;
     const EvalShape shape{p.H, p.node_level, p.per_item, p.fill};
     hipLaunchKernelGGL(k_fill_evals, dim3((unsigned)((p.n + 63) / 64)), dim3(64), 0, s, cands, p.n, shape, evals,
-                       feats);
+                       feats, counters);
     return hipGetLastError();
 }
 
@@ -586,7 +589,7 @@ hipError_t launch_bytes_select(tm_stencil_cost* out, int64_t n, int64_t elem_byt
 }
 
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
-                             unsigned long long* counter, int cus, hipStream_t s, const int64_t* idx, int64_t nidx,
+                             unsigned int* counter, int cus, hipStream_t s, const int64_t* idx, int64_t nidx,
                              int32_t* best_ids) {
     const int64_t n = idx ? nidx : p.n;
     if (n <= 0) return hipSuccess;

@@ -57,7 +57,8 @@ struct tm_plan {
     tmk::DevFeat* d_feats = nullptr;  // the features'
     int32_t* d_arena = nullptr;       // owner tables (processor ids) of the candidates mapped so far
     tmk::DevHeader* d_hdr = nullptr;
-    unsigned long long* d_counter = nullptr;
+    unsigned int* d_counter = nullptr;  // [kCounters] finished workgroups of the runs in flight
+    unsigned int runs = 0, captured = 0;  // whose words are taken in turn
     tmk::DevCand* h_cands = nullptr;  // pinned staging
     tmk::DevHeader* h_hdr = nullptr;
     int64_t* h_seg = nullptr;         // pinned staging for search segments

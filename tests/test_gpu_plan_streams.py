@@ -2,6 +2,7 @@
 another gets."""
 import sys
 
+import numpy as np
 import pytest
 
 import oracle
@@ -81,4 +82,31 @@ def test_run_map_beside_maps(tm):
     assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == win
     assert (wmap.cpu().numpy() == oracle.proc_map(cands[win]).ravel()).all()
     assert all((m.cpu().numpy() == oracle.proc_map(cands[i]).ravel()).all() for i, m in zip(others, maps))
+    plan.close()
+
+
+@pytest.mark.parametrize("n", [5, 64, 96])
+def test_runs_in_flight(tm, n):
+    """Runs of one plan on three streams at once, with outputs of their own, several rounds
+    and then one alone: each counts its own finished workgroups."""
+    import torch
+    say("runs in flight", n)
+    forms, st = menu((40, 70, 33)), W.stencil((2, 1, 2), 8)
+    cands = forms[(np.arange(n) * 11 + 3) % len(forms)]
+    plan, out, best = loaded(tm, cands, st)
+    exp = oracle.stencil_cost_batch(cands, st)
+    win = oracle.select_best(exp)
+    sts = [torch.cuda.Stream() for _ in range(3)]
+    for rnd in range(4):
+        outs = [torch.zeros_like(out) for _ in range(45)]
+        wins = [torch.full_like(best, -9) for _ in outs]
+        torch.cuda.synchronize()
+        for i, (o, w) in enumerate(zip(outs, wins)):
+            with torch.cuda.stream(sts[i % 3]):
+                plan.run(o, w)
+        torch.cuda.synchronize()
+        assert all((o.cpu().numpy() == exp).all() for o in outs), rnd
+        assert [int(w.cpu()[0]) for w in wins] == [win] * len(wins), rnd
+        plan.run(out.zero_(), best.fill_(-9))
+        assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == win
     plan.close()
