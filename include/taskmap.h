@@ -44,6 +44,10 @@
  *     caller-owned device memory (e.g. torch tensors) of the current HIP device and
  *     are written by work enqueued on `stream` (a hipStream_t; NULL = the null
  *     stream).  Results are valid once the stream reaches that work.
+ *   - A stream that captures a HIP graph takes a loaded plan's runs and maps.  The other
+ *     device calls on host arrays of candidates or segments (tm_chain_table, tm_proc_map,
+ *     tm_eval_*, tm_select_best) return TM_ENOTSUP there and record nothing: their
+ *     descriptors are gone when the graph is replayed.
  *   - Opaque handles (tm_plan, tm_ranker) are created and destroyed only here.
  *   - Calls on different streams are independent; one handle must not be used by
  *     two threads at once.
@@ -222,8 +226,8 @@ int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, void* stream
 int tm_eval_stencil_batch(const tm_candidate* c, int64_t n, const tm_stencil* st,
                           tm_stencil_cost* d_out, void* stream);
 
-/* For callers that cannot allocate device memory (code under HIP graph capture,
- * tight serving loops, harnesses that forbid allocation): tm_eval_stencil_batch
+/* For callers that cannot allocate device memory (tight serving loops, harnesses that
+ * forbid allocation): tm_eval_stencil_batch
  * with the same arguments, results and validation, allocating no device memory and
  * no pinned host memory.
  * The descriptors live in a device array of TM_NOALLOC_SCRATCH_BYTES that the library

@@ -235,6 +235,18 @@ void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
 
 // ------------------------------------------------------------------ staging
 
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+}
+
+// A single call's descriptors live until its work is done; the replays of a graph that
+// recorded it come later, when their memory holds other calls' descriptors or is gone.
+int refuse_capture(hipStream_t s) {
+    if (!capturing(s)) return TM_OK;
+    return set_error(TM_ENOTSUP, "the stream is capturing: single calls cannot be recorded (a loaded plan's runs and maps can)");
+}
+
 // Per-thread pinned staging for descriptor uploads; reused once the previous copy
 // out of it has completed.
 struct Staging {
@@ -349,11 +361,6 @@ static int slot_release(const Slot& slot, hipStream_t s) {
     return TM_OK;
 }
 
-// A capture's replays would find other descriptors in a slot.
-static bool slots_fit(size_t bytes, hipStream_t s) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    return bytes <= kSlotBytes && hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-}
 
 // Descriptors that fill writes, for launch to read: in a slot, or larger ones in a device
 // copy.  fill's result: TM_OK, an error, or kGeneral (nothing is launched).  *memory: the
@@ -364,7 +371,9 @@ template <class Fill, class Launch>
 static int with_descriptors(size_t bytes, hipStream_t s, const char* what, int* memory, Fill fill, Launch launch) {
     hipError_t e = hipSuccess;
     int rc;
-    if (slots_fit(bytes, s)) {
+    *memory = refuse_capture(s);
+    if (*memory != TM_OK) return kGeneral;
+    if (bytes <= kSlotBytes) {
         Slot slot;
         *memory = slot_acquire(false, &slot);
         rc = *memory == TM_OK ? fill((void*)slot.host) : kGeneral;
@@ -395,13 +404,15 @@ struct DeviceBatch {
 };
 
 static int upload_batch(const Compiled& cp, DeviceBatch& db, hipStream_t s) {
+    int rc = refuse_capture(s);
+    if (rc != TM_OK) return rc;
     const size_t nc = cp.cands.size() * sizeof(DevCand);
     TM_HIP(hipMallocAsync((void**)&db.cands, std::max<size_t>(nc, 64), s));
     TM_HIP(hipMallocAsync((void**)&db.hdr, sizeof(DevHeader) + 64, s));
     TM_HIP(hipMallocAsync((void**)&db.arena, std::max<size_t>((size_t)cp.arena_words * 4, 64), s));
     TM_HIP(hipMallocAsync((void**)&db.counter, 64, s));
     void* stg = nullptr;
-    int rc = staging_acquire(nc + sizeof(DevHeader), &stg);
+    rc = staging_acquire(nc + sizeof(DevHeader), &stg);
     if (rc != TM_OK) return rc;
     std::memcpy(stg, &cp.hdr, sizeof(DevHeader));
     if (nc) std::memcpy((char*)stg + sizeof(DevHeader), cp.cands.data(), nc);
@@ -462,32 +473,18 @@ extern "C" int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, v
     if (!d_map) return set_error(TM_EINVAL, "null output");
     const EvalShape shape{1, 0, 0, 1};
     const MapShape m = map_shape(c0.vol, c0.npoints, c0.L);
-    hipError_t e = hipSuccess;
-    if (slots_fit(sizeof(DevEval), s)) {
-        Slot slot;
-        rc = slot_acquire(true, &slot);
-        if (rc != TM_OK) return rc;
-        DevEval *h = reinterpret_cast<DevEval*>(slot.host), *d = reinterpret_cast<DevEval*>(slot.scratch);
-        int32_t* ids = reinterpret_cast<int32_t*>(d + 1);
-        fill_eval(c0, shape, h);
-        // every workgroup of the map reads the descriptor: it goes to device memory on the way
-        e = launch_map_ids(h, 1, nullptr, 0, c0.vol, ids, s, d);
-        if (e == hipSuccess) e = launch_map(m, d, 1, nullptr, 0, ids, d_map, s);
-        rc = slot_release(slot, s);
-    } else {
-        void* stg = nullptr;
-        DevEval* d = nullptr;
-        rc = staging_acquire(sizeof(DevEval), &stg);
-        if (rc != TM_OK) return rc;
-        fill_eval(c0, shape, static_cast<DevEval*>(stg));
-        TM_HIP(hipMallocAsync((void**)&d, sizeof(DevEval) + (size_t)map_ids_words(c0.vol) * 4, s));
-        int32_t* ids = reinterpret_cast<int32_t*>(d + 1);
-        e = hipMemcpyAsync(d, stg, sizeof(DevEval), hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) rc = staging_release(s);
-        if (rc == TM_OK && e == hipSuccess) e = launch_map_ids(d, 1, nullptr, 0, c0.vol, ids, s);
-        if (rc == TM_OK && e == hipSuccess) e = launch_map(m, d, 1, nullptr, 0, ids, d_map, s);
-        (void)hipFreeAsync(d, s);
-    }
+    rc = refuse_capture(s);
+    if (rc != TM_OK) return rc;
+    Slot slot;
+    rc = slot_acquire(true, &slot);
+    if (rc != TM_OK) return rc;
+    DevEval *h = reinterpret_cast<DevEval*>(slot.host), *d = reinterpret_cast<DevEval*>(slot.scratch);
+    int32_t* ids = reinterpret_cast<int32_t*>(d + 1);
+    fill_eval(c0, shape, h);
+    // every workgroup of the map reads the descriptor: it goes to device memory on the way
+    hipError_t e = launch_map_ids(h, 1, nullptr, 0, c0.vol, ids, s, d);
+    if (e == hipSuccess) e = launch_map(m, d, 1, nullptr, 0, ids, d_map, s);
+    rc = slot_release(slot, s);
     if (rc == TM_OK && e != hipSuccess) rc = set_error(TM_EDEVICE, "map launch: %s", hipGetErrorString(e));
     return rc;
 }
@@ -772,10 +769,12 @@ extern "C" int tm_select_best(const tm_stencil_cost* d_costs, const int64_t* seg
     for (int64_t i = 0; i < nseg; ++i)
         if (seg[i] < 0 || seg[i + 1] < seg[i]) return set_error(TM_EINVAL, "segment %lld is not ordered", (long long)i);
     if (seg[nseg] > 0 && !d_costs) return set_error(TM_EINVAL, "null costs");
+    int rc = refuse_capture(s);
+    if (rc != TM_OK) return rc;
     int64_t* d_seg = nullptr;
     TM_HIP(hipMallocAsync((void**)&d_seg, (size_t)(nseg + 1) * 8, s));
     void* stg = nullptr;
-    int rc = staging_acquire((size_t)(nseg + 1) * 8, &stg);
+    rc = staging_acquire((size_t)(nseg + 1) * 8, &stg);
     if (rc == TM_OK) {
         std::memcpy(stg, seg, (size_t)(nseg + 1) * 8);
         hipError_t e = hipMemcpyAsync(d_seg, stg, (size_t)(nseg + 1) * 8, hipMemcpyHostToDevice, s);
@@ -889,9 +888,7 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
 // capture, which no run outside a graph takes.
 static unsigned int* plan_counter(tm_plan* p, hipStream_t s) {
     constexpr unsigned int kHalf = kCounters / 2;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
-        return p->d_counter + kHalf + p->captured++ % kHalf;
+    if (capturing(s)) return p->d_counter + kHalf + p->captured++ % kHalf;
     return p->d_counter + p->runs++ % kHalf;
 }
 

@@ -68,6 +68,8 @@ extern "C" int tm_eval_stencil_batch_noalloc(const tm_candidate* c, int64_t n, c
     if (need > (int64_t)TM_NOALLOC_SCRATCH_BYTES)
         return set_error(TM_ECAPACITY, "the batch needs %lld bytes of scratch; the library holds %lld",
                          (long long)need, (long long)TM_NOALLOC_SCRATCH_BYTES);
+    rc = refuse_capture(s);
+    if (rc != TM_OK) return rc;
     char* base = nullptr;
     rc = scratch_ptr((void**)&base);
     if (rc != TM_OK) return rc;

@@ -82,6 +82,9 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
 // parts; the launches).  node_level: the node-level volume.
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 
+// TM_ENOTSUP while s is capturing: for calls whose descriptors do not outlive them.
+int refuse_capture(hipStream_t s);
+
 int64_t plan_size(const tm_plan* p);
 const DevFeat* plan_feats(const tm_plan* p);
 EstimateBatch plan_estimates(const tm_plan* p);

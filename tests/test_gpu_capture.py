@@ -1,0 +1,97 @@
+"""What a caller's graph can record: a loaded plan's calls, whose replays equal the eager
+results; single calls, whose descriptors do not outlive the call, are refused and leave the
+capture whole."""
+import contextlib
+import gc
+import sys
+
+import pytest
+
+import oracle
+import workloads as W
+from test_gpu_volumes import huge
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-case]", *a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def tm():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2507_17087_amd as m
+    m.lib()
+    return m
+
+
+@contextlib.contextmanager
+def recording():
+    """A graph being captured.  Nothing is garbage-collected meanwhile: a graph or a plan of
+    an earlier test would be destroyed, which waits for the device."""
+    import torch
+    g = torch.cuda.CUDAGraph()
+    gc.collect()
+    gc.disable()
+    try:
+        with torch.cuda.graph(g):
+            yield g
+    finally:
+        gc.enable()
+
+
+def code_of(tm, call):
+    """The error code of a call, 0 if it succeeds; no reference to its frames is kept."""
+    try:
+        call()
+    except tm.TaskmapError as e:
+        return e.code
+    return 0
+
+
+def batch():
+    cands = W.c2_candidates(oracle.enumerate_factorizations(128, 3), extent=(24, 40, 17))[3:150:9]
+    st = W.stencil((1, 2, 1), 8)
+    return cands, st, oracle.stencil_cost_batch(cands, st)
+
+
+@pytest.mark.parametrize("before", [False, True])
+def test_single_calls_are_refused(tm, before):
+    """before: the thread has its staging memory and slots already."""
+    import torch
+    say("single calls under capture", before)
+    cands, st, exp = batch()
+    big = W.batch([cands[0], W.candidate((24, 40, 17), 16, 8, [W.merge(0, 1), W.balance_split(0, 33000)])])
+    many = cands[[i % len(cands) for i in range(1200)]]
+    costs = torch.from_numpy(exp).cuda()
+    rows = torch.zeros((len(many), 4), dtype=torch.int64, device="cuda")
+    calls = [lambda: tm.tm_eval_stencil_batch(cands, st, rows), lambda: tm.tm_eval_stencil_batch_noalloc(cands, st, rows),
+             lambda: tm.tm_eval_stencil_batch(many, st, rows),
+             lambda: tm.tm_eval_stencil_node_batch(cands, st, rows), lambda: tm.tm_proc_map(cands[0]),
+             lambda: tm.tm_chain_table(cands[0]), lambda: tm.tm_eval_matmul_batch(cands, 8),
+             lambda: tm.tm_eval_matmul_batch(W.batch([huge((6, 5, 4), 2, 2)]), 8),
+             lambda: tm.tm_eval_redistribution_batch(cands, cands, 8, rows),
+             lambda: tm.tm_eval_redistribution_batch(big, big, 8, rows),
+             lambda: tm.tm_select_best(costs, [0, 3, len(cands)])]
+    if before:
+        for c in calls:
+            c()
+    plan = tm.Plan(len(cands), 1)
+    plan.load(cands, st)
+    out = torch.zeros((len(cands), 4), dtype=torch.int64, device="cuda")
+    best = torch.zeros(1, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    codes = []
+    with recording() as g:
+        codes += [code_of(tm, c) for c in calls]
+        plan.run(out, best)
+    assert codes == [tm.TM_ENOTSUP] * len(calls)
+    for _ in range(3):
+        assert (tm.tm_eval_stencil_batch(cands, st, out.zero_()).cpu().numpy() == exp).all()
+        out.zero_(), best.fill_(-3)
+        g.replay()
+        torch.cuda.synchronize()
+        assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == oracle.select_best(exp)
+    plan.close()
