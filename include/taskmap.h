@@ -310,7 +310,8 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
  * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run is one evaluation
  * launch whatever the candidates' launch ranks (two when their LDS needs differ much),
  * which also selects for batches of at most 128 candidates.  It makes no host
- * synchronisation and can be captured in the caller's own graph.
+ * synchronisation and can be captured in the caller's own graph, and so can the maps; a
+ * graph belongs to the batch that was loaded when it was captured.
  * d_out: tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  A work item is a workgroup:
  * a candidate, or a part of one holding about cells_per_item of its group tuples (0 = a
  * default: whole candidates, but parts where they are too few to fill the GPU; at most

@@ -235,9 +235,18 @@ void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level) {
 
 // ------------------------------------------------------------------ staging
 
-static bool capturing(hipStream_t s) {
+bool capturing(hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+}
+
+hipError_t malloc_anytime(void** p, size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return e;
+    const hipError_t m = hipMalloc(p, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return m;
 }
 
 // A single call's descriptors live until its work is done; the replays of a graph that
@@ -803,6 +812,8 @@ static void plan_free(tm_plan* p) {
     if (p->d_evals) (void)hipFree(p->d_evals);
     if (p->d_feats) (void)hipFree(p->d_feats);
     if (p->d_arena) (void)hipFree(p->d_arena);
+    for (int32_t* a : p->outgrown) (void)hipFree(a);
+    p->outgrown.clear();
     if (p->d_hdr) (void)hipFree(p->d_hdr);
     if (p->d_counter) (void)hipFree(p->d_counter);
     if (p->h_cands) (void)hipHostFree(p->h_cands);
@@ -853,15 +864,21 @@ static void layout_maps(Compiled& cp) {
     cp.map_words = words;
 }
 
-// Device memory for the batch's owner tables; grows (after draining `s`) when needed.
+// Device memory for the batch's owner tables; grows (after draining `s`) when needed.  A
+// capture can neither wait nor free: there the old memory stays until the plan's end, so that
+// the first map of a batch can be recorded too.
 static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
     const int64_t words = std::max<int64_t>(p->cp.map_words, 4);
     if (p->d_arena && p->cap_arena >= words) return TM_OK;
-    TM_HIP(hipStreamSynchronize(s));
-    if (p->d_arena) (void)hipFree(p->d_arena);
+    if (capturing(s)) {
+        if (p->d_arena) p->outgrown.push_back(p->d_arena);
+    } else {
+        TM_HIP(hipStreamSynchronize(s));
+        if (p->d_arena) (void)hipFree(p->d_arena);
+    }
     p->d_arena = nullptr;
     p->cap_arena = 0;
-    if (hipMalloc((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
+    if (malloc_anytime((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
         return set_error(TM_ENOMEM, "table arena of %lld words", (long long)words);
     p->cap_arena = words;
     return TM_OK;

@@ -56,6 +56,7 @@ struct tm_plan {
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
     tmk::DevFeat* d_feats = nullptr;  // the features'
     int32_t* d_arena = nullptr;       // owner tables (processor ids) of the candidates mapped so far
+    std::vector<int32_t*> outgrown;   // earlier ones, replaced during a capture
     tmk::DevHeader* d_hdr = nullptr;
     unsigned int* d_counter = nullptr;  // [kCounters] finished workgroups of the runs in flight
     unsigned int runs = 0, captured = 0;  // whose words are taken in turn
@@ -82,6 +83,9 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
 // parts; the launches).  node_level: the node-level volume.
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 
+bool capturing(hipStream_t s);
+// hipMalloc, also while a stream is capturing (which otherwise forbids it).
+hipError_t malloc_anytime(void** p, size_t bytes);
 // TM_ENOTSUP while s is capturing: for calls whose descriptors do not outlive them.
 int refuse_capture(hipStream_t s);
 

@@ -95,3 +95,51 @@ def test_single_calls_are_refused(tm, before):
         torch.cuda.synchronize()
         assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == oracle.select_best(exp)
     plan.close()
+
+
+@pytest.mark.parametrize("calls", ["map", "map-at-index", "run-map", "all"])
+@pytest.mark.parametrize("reload", [False, True])
+def test_maps_after_a_run(tm, calls, reload):
+    """The first maps of a plan, recorded after a run of it: reload, of a larger batch after
+    the smaller one's map."""
+    import torch
+    say("captured", calls, "after a reload" if reload else "")
+    cands, st, exp = batch()
+    n, win = 24 * 40 * 17, oracle.select_best(exp)
+    other = (win + 2) % len(cands)
+    plan = tm.Plan(len(cands), 1)
+    out = torch.zeros((len(cands), 4), dtype=torch.int64, device="cuda")
+    best = torch.zeros(1, dtype=torch.int64, device="cuda")
+    wmap, omap, smap = (torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(3))
+    if reload:
+        plan.load(cands[:2], st)
+        plan.run(out, best)
+        plan.materialize(smap, index=1)
+    plan.load(cands, st)
+    plan.run(out, best)
+    torch.cuda.synchronize()
+    with recording() as g:
+        if calls == "run-map":
+            plan.run_map(out, best, wmap)
+        elif calls == "all":
+            plan.run(out, best)
+        if calls in ("map", "all"):
+            plan.materialize(wmap, d_index=best)
+        if calls in ("map-at-index", "all"):
+            plan.materialize(omap, index=other)
+    for _ in range(4):
+        wmap.fill_(-1), omap.fill_(-1)
+        if calls in ("run-map", "all"):
+            out.zero_(), best.fill_(-1)
+        plan.materialize(smap, index=(other + 1) % len(cands))  # the plan's own work in between
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == win
+        if calls != "map-at-index":
+            assert (wmap.cpu().numpy() == oracle.proc_map(cands[win]).ravel()).all()
+        if calls in ("map-at-index", "all"):
+            assert (omap.cpu().numpy() == oracle.proc_map(cands[other]).ravel()).all()
+    if reload:
+        assert (smap.cpu().numpy() == oracle.proc_map(cands[(other + 1) % len(cands)]).ravel()).all()
+    plan.close()
