@@ -579,7 +579,6 @@ static int redistribution_groups(const tm_candidate* src, const tm_candidate* ds
             words = std::max(words, w);
             parts = std::max(parts, p->parts);
         }
-        if (n * parts > INT32_MAX) return kGeneral;
         return d_out ? TM_OK : set_error(TM_EINVAL, "null output");
     };
     return with_descriptors((size_t)n * sizeof(DevPair), s, "redistribution", &memory, fill, [&](const void* d) {

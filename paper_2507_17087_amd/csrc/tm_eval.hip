@@ -609,7 +609,7 @@ hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil
     if (fin) A.best = best;
     if (fin) A.best_ids = best_ids;
     hipError_t e = parts > 1 ? launch_zero_costs(out, n, s) : hipSuccess;
-    int64_t grid = n * parts;
+    int64_t grid = std::min<int64_t>(n * parts, kMaxGrid);  // workgroups take the items beyond in turn
     if (p.wg_per_cu > 0) grid = std::min<int64_t>(grid, (int64_t)p.wg_per_cu * cus);
     for (int b = 0; b < 2 && e == hipSuccess; ++b) {
         if (p.words[b] == 0) continue;

@@ -193,6 +193,10 @@ __host__ __device__ inline int32_t group_stride(bool cyclic, int32_t h, bool mas
 // The records are laid out for halos up to 1, 2 or 4.
 __host__ __device__ inline int32_t halo_class(int32_t h) { return h <= 1 ? 1 : (h <= 2 ? 2 : 4); }
 
+// Most workgroups of a launch of at most 256 threads each: a grid dimension holds fewer than
+// 2^32 threads.
+constexpr int64_t kMaxGrid = INT32_MAX / 256;
+
 int set_error(int code, const char* fmt, ...);
 int validate_shapes(const tm_candidate* c, Shapes* sh);
 int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);

@@ -387,14 +387,20 @@ hipError_t launch_pairs(const DevPair* pairs, int64_t n, int32_t parts, int32_t 
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const int64_t grid = n * parts;
-    if (grid <= kPairWide)
-        hipLaunchKernelGGL(k_pairs<1024>, dim3((unsigned)grid), dim3(1024), (size_t)lds_words * 4, s, pairs, parts,
+    if (n * parts <= kPairWide) {
+        hipLaunchKernelGGL(k_pairs<1024>, dim3((unsigned)(n * parts)), dim3(1024), (size_t)lds_words * 4, s, pairs, parts,
                            elem_bytes, out);
-    else
-        hipLaunchKernelGGL(k_pairs<256>, dim3((unsigned)grid), dim3(256), (size_t)lds_words * 4, s, pairs, parts,
-                           elem_bytes, out);
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    const int64_t most = kMaxGrid / parts;  // pairs a launch (parts: at most the groups that fit the LDS)
+    for (int64_t a = 0; a < n; a += most) {
+        const int64_t m = std::min(n - a, most);
+        hipLaunchKernelGGL(k_pairs<256>, dim3((unsigned)(m * parts)), dim3(256), (size_t)lds_words * 4, s, pairs + a, parts,
+                           elem_bytes, out + a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace tmk

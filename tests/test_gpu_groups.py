@@ -131,3 +131,25 @@ def test_workgroups_by_batch(tm, halo, n):
         of = forms["lrank"] == k
         exp[of] = oracle.stencil_cost_batch(forms[of], W.stencil((halo,) * k, 8))
     assert (tm.tm_eval_stencil_batch(forms[pick], st).cpu().numpy() == exp[pick]).all()
+
+
+def test_more_items_than_a_grid(tm):
+    """4,200 candidates cut into items of one tuple, one of them into 16,000: with one-wave
+    workgroups more than 2^32 threads, so workgroups take several items."""
+    import torch
+    say("more items than a grid holds")
+    forms = random_forms(60, 9, 2, 20)
+    cands = forms[np.arange(4200) % len(forms)]
+    cands[4100] = W.candidate((20000, 3), 2000, 8, [merge(0, 1), decompose(0, (16000, 1))])
+    st = W.stencil((1, 1), 8)
+    exp = oracle.stencil_cost_batch(forms, st)[np.arange(4200) % len(forms)]
+    exp[4100] = oracle.stencil_cost_batch(cands[4100:4101], st)[0]
+    plan = tm.Plan(len(cands), 1)
+    plan.load(cands, st, cells_per_item=1)
+    assert plan.info()[1] > 16000
+    out = torch.full((len(cands), 4), -1, dtype=torch.int64, device="cuda")
+    best = torch.empty(1, dtype=torch.int64, device="cuda")
+    plan.run(out, best)
+    assert (out.cpu().numpy() == exp).all()
+    assert int(best.cpu()[0]) == oracle.select_best(exp)
+    plan.close()

@@ -141,3 +141,17 @@ def test_pairs_with_many_block_sizes(tm):
                                          balance_split(4, 17), balance_split(5, 23)], [(0, B)] * 6 + [(1, B)])
     b = W.candidate((101, 4), 1, 13585, [decompose(1, (5, 11, 13, 19))], [(0, B)] * 5)
     check_pairs(tm, [(x, y) for x in (a, b) for y in (a, b)])
+
+
+def test_more_parts_than_a_grid(tm):
+    """16,500 pairs, one of them in 1,024 parts: 2^32 threads in one launch."""
+    say("more parts than a grid holds")
+    big = [W.candidate((4500, 4400), 512, 8, [merge(0, 1), W.decompose(0, f)]) for f in ((4096, 1), (1, 4096))]
+    some = pairs_of(forms(40, 3, 2, (37, 53)), 3)
+    pairs = [some[i % len(some)] for i in range(16500)]
+    pairs[16400] = tuple(big)
+    exp = np.asarray(oracle.redistribution_cost_batch(W.batch([p[0] for p in some]), W.batch([p[1] for p in some]), 8))
+    exp = exp[np.arange(len(pairs)) % len(some)]
+    exp[16400] = np.asarray(oracle.redistribution_cost_batch(W.batch(big[:1]), W.batch(big[1:]), 8))[0]
+    got = tm.tm_eval_redistribution_batch(W.batch([p[0] for p in pairs]), W.batch([p[1] for p in pairs]), 8)
+    assert (got.cpu().numpy() == exp).all()
