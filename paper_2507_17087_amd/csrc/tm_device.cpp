@@ -286,7 +286,7 @@ static int staging_acquire(size_t bytes, void** out) {
         g_stage.cap = 0;
         const size_t cap = std::max<size_t>(bytes, 1 << 20);
         if (hipHostMalloc(&g_stage.ptr, cap, hipHostMallocDefault) != hipSuccess)
-            return set_error(TM_ENOMEM, "pinned staging of %zu bytes", cap);
+            return no_memory("pinned staging of %zu bytes", cap);
         g_stage.cap = cap;
     }
     *out = g_stage.ptr;
@@ -347,11 +347,11 @@ static int slot_acquire(bool scratch, Slot* out) {
     r.device = dev;
     if (!r.host && hipHostMalloc((void**)&r.host, kSlots * kSlotBytes, hipHostMallocDefault) != hipSuccess) {
         r.host = nullptr;
-        return set_error(TM_ENOMEM, "pinned staging of %zu bytes", kSlots * kSlotBytes);
+        return no_memory("pinned staging of %zu bytes", kSlots * kSlotBytes);
     }
     if (scratch && !r.scratch && hipMalloc((void**)&r.scratch, kSlots * kSlotScratch) != hipSuccess) {
         r.scratch = nullptr;
-        return set_error(TM_ENOMEM, "scratch of %zu bytes", kSlots * kSlotScratch);
+        return no_memory("scratch of %zu bytes", kSlots * kSlotScratch);
     }
     const int i = r.next;
     if (!r.ev[i]) TM_HIP(hipEventCreateWithFlags(&r.ev[i], hipEventDisableTiming));
@@ -846,7 +846,7 @@ static int plan_alloc(tm_plan* p, int64_t cands) {
         hipHostMalloc((void**)&p->h_cands, (size_t)cands * sizeof(DevCand), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&p->h_hdr, sizeof(DevHeader), hipHostMallocDefault) != hipSuccess) {
         plan_free(p);
-        return set_error(TM_ENOMEM, "plan buffers for %lld candidates", (long long)cands);
+        return no_memory("plan buffers for %lld candidates", (long long)cands);
     }
     p->cap_cands = cands;
     return TM_OK;
@@ -878,12 +878,14 @@ static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
     p->d_arena = nullptr;
     p->cap_arena = 0;
     if (malloc_anytime((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
-        return set_error(TM_ENOMEM, "table arena of %lld words", (long long)words);
+        return no_memory("table arena of %lld words", (long long)words);
     p->cap_arena = words;
     return TM_OK;
 }
 
+// The batch's descriptors to the device; loaded once they are on their way.
 static int plan_upload(tm_plan* p, hipStream_t s) {
+    p->loaded = false;
     if (p->up_pending) {
         TM_HIP(hipEventSynchronize(p->up_ev));
         p->up_pending = false;
@@ -896,6 +898,7 @@ static int plan_upload(tm_plan* p, hipStream_t s) {
     TM_HIP(hipEventRecord(p->up_ev, s));
     p->up_pending = true;
     TM_HIP(launch_fill_evals(p->cp.eval, p->d_cands, p->d_evals, p->d_feats, p->d_counter, s));
+    p->loaded = true;
     return TM_OK;
 }
 
@@ -930,11 +933,11 @@ extern "C" int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** ou
     if (!out) return set_error(TM_EINVAL, "null output");
     *out = nullptr;
     tm_plan* p = new (std::nothrow) tm_plan();
-    if (!p) return set_error(TM_ENOMEM, "plan");
+    if (!p) return no_memory("plan");
     (void)hipGetDevice(&p->device);
     int rc = plan_alloc(p, max_cands);
     if (rc == TM_OK && max_words > 0) {
-        if (hipMalloc((void**)&p->d_arena, (size_t)max_words * 4) != hipSuccess) rc = set_error(TM_ENOMEM, "arena");
+        if (hipMalloc((void**)&p->d_arena, (size_t)max_words * 4) != hipSuccess) rc = no_memory("arena");
         else p->cap_words = p->cap_arena = max_words;
     }
     if (rc == TM_OK && hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming) != hipSuccess)
@@ -970,6 +973,7 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
     if (n > p->cap_cands) {
         // grow: wait for work that may still read the old buffers
         TM_HIP(hipStreamSynchronize(s));
+        p->loaded = false;  // its buffers go, whether or not larger ones come
         rc = plan_alloc(p, std::max(n, p->cap_cands));
         if (rc != TM_OK) return rc;
         p->up_pending = false;
@@ -979,7 +983,6 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
     layout_maps(cp);
     cp.eval.wg_per_cu = p->wg_per_cu;
     p->cp = std::move(cp);
-    p->loaded = true;
     return plan_upload(p, s);
 }
 
@@ -1166,7 +1169,7 @@ static int ensure_rank_bufs(SearchBufs& b, int64_t n, int64_t m, hipStream_t s) 
         b.cap_n = 0;
         if (hipMalloc((void**)&b.X, (size_t)std::max<int64_t>(n, 1) * kFeat * 2) != hipSuccess ||
             hipMalloc((void**)&b.base, (size_t)std::max<int64_t>(n, 1) * 4) != hipSuccess)
-            return set_error(TM_ENOMEM, "feature buffers");
+            return no_memory("feature buffers");
         b.cap_n = n;
     }
     if (b.cap_sc < sc) {
@@ -1175,7 +1178,7 @@ static int ensure_rank_bufs(SearchBufs& b, int64_t n, int64_t m, hipStream_t s) 
         b.score = nullptr;
         b.cap_sc = 0;
         if (hipMalloc((void**)&b.score, (size_t)sc * 4) != hipSuccess)
-            return set_error(TM_ENOMEM, "score buffers");
+            return no_memory("score buffers");
         b.cap_sc = sc;
     }
     return TM_OK;
@@ -1239,7 +1242,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
             b.cap_pre = 0;
             if (hipMalloc((void**)&b.pre, (size_t)npre * 8) != hipSuccess ||
                 hipMalloc((void**)&b.est, (size_t)npre * 2 * sizeof(double)) != hipSuccess)
-                return set_error(TM_ENOMEM, "prefilter buffer");
+                return no_memory("prefilter buffer");
             b.cap_pre = npre;
         }
         if (b.cap_sel < nsel) {
@@ -1252,7 +1255,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
             b.cap_sel = 0;
             if (hipMalloc((void**)&b.sel, (size_t)nsel * 8) != hipSuccess ||
                 hipMalloc((void**)&b.sub_out, (size_t)nsel * sizeof(tm_stencil_cost)) != hipSuccess)
-                return set_error(TM_ENOMEM, "survivor buffers");
+                return no_memory("survivor buffers");
             b.cap_sel = nsel;
         }
     } else if (b.cap_all < n) {
@@ -1262,7 +1265,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
         b.all_out = nullptr;
         b.cap_all = 0;
         if (hipMalloc((void**)&b.all_out, (size_t)std::max<int64_t>(n, 1) * sizeof(tm_stencil_cost)) != hipSuccess)
-            return set_error(TM_ENOMEM, "cost buffer");
+            return no_memory("cost buffer");
         b.cap_all = n;
     }
     if (b.cap_seg < nseg + 1) {
@@ -1272,7 +1275,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
         b.seg = nullptr;
         b.cap_seg = 0;
         if (hipMalloc((void**)&b.seg, (size_t)(nseg + 1) * 8) != hipSuccess)
-            return set_error(TM_ENOMEM, "segment buffers");
+            return no_memory("segment buffers");
         b.cap_seg = nseg + 1;
     }
     // segments: copy only when they changed (pinned staging, ordered on s)
@@ -1285,7 +1288,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
             if (p->h_seg) (void)hipHostFree(p->h_seg);
             p->h_seg = nullptr;
             if (hipHostMalloc((void**)&p->h_seg, (size_t)(nseg + 1) * 8, hipHostMallocDefault) != hipSuccess)
-                return set_error(TM_ENOMEM, "segment staging");
+                return no_memory("segment staging");
             p->cap_hseg = nseg + 1;
         }
         std::memcpy(p->h_seg, seg, (size_t)(nseg + 1) * 8);

@@ -198,6 +198,12 @@ __host__ __device__ inline int32_t halo_class(int32_t h) { return h <= 1 ? 1 : (
 constexpr int64_t kMaxGrid = INT32_MAX / 256;
 
 int set_error(int code, const char* fmt, ...);
+// TM_ENOMEM for a HIP allocation, whose own error the next launch's check would report.
+template <class... A>
+int no_memory(const char* fmt, A... args) {
+    (void)hipGetLastError();
+    return set_error(TM_ENOMEM, fmt, args...);
+}
 int validate_shapes(const tm_candidate* c, Shapes* sh);
 int fill_devcand(const tm_candidate* c, const Shapes& sh, DevCand* d);
 

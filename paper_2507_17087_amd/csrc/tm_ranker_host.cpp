@@ -87,7 +87,7 @@ static int ranker_buffers(tm_ranker* r, int64_t rows) {
     const int64_t cap = pad_rows(std::max<int64_t>(rows, 1024));
     const size_t bytes = (size_t)cap * (kFeat + 6 * kWidth) * 2 + (size_t)cap * 2 * kOut * 4 + (size_t)(cap / 16) * kColParts * 4 +
                          (size_t)r->L.count * (kMaxSplits + 1) * 4 + 16 * 256;
-    if (hipMalloc(&r->bufmem, bytes) != hipSuccess) return set_error(TM_ENOMEM, "ranker buffers");
+    if (hipMalloc(&r->bufmem, bytes) != hipSuccess) return no_memory("ranker buffers");
     char* q = (char*)r->bufmem;
     auto take = [&](size_t n) {
         void* p = q;
@@ -111,7 +111,7 @@ static int forward_buffer(tm_ranker* r, int64_t rows) {
     if (r->X) TM_HIP(hipFree(r->X));
     r->X = nullptr;
     r->cap_x = 0;
-    if (hipMalloc((void**)&r->X, (size_t)rows * kFeat * 2) != hipSuccess) return set_error(TM_ENOMEM, "ranker features");
+    if (hipMalloc((void**)&r->X, (size_t)rows * kFeat * 2) != hipSuccess) return no_memory("ranker features");
     r->cap_x = rows;
     return TM_OK;
 }
@@ -207,7 +207,7 @@ int tm_ranker_create(uint64_t seed, tm_ranker** out) {
     if (!out) return set_error(TM_EINVAL, "null output");
     *out = nullptr;
     tm_ranker* r = new (std::nothrow) tm_ranker();
-    if (!r) return set_error(TM_ENOMEM, "ranker");
+    if (!r) return no_memory("ranker");
     int rc = ranker_alloc_weights(r);
     if (rc != TM_OK) {
         tm_ranker_destroy(r);
@@ -324,7 +324,7 @@ int tm_ranker_train(tm_ranker* r, const float* d_feat, const tm_stencil_cost* d_
     int rc = TM_OK;
     if (hipMalloc((void**)&d_T, (size_t)n * kOut * 4) != hipSuccess ||
         hipMalloc((void**)&d_perm, (size_t)n * 8) != hipSuccess)
-        rc = set_error(TM_ENOMEM, "training buffers");
+        rc = no_memory("training buffers");
     if (rc == TM_OK) {
         hipLaunchKernelGGL(k_targets, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_cost, d_feat, n, r->mu[0],
                            r->sigma[0], r->mu[1], r->sigma[1], d_T);

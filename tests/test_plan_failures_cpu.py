@@ -1,0 +1,51 @@
+"""A plan whose growth fails for want of memory, over a HIP runtime of host memory: it is not
+loaded any more (nothing is launched on buffers that are gone) and can be loaded again."""
+import os
+import subprocess
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+BODY = """
+import ctypes, sys
+import numpy as np
+fake = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+fail, launches = ctypes.c_int.in_dll(fake, "fake_fail"), ctypes.c_int.in_dll(fake, "fake_launches")
+import paper_2507_17087_amd as tm
+import workloads as W
+L, p = tm.lib(), ctypes.c_void_p()
+out, best, pmap = np.zeros((400, 4), np.int64), np.zeros(1, np.int64), np.zeros(64, np.int32)
+st = W.stencil((1, 1), 8)
+
+def load(n):
+    c = W.batch([W.candidate((8, 8), 2, 2, [])] * n)
+    return L.tm_plan_load(p, c.ctypes.data, n, st.ctypes.data, 0, None)
+
+def run():
+    return L.tm_plan_run(p, out.ctypes.data, best.ctypes.data, None)
+
+assert L.tm_plan_create(4, 1, ctypes.byref(p)) == tm.TM_OK
+assert (load(4), run()) == (tm.TM_OK, tm.TM_OK) and launches.value > 0, L.tm_last_error()
+fail.value = 100000
+assert load(400) == tm.TM_ENOMEM
+n = launches.value
+codes = [run(), L.tm_plan_run_map(p, out.ctypes.data, best.ctypes.data, pmap.ctypes.data, 64, None),
+         L.tm_plan_materialize(p, None, 0, pmap.ctypes.data, 64, None),
+         L.tm_plan_run_stage(p, 1, out.ctypes.data, None, None),
+         L.tm_search(p, None, np.array([0, 4], np.int64).ctypes.data, 1, 0, 1, 0.0, 0.0, best.ctypes.data, None, None)]
+assert codes == [tm.TM_EINVAL] * 5 and launches.value == n, (codes, launches.value - n)
+assert b"not loaded" in L.tm_last_error()
+assert load(5) == tm.TM_OK and run() == tm.TM_OK and launches.value > n
+fail.value = 0
+assert load(400) == tm.TM_OK and run() == tm.TM_OK
+assert L.tm_plan_destroy(p) == tm.TM_OK
+print("done")
+"""
+
+
+def test_growth_without_memory(tmp_path):
+    so = str(tmp_path / "fake_hip.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", so, os.path.join(HERE, "fake_hip.c")], check=True)
+    p = subprocess.run([sys.executable, "-c", BODY, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0 and p.stdout.strip() == "done", p.stdout + p.stderr
