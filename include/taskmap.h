@@ -328,7 +328,9 @@ int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t
                       void* stream);
 /* Processor map of candidate *d_index (device int64; index into the loaded batch),
  * or of host_index when d_index is NULL, into d_map (device int32[cap]); cap must
- * hold the largest candidate of the batch. */
+ * hold the largest candidate of the batch.  TM_EINVAL before a batch of the plan was evaluated
+ * (by a run, a stage of one, an exhaustive search or the autotuner) unless max_words reserved
+ * the memory. */
 int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t host_index, int32_t* d_map,
                         int64_t cap, void* stream);
 /* tm_plan_run, then the processor map of the selected candidate (*d_best) into
@@ -340,8 +342,8 @@ int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, int32_t
 /* Class tuples of the loaded batch, a measure of its size: the sum over its candidates
  * of the product of their per-dim class counts, a class being a run of consecutive
  * coordinates with the same contribution and the same offsets to their star neighbours
- * -> *tuples (host).  Synchronous: waits for `stream`.  TM_EINVAL before the
- * first run. */
+ * -> *tuples (host).  Synchronous: waits for `stream`.  TM_EINVAL where tm_plan_materialize
+ * is. */
 int tm_plan_class_tuples(tm_plan* p, int64_t* tuples, void* stream);
 /* Times cells_per_item and grid variants of the loaded batch's evaluation, keeps the fastest;
  * writes the chosen cells_per_item and workgroups per CU (host pointers, nullable). */

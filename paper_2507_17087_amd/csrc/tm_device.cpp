@@ -829,7 +829,6 @@ static void plan_free(tm_plan* p) {
     p->h_seg = nullptr;
     p->cap_hseg = 0;
     p->cap_cands = 0;
-    p->cap_words = 0;
     p->cap_arena = 0;
 }
 
@@ -924,6 +923,10 @@ static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int6
                              0, best_ids);
 }
 
+// Maps and class tuples are given once a batch of the plan was evaluated (by a run, a stage, an
+// exhaustive search or the autotuner), or where memory for the tables was reserved at creation.
+static bool plan_ready(const tm_plan* p) { return p->ran || p->cap_arena >= p->cp.map_words; }
+
 // Map launch for a device-side index: fits every loaded candidate.
 static MapShape plan_map_shape(const tm_plan* p) { return map_shape(p->cp.max_vol, p->cp.max_points, p->cp.min_row); }
 
@@ -938,7 +941,7 @@ extern "C" int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** ou
     int rc = plan_alloc(p, max_cands);
     if (rc == TM_OK && max_words > 0) {
         if (hipMalloc((void**)&p->d_arena, (size_t)max_words * 4) != hipSuccess) rc = no_memory("arena");
-        else p->cap_words = p->cap_arena = max_words;
+        else p->cap_arena = max_words;
     }
     if (rc == TM_OK && hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming) != hipSuccess)
         rc = set_error(TM_EDEVICE, "event");
@@ -991,7 +994,7 @@ extern "C" int tm_plan_run(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, 
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
     TM_HIP(plan_enqueue(p, -1, d_out, d_best, (hipStream_t)stream));
-    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
+    p->ran = true;
     return TM_OK;
 }
 
@@ -1006,7 +1009,7 @@ extern "C" int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_be
     if (rc != TM_OK) return rc;
     TM_HIP(plan_enqueue(p, -1, d_out, d_best, s, p->d_arena));
     TM_HIP(launch_map(plan_map_shape(p), p->d_evals, p->cp.hdr.n, d_best, 0, p->d_arena, d_map, s));
-    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
+    p->ran = true;
     return TM_OK;
 }
 
@@ -1017,7 +1020,7 @@ extern "C" int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_o
     if (p->cp.hdr.n > 0 && !d_out) return set_error(TM_EINVAL, "null output");
     if (p->cp.hdr.n == 0) return TM_OK;
     TM_HIP(plan_enqueue(p, stage, d_out, d_best, (hipStream_t)stream));
-    p->cap_words = std::max(p->cap_words, p->cp.arena_words);
+    p->ran = true;
     return TM_OK;
 }
 
@@ -1038,8 +1041,7 @@ extern "C" int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t h
         shape = plan_map_shape(p);
     }
     if (cap < need) return set_error(TM_ECAPACITY, "map needs %lld entries", (long long)need);
-    if (p->cap_words < cp.arena_words)
-        return set_error(TM_EINVAL, "not run yet: run the plan before materialising a map");
+    if (!plan_ready(p)) return set_error(TM_EINVAL, "not run yet: run the plan before materialising a map");
     const int rc = plan_ensure_arena(p, (hipStream_t)stream);
     if (rc != TM_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
@@ -1062,7 +1064,7 @@ extern "C" int tm_plan_class_tuples(tm_plan* p, int64_t* tuples, void* stream) {
     if (!tuples) return set_error(TM_EINVAL, "null output");
     *tuples = 0;
     if (p->cp.hdr.n == 0) return TM_OK;
-    if (p->cap_words < p->cp.arena_words) return set_error(TM_EINVAL, "not run yet: run the plan first");
+    if (!plan_ready(p)) return set_error(TM_EINVAL, "not run yet: run the plan first");
     hipStream_t s = (hipStream_t)stream;
     unsigned long long* d_tot = nullptr;
     TM_HIP(hipMallocAsync((void**)&d_tot, 8, s));
@@ -1131,6 +1133,7 @@ extern "C" int tm_plan_autotune(tm_plan* p, tm_stencil_cost* d_out, int64_t* cel
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != TM_OK) return rc;
+    p->ran = true;
     rc = plan_relayout(p, best_c, best_w, s);
     if (cells_per_item) *cells_per_item = best_c;
     if (wg_per_cu) *wg_per_cu = best_w;
@@ -1318,6 +1321,7 @@ int plan_exhaustive_search(tm_plan* p, const int64_t* seg, int64_t nseg, int64_t
     int rc = plan_search_prepare(p, seg, nseg, 0, 0, false, &sb, s);
     if (rc != TM_OK) return rc;
     hipError_t e = plan_enqueue(p, -1, sb->all_out, nullptr, s);
+    if (e == hipSuccess) p->ran = true;
     if (e == hipSuccess) e = launch_select_segments(sb->all_out, sb->seg, nseg, nullptr, 0, d_best, d_best_cost, s);
     if (e != hipSuccess) return set_error(TM_EDEVICE, "exhaustive search: %s", hipGetErrorString(e));
     return TM_OK;

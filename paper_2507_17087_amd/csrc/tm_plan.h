@@ -50,7 +50,6 @@ struct SearchBufs {
 struct tm_plan {
     int device = 0;
     int64_t cap_cands = 0;
-    int64_t cap_words = 0;            // table words of the largest batch run so far (or reserved at creation)
     int64_t cap_arena = 0;            // words of d_arena
     tmk::DevCand* d_cands = nullptr;
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
@@ -68,6 +67,7 @@ struct tm_plan {
     bool up_pending = false;
     tmk::Compiled cp;  // the loaded batch
     bool loaded = false;
+    bool ran = false;  // some batch of it was evaluated
     int64_t cells_per_item = 0;
     int wg_per_cu = 0;
     tmk::SearchBufs sb;

@@ -1,5 +1,6 @@
-"""A plan whose growth fails for want of memory, over a HIP runtime of host memory: it is not
-loaded any more (nothing is launched on buffers that are gone) and can be loaded again."""
+"""The host side of plans over a HIP runtime of host memory.  A plan whose growth fails for
+want of memory is not loaded any more (nothing is launched on buffers that are gone) and can
+be loaded again.  Maps and class tuples are given after whatever evaluates a batch."""
 import os
 import subprocess
 import sys
@@ -7,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
-BODY = """
+HEAD = """
 import ctypes, sys
 import numpy as np
 fake = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
@@ -24,7 +25,9 @@ def load(n):
 
 def run():
     return L.tm_plan_run(p, out.ctypes.data, best.ctypes.data, None)
+"""
 
+GROWTH = HEAD + """
 assert L.tm_plan_create(4, 1, ctypes.byref(p)) == tm.TM_OK
 assert (load(4), run()) == (tm.TM_OK, tm.TM_OK) and launches.value > 0, L.tm_last_error()
 fail.value = 100000
@@ -43,9 +46,45 @@ assert L.tm_plan_destroy(p) == tm.TM_OK
 print("done")
 """
 
+READY = HEAD + """
+tuples, seg = ctypes.c_int64(), np.array([0, 4], np.int64)
+ways = {
+    "run": run,
+    "stage": lambda: L.tm_plan_run_stage(p, 1, out.ctypes.data, best.ctypes.data, None),
+    "run_map": lambda: L.tm_plan_run_map(p, out.ctypes.data, best.ctypes.data, pmap.ctypes.data, 64, None),
+    "search": lambda: L.tm_search(p, None, seg.ctypes.data, 1, 0, 1, 0.0, 0.0, best.ctypes.data, None, None),
+    "autotune": lambda: L.tm_plan_autotune(p, out.ctypes.data, None, None, None),
+}
 
-def test_growth_without_memory(tmp_path):
+def asked():
+    return (L.tm_plan_materialize(p, None, 3, pmap.ctypes.data, 64, None),
+            L.tm_plan_class_tuples(p, ctypes.byref(tuples), None))
+
+OK, NO = (tm.TM_OK,) * 2, (tm.TM_EINVAL,) * 2
+for name, way in ways.items():
+    assert L.tm_plan_create(4, 1, ctypes.byref(p)) == tm.TM_OK
+    assert asked() == NO and load(4) == tm.TM_OK and asked() == NO, name
+    assert way() == tm.TM_OK and asked() == OK, (name, L.tm_last_error())
+    assert L.tm_plan_set_launch(p, 1, 0, None) == tm.TM_OK and asked() == OK, name
+    assert load(4) == tm.TM_OK and asked() == OK, name
+    assert L.tm_plan_destroy(p) == tm.TM_OK
+assert L.tm_plan_create(4, 100000, ctypes.byref(p)) == tm.TM_OK  # room for the tables
+assert load(4) == tm.TM_OK and asked() == OK
+assert L.tm_plan_destroy(p) == tm.TM_OK
+print("done")
+"""
+
+
+def over_host_memory(tmp_path, body):
     so = str(tmp_path / "fake_hip.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", so, os.path.join(HERE, "fake_hip.c")], check=True)
-    p = subprocess.run([sys.executable, "-c", BODY, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    p = subprocess.run([sys.executable, "-c", body, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert p.returncode == 0 and p.stdout.strip() == "done", p.stdout + p.stderr
+
+
+def test_growth_without_memory(tmp_path):
+    over_host_memory(tmp_path, GROWTH)
+
+
+def test_maps_after_any_evaluation(tmp_path):
+    over_host_memory(tmp_path, READY)
