@@ -1,5 +1,5 @@
 // tm_device.cpp -- device entry points of libtaskmap: single-shot evaluation calls
-// and batch plans (persistent counting launch replayed from hipGraphs).
+// and batch plans (descriptors kept on the device, runs launched directly).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,8 +22,8 @@ namespace tmk {
         if (e_ != hipSuccess) return set_error(TM_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
-// Default counting work-item size when the caller gives none: about 16 items per
-// CU over the batch's class-tuple bound, between 2^10 and 2^16 tuples.
+// Class tuples per counted work item (counted_words): about 16 items per CU over the
+// batch's class-tuple bound, between 2^10 and 2^16 tuples.
 static int num_cus();
 static int64_t default_tuples_per_item(int64_t tuples) {
     const int64_t target = tuples / (int64_t(num_cus()) * 16);
@@ -87,22 +87,21 @@ static int32_t blocks_and_dims(const DevCand& d) {
     return (int32_t)std::min<int64_t>(n, INT32_MAX);
 }
 
-// Counting work items of every candidate, a word of the arena each.
-static void layout_items(Compiled& cp, int64_t tuples_per_item) {
-    int64_t items = 0;
-    for (auto& d : cp.cands) {
-        d.citems = count_items(d, tuples_per_item);
-        d.item_first = items;
-        items += d.citems;
+int64_t counted_words(const Compiled& cp) {
+    int64_t tuples = 0, items = 0;
+    for (const auto& d : cp.cands) {
+        int64_t b = 1;
+        for (int k = 0; k < d.lrank; ++k) b = std::min<int64_t>(b * d.cls_cap[k], int64_t(1) << 50);
+        tuples += b;
     }
-    cp.items = items;
-    cp.arena_words = cp.tables_words + up4(items);
+    const int64_t per = default_tuples_per_item(tuples);
+    for (const auto& d : cp.cands) items += count_items(d, per);
+    return cp.arena_words + up4(items);
 }
 
-// Validates and compiles n candidates.  st == nullptr: tables without halo flags.
+// Validates and compiles n candidates.  st == nullptr: tables without classes.
 // need_lds: every candidate's tables must fit the LDS budget of the kernels.
-int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_t tuples_per_item, bool need_lds,
-                  Compiled& cp) {
+int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, bool need_lds, Compiled& cp) {
     if (n < 0) return set_error(TM_EINVAL, "n = %lld", (long long)n);
     if (n > 0 && !c) return set_error(TM_EINVAL, "null candidate array");
     cp.cands.resize((size_t)n);
@@ -118,7 +117,6 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
             cp.hdr.halo[d] = st->halo[d];
         }
         if (hmax > kMaxHalo) return set_error(TM_ENOTSUP, "halo %d above the kernels' limit of %d", hmax, kMaxHalo);
-        cp.K = 0;  // the largest launch rank in the batch
         cp.H = std::max(1, hmax);
         cp.hdr.elem_bytes = st->elem_bytes;
         cp.hdr.lrank = st->lrank;
@@ -144,15 +142,9 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
             return set_error(TM_ENOTSUP, "candidate %lld: more than 2^30 rows", (long long)i);
         d.arena_off = words;
         words += d.words;
-        cp.max_words = std::max(cp.max_words, d.lds_words);
-        cp.max_all_words = std::max(cp.max_all_words, d.words);
         if (st) {
-            const int64_t cw = up4(d.vol) + d.cls_words;  // counting: staged when it fits, else read in place
+            const int64_t cw = up4(d.vol) + d.cls_words;  // staged when it fits, else read in place
             if (cw <= kMaxLdsWords) cp.cnt_words = std::max<int32_t>(cp.cnt_words, (int32_t)cw);
-            int64_t b = 1;
-            for (int k = 0; k < d.lrank; ++k) b = std::min<int64_t>(b * d.cls_cap[k], int64_t(1) << 50);
-            cp.tuples += b;
-            cp.K = std::max(cp.K, (int)d.lrank);
         }
         cp.points += d.npoints;
         cp.max_points = std::max(cp.max_points, d.npoints);
@@ -160,9 +152,7 @@ int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_
         cp.max_blocks = std::max(cp.max_blocks, blocks_and_dims(d));
         cp.min_row = std::min(cp.min_row, d.L);
     }
-    cp.tables_words = words;
     cp.arena_words = words;
-    layout_items(cp, tuples_per_item > 0 ? tuples_per_item : default_tuples_per_item(cp.tuples));
     return TM_OK;
 }
 
@@ -454,7 +444,7 @@ using namespace tmk;
 extern "C" int tm_chain_table(const tm_candidate* c, int32_t* d_out, int64_t cap, int64_t* count, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     Compiled cp;
-    int rc = compile_batch(c, 1, nullptr, 0, false, cp);
+    int rc = compile_batch(c, 1, nullptr, false, cp);
     if (rc != TM_OK) return rc;
     if (count) *count = cp.cands[0].vol;
     if (cap < cp.cands[0].vol) return set_error(TM_ECAPACITY, "chain table has %d entries", cp.cands[0].vol);
@@ -473,7 +463,7 @@ extern "C" int tm_chain_table(const tm_candidate* c, int32_t* d_out, int64_t cap
 extern "C" int tm_proc_map(const tm_candidate* c, int32_t* d_map, int64_t len, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     Compiled cp;
-    int rc = compile_batch(c, 1, nullptr, 0, true, cp);
+    int rc = compile_batch(c, 1, nullptr, true, cp);
     if (rc != TM_OK) return rc;
     const DevCand& c0 = cp.cands[0];
     if (len != c0.npoints)
@@ -536,7 +526,7 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
         if (rc != kGeneral) return rc;
     }
     Compiled cp;
-    int rc = compile_batch(c, n, st, 0, true, cp);
+    int rc = compile_batch(c, n, st, true, cp);
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
@@ -643,7 +633,7 @@ extern "C" int tm_eval_redistribution_batch(const tm_candidate* src, const tm_ca
         std::memcpy(both.data() + n, dst, (size_t)n * sizeof(tm_candidate));
     }
     Compiled cp;
-    int rc = compile_batch(both.data(), 2 * n, nullptr, 0, false, cp);
+    int rc = compile_batch(both.data(), 2 * n, nullptr, false, cp);
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
@@ -709,7 +699,7 @@ extern "C" int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_m
     tm_stencil zs{};
     zs.lrank = TM_MAX_LRANK;
     Compiled cp;
-    int rc = compile_batch(c, n, &zs, 0, false, cp);
+    int rc = compile_batch(c, n, &zs, false, cp);
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
@@ -832,7 +822,7 @@ static void plan_free(tm_plan* p) {
     p->cap_arena = 0;
 }
 
-// Descriptor buffers for up to `cands` candidates (the table arena is allocated
+// Descriptor buffers for up to `cands` candidates (the owner tables' memory is allocated
 // separately, on first use, by plan_ensure_arena).
 static int plan_alloc(tm_plan* p, int64_t cands) {
     plan_free(p);
@@ -877,7 +867,7 @@ static int plan_ensure_arena(tm_plan* p, hipStream_t s) {
     p->d_arena = nullptr;
     p->cap_arena = 0;
     if (malloc_anytime((void**)&p->d_arena, (size_t)words * 4) != hipSuccess)
-        return no_memory("table arena of %lld words", (long long)words);
+        return no_memory("owner tables of %lld words", (long long)words);
     p->cap_arena = words;
     return TM_OK;
 }
@@ -971,7 +961,7 @@ extern "C" int tm_plan_load(tm_plan* p, const tm_candidate* c, int64_t n, const 
         return set_error(TM_EINVAL, "cells_per_item %lld (at most 2^26)", (long long)cells_per_item);
     hipStream_t s = (hipStream_t)stream;
     Compiled cp;
-    int rc = compile_batch(c, n, st, cells_per_item > 0 ? cells_per_item : p->cells_per_item, true, cp);
+    int rc = compile_batch(c, n, st, true, cp);
     if (rc != TM_OK) return rc;
     if (n > p->cap_cands) {
         // grow: wait for work that may still read the old buffers
@@ -1084,7 +1074,6 @@ static int plan_relayout(tm_plan* p, int64_t cells_per_item, int wg_per_cu, hipS
     p->cells_per_item = cells_per_item;
     p->wg_per_cu = wg_per_cu;
     if (p->cp.hdr.n == 0) return TM_OK;
-    layout_items(p->cp, cells_per_item > 0 ? cells_per_item : default_tuples_per_item(p->cp.tuples));
     layout_eval(p->cp, cells_per_item, false);
     p->cp.eval.wg_per_cu = wg_per_cu;
     return plan_upload(p, s);

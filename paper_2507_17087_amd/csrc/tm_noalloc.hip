@@ -1,8 +1,7 @@
 // tm_noalloc.hip -- tm_eval_stencil_batch_noalloc: the stencil evaluation of
-// tm_eval_stencil_batch for callers that cannot allocate device memory.  Its batch
-// header, descriptors, table arena and work counter live in `scratch`, a file-scope
-// device array of TM_NOALLOC_SCRATCH_BYTES held by every GPU the library runs on
-// until the process ends.  Host code never uses the array's name as an address (it
+// tm_eval_stencil_batch for callers that cannot allocate device memory.  Its descriptors
+// live in `scratch`, a file-scope device array of TM_NOALLOC_SCRATCH_BYTES held by every
+// GPU the library runs on until the process ends.  Host code never uses the array's name as an address (it
 // is a host-side stand-in): the device address comes from hipGetSymbolAddress, once
 // per device, and only that pointer is passed to the kernels and copies.
 #include <hip/hip_runtime.h>
@@ -56,15 +55,14 @@ extern "C" int tm_eval_stencil_batch_noalloc(const tm_candidate* c, int64_t n, c
     hipStream_t s = (hipStream_t)stream;
     if (!st) return set_error(TM_EINVAL, "null stencil");
     Compiled cp;
-    int rc = compile_batch(c, n, st, 0, true, cp);
+    int rc = compile_batch(c, n, st, true, cp);
     if (rc != TM_OK) return rc;
     if (n == 0) return TM_OK;
     if (!d_out) return set_error(TM_EINVAL, "null output");
-    // scratch layout: header | descriptors | table arena | work counter
-    const int64_t o_cands = up256((int64_t)sizeof(DevHeader));
-    const int64_t o_arena = o_cands + up256(n * (int64_t)sizeof(DevCand));
-    const int64_t o_count = o_arena + up256(cp.arena_words * 4);
-    const int64_t need = o_count + 256;
+    // what counts: a header, descriptors, tables, a work counter; what is stored, past the
+    // header's place: the evaluation's descriptors
+    const int64_t header = up256((int64_t)sizeof(DevHeader));
+    const int64_t need = header + up256(n * (int64_t)sizeof(DevCand)) + up256(counted_words(cp) * 4) + 256;
     if (need > (int64_t)TM_NOALLOC_SCRATCH_BYTES)
         return set_error(TM_ECAPACITY, "the batch needs %lld bytes of scratch; the library holds %lld",
                          (long long)need, (long long)TM_NOALLOC_SCRATCH_BYTES);
@@ -77,7 +75,7 @@ extern "C" int tm_eval_stencil_batch_noalloc(const tm_candidate* c, int64_t n, c
     const EvalShape shape{cp.eval.H, cp.eval.node_level, cp.eval.per_item, cp.eval.fill};
     std::vector<DevEval> evals((size_t)n);
     for (int64_t i = 0; i < n; ++i) fill_eval(cp.cands[(size_t)i], shape, &evals[(size_t)i]);
-    DevEval* d_evals = reinterpret_cast<DevEval*>(base + o_cands);
+    DevEval* d_evals = reinterpret_cast<DevEval*>(base + header);
     // the descriptors go up from this call's host memory; waiting for the copy keeps it
     // alive until it is done (nothing here allocates pinned staging)
     hipError_t e = hipMemcpyAsync(d_evals, evals.data(), (size_t)n * sizeof(DevEval), hipMemcpyHostToDevice, s);

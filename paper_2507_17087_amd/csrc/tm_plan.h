@@ -16,18 +16,14 @@ namespace tmk {
 struct Compiled {
     std::vector<DevCand> cands;
     DevHeader hdr{};
-    int64_t arena_words = 0, items = 0, points = 0, max_points = 0;
-    int32_t max_words = 0;      // largest LDS-staged prefix
-    int32_t max_all_words = 0;  // largest whole table block of one candidate
+    int64_t arena_words = 0, points = 0, max_points = 0;
     int32_t max_vol = 0;        // largest final-space volume
     int32_t max_blocks = 0;     // most blocks of all launch dims of a candidate (estimates' records)
     int32_t min_row = INT32_MAX;  // shortest row (last extent)
-    int32_t cnt_words = 0;      // LDS words of the counting launch (largest staged owner table + class blocks)
-    int64_t tuples = 0;         // class-tuple bound of the batch (sum of the candidates')
-    int64_t tables_words = 0;   // arena words of the tables (the item table follows)
+    int32_t cnt_words = 0;      // most LDS words of an owner table with its class blocks that fit (matmul batches)
     int64_t map_words = 0;      // plans: words of all owner tables (each candidate's arena_off is among them)
     EvalPlan eval;              // the evaluation's launches
-    int K = 0, H = 1;
+    int H = 1;
 };
 
 // Device buffers of a search over a loaded plan (grown on demand).
@@ -77,8 +73,10 @@ namespace tmk {
 
 // Validates and compiles n candidates on the host (st == nullptr: tables without
 // classes; need_lds: every owner table must fit the kernels' LDS budget).
-int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, int64_t tuples_per_item, bool need_lds,
-                  Compiled& cp);
+int compile_batch(const tm_candidate* c, int64_t n, const tm_stencil* st, bool need_lds, Compiled& cp);
+// Words that tm_eval_stencil_batch_noalloc counts for the tables and the work items of a
+// compiled stencil batch against its scratch.
+int64_t counted_words(const Compiled& cp);
 // Lays out the evaluation of a compiled stencil batch (per-candidate LDS words, dim and
 // parts; the launches).  node_level: the node-level volume.
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
