@@ -1043,7 +1043,10 @@ hipError_t launch_publish(const float* p, int64_t count, const RankerWeights& W,
     return hipGetLastError();
 }
 
-// 16 waves a workgroup for segments longer than this on average.
+// 16 waves a workgroup for segments longer than this on average: their passes share more
+// lanes, but every barrier waits for more waves.  The 64 smallest of 457 segments, 16 waves and
+// four, us: 256 scores each 9.5 and 6.8, 768 10.2 and 9.4, 1,024 10.9 and 10.6, 1,536 12.5 and
+// 13.2, 4,096 19.6 and 25.4; of 8 segments 512 6.9 and 6.8, 1,024 7.5 and 9.1, 4,096 12.7 and 21.6.
 constexpr int64_t kSelWide = 1024;
 
 hipError_t launch_select(const float* score, const int64_t* seg, int64_t nseg, int64_t n, int64_t stride, int k,

@@ -33,9 +33,13 @@ static_assert(sizeof(DevPair) % 16 == 0 && sizeof(DevPair) / 16 <= 256, "staged 
 // 16,384 tuples; on 4,096 processors 273 pairs take 403 us, with four times as many tuples
 // a workgroup 693 us.
 constexpr int64_t kPairTuples = 16384;
-// Up to this many workgroups have 16 waves each; the call is then bound by latency
-// (108 pairs 12.3 us, with four waves 24.0; 540 pairs 19.9 and 24.8; 1,080 pairs 29.5 and
-// 26.4; 4,320 pairs 91 and 41).
+// Up to this many workgroups have 16 waves each: two a CU, whose latency bounds the call where
+// a pair has many tuples, and which cost nothing where it has few, since the pairs are then
+// read in place from host memory (478 at most).  Beyond, 16 waves still gain on pairs of up to
+// 16,384 tuples until about 900 of them, but take twice as long on pairs of 1,024.  Transposes
+// on 128 processors, 16 waves and four, us: 108 pairs 16.2 and 26.8, 400 29.9 and 42.2, 512 20.0
+// and 25.5, 900 25.4 and 26.0, 1,024 28.4 and 26.3, 2,048 48 and 31; on 32 processors: 108
+// 10.6 and 10.6, 400 23.7 and 24.3, 512 11.2 and 7.6, 1,024 19.2 and 7.8, 2,048 35 and 11.
 constexpr int64_t kPairWide = 512;
 // Most tuples of one group of dim_d (they are indexed in floats, see div_small).
 constexpr int64_t kPairRowTuples = int64_t(1) << 20;
