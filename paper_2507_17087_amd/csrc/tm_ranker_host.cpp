@@ -48,6 +48,7 @@ struct tm_ranker {
     // bf16 features of a forward call (grown on demand)
     uint16_t* X = nullptr;
     int64_t cap_x = 0;
+    std::vector<void*> outgrown;  // buffers replaced during a capture, which may not free
 };
 
 namespace tmk {
@@ -78,16 +79,27 @@ static int ranker_alloc_weights(tm_ranker* r) {
 
 static int64_t pad_rows(int64_t rows) { return (rows + 31) / 32 * 32; }
 
+// Buffers hold at least this many rows, so that calls of growing sizes do not allocate each.
+constexpr int64_t kMinRows = 1024;
+
+static int release_buffer(tm_ranker* r, void* buf, hipStream_t s) {
+    if (!buf) return TM_OK;
+    if (capturing(s)) r->outgrown.push_back(buf);
+    else TM_HIP(hipFree(buf));
+    return TM_OK;
+}
+
 // Buffers of a batch of `rows` rows.
-static int ranker_buffers(tm_ranker* r, int64_t rows) {
+static int ranker_buffers(tm_ranker* r, int64_t rows, hipStream_t s) {
     if (rows <= r->cap_rows) return TM_OK;
-    if (r->bufmem) TM_HIP(hipFree(r->bufmem));
+    const int rc = release_buffer(r, r->bufmem, s);
+    if (rc != TM_OK) return rc;
     r->bufmem = nullptr;
     r->cap_rows = 0;
-    const int64_t cap = pad_rows(std::max<int64_t>(rows, 1024));
+    const int64_t cap = pad_rows(std::max(rows, kMinRows));
     const size_t bytes = (size_t)cap * (kFeat + 6 * kWidth) * 2 + (size_t)cap * 2 * kOut * 4 + (size_t)(cap / 16) * kColParts * 4 +
                          (size_t)r->L.count * (kMaxSplits + 1) * 4 + 16 * 256;
-    if (hipMalloc(&r->bufmem, bytes) != hipSuccess) return no_memory("ranker buffers");
+    if (malloc_anytime(&r->bufmem, bytes) != hipSuccess) return no_memory("ranker buffers");
     char* q = (char*)r->bufmem;
     auto take = [&](size_t n) {
         void* p = q;
@@ -106,12 +118,14 @@ static int ranker_buffers(tm_ranker* r, int64_t rows) {
 }
 
 // Features buffer of a forward call of `rows` rows at a time.
-static int forward_buffer(tm_ranker* r, int64_t rows) {
+static int forward_buffer(tm_ranker* r, int64_t rows, hipStream_t s) {
     if (rows <= r->cap_x) return TM_OK;
-    if (r->X) TM_HIP(hipFree(r->X));
+    const int rc = release_buffer(r, r->X, s);
+    if (rc != TM_OK) return rc;
     r->X = nullptr;
     r->cap_x = 0;
-    if (hipMalloc((void**)&r->X, (size_t)rows * kFeat * 2) != hipSuccess) return no_memory("ranker features");
+    rows = std::max(rows, kMinRows);
+    if (malloc_anytime((void**)&r->X, (size_t)rows * kFeat * 2) != hipSuccess) return no_memory("ranker features");
     r->cap_x = rows;
     return TM_OK;
 }
@@ -245,6 +259,7 @@ int tm_ranker_destroy(tm_ranker* r) {
     if (r->bf) (void)hipFree(r->bf);
     if (r->bufmem) (void)hipFree(r->bufmem);
     if (r->X) (void)hipFree(r->X);
+    for (void* b : r->outgrown) (void)hipFree(b);
     delete r;
     return TM_OK;
 }
@@ -275,7 +290,7 @@ int tm_ranker_forward(tm_ranker* r, const float* d_feat, int64_t n, float* d_out
     if (!r || n < 0 || (n > 0 && (!d_feat || !d_out))) return set_error(TM_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
     const int64_t chunk = 1 << 18;
-    const int rc = forward_buffer(r, std::min<int64_t>(n, chunk));
+    const int rc = forward_buffer(r, std::min<int64_t>(n, chunk), s);
     if (rc != TM_OK) return rc;
     for (int64_t a = 0; a < n; a += chunk) {
         const int64_t rows = std::min(chunk, n - a);
@@ -291,7 +306,7 @@ int tm_ranker_grad(tm_ranker* r, const float* d_feat, const float* d_target, int
                    void* stream) {
     if (!r || n <= 0 || !d_feat || !d_target || !d_grad) return set_error(TM_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    int rc = ranker_buffers(r, n);
+    int rc = ranker_buffers(r, n, s);
     if (rc != TM_OK) return rc;
     rc = ranker_batch_grad(r, TrainBatch{d_feat, d_target, nullptr, 0, n}, d_grad, s);
     if (rc != TM_OK) return rc;
@@ -328,7 +343,7 @@ int tm_ranker_train(tm_ranker* r, const float* d_feat, const tm_stencil_cost* d_
     if (rc == TM_OK) {
         hipLaunchKernelGGL(k_targets, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_cost, d_feat, n, r->mu[0],
                            r->sigma[0], r->mu[1], r->sigma[1], d_T);
-        rc = ranker_buffers(r, batch);
+        rc = ranker_buffers(r, batch, s);
     }
     std::vector<int64_t> perm((size_t)n);
     uint64_t st = seed ^ 0x2545F4914F6CDD1DULL;

@@ -6,6 +6,7 @@
 
 int fake_fail = 0;      /* device allocations above this many bytes fail (0: none does) */
 int fake_launches = 0;  /* kernels launched so far */
+int fake_allocs = 0;    /* device allocations so far */
 static int last = 0;
 
 static int result(int e) {
@@ -22,7 +23,10 @@ int hipGetLastError(void) {
     last = 0;
     return e;
 }
-int hipMalloc(void** p, size_t n) { return alloc(p, n); }
+int hipMalloc(void** p, size_t n) {
+    ++fake_allocs;
+    return alloc(p, n);
+}
 int hipHostMalloc(void** p, size_t n, unsigned flags) { return alloc(p, n); }
 int hipMallocAsync(void** p, size_t n, void* s) { return alloc(p, n); }
 int hipFree(void* p) { free(p); return 0; }
@@ -30,6 +34,7 @@ int hipFreeAsync(void* p, void* s) { free(p); return 0; }
 int hipHostFree(void* p) { free(p); return 0; }
 int hipMemset(void* p, int v, size_t n) { memset(p, v, n); return 0; }
 int hipMemsetAsync(void* p, int v, size_t n, void* s) { memset(p, v, n); return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int kind) { memcpy(d, s, n); return 0; }
 int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* st) { memcpy(d, s, n); return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int a, int d) { *v = 256; return 0; }

@@ -30,7 +30,8 @@ def tm():
 @contextlib.contextmanager
 def recording():
     """A graph being captured.  Nothing is garbage-collected meanwhile: a graph or a plan of
-    an earlier test would be destroyed, which waits for the device."""
+    an earlier test would be destroyed, which waits for the device (and so would be the last
+    graph of a loop, when the next one takes its name)."""
     import torch
     g = torch.cuda.CUDAGraph()
     gc.collect()
@@ -143,3 +144,31 @@ def test_maps_after_a_run(tm, calls, reload):
     if reload:
         assert (smap.cpu().numpy() == oracle.proc_map(cands[(other + 1) % len(cands)]).ravel()).all()
     plan.close()
+
+
+@pytest.mark.parametrize("n", [700, 5000])
+@pytest.mark.parametrize("first", ["forward", "grad"])
+def test_ranker_after_the_other_call(tm, first, n):
+    """A forward pass recorded where only gradients were taken before, and the other way
+    round; rows in the range of the buffers' smallest size and beyond."""
+    import torch
+    say("captured ranker call after", first, n)
+    gen = torch.Generator().manual_seed(5)
+    rk, ref = tm.Ranker(seed=4), tm.Ranker(seed=4)
+    feat, target = torch.randn((n, 64), generator=gen).cuda(), torch.randn((n, 2), generator=gen).cuda()
+    calls = [lambda r: r.forward(feat), lambda r: r.grad(feat, target)]
+    if first == "grad":
+        calls.reverse()
+    exp = calls[1](ref)
+    calls[0](rk)
+    torch.cuda.synchronize()
+    with recording() as g:
+        got = calls[1](rk)
+    for _ in range(3):
+        got.fill_(7)
+        calls[0](rk)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, exp)
+    rk.close(), ref.close()

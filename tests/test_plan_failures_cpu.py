@@ -1,6 +1,7 @@
-"""The host side of plans over a HIP runtime of host memory.  A plan whose growth fails for
+"""The host side of plans and rankers over a HIP runtime of host memory.  A plan whose growth fails for
 want of memory is not loaded any more (nothing is launched on buffers that are gone) and can
-be loaded again.  Maps and class tuples are given after whatever evaluates a batch."""
+be loaded again.  Maps and class tuples are given after whatever evaluates a batch.  A
+ranker's buffers are not allocated anew for every size."""
 import os
 import subprocess
 import sys
@@ -74,6 +75,24 @@ assert L.tm_plan_destroy(p) == tm.TM_OK
 print("done")
 """
 
+SIZES = HEAD + """
+allocs = ctypes.c_int.in_dll(fake, "fake_allocs")
+feat, y = np.zeros((4096, 64), np.float32), np.zeros((4096, 2), np.float32)
+grad = np.zeros(L.tm_ranker_param_count(), np.float32)
+assert L.tm_ranker_create(1, ctypes.byref(p)) == tm.TM_OK
+counts = []
+for sizes in (range(1, 1025), range(1024, 0, -1), (4096, 4095, 1)):
+    at = allocs.value
+    for n in sizes:
+        assert L.tm_ranker_forward(p, feat.ctypes.data, n, y.ctypes.data, None) == tm.TM_OK
+        if n % 97 == 1:
+            assert L.tm_ranker_grad(p, feat.ctypes.data, y.ctypes.data, n, grad.ctypes.data, None) == tm.TM_OK
+    counts.append(allocs.value - at)
+assert counts == [2, 0, 1], counts
+assert L.tm_ranker_destroy(p) == tm.TM_OK
+print("done")
+"""
+
 
 def over_host_memory(tmp_path, body):
     so = str(tmp_path / "fake_hip.so")
@@ -88,3 +107,7 @@ def test_growth_without_memory(tmp_path):
 
 def test_maps_after_any_evaluation(tmp_path):
     over_host_memory(tmp_path, READY)
+
+
+def test_buffers_of_many_sizes(tmp_path):
+    over_host_memory(tmp_path, SIZES)
