@@ -231,12 +231,8 @@ bool capturing(hipStream_t s) {
 }
 
 hipError_t malloc_anytime(void** p, size_t bytes) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
-    if (e != hipSuccess) return e;
-    const hipError_t m = hipMalloc(p, bytes);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    return m;
+    AnytimeMemory anytime;
+    return hipMalloc(p, bytes);
 }
 
 // A single call's descriptors live until its work is done; the replays of a graph that
@@ -260,6 +256,7 @@ static thread_local Staging g_stage;
 static int staging_acquire(size_t bytes, void** out) {
     int dev = 0;
     TM_HIP(hipGetDevice(&dev));
+    AnytimeMemory anytime;
     if (g_stage.pending) {
         TM_HIP(hipEventSynchronize(g_stage.ev));
         g_stage.pending = false;
@@ -307,14 +304,17 @@ struct SlotRing {
     bool pending[kSlots] = {};
     int next = 0;
 
+    // Also at the thread's end, when another thread may be capturing.
     void drop() {
+        if (!host) return;
+        AnytimeMemory anytime;
         for (int i = 0; i < kSlots; ++i) {
             if (pending[i]) (void)hipEventSynchronize(ev[i]);
             if (ev[i]) (void)hipEventDestroy(ev[i]);
             ev[i] = nullptr;
             pending[i] = false;
         }
-        if (host) (void)hipHostFree(host);
+        (void)hipHostFree(host);
         if (scratch) (void)hipFree(scratch);
         host = scratch = nullptr;
         device = -1;
@@ -335,17 +335,23 @@ static int slot_acquire(bool scratch, Slot* out) {
     SlotRing& r = g_ring;
     if (r.device != dev) r.drop();
     r.device = dev;
-    if (!r.host && hipHostMalloc((void**)&r.host, kSlots * kSlotBytes, hipHostMallocDefault) != hipSuccess) {
-        r.host = nullptr;
-        return no_memory("pinned staging of %zu bytes", kSlots * kSlotBytes);
-    }
-    if (scratch && !r.scratch && hipMalloc((void**)&r.scratch, kSlots * kSlotScratch) != hipSuccess) {
-        r.scratch = nullptr;
-        return no_memory("scratch of %zu bytes", kSlots * kSlotScratch);
+    if (!r.host || (scratch && !r.scratch)) {
+        AnytimeMemory anytime;
+        if (!r.host && hipHostMalloc((void**)&r.host, kSlots * kSlotBytes, hipHostMallocDefault) != hipSuccess) {
+            r.host = nullptr;
+            return no_memory("pinned staging of %zu bytes", kSlots * kSlotBytes);
+        }
+        if (scratch && !r.scratch && hipMalloc((void**)&r.scratch, kSlots * kSlotScratch) != hipSuccess) {
+            r.scratch = nullptr;
+            return no_memory("scratch of %zu bytes", kSlots * kSlotScratch);
+        }
     }
     const int i = r.next;
     if (!r.ev[i]) TM_HIP(hipEventCreateWithFlags(&r.ev[i], hipEventDisableTiming));
-    if (r.pending[i]) TM_HIP(hipEventSynchronize(r.ev[i]));
+    if (r.pending[i]) {
+        AnytimeMemory anytime;
+        TM_HIP(hipEventSynchronize(r.ev[i]));
+    }
     r.pending[i] = false;
     *out = Slot{i, r.host + (size_t)i * kSlotBytes, r.scratch ? r.scratch + (size_t)i * kSlotScratch : nullptr};
     return TM_OK;
@@ -359,7 +365,6 @@ static int slot_release(const Slot& slot, hipStream_t s) {
     r.next = (slot.index + 1) % kSlots;
     return TM_OK;
 }
-
 
 // Descriptors that fill writes, for launch to read: in a slot, or larger ones in a device
 // copy.  fill's result: TM_OK, an error, or kGeneral (nothing is launched).  *memory: the
@@ -434,6 +439,8 @@ static int num_cus() {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
     return n;
 }
+// The CUs that a launch bounded by them asks for.
+static int eval_cus(const EvalPlan& p) { return p.wg_per_cu > 0 ? num_cus() : 0; }
 
 }  // namespace tmk
 
@@ -504,7 +511,7 @@ static int eval_stencil(const tm_candidate* c, int64_t n, const tm_stencil* st, 
     if (!st) return set_error(TM_EINVAL, "null stencil");
     EvalPlan plan;
     auto launch = [&](const void* d) {
-        return launch_eval_batch(plan, static_cast<const DevEval*>(d), d_out, nullptr, nullptr, num_cus(), s);
+        return launch_eval_batch(plan, static_cast<const DevEval*>(d), d_out, nullptr, nullptr, 0, s);
     };
     const int H = stencil_slots(*st);
     int memory = TM_OK;
@@ -909,8 +916,8 @@ static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int6
     const Compiled& cp = p->cp;
     if (stage == 0) return launch_zero_costs(out, cp.hdr.n, s);
     if (stage == 2) return launch_bytes_select(out, cp.hdr.n, cp.hdr.elem_bytes, best, s);
-    return launch_eval_batch(cp.eval, p->d_evals, out, best, best ? plan_counter(p, s) : nullptr, num_cus(), s, nullptr,
-                             0, best_ids);
+    return launch_eval_batch(cp.eval, p->d_evals, out, best, best ? plan_counter(p, s) : nullptr, eval_cus(cp.eval), s,
+                             nullptr, 0, best_ids);
 }
 
 // Maps and class tuples are given once a batch of the plan was evaluated (by a run, a stage, an
@@ -1297,7 +1304,7 @@ int plan_search_prepare(tm_plan* p, const int64_t* seg, int64_t nseg, int32_t pr
 // The best of the candidates chosen in sb (sb->sel), by their exact costs.
 hipError_t plan_eval_chosen(tm_plan* p, SearchBufs* sb, int64_t* d_best, tm_stencil_cost* d_best_cost, hipStream_t s) {
     const int64_t nsel = sb->nseg * sb->k;
-    const hipError_t e = launch_eval_batch(p->cp.eval, p->d_evals, sb->sub_out, nullptr, nullptr, num_cus(), s,
+    const hipError_t e = launch_eval_batch(p->cp.eval, p->d_evals, sb->sub_out, nullptr, nullptr, eval_cus(p->cp.eval), s,
                                            sb->sel, nsel);
     if (e != hipSuccess) return e;
     return launch_select_segments(sb->sub_out, sb->seg, sb->nseg, sb->sel, sb->k, d_best, d_best_cost, s);

@@ -43,6 +43,7 @@ struct EvalPlan {
 // device word of this launch's own that holds 0 before it (and after it).  With idx, the nidx candidates idx[i] instead
 // (whole ones; rows of negative entries are left alone).  best_ids: the selected candidate's
 // owner table as processor ids (for its map), written at its offset by the workgroup that selects.
+// cus: the GPU's, used with wg_per_cu.
 hipError_t launch_eval_batch(const EvalPlan& p, const DevEval* evals, tm_stencil_cost* out, int64_t* best,
                              unsigned int* counter, int cus, hipStream_t s, const int64_t* idx = nullptr,
                              int64_t nidx = 0, int32_t* best_ids = nullptr);

@@ -82,7 +82,14 @@ int64_t counted_words(const Compiled& cp);
 void layout_eval(Compiled& cp, int64_t tuples_per_item, bool node_level);
 
 bool capturing(hipStream_t s);
-// hipMalloc, also while a stream is capturing (which otherwise forbids it).
+// While it lives, this thread may allocate, free and wait for events although a stream is
+// capturing, on this thread or another (which otherwise fails, and ends the capture).
+struct AnytimeMemory {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    AnytimeMemory() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~AnytimeMemory() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    AnytimeMemory(const AnytimeMemory&) = delete;
+};
 hipError_t malloc_anytime(void** p, size_t bytes);
 // TM_ENOTSUP while s is capturing: for calls whose descriptors do not outlive them.
 int refuse_capture(hipStream_t s);

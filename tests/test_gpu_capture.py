@@ -4,7 +4,9 @@ capture whole."""
 import contextlib
 import gc
 import sys
+import threading
 
+import numpy as np
 import pytest
 
 import oracle
@@ -172,3 +174,60 @@ def test_ranker_after_the_other_call(tm, first, n):
         torch.cuda.synchronize()
         assert torch.equal(got, exp)
     rk.close(), ref.close()
+
+
+@pytest.mark.parametrize("warm", [True, False])
+def test_thread_ends_during_a_capture(tm, warm):
+    """Another thread's single calls, and the end of that thread, while this one captures;
+    warm: it has made calls before."""
+    import torch
+    say("a thread ends during a capture", warm)
+    cands, st, exp = batch()
+    plan = tm.Plan(len(cands), 1)
+    plan.load(cands, st)
+    out, theirs = (torch.zeros((len(cands), 4), dtype=torch.int64, device="cuda") for _ in range(2))
+    best = torch.zeros(1, dtype=torch.int64, device="cuda")
+    many = cands[[i % len(cands) for i in range(1200)]]
+    rows = torch.zeros((1200, 4), dtype=torch.int64, device="cuda")
+    pmap = torch.zeros(24 * 40 * 17, dtype=torch.int32, device="cuda")
+    side, ready, go, fail = torch.cuda.Stream(), threading.Event(), threading.Event(), []
+
+    def calls():
+        with torch.cuda.stream(side):
+            for _ in range(6):
+                tm.tm_eval_stencil_batch(cands, st, theirs)
+                tm.tm_proc_map(cands[4], pmap)
+                tm.tm_eval_stencil_batch(many, st, rows)  # larger than a slot
+
+    def work():
+        try:
+            if warm:
+                calls()
+                side.synchronize()
+            ready.set()
+            go.wait(60)
+            calls()
+        except BaseException as e:  # noqa: BLE001  (reported by the test)
+            fail.append(repr(e))
+            ready.set()
+
+    th = threading.Thread(target=work)
+    th.start()
+    assert ready.wait(60) and not fail, fail
+    torch.cuda.synchronize()
+    with recording() as g:
+        plan.run(out, best)
+        go.set()
+        th.join()
+        plan.materialize(pmap, d_index=best)
+    assert not fail, fail
+    torch.cuda.synchronize()
+    assert (theirs.cpu().numpy() == exp).all()
+    assert (rows.cpu().numpy() == exp[np.arange(1200) % len(exp)]).all()
+    assert (pmap.cpu().numpy() == oracle.proc_map(cands[4]).ravel()).all()
+    g.replay()
+    torch.cuda.synchronize()
+    win = oracle.select_best(exp)
+    assert (out.cpu().numpy() == exp).all() and int(best.cpu()[0]) == win
+    assert (pmap.cpu().numpy() == oracle.proc_map(cands[win]).ravel()).all()
+    plan.close()
