@@ -48,6 +48,8 @@ __global__ __launch_bounds__(256) void k_estimate_scores(const double2* __restri
     score[i] = __builtin_isfinite(v) ? v : INFINITY;
 }
 
+typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));  // a caller's rows
+
 struct EstimateArgs {
     const DevEval* evals;
     const int64_t* idx;
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(NT) void k_block_estimates(const EstimateArgs A) {
                 }
             }
         }
-        if (tid == 0) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
+        if (tid == 0) *reinterpret_cast<f64x2*>(A.est + 2 * i) = f64x2{tot, inter};
     }
 }
 
@@ -339,7 +341,7 @@ __global__ __launch_bounds__(256) void k_crossing_estimates(const DevCand* __res
                 inter += dred[w][1];
             }
         }
-        if (tid == 0) *reinterpret_cast<double2*>(A.est + 2 * i) = make_double2(tot, inter);
+        if (tid == 0) *reinterpret_cast<f64x2*>(A.est + 2 * i) = f64x2{tot, inter};
     }
 }
 

@@ -47,3 +47,16 @@ def test_estimates_from_records(tm, recs, halo):
     exp = np.array([mlp.block_estimates(c, halo[:int(c["lrank"])], oracle.chain_table) for c in recs])
     assert (got == exp).all()
     torch.cuda.synchronize()
+
+
+def test_estimates_at_an_address_of_8_bytes(tm):
+    import torch
+    print("[gpu-case] estimates at an address of 8 bytes", file=sys.stderr, flush=True)
+    recs = SMALL + [W.candidate((40, 9), 4, 6, [], [(0, W.CYCLIC), (1, W.BLOCK)])]
+    p = tm.Plan(len(recs)).load(W.batch(recs), W.stencil((1, 2, 1, 1), 8))
+    buf = torch.full((2 * len(recs) + 2,), -1.0, dtype=torch.float64, device="cuda")
+    assert buf.data_ptr() % 16 == 0
+    assert tm.lib().tm_ranker_block_estimates(p._p, buf.data_ptr() + 8, None) == tm.TM_OK
+    torch.cuda.synchronize()
+    assert torch.equal(buf[1:-1].view(-1, 2), tm.tm_ranker_block_estimates(p))
+    assert float(buf[0]) == -1.0 and float(buf[-1]) == -1.0
