@@ -51,7 +51,7 @@ PEAK_HBM = 8.0e12                     # bytes/s
 # profiles/c2_512cube_hbm_traffic.txt.
 KERNEL_SOURCES = ["paper_2507_17087_amd/csrc/tm_map.hip", "paper_2507_17087_amd/csrc/tm_map.h",
                   "paper_2507_17087_amd/csrc/tm_groups.h"]
-TRAFFIC_SOURCE_HASH = "3135e7d597db0113"
+TRAFFIC_SOURCE_HASH = "e2f70ec324bc6bf2"
 TRAFFIC_BYTES = {"k_map": 537.05e6}
 
 

@@ -255,12 +255,13 @@ int tm_eval_stencil_node_batch(const tm_candidate* c, int64_t n, const tm_stenci
  * differs from their owner under dst -- the data a change of mapping moves, e.g. a
  * transpose by all-to-all exchanges (App. A.3; dst from tm_transpose_target) -- and
  * the part whose owner's node changes.  d_out (device, tm_redist_cost[n]).  Counted
- * exactly over joint coordinate classes: along each launch dim, consecutive
- * coordinates with the same contributions under both mappings form a class, and the
- * cells of a tuple of classes all move or all stay.  TM_EINVAL if a pair differs in
+ * exactly over joint coordinate groups: along each launch dim the coordinates with the
+ * same contributions under both mappings form a group, and the cells of a tuple of
+ * groups all move or all stay.  TM_EINVAL if a pair differs in
  * launch rank, extents or machine (validation messages number src[i] as candidate i
- * and dst[i] as candidate n + i).  Owner tables and classes have no size limit
- * (those that do not fit the LDS budget together are read from global memory). */
+ * and dst[i] as candidate n + i).  Owner tables and groups have no size limit (a batch
+ * with a pair whose tables do not fit the LDS budget is counted over runs of equal
+ * coordinates from tables in global memory). */
 int tm_eval_redistribution_batch(const tm_candidate* src, const tm_candidate* dst, int64_t n, int64_t elem_bytes,
                                  tm_redist_cost* d_out, void* stream);
 
@@ -268,10 +269,11 @@ int tm_eval_redistribution_batch(const tm_candidate* src, const tm_candidate* ds
  * Johnson's 3-D, Solomonik's 2.5-D -- differ in) of n rank-3 candidates:
  * d_per_proc (device, int64[sum P_c][3],
  * candidates back to back, may be NULL) and d_out (device, tm_matmul_cost[n]).
- * Counted over coordinate classes: along each launch dim, consecutive coordinates
- * with the same contribution to the final index form a class; all tiles of one pair
- * of classes have the same owner set along the reduction dim, so each owner of the
- * pair counts its tiles at once.  TM_ENOTSUP if a candidate has more than 1024
+ * Counted over coordinate groups: along each launch dim the coordinates with the same
+ * contribution to the final index form a group; all tiles of one pair of groups have the
+ * same owner set along the reduction dim, so each owner of the pair counts its tiles at
+ * once (a batch with tables beyond the LDS budget: over runs of equal coordinates).
+ * TM_ENOTSUP if a candidate has more than 1024
  * processors or a matrix has more than 2^31 tiles. */
 int tm_eval_matmul_batch(const tm_candidate* c, int64_t n, const tm_matmul* mm,
                          int64_t* d_per_proc, tm_matmul_cost* d_out, void* stream);
@@ -308,8 +310,9 @@ int tm_parse_index_task_map(const char* source, const char* task, int32_t lrank,
  * A plan owns device memory for up to max_cands candidates and, once a map is asked for,
  * a place for each candidate's owner table (max_words words reserved; both grow).  tm_plan_load validates a batch on the host
  * and uploads its descriptors (asynchronously, on `stream`); tm_plan_run is one evaluation
- * launch whatever the candidates' launch ranks (two when their LDS needs differ much),
- * which also selects for batches of at most 128 candidates.  It makes no host
+ * launch whatever the candidates' launch ranks (two when their LDS needs differ much).
+ * One launch of at most 96 whole candidates also selects; larger batches, two launches and
+ * candidates cut into parts have the selection in a launch of its own.  A run makes no host
  * synchronisation and can be captured in the caller's own graph, and so can the maps; a
  * graph belongs to the batch that was loaded when it was captured.
  * d_out: tm_stencil_cost[n]; d_best: int64[1] (may be NULL).  A work item is a workgroup:
@@ -335,8 +338,9 @@ int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t host_index, 
                         int64_t cap, void* stream);
 /* tm_plan_run, then the processor map of the selected candidate (*d_best) into
  * d_map (device int32[cap], cap holding the batch's largest candidate): Sec. 4.2's
- * choice and the map Sec. 3.2 defines for it, with no host step between them.  d_out, d_best and d_map must not be NULL (TM_EINVAL); an empty
- * batch is TM_EINVAL, a short map TM_ECAPACITY. */
+ * choice and the map Sec. 3.2 defines for it, with no host step between them.  d_out,
+ * d_best and d_map must not be NULL (TM_EINVAL); an empty batch is TM_EINVAL, a short map
+ * TM_ECAPACITY. */
 int tm_plan_run_map(tm_plan* p, tm_stencil_cost* d_out, int64_t* d_best, int32_t* d_map, int64_t cap,
                     void* stream);
 /* Class tuples of the loaded batch, a measure of its size: the sum over its candidates

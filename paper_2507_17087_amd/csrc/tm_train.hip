@@ -410,8 +410,8 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const RankerLayout L, const
     if (i < L.count && in_matrix(i, L)) grad[i] = grad_at(i, L, part, splits, grad);
 }
 
-// Adam on the fp32 master copy; refreshes the bf16 copies (row-major and transposed) of
-// the matrices.  Parameter layout: see RankerLayout.
+// Adam on the fp32 master copy; refreshes the bf16 copies (in fragment order, of the matrices
+// and of their transposes).  Parameter layout: see RankerLayout.
 __global__ __launch_bounds__(256) void k_reduce_adam(float* __restrict__ p, const float* __restrict__ part, int splits,
                                                      const float* __restrict__ grad, float* __restrict__ m,
                                                      float* __restrict__ v, float lr, float b1, float b2, float eps,
