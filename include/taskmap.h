@@ -332,8 +332,8 @@ int tm_plan_run_stage(tm_plan* p, int32_t stage, tm_stencil_cost* d_out, int64_t
 /* Processor map of candidate *d_index (device int64; index into the loaded batch),
  * or of host_index when d_index is NULL, into d_map (device int32[cap]); cap must
  * hold the largest candidate of the batch.  TM_EINVAL before a batch of the plan was evaluated
- * (by a run, a stage of one, an exhaustive search or the autotuner) unless max_words reserved
- * the memory. */
+ * (by a run, a stage of one, an exhaustive search or the autotuner), unless max_words reserved
+ * the words of all its candidates' tables (owners, coordinates, classes). */
 int tm_plan_materialize(tm_plan* p, const int64_t* d_index, int64_t host_index, int32_t* d_map,
                         int64_t cap, void* stream);
 /* tm_plan_run, then the processor map of the selected candidate (*d_best) into

@@ -827,6 +827,7 @@ static void plan_free(tm_plan* p) {
     p->cap_hseg = 0;
     p->cap_cands = 0;
     p->cap_arena = 0;
+    p->reserved = 0;
 }
 
 // Descriptor buffers for up to `cands` candidates (the owner tables' memory is allocated
@@ -921,8 +922,9 @@ static hipError_t plan_enqueue(tm_plan* p, int stage, tm_stencil_cost* out, int6
 }
 
 // Maps and class tuples are given once a batch of the plan was evaluated (by a run, a stage, an
-// exhaustive search or the autotuner), or where memory for the tables was reserved at creation.
-static bool plan_ready(const tm_plan* p) { return p->ran || p->cap_arena >= p->cp.map_words; }
+// exhaustive search or the autotuner), or where the words reserved at creation hold all
+// the tables of the batch's compiled candidates (DevCand::words).
+static bool plan_ready(const tm_plan* p) { return p->ran || p->reserved >= p->cp.arena_words; }
 
 // Map launch for a device-side index: fits every loaded candidate.
 static MapShape plan_map_shape(const tm_plan* p) { return map_shape(p->cp.max_vol, p->cp.max_points, p->cp.min_row); }
@@ -938,7 +940,7 @@ extern "C" int tm_plan_create(int64_t max_cands, int64_t max_words, tm_plan** ou
     int rc = plan_alloc(p, max_cands);
     if (rc == TM_OK && max_words > 0) {
         if (hipMalloc((void**)&p->d_arena, (size_t)max_words * 4) != hipSuccess) rc = no_memory("arena");
-        else p->cap_arena = max_words;
+        else p->reserved = p->cap_arena = max_words;
     }
     if (rc == TM_OK && hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming) != hipSuccess)
         rc = set_error(TM_EDEVICE, "event");

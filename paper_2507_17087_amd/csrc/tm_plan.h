@@ -47,6 +47,7 @@ struct tm_plan {
     int device = 0;
     int64_t cap_cands = 0;
     int64_t cap_arena = 0;            // words of d_arena
+    int64_t reserved = 0;             // of them asked for at creation
     tmk::DevCand* d_cands = nullptr;
     tmk::DevEval* d_evals = nullptr;  // the evaluation's view of the batch
     tmk::DevFeat* d_feats = nullptr;  // the features'

@@ -72,6 +72,9 @@ for name, way in ways.items():
 assert L.tm_plan_create(4, 100000, ctypes.byref(p)) == tm.TM_OK  # room for the tables
 assert load(4) == tm.TM_OK and asked() == OK
 assert L.tm_plan_destroy(p) == tm.TM_OK
+assert L.tm_plan_create(4, 16, ctypes.byref(p)) == tm.TM_OK  # for the owner tables only
+assert load(4) == tm.TM_OK and asked() == NO
+assert L.tm_plan_destroy(p) == tm.TM_OK
 print("done")
 """
 
